@@ -32,7 +32,7 @@ struct tapout_ctx {
     int round_K = 0;                                           // its K (0: no draft_stats call yet)
     int positions = 1;                                         // bandits per slot: 1, or max_k for token-level bandits
     int wgs_target = 4096;        // workgroups a streaming launch aims for
-    int min_slice = 4096;         // smallest slice (elements) a row is cut into
+    int min_slice = 0;            // smallest slice (elements) a row is cut into; 0: whole batches of the streaming kernel (choose_slices)
     int slice_bytes = 65536;      // slice size aimed for when the rows alone give enough workgroups
     int fuse_head = -1;           // tapout_verify: accept decisions inside the slice kernel (1), in a launch of their own (0), by size (-1)
     int exp_lookup = 1;           // final token: exponentials of bfloat16 row pairs from the table (1) or computed (0)
@@ -87,39 +87,86 @@ struct DeviceGuard {
     ~DeviceGuard() { if (changed) (void)hipSetDevice(prev); }
 };
 
-// Vectors per slice: a multiple of 64 (whole 1 KB wavefront loads) such that nsplit slices cover a row
-// whatever its alignment (an unaligned row has at most one vector more than an aligned one).
-int slice_vectors(int V, int dtype, int nsplit)
+// How a streaming launch cuts its rows: n slices of `per` 16-byte vectors (a multiple of 64: whole 1 KB wavefront loads;
+// n * per covers a row whatever its alignment: an unaligned one has no more whole vectors than an aligned one).
+struct Slices { int n, per; };
+
+// Slices wanted: enough for about wgs_target workgroups per launch when rows are few, and slices of about slice_bytes when
+// rows are many (a launch ends ragged by about half the duration of one workgroup, so workgroups that stream a whole long
+// row cost several percent of the launch).  slice_bytes is the size for 2-byte elements; slices of 4-byte elements hold as
+// many elements, twice the bytes (a workgroup's arithmetic goes by the element, and a launch of many short workgroups is
+// held up by their dispatch: V = 256000, 512 sequences, binary32 target rows in 128 KB slices 828 us, in 64 KB slices
+// 840 us; bfloat16 draft rows the other way round, 401 / 385 us).
+int64_t slices_wanted(int wgs_target, int slice_bytes, int64_t rows, int V, int dtype, int64_t *by_bytes)
 {
-    const int vec = dtype == TAPOUT_F32 ? 4 : 8;
-    const int nvec = (V + vec - 1) / vec + 1;
-    return (((nvec + nsplit - 1) / nsplit) + 63) & ~63;
+    const int esz = dtype == TAPOUT_F32 ? 4 : 2;
+    *by_bytes = (int64_t)V * esz / ((int64_t)slice_bytes * (dtype == TAPOUT_F32 ? 2 : 1));
+    const int64_t by_rows = (wgs_target + rows - 1) / rows;
+    return by_rows > *by_bytes ? by_rows : *by_bytes;
 }
 
-// Slices per row: enough for about wgs_target workgroups per launch when rows are few, and slices of about
-// slice_bytes when rows are many (a launch ends ragged by about half the duration of one workgroup, so
-// workgroups that stream a whole long row cost several percent of the launch); never below min_slice
-// elements per slice, which no longer amortises a workgroup's fixed cost.  slice_bytes is the size for 2-byte
-// elements; slices of 4-byte elements hold as many elements, twice the bytes (a workgroup's arithmetic goes by the
-// element, and a launch of many short workgroups is held up by their dispatch: V = 256000, 512 sequences, binary32
-// target rows in 128 KB slices 828 us, in 64 KB slices 840 us; bfloat16 draft rows the other way round, 401 / 385 us).
-int choose_nsplit_for(int wgs_target, int min_slice, int slice_bytes, int64_t rows, int V, int dtype)
+// A fixed smallest slice of min_slice elements (the option "min_slice"; also the rule whose slice count bounds what
+// tapout_draft_stats_static accepts).
+int slices_by_elements(int wgs_target, int min_slice, int slice_bytes, int64_t rows, int V, int dtype)
 {
-    const int64_t row_bytes = (int64_t)V * (dtype == TAPOUT_F32 ? 4 : 2);
-    int64_t want = (wgs_target + rows - 1) / rows;
-    const int64_t by_bytes = row_bytes / ((int64_t)slice_bytes * (dtype == TAPOUT_F32 ? 2 : 1));
-    if (want < by_bytes) want = by_bytes;
+    int64_t by_bytes;
+    int64_t want = slices_wanted(wgs_target, slice_bytes, rows, V, dtype, &by_bytes);
     int64_t by_size = V / min_slice;
     if (by_size < 1) by_size = 1;
     if (want > by_size) want = by_size;
     if (want > kStageCap) want = kStageCap;      // an epilogue stages whole rows of partials in LDS
-    if (want < 1) want = 1;
-    return (int)want;
+    return (int)(want < 1 ? 1 : want);
 }
 
-int choose_nsplit(const tapout_ctx *ctx, int64_t rows, int V, int dtype)
+// n slices of equal length; up to two batches of the streaming kernel (kBlock * kStreamU vectors, 16 KB: what a workgroup
+// has in flight at a time) long, whole batches: a slice of a batch and a bit takes as long as one of two.  (Slices at the
+// end of a row may then be empty.)
+Slices cut_evenly(int n, int V, int dtype)
 {
-    return choose_nsplit_for(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, V, dtype);
+    const int vec = dtype == TAPOUT_F32 ? 4 : 8;
+    return Slices{n, ((((V + vec - 1) / vec + 1 + n - 1) / n) + 63) & ~63};
+}
+constexpr int kBatchVecs = kBlock * kStreamU;
+Slices cut_in_batches(int n, int V, int dtype)
+{
+    const int vec = dtype == TAPOUT_F32 ? 4 : 8;
+    const int even = (V / vec + n - 1) / n, whole = (even + kBatchVecs - 1) / kBatchVecs * kBatchVecs;
+    return n > 1 && even <= 2 * kBatchVecs ? Slices{n, whole} : cut_evenly(n, V, dtype);
+}
+
+// KK: rows per sequence, over which one workgroup of an epilogue merges the partials.
+Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t rows, int KK, int V, int dtype)
+{
+    if (min_slice > 0) return cut_evenly(slices_by_elements(wgs_target, min_slice, slice_bytes, rows, V, dtype), V, dtype);
+    // By itself a slice is one or two whole batches where rows are few: a slice of half a batch pays a workgroup's fixed
+    // cost for half its loads, one of a batch and a bit pays a second round of them for the bit.  Not more slices than
+    // the epilogues can merge across lanes (16, fewer for long drafts; see lane_merge_shift) unless the rows are so long
+    // that those would be beyond slice_bytes: walked one after the other, 31 partials a row cost the draft epilogue and
+    // the accept decisions 7 us each.  (Measured against slices of at least 4096 elements: V = 128256, bfloat16, 64
+    // sequences of one row, 16 instead of 31 slices: pass 10.4 -> 7.5 us, draft epilogue 15.6 -> 8.2; one sequence, K = 8:
+    // draft epilogue 14.8 -> 7.6, slice kernel with the accept decisions 15.9 -> 9.8; V = 32000, 32 sequences, K = 8, 4
+    // instead of 7 slices: pair launch 14.2 -> 9.8; V = 50257, 48 sequences, K = 7, 7 instead of 12: pass 16.6 -> 12.5.)
+    int64_t by_bytes;
+    int64_t want = slices_wanted(wgs_target, slice_bytes, rows, V, dtype, &by_bytes);
+    int64_t lane_cap = 1;
+    if (KK <= 64)
+        for (int p = 2; p <= 16 && KK * p <= 512; p *= 2) lane_cap = p;
+    else lane_cap = kStageCap;
+    const int64_t cap = by_bytes > lane_cap ? by_bytes : lane_cap;
+    if (want > cap) want = cap;
+    const int64_t nb = V <= kBatchVecs * (dtype == TAPOUT_F32 ? 4 : 8) ? 1 : (V / (dtype == TAPOUT_F32 ? 4 : 8) + kBatchVecs - 1) / kBatchVecs;
+    if (want < 1) want = 1;
+    if (want > nb) want = nb;
+    int64_t pb = (2 * nb + want) / (2 * want);     // batches per slice, rounded to nearest
+    if ((nb + pb - 1) / pb > cap) pb = (nb + cap - 1) / cap;
+    if (pb <= 2) want = (nb + pb - 1) / pb;
+    if (want > kStageCap) want = kStageCap;       // an epilogue stages whole rows of partials in LDS
+    return cut_in_batches((int)want, V, dtype);
+}
+
+Slices choose_slices(const tapout_ctx *ctx, int64_t rows, int KK, int V, int dtype)
+{
+    return choose_slices(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, KK, V, dtype);
 }
 
 // ---- device address of the static scratch, per device ------------------------------------------------
@@ -272,7 +319,7 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     const size_t rows = (size_t)cfg->max_batch * (cfg->max_k + 1);
     int64_t by_bytes_max = (int64_t)cfg->vocab * 4 / kMinSliceBytes;
     by_bytes_max = by_bytes_max < 1 ? 1 : (by_bytes_max > kStageCap ? kStageCap : by_bytes_max);
-    c->part_cap = rows * (size_t)by_bytes_max + kMaxWgsTarget;   // rows * nsplit under either rule of choose_nsplit
+    c->part_cap = rows * (size_t)by_bytes_max + kMaxWgsTarget;   // rows * nsplit under either rule of choose_slices
     c->positions = cfg->granularity == TAPOUT_TOKEN_LEVEL ? cfg->max_k : 1;
     const size_t nstate = (size_t)cfg->n_bandits * c->positions * cfg->n_arms;
     c->nsl_max = (cfg->vocab + kSampleSlice - 1) / kSampleSlice;
@@ -435,7 +482,7 @@ hipError_t stream_pair(tapout_ctx *ctx, const RowReduceArgs &d, int d_dtype, con
 RowReduceArgs target_pass_args(tapout_ctx *ctx, const VerifyCall &c);
 
 // tapout_draft_stats.  pair != NULL (tapout_round): the streaming pass is one launch over the draft rows and the target
-// rows of *pair, with pair_nsplit slices per row for both.  defer != NULL (tapout_round): the epilogue is not launched;
+// rows of *pair.  slices.n > 0 (tapout_round): how the draft rows are cut; else chosen here.  defer != NULL (tapout_round): the epilogue is not launched;
 // its arguments go to *defer for the caller to run later, the slice count to *defer_nsplit, and the streaming pass
 // leaves the logits of the drafted tokens in its partials.
 tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
@@ -445,7 +492,7 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
                                  float *lse, float *entropy, float *p_top1, float *p_top2, float *margin,
                                  int32_t *top1_id, float *logq_tok, int32_t *sampled_tok,
                                  int32_t *n_stop, uint8_t *stop_fired, uint32_t *flags, void *stream,
-                                 const VerifyCall *pair, int pair_nsplit, DraftFinalArgs *defer = nullptr, int *defer_nsplit = nullptr)
+                                 const VerifyCall *pair, Slices slices, DraftFinalArgs *defer = nullptr, int *defer_nsplit = nullptr)
 {
     if (!ctx) return TAPOUT_EINVAL;
     tapout_status s = check_shape(ctx, B, K, V);
@@ -460,10 +507,11 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
     DeviceGuard guard(ctx->cfg.device);
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = (int64_t)B * K;
-    const int nsplit = pair ? pair_nsplit : choose_nsplit(ctx, rows, V, draft->dtype);
+    if (slices.n <= 0) slices = choose_slices(ctx, rows, K, V, draft->dtype);
+    const int nsplit = slices.n;
     if ((size_t)(rows * nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
 
-    RowReduceArgs r{draft->ptr, draft->stride_b, draft->stride_k, V, K, nsplit, slice_vectors(V, draft->dtype, nsplit), (int32_t)rows, k_len, 0, ctx->part};
+    RowReduceArgs r{draft->ptr, draft->stride_b, draft->stride_k, V, K, nsplit, slices.per, (int32_t)rows, k_len, 0, ctx->part};
     if (defer) {
         if (u_draft || !draft_tok) return fail(ctx, TAPOUT_EINVAL, "internal: a deferred epilogue needs the caller's draft tokens");
         r.tok = draft_tok; r.tok_rows = K;
@@ -521,7 +569,7 @@ tapout_status tapout_draft_stats(tapout_ctx *ctx, const tapout_logits *draft,
                                  int32_t *n_stop, uint8_t *stop_fired, uint32_t *flags, void *stream)
 {
     return draft_stats_impl(ctx, draft, B, K, V, draft_tok, k_len, arm, u_draft, lse, entropy, p_top1, p_top2, margin,
-                            top1_id, logq_tok, sampled_tok, n_stop, stop_fired, flags, stream, nullptr, 0);
+                            top1_id, logq_tok, sampled_tok, n_stop, stop_fired, flags, stream, nullptr, Slices{0, 0});
 }
 
 tapout_status tapout_draft_stats_static(const tapout_logits *draft, int32_t B, int32_t K, int32_t V,
@@ -548,17 +596,21 @@ tapout_status tapout_draft_stats_static(const tapout_logits *draft, int32_t B, i
         }
     }
     const int64_t rows = (int64_t)B * K;
-    const int nsplit = choose_nsplit_for(4096, 4096, 65536, rows, V, draft->dtype);       // the defaults of a context
-    if ((uint64_t)rows * (uint64_t)nsplit > kStaticPartials)
+    // what is accepted: the documented bound; how the rows are cut: as a context with default options would
+    const int bound = slices_by_elements(4096, 4096, 65536, rows, V, draft->dtype);
+    if ((uint64_t)rows * (uint64_t)bound > kStaticPartials)
         return fail(nullptr, TAPOUT_EINVAL, "B * K * slices = %lld x %d exceeds the static scratch of %zu slice partials",
-                    (long long)rows, nsplit, kStaticPartials);
+                    (long long)rows, bound, kStaticPartials);
+    Slices slices = choose_slices(4096, 0, 65536, rows, K, V, draft->dtype);
+    if ((uint64_t)rows * (uint64_t)slices.n > kStaticPartials) slices = choose_slices(4096, 4096, 65536, rows, K, V, draft->dtype);
+    const int nsplit = slices.n;
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(nullptr, e, "hipGetDevice");
     Partial *part = static_scratch(dev, &e);
     if (!part) return hip_fail(nullptr, e, "hipGetSymbolAddress(scratch)");
     hipStream_t st = (hipStream_t)stream;
-    RowReduceArgs r{draft->ptr, draft->stride_b, draft->stride_k, V, K, nsplit, slice_vectors(V, draft->dtype, nsplit), (int32_t)rows, k_len, 0, part};
+    RowReduceArgs r{draft->ptr, draft->stride_b, draft->stride_k, V, K, nsplit, slices.per, (int32_t)rows, k_len, 0, part};
     e = launch_row_reduce(r, draft->dtype, true, st, Timing{});
     if (e != hipSuccess) return hip_fail(nullptr, e, "draft pass launch");
     DraftFinalArgs f{};
@@ -595,9 +647,10 @@ tapout_status tapout_shard_stats(tapout_ctx *ctx, const tapout_logits *shard,
     DeviceGuard guard(ctx->cfg.device);
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = (int64_t)B * KK;
-    const int nsplit = choose_nsplit(ctx, rows, Vs, shard->dtype);
+    const Slices slices = choose_slices(ctx, rows, KK, Vs, shard->dtype);
+    const int nsplit = slices.n;
     if ((size_t)(rows * nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
-    RowReduceArgs r{shard->ptr, shard->stride_b, shard->stride_k, Vs, KK, nsplit, slice_vectors(Vs, shard->dtype, nsplit), (int32_t)rows, len, rows_mode, ctx->part};
+    RowReduceArgs r{shard->ptr, shard->stride_b, shard->stride_k, Vs, KK, nsplit, slices.per, (int32_t)rows, len, rows_mode, ctx->part};
     // the draft pass also tracks the second maximum and the entropy sum; target rows need neither, but a record has one layout
     hipError_t e = timed(ctx, rows_mode ? TAPOUT_PROFILE_TARGET_PASS : TAPOUT_PROFILE_DRAFT_PASS,
                          [&](Timing tm) { return launch_row_reduce(r, shard->dtype, true, st, tm); });
@@ -746,7 +799,7 @@ struct VerifyCall {
     const float *u_accept, *u_sample;
     int32_t *accept_len, *out_tok, *n_out; float *target_lse, *logp_tok; int32_t *target_top1; uint32_t *flags;
     // derived by verify_check
-    int nsplit, nsl; bool fused;
+    Slices slices; int nsl; bool fused;
 };
 
 tapout_status verify_check(tapout_ctx *ctx, VerifyCall &c)
@@ -760,8 +813,8 @@ tapout_status verify_check(tapout_ctx *ctx, VerifyCall &c)
         return fail(ctx, TAPOUT_EINVAL, "draft_lse, logq_tok, draft_tok, n_draft, u_accept and u_sample are required");
     if (!c.accept_len || !c.out_tok || !c.n_out) return fail(ctx, TAPOUT_EINVAL, "accept_len, out_tok and n_out are required");
     const int64_t rows = (int64_t)c.B * (c.K + 1);
-    c.nsplit = choose_nsplit(ctx, rows, c.V, c.target->dtype);
-    if ((size_t)(rows * c.nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
+    c.slices = choose_slices(ctx, rows, c.K + 1, c.V, c.target->dtype);
+    if ((size_t)(rows * c.slices.n) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
     // With few sequences the final-token slice kernel is a handful of workgroups per compute unit and its launch
     // is latency: then the accept decisions are taken inside it (by every workgroup of a sequence again) and the
     // head launch with its hand-over through memory goes away.  With many sequences that kernel is bound by
@@ -777,7 +830,7 @@ tapout_status verify_check(tapout_ctx *ctx, VerifyCall &c)
 RowReduceArgs target_pass_args(tapout_ctx *ctx, const VerifyCall &c)
 {
     const int64_t rows = (int64_t)c.B * (c.K + 1);
-    return RowReduceArgs{c.target->ptr, c.target->stride_b, c.target->stride_k, c.V, c.K + 1, c.nsplit, slice_vectors(c.V, c.target->dtype, c.nsplit),
+    return RowReduceArgs{c.target->ptr, c.target->stride_b, c.target->stride_k, c.V, c.K + 1, c.slices.n, c.slices.per,
                          (int32_t)rows, c.n_draft, 1, ctx->part_t,
                          c.fused ? ctx->jobs : nullptr, c.draft_tok, c.K};     // the pass also picks up the logits of the drafted tokens
 }
@@ -815,7 +868,7 @@ hipError_t verify_rest(tapout_ctx *ctx, const VerifyCall &c, hipStream_t st, con
     }
     va.tbase = c.target->ptr; va.t_dtype = c.target->dtype; va.t_stride_b = c.target->stride_b; va.t_stride_k = c.target->stride_k;
     va.dbase = c.draft->ptr; va.d_dtype = c.draft->dtype; va.d_stride_b = c.draft->stride_b; va.d_stride_k = c.draft->stride_k;
-    va.B = c.B; va.K = c.K; va.V = c.V; va.nsplit = c.nsplit; va.nsl = c.nsl;
+    va.B = c.B; va.K = c.K; va.V = c.V; va.nsplit = c.slices.n; va.nsl = c.nsl;
     va.jps = 1; va.n_jobs = c.B; va.fused_head = c.fused ? 1 : 0;
     va.part = ctx->part_t;
     va.draft_lse = c.draft_lse; va.logq_tok = c.logq_tok; va.draft_tok = c.draft_tok; va.n_draft = c.n_draft; va.greedy = c.greedy;
@@ -843,7 +896,7 @@ tapout_status tapout_verify(tapout_ctx *ctx, const tapout_logits *target, const 
 {
     if (!ctx) return TAPOUT_EINVAL;
     VerifyCall c{target, draft, B, K, V, draft_lse, logq_tok, draft_tok, n_draft, greedy, u_accept, u_sample,
-                 accept_len, out_tok, n_out, target_lse, logp_tok, target_top1, flags, 0, 0, false};
+                 accept_len, out_tok, n_out, target_lse, logp_tok, target_top1, flags, Slices{0, 0}, 0, false};
     tapout_status s = verify_check(ctx, c);
     if (s != TAPOUT_OK || B == 0) return s;
     DeviceGuard guard(ctx->cfg.device);
@@ -865,7 +918,7 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     if ((ctx->cfg.policy == TAPOUT_TS_BETA || ctx->cfg.policy == TAPOUT_TS_GAUSS) && !a->u_ts_next) return fail(ctx, TAPOUT_EINVAL, "Thompson Sampling needs u_ts_next");
     const int32_t *n_draft = a->n_draft ? a->n_draft : a->n_stop;
     VerifyCall c{a->target, a->draft, a->B, a->K, a->V, a->lse, a->logq_tok, a->draft_tok, n_draft, a->greedy, a->u_accept, a->u_sample,
-                 a->accept_len, a->out_tok, a->n_out, a->target_lse, a->logp_tok, a->target_top1, a->verify_flags, 0, 0, false};
+                 a->accept_len, a->out_tok, a->n_out, a->target_lse, a->logp_tok, a->target_top1, a->verify_flags, Slices{0, 0}, 0, false};
     tapout_status s = verify_check(ctx, c);
     if (s != TAPOUT_OK || a->B == 0) return s;
     DeviceGuard guard(ctx->cfg.device);
@@ -879,22 +932,24 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
         // slices for the rows of both tensors together: half as many, twice as long, as either pass would take alone
         // (the slice count of the tensor with the larger elements: never more slices than the other would take)
         const int wide = (a->target->dtype == TAPOUT_F32 || a->draft->dtype == TAPOUT_F32) ? TAPOUT_F32 : TAPOUT_BF16;
-        c.nsplit = choose_nsplit(ctx, (int64_t)a->B * (2 * a->K + 1), a->V, wide);
-        if ((size_t)((int64_t)a->B * (a->K + 1) * c.nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
+        c.slices = choose_slices(ctx, (int64_t)a->B * (2 * a->K + 1), a->K + 1, a->V, wide);
+        if (wide != a->target->dtype) c.slices = ctx->min_slice > 0 ? cut_evenly(c.slices.n, a->V, a->target->dtype) : cut_in_batches(c.slices.n, a->V, a->target->dtype);
+        if ((size_t)((int64_t)a->B * (a->K + 1) * c.slices.n) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
     }
     // With n_draft from the caller nothing of the verification waits for the draft epilogue's outputs if the accept
     // decisions form log q(tok) from the draft partials themselves (shapes whose partials one workgroup merges across
     // lanes; the stateful rules' epilogue hands entropies to the end of the round, so it keeps its place): then the
     // epilogue, a latency-bound kernel of B workgroups, runs beside the final-token locate kernel, another one, in
     // one launch.
-    const int d_nsplit = pair ? c.nsplit : choose_nsplit(ctx, (int64_t)a->B * a->K, a->V, a->draft->dtype);
+    const Slices d_slices = !pair ? choose_slices(ctx, (int64_t)a->B * a->K, a->K, a->V, a->draft->dtype)
+                                  : ctx->min_slice > 0 ? cut_evenly(c.slices.n, a->V, a->draft->dtype) : cut_in_batches(c.slices.n, a->V, a->draft->dtype);
     const bool defer = a->n_draft != nullptr && a->n_draft != a->n_stop && !ctx->stateful && ctx->defer_epilogue &&
-                       own_q_shape(a->K, c.nsplit, d_nsplit);
+                       own_q_shape(a->K, c.slices.n, d_slices.n);
     DraftFinalArgs fin{};
     int fin_nsplit = 0;
     s = draft_stats_impl(ctx, a->draft, a->B, a->K, a->V, a->draft_tok, a->k_len, a->arm, nullptr,
                          a->lse, a->entropy, a->p_top1, a->p_top2, a->margin, a->top1_id, a->logq_tok, nullptr,
-                         a->n_stop, a->stop_fired, a->draft_flags, stream, pair ? &c : nullptr, c.nsplit,
+                         a->n_stop, a->stop_fired, a->draft_flags, stream, pair ? &c : nullptr, d_slices,
                          defer ? &fin : nullptr, &fin_nsplit);
     if (s != TAPOUT_OK) return s;
     hipError_t e = hipSuccess;
