@@ -61,6 +61,12 @@ constexpr int kMaxWgsTarget = 1 << 16;
 // up to 1280 workgroups and loses by 1-2 us from 1536 on).  Four per CU when a row is bfloat16: the table of
 // exponentials takes 36 KB of LDS per workgroup.
 constexpr int kFuseHeadMaxWgs = 1280, kFuseHeadMaxWgsBf16 = 1024;
+// tapout_round up to the stop position: target tensors of at most this many bytes are streamed with the draft rows, before
+// the stop position is known.  Saves the target pass's launch, costs the rows beyond the stop position (measured, K = 8,
+// stop positions of 1 to 3, us per round with the target pass after / with the draft rows: V = 128256 bfloat16 2 MB
+// 30.4 / 27.1, 9 MB 32.7 / 30.4, 18 MB 35.8 / 34.1, 37 MB 40.3 / 40.3, 74 MB 50.4 / 53.4; binary32 9 MB 31.9 / 27.9,
+// 18 MB 34.0 / 31.0, 37 MB 39.3 / 38.8, 74 MB 46.8 / 49.3; V = 32000 the same picture).
+constexpr int64_t kPairAllRowsBytes = 24 << 20;
 constexpr int kMinSliceBytes = 16384;            // lower limit of the "slice_bytes" option (sizes the partial buffer)
 thread_local char g_create_err[256] = {0};
 
@@ -800,6 +806,8 @@ struct VerifyCall {
     int32_t *accept_len, *out_tok, *n_out; float *target_lse, *logp_tok; int32_t *target_top1; uint32_t *flags;
     // derived by verify_check
     Slices slices; int nsl; bool fused;
+    // rows the target pass reads: 0..len[b]; n_draft, except where the pass runs before n_draft is known
+    const int32_t *len;
 };
 
 tapout_status verify_check(tapout_ctx *ctx, VerifyCall &c)
@@ -826,12 +834,12 @@ tapout_status verify_check(tapout_ctx *ctx, VerifyCall &c)
     return TAPOUT_OK;
 }
 
-// The streaming pass over the target rows (it needs n_draft and the drafted tokens, nothing the draft pass computes).
+// The streaming pass over the target rows (it needs the drafted tokens and which rows to read, nothing the draft pass computes).
 RowReduceArgs target_pass_args(tapout_ctx *ctx, const VerifyCall &c)
 {
     const int64_t rows = (int64_t)c.B * (c.K + 1);
     return RowReduceArgs{c.target->ptr, c.target->stride_b, c.target->stride_k, c.V, c.K + 1, c.slices.n, c.slices.per,
-                         (int32_t)rows, c.n_draft, 1, ctx->part_t,
+                         (int32_t)rows, c.len, 1, ctx->part_t,
                          c.fused ? ctx->jobs : nullptr, c.draft_tok, c.K};     // the pass also picks up the logits of the drafted tokens
 }
 
@@ -896,7 +904,7 @@ tapout_status tapout_verify(tapout_ctx *ctx, const tapout_logits *target, const 
 {
     if (!ctx) return TAPOUT_EINVAL;
     VerifyCall c{target, draft, B, K, V, draft_lse, logq_tok, draft_tok, n_draft, greedy, u_accept, u_sample,
-                 accept_len, out_tok, n_out, target_lse, logp_tok, target_top1, flags, Slices{0, 0}, 0, false};
+                 accept_len, out_tok, n_out, target_lse, logp_tok, target_top1, flags, Slices{0, 0}, 0, false, n_draft};
     tapout_status s = verify_check(ctx, c);
     if (s != TAPOUT_OK || B == 0) return s;
     DeviceGuard guard(ctx->cfg.device);
@@ -918,7 +926,7 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     if ((ctx->cfg.policy == TAPOUT_TS_BETA || ctx->cfg.policy == TAPOUT_TS_GAUSS) && !a->u_ts_next) return fail(ctx, TAPOUT_EINVAL, "Thompson Sampling needs u_ts_next");
     const int32_t *n_draft = a->n_draft ? a->n_draft : a->n_stop;
     VerifyCall c{a->target, a->draft, a->B, a->K, a->V, a->lse, a->logq_tok, a->draft_tok, n_draft, a->greedy, a->u_accept, a->u_sample,
-                 a->accept_len, a->out_tok, a->n_out, a->target_lse, a->logp_tok, a->target_top1, a->verify_flags, Slices{0, 0}, 0, false};
+                 a->accept_len, a->out_tok, a->n_out, a->target_lse, a->logp_tok, a->target_top1, a->verify_flags, Slices{0, 0}, 0, false, n_draft};
     tapout_status s = verify_check(ctx, c);
     if (s != TAPOUT_OK || a->B == 0) return s;
     DeviceGuard guard(ctx->cfg.device);
@@ -927,8 +935,14 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     // streams the draft rows and the target rows together, both cut into the same number of slices.
     // (Tensors of different element sizes too: slices go by the element, so both halves want the same number of them.
     // V = 256000, 512 sequences, bfloat16 draft and binary32 target rows: 1213 us against 388 + 828 us.)
-    const bool pair = a->n_draft != nullptr && a->n_draft != a->n_stop && 2 * a->B <= 65535;
-    if (pair) {
+    const bool given = a->n_draft != nullptr && a->n_draft != a->n_stop;
+    // Up to the stop position the pair streams every target row that could be wanted, 0..k_len[b], where that is little
+    // data (kPairAllRowsBytes).  Both halves are then cut as their own passes would be: same partials, same bits.
+    // (Given k_len only: a test for a missing one in the streaming kernels cost the 64-sequence rounds 1 to 2 us.)
+    const bool pair_all = !given && a->k_len && 2 * a->B <= 65535 && (int64_t)a->B * (a->K + 1) * a->V * (a->target->dtype == TAPOUT_F32 ? 4 : 2) <= kPairAllRowsBytes;
+    const bool pair = (given && 2 * a->B <= 65535) || pair_all;
+    if (pair_all) c.len = a->k_len;
+    else if (pair) {
         // slices for the rows of both tensors together: half as many, twice as long, as either pass would take alone
         // (the slice count of the tensor with the larger elements: never more slices than the other would take)
         const int wide = (a->target->dtype == TAPOUT_F32 || a->draft->dtype == TAPOUT_F32) ? TAPOUT_F32 : TAPOUT_BF16;
@@ -941,9 +955,9 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     // lanes; the stateful rules' epilogue hands entropies to the end of the round, so it keeps its place): then the
     // epilogue, a latency-bound kernel of B workgroups, runs beside the final-token locate kernel, another one, in
     // one launch.
-    const Slices d_slices = !pair ? choose_slices(ctx, (int64_t)a->B * a->K, a->K, a->V, a->draft->dtype)
+    const Slices d_slices = !pair || pair_all ? choose_slices(ctx, (int64_t)a->B * a->K, a->K, a->V, a->draft->dtype)
                                   : ctx->min_slice > 0 ? cut_evenly(c.slices.n, a->V, a->draft->dtype) : cut_in_batches(c.slices.n, a->V, a->draft->dtype);
-    const bool defer = a->n_draft != nullptr && a->n_draft != a->n_stop && !ctx->stateful && ctx->defer_epilogue &&
+    const bool defer = given && !ctx->stateful && ctx->defer_epilogue &&
                        own_q_shape(a->K, c.slices.n, d_slices.n);
     DraftFinalArgs fin{};
     int fin_nsplit = 0;
@@ -960,7 +974,8 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     // Sequence-level UCB bandits, one per sequence: the final-token locate kernel, one workgroup per sequence, also
     // applies the reward and picks the next arm.  Gaussian Thompson Sampling, shared and token-level bandits take a
     // launch of their own.
-    const bool own = ctx->positions == 1 && ctx->cfg.n_bandits != 1;
+    // (a shared bandit with one sequence is that sequence's own)
+    const bool own = ctx->positions == 1 && (ctx->cfg.n_bandits != 1 || a->B == 1);
     const bool tail = own && (ctx->cfg.policy == TAPOUT_UCB1 || ctx->cfg.policy == TAPOUT_UCB_TUNED);
     // Thompson Sampling with Beta posteriors: the same launch carries the end of the round as workgroups of its own
     const bool ts_tail = own && ctx->cfg.policy == TAPOUT_TS_BETA && a->u_ts_next != nullptr;

@@ -128,13 +128,13 @@ __global__ __launch_bounds__(64) void bandit_update_select_ts_kernel(BanditArgs 
 
 }  // namespace
 
-// Update followed by the next selection.  One launch where every sequence has a sequence-level bandit of its own;
-// otherwise (shared bandit, token-level bandits) the two kernels one after the other.
+// Update followed by the next selection.  One launch where every sequence has a sequence-level bandit of its own (or
+// there is one sequence: bandit 0 either way); otherwise (shared bandit, token-level bandits) the two kernels one after the other.
 hipError_t launch_bandit_update_select(const BanditArgs &a, const int32_t *arm, const int32_t *accept_len,
                                        const int32_t *n_draft, const int32_t *gamma, const uint8_t *active,
                                        const float *u_ts, int32_t *arm_out, uint32_t *flags, hipStream_t st, Timing tm)
 {
-    if (a.positions > 1 || a.n_bandits == 1) {
+    if (a.positions > 1 || (a.n_bandits == 1 && a.B > 1)) {
         hipError_t e = launch_bandit_update(a, arm, accept_len, n_draft, gamma, active, st, tm);
         if (e != hipSuccess) return e;
         return launch_bandit_select(a, u_ts, arm_out, flags, st, Timing{});

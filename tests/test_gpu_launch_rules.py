@@ -41,3 +41,46 @@ def test_slices_of_whole_batches(B, K, V, dt, tt):
          pu.check_round_call(tp, rnd, arm.clone(), truncate=False), pu.check_round_call(tp, rnd, arm.clone(), truncate=True)]
     # near ties: a few per thousand decisions at the tolerance of 1e-5
     assert sum(x["accept_flagged"] + x["icdf_flagged"] + x["stop_flagged"] for x in c) <= 2 + 4 * B * K // 500
+
+
+@pytest.mark.parametrize("V,dt", [(32000, f32), (9001, bf16)])
+def test_round_up_to_the_stop_position_reads_no_target_row_beyond_the_cap(V, dt):
+    """Small rounds stream the target rows before the stop position is known: rows 0..k_len of each sequence and no other."""
+    B, K = 5, 6
+    rnd = mixed_round(B, K, V, dt, dt, seed=V, k_len=[1, 2, 4, 6, 3])
+    for b, n in enumerate([1, 2, 4, 6, 3]):
+        rnd["target"][b, n + 1:] = float("nan")
+    for arm in range(3):
+        for thresholds in ((0.6, 0.8, 0.2), (1e9, 0.0, -1.0)):             # the second: no rule fires, every row up to the cap counts
+            tp = binding.Tapout(B, K, V, thresholds=thresholds)
+            c = pu.check_round_call(tp, rnd, torch.full((B,), arm, dtype=torch.int32, device=DEV), truncate=True, thresholds=thresholds)
+            assert c["accept_flagged"] + c["icdf_flagged"] + c["stop_flagged"] <= 1
+
+
+@pytest.mark.parametrize("policy", [binding.UCB1, binding.UCB_TUNED, binding.TS_BETA, binding.TS_GAUSS])
+@pytest.mark.parametrize("max_batch", [1, 3])
+@pytest.mark.parametrize("five", [False, True])
+def test_one_sequence_of_a_shared_bandit_is_its_own(policy, max_batch, five):
+    """With one sequence a shared bandit takes the launches of a bandit of its own: same arms and state as the separate calls."""
+    pool = dict(rules=(0, 1, 2, 3, 4), thresholds=(0.6, 0.8, 0.2, 0.2, 0.4)) if five else {}
+    a, b = (binding.Tapout(max_batch, 4, 3000, policy=policy, shared_bandit=True, **pool) for _ in range(2))
+    g = torch.Generator(device=DEV).manual_seed(1)
+    arm_a = arm_b = torch.zeros(1, dtype=torch.int32, device=DEV)
+    for t in range(8):
+        rnd = mixed_round(1, 4, 3000, bf16, bf16, seed=t)
+        u = torch.rand(1, a.cfg.n_arms, 48, generator=g, device=DEV)
+        arm_a = arm_a.clone()
+        args, out = a.round_args(rnd, arm_a, bool(t & 1), u_ts_next=u)
+        a.round(args)
+        ds = b.draft_stats(rnd["draft"], rnd["draft_tok"], rnd["k_len"], arm_b)
+        n = ds["n_stop"] if t & 1 else rnd["k_len"]
+        vf = b.verify(rnd["target"], rnd["draft"], ds["lse"], ds["logq_tok"], rnd["draft_tok"], n, rnd["u_accept"], rnd["u_sample"])
+        b.bandit_update(arm_b, vf["accept_len"], n, rnd["k_len"])
+        arm_b = b.bandit_select(1, u_ts=u)
+        torch.cuda.synchronize()
+        assert torch.equal(arm_a, arm_b) and torch.equal(out["verify"]["out_tok"], vf["out_tok"])
+        for x, y in zip(a.bandit_get_state(moments=True), b.bandit_get_state(moments=True)):
+            assert (x == y).all()
+    if five:
+        sa, sb = a.rule_state_get(), b.rule_state_get()
+        assert all((sa[k][:1] == sb[k][:1]).all() for k in ("accept_rate", "lam"))
