@@ -239,16 +239,25 @@ __device__ inline void draft_rows_lse_finish(const DraftLseRegs &r, int rows, in
 // -inf beyond V), so that a kernel can hold several requests in flight in few registers and widen them, exactly, when
 // their turn comes.
 template <int DT> struct Raw8 { u32x4 w[DT == TAPOUT_F32 ? 2 : 1]; };
+// Sixteen bytes at an element's address: one request whatever the alignment (the target's memory mode allows it; a
+// vector across two cache lines costs a second access).  Rows of an odd vocabulary size start at every alignment, and
+// element loads there made the slice kernel wait for memory several times per vector (V = 50257, 48 sequences, bfloat16
+// draft and binary32 target rows: 22.6 us with element loads, 14.4 with these; locate kernel 8.0 / 6.9).
+typedef uint32_t u32x4_at2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 template <int DT>
-__device__ inline Raw8<DT> load_raw8(const char *rowp, bool aligned, int j, int V)
+__device__ inline u32x4 load16(const char *p)
+{
+    if constexpr (DT == TAPOUT_F32) return *(const u32x4_at4 *)p;
+    else return *(const u32x4_at2 *)p;
+}
+template <int DT>
+__device__ inline Raw8<DT> load_raw8(const char *rowp, int j, int V)
 {
     Raw8<DT> r;
-    if (aligned && j + kPer <= V) {
-        if constexpr (DT == TAPOUT_BF16) {
-            r.w[0] = *(const u32x4 *)(rowp + (int64_t)j * 2);
-        } else {
-            r.w[0] = *(const u32x4 *)(rowp + (int64_t)j * 4); r.w[1] = *(const u32x4 *)(rowp + (int64_t)j * 4 + 16);
-        }
+    if (j + kPer <= V) {
+        r.w[0] = load16<DT>(rowp + (int64_t)j * Elem<DT>::size);
+        if constexpr (DT == TAPOUT_F32) r.w[1] = load16<DT>(rowp + (int64_t)j * 4 + 16);
     } else if (j >= V) {
         // beyond the row: nothing to load (the usual case in a row's last slice)
         constexpr uint32_t ninf = DT == TAPOUT_BF16 ? 0xff80ff80u : 0xff800000u;
@@ -550,7 +559,6 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
 
 struct Rows {
     const char *trow, *drow;
-    bool t_al, d_al;
 };
 
 template <int TD, int DD>
@@ -559,8 +567,6 @@ __device__ inline Rows job_rows(const VerifyArgs &a, int b, const SampleJob &job
     Rows r;
     r.trow = (const char *)row_address(a.tbase, TD, a.t_stride_b, a.t_stride_k, b, job.row);
     r.drow = (const char *)row_address(a.dbase, DD, a.d_stride_b, a.d_stride_k, b, job.kind == 1 ? job.row : 0);
-    r.t_al = ((uintptr_t)r.trow & 15u) == 0;
-    r.d_al = ((uintptr_t)r.drow & 15u) == 0;
     return r;
 }
 
@@ -813,10 +819,10 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     }
     Raw8<TD> qt[kChunks];
     Raw8<DD> qd[kChunks];
-    // A slice that lies wholly inside aligned rows (all but a row's last one) is requested in straight-line code:
+    // A slice that lies wholly inside the rows (all but a row's last one) is requested in straight-line code:
     // the per-request checks of the general path are branches, and across branches the compiler waits for every
     // outstanding request where the first chunk's would do.
-    const bool whole = live && r.t_al && (r.d_al || !resid) && (s + 1) * kSampleSlice <= a.V;       // wavefront-uniform
+    const bool whole = live && (s + 1) * kSampleSlice <= a.V;       // wavefront-uniform
     if (__builtin_expect(whole, 1)) {
         const char *tp = r.trow + (int64_t)base * Elem<TD>::size;
         const char *dp = r.drow + (int64_t)base * Elem<DD>::size;
@@ -826,7 +832,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
             if (c < kAhead) {
 #pragma unroll
                 for (int h = 0; h < (TD == TAPOUT_F32 ? 2 : 1); ++h)
-                    qt[c].w[h] = *(const u32x4 *)(tp + (int64_t)c * kWave * kPer * Elem<TD>::size + 16 * h);
+                    qt[c].w[h] = load16<TD>(tp + (int64_t)c * kWave * kPer * Elem<TD>::size + 16 * h);
             }
         }
         if (resid) {
@@ -834,15 +840,15 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
             for (int c = 0; c < kAhead; ++c)
 #pragma unroll
                 for (int h = 0; h < (DD == TAPOUT_F32 ? 2 : 1); ++h)
-                    qd[c].w[h] = *(const u32x4 *)(dp + (int64_t)c * kWave * kPer * Elem<DD>::size + 16 * h);
+                    qd[c].w[h] = load16<DD>(dp + (int64_t)c * kWave * kPer * Elem<DD>::size + 16 * h);
         }
     } else {
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
             qt[c] = Raw8<TD>{}; qd[c] = Raw8<DD>{};
             if (c < kAhead && live) {
-                qt[c] = load_raw8<TD>(r.trow, r.t_al, base + c * kWave * kPer, a.V);
-                if (resid) qd[c] = load_raw8<DD>(r.drow, r.d_al, base + c * kWave * kPer, a.V);
+                qt[c] = load_raw8<TD>(r.trow, base + c * kWave * kPer, a.V);
+                if (resid) qd[c] = load_raw8<DD>(r.drow, base + c * kWave * kPer, a.V);
             }
         }
     }
@@ -867,8 +873,8 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
         for (int c = 0; c < kChunks; ++c) {
             if (c + kAhead < kChunks) {
                 const int jn = base + (c + kAhead) * kWave * kPer;
-                qt[c + kAhead] = load_raw8<TD>(r.trow, r.t_al, jn, a.V);
-                if (resid) qd[c + kAhead] = load_raw8<DD>(r.drow, r.d_al, jn, a.V);
+                qt[c + kAhead] = load_raw8<TD>(r.trow, jn, a.V);
+                if (resid) qd[c + kAhead] = load_raw8<DD>(r.drow, jn, a.V);
             }
             float ct[kPer], cd[kPer];
             widen8<TD>(qt[c], ct);
@@ -974,22 +980,22 @@ __device__ inline void thread_weights(const Weights &w, const Rows &r, int s, in
     const int j0 = s * kSampleSlice + threadIdx.x * kThreadPer;
 #pragma unroll
     for (int g = 0; g < kThreadPer / kPer; ++g) {
-        // both rows' requests side by side where the run lies inside aligned rows (the usual case): the checks of the
+        // both rows' requests side by side where the run lies inside the rows (the usual case): the checks of the
         // general path are branches, and the compiler waits for the target row's data before it requests the draft row's
         const int j = j0 + g * kPer;
         const bool pair = w.kind == 1;
         Raw8<TD> qt;
         Raw8<DD> qd = Raw8<DD>{};
-        if (r.t_al && (r.d_al || !pair) && j + kPer <= V) {
+        if (j + kPer <= V) {
 #pragma unroll
-            for (int h = 0; h < (TD == TAPOUT_F32 ? 2 : 1); ++h) qt.w[h] = *(const u32x4 *)(r.trow + (int64_t)j * Elem<TD>::size + 16 * h);
+            for (int h = 0; h < (TD == TAPOUT_F32 ? 2 : 1); ++h) qt.w[h] = load16<TD>(r.trow + (int64_t)j * Elem<TD>::size + 16 * h);
             if (pair) {
 #pragma unroll
-                for (int h = 0; h < (DD == TAPOUT_F32 ? 2 : 1); ++h) qd.w[h] = *(const u32x4 *)(r.drow + (int64_t)j * Elem<DD>::size + 16 * h);
+                for (int h = 0; h < (DD == TAPOUT_F32 ? 2 : 1); ++h) qd.w[h] = load16<DD>(r.drow + (int64_t)j * Elem<DD>::size + 16 * h);
             }
         } else {
-            qt = load_raw8<TD>(r.trow, r.t_al, j, V);
-            if (pair) qd = load_raw8<DD>(r.drow, r.d_al, j, V);
+            qt = load_raw8<TD>(r.trow, j, V);
+            if (pair) qd = load_raw8<DD>(r.drow, j, V);
         }
         float xt[kPer], xd[kPer];
         widen8<TD>(qt, xt);

@@ -84,3 +84,17 @@ def test_one_sequence_of_a_shared_bandit_is_its_own(policy, max_batch, five):
     if five:
         sa, sb = a.rule_state_get(), b.rule_state_get()
         assert all((sa[k][:1] == sb[k][:1]).all() for k in ("accept_rate", "lam"))
+
+
+@pytest.mark.parametrize("V", [2047, 2049, 2055, 4097, 6150, 8191])
+@pytest.mark.parametrize("dt,tt", [(bf16, bf16), (bf16, f32), (f32, f32), (f32, bf16)])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_final_token_on_rows_at_every_alignment(V, dt, tt, fuse):
+    """Whole 2048-element slices, the last short one and the in-slice search on rows that start at any element."""
+    B, K = 9, 3
+    rnd = mixed_round(B, K, V, dt, tt, seed=V)
+    tp = binding.Tapout(B, K, V)
+    tp.set_option("fuse_head", fuse)
+    for u in (0.0, 0.5, 1.0 - 2.0 ** -24):                     # the first slice, a middle one, the row's last elements
+        rnd["u_sample"] = torch.full((B,), u, device=DEV)
+        assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
