@@ -84,31 +84,15 @@ __device__ inline int ts_gauss_arm(const double *S, const int64_t *N, int A, con
     return best;
 }
 
-__device__ inline int ts_arm(const double *S, const int64_t *N, int A, const float *u, bool *exhausted)
-{
-    int best = 0;
-    double best_v = -INFINITY;
-    for (int a = 0; a < A; ++a) {
-        double alpha = 1.0 + S[a];
-        double beta = 1.0 + ((double)N[a] - S[a]);
-        const float *ua = u + (size_t)a * TAPOUT_TS_UNIFORMS_PER_ARM;
-        double g1 = gamma_draw(alpha, ua, exhausted);
-        double g2 = gamma_draw(beta, ua + kAttempts * 3, exhausted);
-        double th = g1 / (g1 + g2);
-        if (a == 0 || th > best_v) { best = a; best_v = th; }
-    }
-    return best;
-}
-
-__device__ inline int select_arm(const BanditArgs &a, size_t nb, const float *u_ts, bool *ex)
+// Every policy but Thompson Sampling with Beta posteriors, whose draws take a lane each.
+__device__ inline int select_arm(const BanditArgs &a, size_t nb, const float *u_ts)
 {
     const double *S = a.sum_r + nb;
     const int64_t *N = a.count + nb;
     const float *u = u_ts ? u_ts + nb * TAPOUT_TS_UNIFORMS_PER_ARM : nullptr;
     if (a.policy == TAPOUT_UCB1) return ucb1_arm(S, N, a.n_arms);
     if (a.policy == TAPOUT_UCB_TUNED) return ucb_tuned_arm(S, a.sum_r2 + nb, N, a.n_arms);
-    if (a.policy == TAPOUT_TS_GAUSS) return ts_gauss_arm(S, N, a.n_arms, u);
-    return ts_arm(S, N, a.n_arms, u, ex);
+    return ts_gauss_arm(S, N, a.n_arms, u);
 }
 
 __device__ inline void apply_reward(const BanditArgs &a, int nb, int arm, int m, int n, int g)
@@ -119,22 +103,6 @@ __device__ inline void apply_reward(const BanditArgs &a, int nb, int arm, int m,
     a.count[(size_t)nb * a.n_arms + arm] += 1;
     a.sum_r[(size_t)nb * a.n_arms + arm] += r;
     a.sum_r2[(size_t)nb * a.n_arms + arm] += r * r;
-}
-
-// Token-level bandits (Section 3.1 / 3.2): position k < m is an accepted play (reward 1) of the arm chosen
-// there, position m < n the rejected one (reward 0); later positions were never evaluated.
-__device__ inline void apply_token_rewards(const BanditArgs &a, int nb, const int32_t *arm_b, int m, int n)
-{
-    if (n > a.positions) n = a.positions;
-    for (int k = 0; k < n && k <= m; ++k) {
-        const int arm = arm_b[k];
-        if (arm < 0 || arm >= a.n_arms) continue;
-        const size_t i = ((size_t)nb * a.positions + k) * a.n_arms + arm;
-        const double r = k < m ? 1.0 : 0.0;
-        a.count[i] += 1;
-        a.sum_r[i] += r;
-        a.sum_r2[i] += r;
-    }
 }
 
 // Carried state of the stateful stop rules after one draft of sequence b (Appendix A.1).
@@ -161,42 +129,18 @@ __device__ inline bool playable(const BanditArgs &a, int b, const int32_t *arm, 
     return a.positions > 1 || (arm[b] >= 0 && arm[b] < a.n_arms);           // token-level arms are checked per position
 }
 
-__device__ inline void play(const BanditArgs &a, int nb, int b, const int32_t *arm, const int32_t *accept_len,
-                            const int32_t *n_draft, const int32_t *gamma)
-{
-    if (a.positions > 1) apply_token_rewards(a, nb, arm + (size_t)b * a.positions, accept_len[b], n_draft[b]);
-    else apply_reward(a, nb, arm[b], accept_len[b], n_draft[b], gamma[b]);
-}
-
 // Update of sequence b's own sequence-level bandit followed by its next selection, by one thread: the selection
 // reads the state the thread has just written (program order).
 __device__ inline void update_select_one(const BanditArgs &a, int b, const int32_t *arm, const int32_t *accept_len,
                                          const int32_t *n_draft, const int32_t *gamma, const uint8_t *active,
                                          const float *u_ts, int32_t *arm_out, uint32_t *flags)
 {
-    if (playable(a, b, arm, n_draft, gamma, active)) play(a, b, b, arm, accept_len, n_draft, gamma);
+    if (playable(a, b, arm, n_draft, gamma, active)) apply_reward(a, b, arm[b], accept_len[b], n_draft[b], gamma[b]);
     if (a.accept_rate && !(active && !active[b])) {
         const int n = n_draft[b];
         if (n >= 1 && (a.round_K == 0 || n <= a.round_K)) advance_rule_state(a, b, accept_len[b], n);
     }
-    bool ex = false;
-    arm_out[b] = select_arm(a, (size_t)b * a.n_arms, u_ts, &ex);
-    if (flags) flags[b] = ex ? TAPOUT_FLAG_SAMPLER_EXHAUSTED : 0u;
-}
-
-// The same restricted to the UCB policies (no caller uniforms, no Gamma / Gaussian draws in the code).
-__device__ inline void update_select_ucb(const BanditArgs &a, int b, const int32_t *arm, const int32_t *accept_len,
-                                         const int32_t *n_draft, const int32_t *gamma, const uint8_t *active,
-                                         int32_t *arm_out, uint32_t *flags)
-{
-    if (playable(a, b, arm, n_draft, gamma, active)) play(a, b, b, arm, accept_len, n_draft, gamma);
-    if (a.accept_rate && !(active && !active[b])) {
-        const int n = n_draft[b];
-        if (n >= 1 && (a.round_K == 0 || n <= a.round_K)) advance_rule_state(a, b, accept_len[b], n);
-    }
-    const size_t nb = (size_t)b * a.n_arms;
-    arm_out[b] = a.policy == TAPOUT_UCB1 ? ucb1_arm(a.sum_r + nb, a.count + nb, a.n_arms)
-                                         : ucb_tuned_arm(a.sum_r + nb, a.sum_r2 + nb, a.count + nb, a.n_arms);
+    arm_out[b] = select_arm(a, (size_t)b * a.n_arms, u_ts);
     if (flags) flags[b] = 0u;
 }
 

@@ -1,8 +1,10 @@
 """The rules by which the library picks a launch shape or a kernel from sizes, types and alignment, at the sizes where each
 rule turns, against the CPU oracle.  Tolerances are parity_util's."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as orc
 from paper_2511_02017_amd import binding
 from tests import parity_util as pu
 from tests.test_gpu_parity import random_arms, random_round
@@ -95,6 +97,34 @@ def test_final_token_on_rows_at_every_alignment(V, dt, tt, fuse):
     rnd = mixed_round(B, K, V, dt, tt, seed=V)
     tp = binding.Tapout(B, K, V)
     tp.set_option("fuse_head", fuse)
-    for u in (0.0, 0.5, 1.0 - 2.0 ** -24):                     # the first slice, a middle one, the row's last elements
+    # The first slice, a middle one, the row's last elements.  (Not u = 0: the target is then the edge of the first cell, a
+    # near tie by definition in all B sequences; else a cell edge within 1e-9 of the target is a chance of about V 1e-9.)
+    for u in (2.0 ** -12, 0.5, 1.0 - 2.0 ** -24):
         rnd["u_sample"] = torch.full((B,), u, device=DEV)
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
+
+
+@pytest.mark.parametrize("policy", [binding.TS_BETA, binding.UCB_TUNED])
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("B,K,A", [(3, 2, 8), (5, 16, 1), (67, 17, 3), (2, 65, 5)])
+def test_token_level_bandit_at_the_edges_of_its_workgroups(policy, shared, B, K, A):
+    """Sixteen positions per pass of the selection's workgroups, 64 positions per workgroup of the update."""
+    tp = binding.Tapout(B, K, 100, policy=policy, shared_bandit=shared, token_level=True, rules=(0,) * A, thresholds=(0.5,) * A)
+    ob = orc.Bandit(policy, 1 if shared else B, A, positions=K)
+    g = torch.Generator().manual_seed(K)
+    for r in range(12):
+        u = torch.rand(B, K, A, 48, generator=g)
+        if r == 5:
+            u[B - 1, K - 1, :, ::3] = 0.0                       # every attempt of the last position's samplers is rejected
+        fl = torch.full((B,), 7, dtype=torch.int32, device=DEV)
+        arm = tp.bandit_select(B, u_ts=u.to(DEV) if policy == binding.TS_BETA else None, flags=fl)
+        o_arm, o_fl = ob.select(B, u.numpy())
+        assert (arm.cpu().numpy() == o_arm).all() and (fl.cpu().numpy().astype(np.uint32) == o_fl).all(), f"round {r}"
+        n = torch.randint(0, K + 2, (B,), generator=g, dtype=torch.int32).clamp_(max=K)
+        m = (torch.rand(B, generator=g) * (n + 1)).floor().clamp(max=n).to(torch.int32)
+        gamma = torch.full((B,), K, dtype=torch.int32)
+        arm[0, 0] = A if r == 7 else arm[0, 0]                  # an arm out of range is not played
+        tp.bandit_update(arm, m.to(DEV), n.to(DEV), gamma.to(DEV))
+        ob.update(arm.cpu().numpy(), m.numpy(), n.numpy(), gamma.numpy())
+    s, q, c = tp.bandit_get_state(moments=True)
+    assert (c == ob.count).all() and (s == ob.sum_r).all() and (q == ob.sum_r2).all()
