@@ -140,8 +140,8 @@ typedef struct {
     double adaedl_eps;                    /* step of lambda (0.01)                              */
     double adaedl_rate0;                  /* initial smoothed acceptance rate (= adaedl_alpha)  */
     int32_t draft_sampling;               /* 1: tapout_draft_stats may draw the draft tokens    */
-                                          /* (u_draft); sizes the final-token scratch for one   */
-                                          /* job per draft row instead of one per sequence      */
+                                          /* (u_draft); sizes the scratch for slice sums of     */
+                                          /* every draft row                                    */
     int32_t adaedl_steer;                 /* 0: lambda follows the smoothed rate; 1: r itself   */
 } tapout_config;
 
@@ -612,8 +612,9 @@ enum {
     TAPOUT_PROFILE_VERIFY_SLICES = 5,   /* final token: slice sums of the row pair                  */
     TAPOUT_PROFILE_VERIFY_LOCATE = 6,   /* final token: normalisers, slice, token                   */
     TAPOUT_PROFILE_UPDATE = 7,          /* bandit update                                            */
-    TAPOUT_PROFILE_SAMPLE_HEAD = 8,     /* draft-token sampling: one job per draft row              */
-    TAPOUT_PROFILE_SAMPLE_SLICES = 9,   /* draft-token sampling: slice sums of every draft row      */
+    TAPOUT_PROFILE_SAMPLE_HEAD = 8,     /* not launched (the slice kernel does this)                */
+    TAPOUT_PROFILE_SAMPLE_SLICES = 9,   /* draft-token sampling: slice sums of every draft row;     */
+                                        /* signals + stop scan                                      */
     TAPOUT_PROFILE_SAMPLE_LOCATE = 10,  /* draft-token sampling: slice, token                       */
     TAPOUT_PROFILE_STREAM_PAIR = 11,    /* tapout_round: draft and target rows in one streaming pass */
     TAPOUT_PROFILE_KINDS = 12

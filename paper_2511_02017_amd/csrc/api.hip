@@ -17,8 +17,9 @@ struct tapout_ctx {
     tapout_config cfg;
     Partial *part = nullptr;      size_t part_cap = 0;       // slice partials of the draft pass (and of a shard pass)
     Partial *part_t = nullptr;                                 // slice partials of the target pass (same capacity)
-    double *part1 = nullptr, *part2 = nullptr;                // residual sampler slice sums
-    JobRecord *jobs = nullptr;                                 // per final-token job: what to draw from, and its band list
+    double *part1 = nullptr, *part2 = nullptr;                // slice sums of the inverse CDFs
+    double *sampled_lse = nullptr;                             // [max_batch, max_k] lse of the draft rows (draft-token sampling only)
+    JobRecord *jobs = nullptr;                                 // per sequence: what its final token is drawn from, and its band list
     uint32_t *flags_ws = nullptr;
     int32_t *arm_played = nullptr;                             // [max_batch]: the arms a round was drafted under (see draft_stats_impl)
     double *exp_table = nullptr;                               // 2^(k/256), k = 0..255, for the final-token passes
@@ -329,8 +330,8 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     c->positions = cfg->granularity == TAPOUT_TOKEN_LEVEL ? cfg->max_k : 1;
     const size_t nstate = (size_t)cfg->n_bandits * c->positions * cfg->n_arms;
     c->nsl_max = (cfg->vocab + kSampleSlice - 1) / kSampleSlice;
-    // final-token jobs: one per sequence (verification) or one per draft row (draft-token sampling)
-    const size_t njobs = (size_t)cfg->max_batch * (cfg->draft_sampling ? cfg->max_k : 1);
+    // slice sums: five per slice of a sequence's row pair (verification), or one per slice of a draft row (draft-token sampling)
+    const size_t nsums = (size_t)cfg->max_batch * (cfg->draft_sampling && cfg->max_k > 5 ? cfg->max_k : 5);
     // 2^(k/256), then exp(x) of every bfloat16 x with 2^-12 <= |x| < 63.5: entry idx (x > 0) or pairs + idx (x < 0),
     // idx = 1 + (magnitude bits - (115 << 7)); idx 0 stands for all smaller magnitudes and holds NaN (the kernels
     // notice and compute), the last idx for all larger ones and holds zeros
@@ -353,11 +354,12 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     }
     bool ok = hipMalloc(&c->part, c->part_cap * sizeof(Partial)) == hipSuccess
            && hipMalloc(&c->part_t, c->part_cap * sizeof(Partial)) == hipSuccess
-           && hipMalloc(&c->part1, njobs * c->nsl_max * 5 * sizeof(double)) == hipSuccess
-           && hipMalloc(&c->part2, njobs * c->nsl_max * sizeof(double)) == hipSuccess
+           && hipMalloc(&c->part1, nsums * c->nsl_max * sizeof(double)) == hipSuccess
+           && hipMalloc(&c->part2, (size_t)cfg->max_batch * c->nsl_max * sizeof(double)) == hipSuccess
+           && (!cfg->draft_sampling || hipMalloc(&c->sampled_lse, (size_t)cfg->max_batch * cfg->max_k * sizeof(double)) == hipSuccess)
            && hipMalloc(&c->exp_table, table.size() * sizeof(double)) == hipSuccess
            && hipMemcpy(c->exp_table, table.data(), table.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess
-           && hipMalloc(&c->jobs, njobs * sizeof(JobRecord)) == hipSuccess
+           && hipMalloc(&c->jobs, (size_t)cfg->max_batch * sizeof(JobRecord)) == hipSuccess
            && hipMalloc(&c->flags_ws, (size_t)cfg->max_batch * sizeof(uint32_t)) == hipSuccess
            && hipMalloc(&c->arm_played, (size_t)cfg->max_batch * sizeof(int32_t)) == hipSuccess
            && hipMalloc(&c->sum_r, nstate * sizeof(double)) == hipSuccess
@@ -397,7 +399,7 @@ tapout_status tapout_destroy(tapout_ctx *ctx)
     profile_release(ctx);
     (void)hipFree(ctx->part); (void)hipFree(ctx->part_t); (void)hipFree(ctx->part1); (void)hipFree(ctx->part2);
     (void)hipFree(ctx->jobs); (void)hipFree(ctx->flags_ws); (void)hipFree(ctx->arm_played);
-    (void)hipFree(ctx->exp_table);
+    (void)hipFree(ctx->exp_table); (void)hipFree(ctx->sampled_lse);
     (void)hipFree(ctx->sum_r); (void)hipFree(ctx->sum_r2); (void)hipFree(ctx->count);
     (void)hipFree(ctx->prev_entropy); (void)hipFree(ctx->accept_rate); (void)hipFree(ctx->lambda); (void)hipFree(ctx->round_entropy);
     delete ctx;
@@ -529,22 +531,13 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
     hipError_t e = pair ? stream_pair(ctx, r, draft->dtype, *pair, st)
                         : timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_row_reduce(r, draft->dtype, true, st, tm); });
     if (e != hipSuccess) return hip_fail(ctx, e, "draft pass launch");
+    SampleArgs sa{};
     if (u_draft) {
-        // draw the tokens first (one final-token job per draft row), so that the finaliser can form log q(tok)
-        VerifyArgs va{};
-        va.tbase = draft->ptr; va.t_dtype = draft->dtype; va.t_stride_b = draft->stride_b; va.t_stride_k = draft->stride_k;
-        va.dbase = draft->ptr; va.d_dtype = draft->dtype; va.d_stride_b = draft->stride_b; va.d_stride_k = draft->stride_k;
-        va.B = B; va.K = K; va.V = V; va.nsplit = nsplit; va.nsl = (V + kSampleSlice - 1) / kSampleSlice;
-        va.jps = K; va.n_jobs = (int32_t)rows;
-        va.part = ctx->part; va.n_draft = k_len; va.u_sample = u_draft; va.tok_direct = sampled_tok;
-        va.flags_ws = ctx->flags_ws; va.jobs = ctx->jobs;
-        va.part1 = ctx->part1; va.part2 = ctx->part2; va.exp_table = ctx->exp_table;
-        if (!ctx->exp_lookup) va.vflags |= kVerifyNoExpTable;
-        e = timed(ctx, TAPOUT_PROFILE_SAMPLE_HEAD, [&](Timing tm) { return launch_sample_head(va, st, tm); });
-        for (int pass = 1; pass <= 2 && e == hipSuccess; ++pass)
-            e = timed(ctx, TAPOUT_PROFILE_SAMPLE_SLICES + pass - 1, [&](Timing tm) { return launch_verify(va, pass, st, tm); });
-        if (e != hipSuccess) return hip_fail(ctx, e, "draft sampling launch");
-        draft_tok = sampled_tok;
+        sa.base = draft->ptr; sa.dtype = draft->dtype; sa.stride_b = draft->stride_b; sa.stride_k = draft->stride_k;
+        sa.vflags = ctx->exp_lookup ? 0 : kVerifyNoExpTable;
+        sa.B = B; sa.K = K; sa.V = V; sa.nsplit = nsplit; sa.nsl = (V + kSampleSlice - 1) / kSampleSlice;
+        sa.part = ctx->part; sa.k_len = k_len; sa.u = u_draft; sa.tok = sampled_tok; sa.logq_tok = logq_tok;
+        sa.sums = ctx->part1; sa.lse = ctx->sampled_lse; sa.exp_table = ctx->exp_table;
     }
     DraftFinalArgs f{};
     f.base = draft->ptr; f.dtype = draft->dtype; f.stride_b = draft->stride_b; f.stride_k = draft->stride_k;
@@ -561,6 +554,13 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
         ctx->round_K = K;
     }
     if (defer) { *defer = f; *defer_nsplit = nsplit; return TAPOUT_OK; }
+    if (u_draft) {
+        // the epilogue waits for no token (their log q is formed where they are found) and rides in the slice launch
+        f.draft_tok = nullptr; f.logq_tok = nullptr; f.sampled_lse = ctx->sampled_lse;
+        e = timed(ctx, TAPOUT_PROFILE_SAMPLE_SLICES, [&](Timing tm) { return launch_sample(sa, f, 0, st, tm); });
+        if (e == hipSuccess) e = timed(ctx, TAPOUT_PROFILE_SAMPLE_LOCATE, [&](Timing tm) { return launch_sample(sa, f, 1, st, tm); });
+        return e == hipSuccess ? TAPOUT_OK : hip_fail(ctx, e, "draft sampling launch");
+    }
     e = timed(ctx, TAPOUT_PROFILE_DRAFT_FINALIZE, [&](Timing tm) { return launch_draft_finalize(f, st, tm); });
     return e == hipSuccess ? TAPOUT_OK : hip_fail(ctx, e, "draft finalize launch");
 }
@@ -722,7 +722,7 @@ tapout_status tapout_verify_accept_sharded(tapout_ctx *ctx, const tapout_shard_s
     DeviceGuard guard(ctx->cfg.device);
     hipStream_t st = (hipStream_t)stream;
     VerifyArgs va{};
-    va.B = B; va.K = K; va.V = V; va.nsplit = G; va.shards = G; va.jps = 1; va.n_jobs = B;
+    va.B = B; va.K = K; va.V = V; va.nsplit = G; va.shards = G;
     va.part = (const Partial *)stats;
     va.logq_tok = logq_tok; va.draft_tok = draft_tok; va.n_draft = n_draft; va.greedy = greedy; va.u_accept = u_accept;
     va.draft_lse = draft_lse; va.final_jobs = (SampleJob *)final_jobs;
@@ -750,7 +750,6 @@ tapout_status shard_final_args(tapout_ctx *ctx, const tapout_logits *target_shar
     va.tbase = target_shard->ptr; va.t_dtype = target_shard->dtype; va.t_stride_b = target_shard->stride_b; va.t_stride_k = target_shard->stride_k;
     va.dbase = draft_shard->ptr; va.d_dtype = draft_shard->dtype; va.d_stride_b = draft_shard->stride_b; va.d_stride_k = draft_shard->stride_k;
     va.B = B; va.K = K; va.V = Vs; va.nsl = (Vs + kSampleSlice - 1) / kSampleSlice;
-    va.jps = 1; va.n_jobs = B;
     va.jobs = ctx->jobs; va.part1 = ctx->part1; va.part2 = ctx->part2; va.exp_table = ctx->exp_table;
     if (!ctx->exp_lookup) va.vflags |= kVerifyNoExpTable;
     a.jobs_in = (const SampleJob *)jobs;
@@ -877,7 +876,7 @@ hipError_t verify_rest(tapout_ctx *ctx, const VerifyCall &c, hipStream_t st, con
     va.tbase = c.target->ptr; va.t_dtype = c.target->dtype; va.t_stride_b = c.target->stride_b; va.t_stride_k = c.target->stride_k;
     va.dbase = c.draft->ptr; va.d_dtype = c.draft->dtype; va.d_stride_b = c.draft->stride_b; va.d_stride_k = c.draft->stride_k;
     va.B = c.B; va.K = c.K; va.V = c.V; va.nsplit = c.slices.n; va.nsl = c.nsl;
-    va.jps = 1; va.n_jobs = c.B; va.fused_head = c.fused ? 1 : 0;
+    va.fused_head = c.fused ? 1 : 0;
     va.part = ctx->part_t;
     va.draft_lse = c.draft_lse; va.logq_tok = c.logq_tok; va.draft_tok = c.draft_tok; va.n_draft = c.n_draft; va.greedy = c.greedy;
     va.u_accept = c.u_accept; va.u_sample = c.u_sample;

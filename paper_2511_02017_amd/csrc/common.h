@@ -113,6 +113,9 @@ struct DraftFinalArgs {
     const double *lambda;         // [B, n_arms] AdaEDL thresholds
     double adaedl_gamma;
     float *round_entropy;         // [B, K] entropies of this draft, kept for the state update
+    // the library draws the draft tokens after this epilogue: it leaves each row's lse here (in double) for their log q, and a
+    // bad row gets no token (BAD_TOKEN with BAD_ROW); else NULL
+    double *sampled_lse;
     // vocabulary-sharded input: part holds the records of `shards` vocabulary shards, shard-major [shards, B*K], instead
     // of slice partials [B*K, nsplit] (then nsplit = shards; the argmax of a record is exact and global, the logit of
     // the drafted token travels in the record, and base is not used)
@@ -177,11 +180,6 @@ struct VerifyArgs {
     const void *dbase; int32_t d_dtype; int32_t d_nsplit; int64_t d_stride_b, d_stride_k;
     int32_t B, K, V, nsplit;      // nsplit: slices per row of the streaming pass
     int32_t nsl;                  // slices per row of the final-token passes (kSampleSlice elements each)
-    // The slice and locate kernels work on "jobs": one per sequence for verification (jps = 1, job j belongs to
-    // sequence j), one per draft row for draft-token sampling (jps = K, job j = row j % K of sequence j / K).
-    // jobs, part1, part2 and u_sample are indexed by job; the rows of a job are rows job.row of its sequence.
-    int32_t jps, n_jobs;
-    int32_t *tok_direct;          // draft-token sampling: token of job j goes to tok_direct[j] instead of out_tok
     int32_t shards;               // > 0: part holds records of vocabulary shards, shard-major [shards, B*(K+1)] (head kernel only)
     int32_t fused_head;           // 1: no head launch; every workgroup of the slice kernel works out its sequence's job itself
     SampleJob *final_jobs;        // sharded head: the job of every sequence for the caller (or NULL)
@@ -191,11 +189,11 @@ struct VerifyArgs {
     int32_t *accept_len, *out_tok, *n_out;
     float *target_lse, *logp_tok; int32_t *target_top1; uint32_t *flags;
     uint32_t *flags_ws;           // internal copy of the flags (always present)
-    JobRecord *jobs;              // [jobs]
-    double *part1;                // [jobs, nsl, 5]  A, B, R~, D, U of each slice
+    JobRecord *jobs;              // [B]
+    double *part1;                // [B, nsl, 5]  A, B, R~, D, U of each slice
     double *part2;                // [B, nsl]     exact weight of each slice (slow path)
     const double *exp_table;      // 2^(k/256), k = 0..255, then the kExpBf16Doubles entries of the bfloat16 table
-    // tapout_round (jps = 1): the locate kernel also ends the round of its sequence: reward into the sequence's bandit
+    // tapout_round: the locate kernel also ends the round of its sequence: reward into the sequence's bandit
     // (arm b_arm_in[b], accept_len, n_draft, b_gamma, b_active as tapout_bandit_update) and the arm of the next round
     // (b_arm_out, b_flags as tapout_bandit_select).  Sequence-level UCB bandits, one per sequence.
     int32_t bandit_tail;
@@ -222,11 +220,22 @@ inline bool own_q_shape(int K, int nsplit_target, int nsplit_draft)
     return fits(K + 1, nsplit_target) && fits(K, nsplit_draft);
 }
 
-// Draft-token sampling (Algorithm 1, the sampling step of the draft loop): one job per live draft row with the
-// row's maximum as exponent reference; bad live rows get token -1 at once.  The slice and locate kernels of
-// the final token then draw the tokens.  Arguments as VerifyArgs with the draft tensor in the target slots:
-// tbase/t_* = draft logits, part = draft partials [B*K, nsplit], n_draft = k_len (or NULL), jps = K.
-hipError_t launch_sample_head(const VerifyArgs &a, hipStream_t st, Timing tm);
+// Draft-token sampling (Algorithm 1, the sampling step of the draft loop): the inverse CDF of every live draft row, from
+// the partials of the draft pass (the rows' maxima) and the logits.
+struct SampleArgs {
+    const void *base; int32_t dtype; int32_t vflags; int64_t stride_b, stride_k;      // vflags: kVerifyNoExpTable
+    int32_t B, K, V, nsplit;      // nsplit: slices per row of the streaming pass
+    int32_t nsl;                  // slices per row of this pass (kSampleSlice elements each)
+    int32_t n_waves;              // wavefronts of the slice launch, and the step from one of a wavefront's slices to its next:
+    int32_t step_b, step_k, step_s;   // n_waves = (step_b * K + step_k) * nsl + step_s
+    const Partial *part; const int32_t *k_len; const float *u;
+    int32_t *tok; float *logq_tok;    // [B, K] token of each live row (-1: bad row) and its log q (or NULL)
+    double *sums;                 // [B * K, nsl]  sum of exp(x - row maximum) over each slice
+    const double *lse;            // [B * K] from the epilogue
+    const double *exp_table;
+};
+// pass 0: slice sums (fills in n_waves and the steps), and the draft epilogue `fin` beside them in one launch; 1: tokens.
+hipError_t launch_sample(SampleArgs a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm);
 
 // Final token over vocabulary shards (see tapout_shard_final_sums / tapout_shard_final_token).  The VerifyArgs
 // describe this shard's column slices (V = its width, nsl = its slices, jobs / part1 / part2 of the context).

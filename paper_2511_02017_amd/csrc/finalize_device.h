@@ -1,6 +1,6 @@
-// Device code of the draft epilogue (see finalize.hip), in a header because two kernels run it: the epilogue kernel
+// Device code of the draft epilogue (see finalize.hip), in a header because several kernels run it: the epilogue kernel
 // of its own, and the final-token locate kernel of a whole-round call, whose launch carries the epilogue's
-// workgroups beside its own.
+// workgroups beside its own (as does the slice kernel of the draft-token draw).
 #pragma once
 #include <type_traits>
 
@@ -183,7 +183,7 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
             float lse, H, p1, p2, mg;
             double lse_d = NAN;
             if (__builtin_expect(r.bad, 0)) {
-                f |= TAPOUT_FLAG_BAD_ROW;
+                f |= TAPOUT_FLAG_BAD_ROW | (a.sampled_lse ? TAPOUT_FLAG_BAD_TOKEN : 0u);
                 lse = H = p1 = p2 = mg = NAN;
             } else {
                 const RowSignals g = row_signals(r, a.V > 1);
@@ -191,6 +191,7 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
                 lse = (float)g.lse; H = (float)g.H;
                 p1 = (float)g.p1; p2 = (float)g.p2; mg = (float)g.margin;
             }
+            if (a.sampled_lse) a.sampled_lse[i] = lse_d;
             if (a.lse) a.lse[i] = lse;
             if (a.entropy) a.entropy[i] = H;
             if (a.p_top1) a.p_top1[i] = p1;

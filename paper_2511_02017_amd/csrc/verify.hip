@@ -750,12 +750,9 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     __shared__ double shT[256];
     __shared__ __align__(16) unsigned char sh_raw[kRaw];
     warm_args(a);
-    // (the grid's shape from the arguments, not from the hidden ones: see warm_args)
-    const int j = blockIdx.z * min(a.n_jobs, 65535) + blockIdx.y;
     [[maybe_unused]] const int wg = WG_LINEAR();
     WG_STAMP(g_stamps_slices, 8, wg, 0);                         // entry
-    if (j >= a.n_jobs) return;
-    const int b = j / a.jps;
+    const int b = blockIdx.y;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     // FUSED: the sequence's last workgroup writes the sequence's outputs, from its first wavefront, which therefore
     // takes the group's last slice: most often none at all, or the row's short last one
@@ -792,7 +789,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
         uint8_t *sh_dec = q;
         job = verify_head<false>(a, b, writer, sh_part, sh_dec, sh_flags, sh_bcast, sh_lse, sh_qrows, shT, request_table);
     } else {
-        job = a.jobs[j].job;
+        job = a.jobs[b].job;
     }
     WG_STAMP(g_stamps_slices, 8, wg, 1);                         // job known
     if (job.kind == 0) return;
@@ -906,8 +903,8 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
                         const double diff = fma(-lam, bv, av);
                         if (fabs(diff) < band * bv) {
                             U += bv;
-                            const int pos = atomicAdd(&a.jobs[j].band_cnt, 1);
-                            if (pos < kBandCap) a.jobs[j].band_idx[pos] = base + c * kWave * kPer + i;
+                            const int pos = atomicAdd(&a.jobs[b].band_cnt, 1);
+                            if (pos < kBandCap) a.jobs[b].band_idx[pos] = base + c * kWave * kPer + i;
                         }
                     }
                 }
@@ -942,7 +939,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     A = wave_sum_d(A) * sc.ct;
     if (resid) { Bs = wave_sum_d(Bs) * sc.cd; R = wave_sum_d(R) * sc.ct; D = wave_sum_d(D) * sc.cd; U = wave_sum_d(U) * sc.cd; }
     if (lane == 0) {
-        double *o = a.part1 + ((int64_t)j * a.nsl + s) * kSliceVals;
+        double *o = a.part1 + ((int64_t)b * a.nsl + s) * kSliceVals;
         o[0] = A; o[1] = Bs; o[2] = R; o[3] = D; o[4] = U;
     }
     WG_STAMP(g_stamps_slices, 8, wg, 7);                         // first wavefront's sums stored
@@ -1070,6 +1067,65 @@ __device__ inline int locate_in_slice(const Weights &w, const Rows &r, int s, in
     return h == 0x7fffffff ? -1 : h;
 }
 
+// Token of a draw: the first element whose running sum over the row exceeds `target`; whole workgroup.  z_mine: the weight
+// of slice threadIdx.x (rows of at most kVBlock slices; others call slice_weight, one thread).
+template <int TD, int DD, class SliceWeight>
+__device__ inline int find_token(const Weights &w, const Rows &r, int V, int nsl, const double *T, double target, double z_mine,
+                                 SliceWeight slice_weight, LocateShared *sh, int &phase)
+{
+    const int tid = threadIdx.x;
+    // slice whose inclusive prefix (slice order) first exceeds the target
+    double cum_at = 0.0;
+    int s_found = -1;
+    if (__builtin_expect(nsl <= kVBlock, 1)) {
+        if (tid >= nsl) z_mine = 0.0;
+        double ztot;
+        const double excl = block_excl_scan_d(z_mine, sh->scan[phase++ & 1], &ztot);
+        const int cand = wave_min_i32((tid < nsl && excl + z_mine > target) ? tid : 0x7fffffff);
+        if ((tid & (kWave - 1)) == 0) sh->hits[phase & 1][tid / kWave] = cand;
+        __syncthreads();
+        const int *hh = sh->hits[phase & 1];
+        const int sf = min(min(hh[0], hh[1]), min(hh[2], hh[3]));
+        ++phase;
+        s_found = sf == 0x7fffffff ? -1 : sf;
+        if (tid == s_found) sh->bc[0] = excl;
+        __syncthreads();
+        if (s_found >= 0) cum_at = sh->bc[0];
+    } else {
+        // very large vocabularies: the first thread walks the slice weights
+        if (tid == 0) {
+            double c = 0.0; int sf = -1;
+            for (int s = 0; s < nsl; ++s) { const double v = slice_weight(s); if (c + v > target) { sf = s; break; } c += v; }
+            sh->bc[0] = c; sh->slice = sf;
+        }
+        __syncthreads();
+        cum_at = sh->bc[0]; s_found = sh->slice;
+        __syncthreads();
+    }
+    LOCATE_STAMP(3);                                             // slice found
+    // slice sums and the in-slice scan round differently: if the crossing is not inside the chosen
+    // slice, continue into the following ones
+    int token = -1;
+    if (s_found >= 0) {
+        double cum = cum_at;
+        for (int s = s_found; s < nsl && token < 0; ++s) {
+            double slice_total;
+            token = locate_in_slice<TD, DD>(w, r, s, V, T, cum, target, sh, phase++, &slice_total);
+            cum += slice_total;
+        }
+    }
+    if (__builtin_expect(token < 0, 0)) {
+        // rounding left no crossing: the largest index with positive weight
+        for (int s = 0; s < nsl; ++s) {
+            double slice_total;
+            locate_in_slice<TD, DD>(w, r, s, V, T, 0.0, INFINITY, sh, phase++, &slice_total, true);
+        }
+        __syncthreads();
+        token = sh->last;
+    }
+    return token;
+}
+
 // Band elements of a sequence (see the slice kernel).  Each listed element is evaluated with the exact L; what it
 // contributed to the slice sums under L~ (recomputed here with the slice kernel's own arithmetic, hence the same
 // number) is taken back: correction = max(0, a - L b) - (max(0, a - L~ b) - delta [a > L~ b] b).  The list is
@@ -1124,7 +1180,7 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     // accepted lengths of an earlier one, so it rides along as workgroups of its own behind the others, sixteen
     // sequences each (sixteen lanes per sequence), instead of taking a launch after this one.
     if (a.bandit_tail == 2) {
-        const int first = (FIN ? a.B : 0) + a.n_jobs;
+        const int first = (FIN ? a.B : 0) + a.B;
         if ((int)blockIdx.x >= first) {
             update_select_ts_lanes(a.bandit, ((int)blockIdx.x - first) * (kVBlock / 16) + (int)(threadIdx.x >> 4), threadIdx.x & 15,
                                    a.b_arm_in, a.accept_len, a.n_draft, a.b_gamma, a.b_active, a.b_u_ts, a.b_arm_out, a.b_flags);
@@ -1143,12 +1199,11 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     __shared__ double shT[256];
     __shared__ double sh_red[kSliceVals][kVBlock / kWave];
     __shared__ LocateShared shl;
-    const int j = FIN ? blockIdx.x - a.B : blockIdx.x;               // job; its sequence is b
-    const int b = j / a.jps;
+    const int b = FIN ? blockIdx.x - a.B : blockIdx.x;
     const int tid = threadIdx.x;
     // the slice sums, the table and the uniform are requested before the job is looked at (one round trip)
-    const double *ps = a.part1 + (int64_t)j * a.nsl * kSliceVals;
-    double *zs = a.part2 + (int64_t)j * a.nsl;                       // exact slice weights (slow path only)
+    const double *ps = a.part1 + (int64_t)b * a.nsl * kSliceVals;
+    double *zs = a.part2 + (int64_t)b * a.nsl;                       // exact slice weights (slow path only)
     // First all loads that do not depend on each other, then their uses: written so that no wait separates the
     // requests (the first slice of each thread without a loop; 256 threads fetch the 256 table entries).
     static_assert(kVBlock == 256, "one table entry per thread");
@@ -1157,10 +1212,10 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     const double *pf = ps + (has_first ? tid : 0) * kSliceVals;
     const double f0 = pf[0], f1 = pf[1], f2 = pf[2], f3 = pf[3], f4 = pf[4];     // slot 0 always exists: harmless when unused
     const double tv = a.exp_table[tid];
-    const float u32v = a.u_sample[j];
-    const int band_n = a.jobs[j].band_cnt;
-    const int band_i = a.jobs[j].band_idx[tid & (kBandCap - 1)];                                  // stale beyond band_n: unused
-    const SampleJob job = a.jobs[j].job;
+    const float u32v = a.u_sample[b];
+    const int band_n = a.jobs[b].band_cnt;
+    const int band_i = a.jobs[b].band_idx[tid & (kBandCap - 1)];                                  // stale beyond band_n: unused
+    const SampleJob job = a.jobs[b].job;
     // TAIL: the first thread also requests what the end of the round reads (bandit state of the sequence, its arm,
     // lengths; the accepted length is the head's, written by an earlier launch)
     UcbLane ucb;
@@ -1273,74 +1328,24 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     LOCATE_STAMP(2);                                             // total weight known (certified, settled or recomputed)
     int token = -1;
     if (Z > 0.0) {
-        const double target = u * Z;
-        // slice whose inclusive prefix (slice order) first exceeds the target
-        double cum_at = 0.0;
-        int s_found = -1;
-        if (__builtin_expect(a.nsl <= kVBlock, 1)) {
-            // this thread's slice is the one whose sums it fetched with the first round trip: no second look at memory
-            double z_mine = 0.0;
-            if (tid < a.nsl) {
-                if (exact_sums) z_mine = zs[tid];
-                else if (w.kind == 2) z_mine = f0;
-                else {
-                    z_mine = f2 - delta * f3;
-                    z_mine = z_mine > 0.0 ? z_mine : 0.0;
-                    for (int q = 0; q < n_band; ++q)
-                        if (shl.band_key[q] / kSampleSlice == tid) z_mine += shl.band_val[q];
-                }
-            }
-            double ztot;
-            const double excl = block_excl_scan_d(z_mine, shl.scan[phase++ & 1], &ztot);
-            const int cand = wave_min_i32((tid < a.nsl && excl + z_mine > target) ? tid : 0x7fffffff);
-            if ((tid & (kWave - 1)) == 0) shl.hits[phase & 1][tid / kWave] = cand;
-            __syncthreads();
-            const int *hh = shl.hits[phase & 1];
-            const int sf = min(min(hh[0], hh[1]), min(hh[2], hh[3]));
-            ++phase;
-            s_found = sf == 0x7fffffff ? -1 : sf;
-            if (tid == s_found) shl.bc[0] = excl;
-            __syncthreads();
-            if (s_found >= 0) cum_at = shl.bc[0];
-        } else {
-            // very large vocabularies: the first thread walks the slice weights
-            if (tid == 0) {
-                double c = 0.0; int sf = -1;
-                for (int s = 0; s < a.nsl; ++s) { const double v = slice_weight(s); if (c + v > target) { sf = s; break; } c += v; }
-                shl.bc[0] = c; shl.slice = sf;
-            }
-            __syncthreads();
-            cum_at = shl.bc[0]; s_found = shl.slice;
-            __syncthreads();
-        }
-        LOCATE_STAMP(3);                                         // slice found
-        // slice sums and the in-slice scan round differently: if the crossing is not inside the chosen
-        // slice, continue into the following ones
-        if (s_found >= 0) {
-            double cum = cum_at;
-            for (int s = s_found; s < a.nsl && token < 0; ++s) {
-                double slice_total;
-                token = locate_in_slice<TD, DD>(w, r, s, a.V, shT, cum, target, &shl, phase++, &slice_total);
-                cum += slice_total;
+        // this thread's slice is the one whose sums it fetched with the first round trip: no second look at memory
+        double z_mine = 0.0;
+        if (tid < a.nsl && a.nsl <= kVBlock) {
+            if (exact_sums) z_mine = zs[tid];
+            else if (w.kind == 2) z_mine = f0;
+            else {
+                z_mine = f2 - delta * f3;
+                z_mine = z_mine > 0.0 ? z_mine : 0.0;
+                for (int q = 0; q < n_band; ++q)
+                    if (shl.band_key[q] / kSampleSlice == tid) z_mine += shl.band_val[q];
             }
         }
-        if (__builtin_expect(token < 0, 0)) {
-            // rounding left no crossing: the largest index with positive weight
-            {
-                for (int s = 0; s < a.nsl; ++s) {
-                    double slice_total;
-                    locate_in_slice<TD, DD>(w, r, s, a.V, shT, 0.0, INFINITY, &shl, phase++, &slice_total, true);
-                }
-                __syncthreads();
-            }
-            token = shl.last;
-        }
+        token = find_token<TD, DD>(w, r, a.V, a.nsl, shT, u * Z, z_mine, slice_weight, &shl, phase);
     }
     LOCATE_STAMP(4);                                             // token found
     if (tid == 0) {
         if (token < 0) token = 0;
-        if (a.tok_direct) a.tok_direct[j] = token;
-        else a.out_tok[(int64_t)b * (a.K + 1) + job.row] = token;
+        a.out_tok[(int64_t)b * (a.K + 1) + job.row] = token;
         if (__builtin_expect(draft_bad, 0)) {
             uint32_t f = a.flags_ws[b] | TAPOUT_FLAG_BAD_ROW;
             a.flags_ws[b] = f;
@@ -1351,34 +1356,215 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     LOCATE_STAMP(5);                                             // round ended (bandit update, next arm)
 }
 
-// ---- draft-token sampling: one job per draft row --------------------------------------------
-// One thread per row (b, k): merges the row's slice partials straight from memory (a few dozen bytes) for
-// the maximum, the exponent reference of the draw.
-__global__ __launch_bounds__(kVBlock) void sample_head_kernel(VerifyArgs a)
+// ---- draft-token sampling: the inverse CDF of every live draft row ---------------------------
+constexpr int kSampleBlock = 512;
+constexpr int kSampleWgs = 512;      // two per CU: what the kernel's registers let be resident at once
+
+__device__ inline float wave_max_f(float v)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= a.n_jobs) return;
-    const int b = j / a.K, k = j - b * a.K;
-    int kb = a.n_draft ? a.n_draft[b] : a.K;
-    kb = kb > a.K ? a.K : kb;
-    SampleJob job;
-    job.kind = 0; job.row = k; job.ref_p = 0.0f; job.ref_q = 0.0f; job.lam = 0.0;
-    if (k < kb) {
-        // the row's maximum, and the finaliser's bad-row rule: a NaN anywhere poisons a slice's sum (also from inside
-        // the batch the draft pass leaves out of it), an infinite maximum has no softmax
-        float M = -INFINITY;
-        bool bad = false;
-        for (int sl = 0; sl < a.nsplit; ++sl) {
-            const Partial p = a.part[(int64_t)j * a.nsplit + sl];
-            M = fmaxf(M, p.v1);
-            bad |= !(p.S >= 0.0f) || p.S == INFINITY;
-        }
-        bad |= M == -INFINITY || M == INFINITY;
-        if (bad) a.tok_direct[j] = -1;           // NaN in the row or no finite maximum: nothing to draw from
-        else { job.kind = 2; job.ref_p = M; }
+    auto mv = [](float x, auto ctrl) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    v = fmaxf(v, mv(v, std::integral_constant<int, 0xB1>{})); v = fmaxf(v, mv(v, std::integral_constant<int, 0x4E>{}));
+    v = fmaxf(v, mv(v, std::integral_constant<int, 0x141>{})); v = fmaxf(v, mv(v, std::integral_constant<int, 0x140>{}));
+    auto at = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); };
+    return fmaxf(fmaxf(at(0), at(16)), fmaxf(at(32), at(48)));
+}
+
+// A row's maximum, the exponent reference of its draw, and the epilogue's bad-row rule, from the row's partials, by one
+// wavefront: a NaN anywhere poisons a slice's sum (also from inside the batch the draft pass leaves out of it), a row
+// without a finite maximum has no softmax.  In two steps, request and use.
+struct RowRefRegs { float v1, S; };
+__device__ inline RowRefRegs row_ref_issue(const Partial *p, int nsplit)
+{
+    const int sl = min((int)(threadIdx.x & (kWave - 1)), nsplit - 1);       // surplus lanes ask for the last partial again
+    return RowRefRegs{p[sl].v1, p[sl].S};
+}
+__device__ inline float row_ref_finish(RowRefRegs r, const Partial *p, int nsplit, bool *bad)
+{
+    bool mine = !(r.S >= 0.0f) || r.S == INFINITY;
+    for (int sl = (int)(threadIdx.x & (kWave - 1)) + kWave; sl < nsplit; sl += kWave) {
+        const float S = p[sl].S;
+        r.v1 = fmaxf(r.v1, p[sl].v1);
+        mine |= !(S >= 0.0f) || S == INFINITY;
     }
-    a.jobs[j].job = job;
-    a.jobs[j].band_cnt = 0;
+    const float M = wave_max_f(r.v1);
+    *bad = __builtin_amdgcn_ballot_w64(mine) != 0 || M == -INFINITY || M == INFINITY;
+    return M;
+}
+
+// Slice sums of every live row: sums[row, s] = sum of exp(x - M) over slice s, M the row's maximum, in double and with the
+// arithmetic of the final-token slice kernel.  A wavefront per slice; the workgroups are as many as are resident at once
+// and each wavefront takes every n_waves-th slice, so that the table of bfloat16 exponentials is copied to LDS once per
+// workgroup: with a workgroup per four slices its 37 KB were twice the logits they served (and the slices here are all
+// alike, so a fixed stride keeps the wavefronts level).  A wavefront requests its next slice and that row's partials
+// before it works on the one at hand.  Bound by the look-ups' LDS reads and the second reading of the logits.
+// Measured at V = 128256, 512 rows, bfloat16: 42.1 us with a workgroup per four slices, behind a launch of 4.8 that found
+// the rows' maxima; this, which finds them itself and carries the epilogue's workgroups (7.9 alone), 33.9; 64 rows: 4.2 + 8.4 + 8.2 against
+// 11.2.
+template <int DT>
+__global__ __launch_bounds__(kSampleBlock) void sample_slices_kernel(SampleArgs a, DraftFinalArgs fin)
+{
+    constexpr bool kTab = DT == TAPOUT_BF16;
+    __shared__ double shT[256];
+    __shared__ __align__(16) double shE[kTab ? kTabDoubles : 2];
+    warm_args(a, fin);
+    if ((int)blockIdx.x < a.B) {
+        // the draft epilogue of one sequence, by the first wavefronts (whole wavefronts leave: barriers do not wait for them)
+        if (threadIdx.x < kFinalBlock) draft_finalize_body<false>(fin, blockIdx.x);
+        return;
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const u32x4 *src = (const u32x4 *)(a.exp_table + 256);
+    constexpr int kRounds = kTab ? (kTabVecs + kSampleBlock - 1) / kSampleBlock : 1;
+    u32x4 tw[kRounds];
+    const double tv = a.exp_table[threadIdx.x & 255];
+    if constexpr (kTab) {
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) tw[q] = src[min(q * kSampleBlock + (int)threadIdx.x, kTabVecs - 1)];
+    }
+    struct Slice { int b, k, s; };
+    const int first = __builtin_amdgcn_readfirstlane((int)((blockIdx.x - a.B) * (kSampleBlock / kWave) + threadIdx.x / kWave));
+    Slice cur;
+    {
+        const int row = first / a.nsl;
+        cur.s = first - row * a.nsl;
+        cur.b = row / a.K;
+        cur.k = row - cur.b * a.K;
+    }
+    auto advance = [&](Slice t) {
+        t.s += a.step_s; t.k += a.step_k; t.b += a.step_b;
+        if (t.s >= a.nsl) { t.s -= a.nsl; ++t.k; }
+        if (t.k >= a.K) { t.k -= a.K; ++t.b; }
+        return t;
+    };
+    auto live = [&](const Slice &t) { return t.b < a.B && (!a.k_len || t.k < a.k_len[t.b]); };
+    struct Regs { Raw8<DT> q[kChunks]; RowRefRegs r; };
+    auto request = [&](const Slice &t) {
+        Regs o;
+        const char *row = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, t.b, t.k);
+        const int base = t.s * kSampleSlice + lane * kPer;
+        o.r = row_ref_issue(a.part + ((int64_t)t.b * a.K + t.k) * a.nsplit, a.nsplit);
+        if (__builtin_expect((t.s + 1) * kSampleSlice <= a.V, 1)) {          // straight-line requests (see the final-token slice kernel)
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c)
+#pragma unroll
+                for (int h = 0; h < (DT == TAPOUT_F32 ? 2 : 1); ++h)
+                    o.q[c].w[h] = load16<DT>(row + (int64_t)(base + c * kWave * kPer) * Elem<DT>::size + 16 * h);
+        } else {
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c) o.q[c] = load_raw8<DT>(row, base + c * kWave * kPer, a.V);
+        }
+        return o;
+    };
+    bool on = live(cur);
+    Regs at{};
+    if (on) at = request(cur);
+    if (threadIdx.x < 256) shT[threadIdx.x] = tv;
+    if constexpr (kTab) {
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q)
+            if (q * kSampleBlock + (int)threadIdx.x < kTabVecs) ((u32x4 *)shE)[q * kSampleBlock + threadIdx.x] = tw[q];
+    }
+    __syncthreads();
+    while (cur.b < a.B) {
+        const Slice nxt = advance(cur);
+        const bool nxt_on = live(nxt);
+        Regs ahead{};
+        if (nxt_on) ahead = request(nxt);
+        if (on) {
+            const int64_t row = (int64_t)cur.b * a.K + cur.k;
+            bool bad;
+            const float M = row_ref_finish(at.r, a.part + row * a.nsplit, a.nsplit, &bad);
+            if (!bad) {
+                SampleJob job;
+                job.kind = 2; job.row = cur.k; job.ref_p = M; job.ref_q = 0.0f; job.lam = 0.0;
+                double A = 0.0, scale = 1.0;
+                if (kTab && !(a.vflags & kVerifyNoExpTable) && tab_job_ok(job)) {
+                    scale = exp_fast_d(-(double)M, shT);
+#pragma unroll
+                    for (int c = 0; c < kChunks; ++c) {
+                        double cA = chunk_one_tab(at.q[c].w[0], shE);
+                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(cA != cA) != 0, 0)) {        // a magnitude below the table
+                            asm volatile("" ::: "memory");
+                            float x[kPer];
+                            widen8<DT>(at.q[c], x);
+                            cA = 0.0;
+#pragma unroll
+                            for (int i = 0; i < kPer; ++i) cA += tab_exp_any(x[i], shE);
+                        }
+                        A += cA;
+                    }
+                } else {
+                    ExpRef ref;
+                    ref.set((double)M);
+                    double c2 = kExpC2;
+                    float top = INFINITY;
+                    asm volatile("" : "+v"(c2), "+v"(top));               // stay in vector registers
+#pragma unroll
+                    for (int c = 0; c < kChunks; ++c) {
+                        float x[kPer];
+                        widen8<DT>(at.q[c], x);
+                        double cA = 0.0;
+#pragma unroll
+                        for (int i = 0; i < kPer; ++i) cA += exp_fast(x[i], ref.neg_ref_c, ref.lo, shT, c2, top);
+                        A += cA;
+                    }
+                }
+                A = wave_sum_d(A) * scale;
+                if (lane == 0) a.sums[row * a.nsl + cur.s] = A;
+            }
+        }
+        cur = nxt; at = ahead; on = nxt_on;
+    }
+}
+
+// Tokens: one workgroup per draft row finds the slice and the element that hold u * Z, and forms log q(tok).
+template <int DT>
+__global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
+{
+    warm_args(a);
+    __shared__ double shT[256];
+    __shared__ double sh_red[kVBlock / kWave];
+    __shared__ LocateShared shl;
+    const int row = blockIdx.x, b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
+    const double *ps = a.sums + (int64_t)row * a.nsl;
+    // everything is requested before anything is looked at: one round trip
+    const double f0 = ps[min(tid, a.nsl - 1)];
+    const double tv = a.exp_table[tid];
+    const float u32v = a.u[row];
+    const RowRefRegs rr = row_ref_issue(a.part + (int64_t)row * a.nsplit, a.nsplit);
+    const int kl = a.k_len ? a.k_len[b] : a.K;
+    const double lse = a.lse[row];
+    asm volatile("" :: "v"(f0), "v"(tv), "v"(u32v), "v"(rr.v1), "v"(rr.S), "v"(lse));
+    shT[tid] = tv;
+    if (k >= kl) return;
+    bool bad;
+    const float M = row_ref_finish(rr, a.part + (int64_t)row * a.nsplit, a.nsplit, &bad);
+    if (__builtin_expect(bad, 0)) {                                      // nothing to draw from
+        if (tid == 0) { a.tok[row] = -1; if (a.logq_tok) a.logq_tok[row] = NAN; }
+        return;
+    }
+    double acc = tid < a.nsl ? f0 : 0.0;
+    for (int s = tid + kVBlock; s < a.nsl; s += kVBlock) acc += ps[s];   // vocabularies beyond 256 slices
+    acc = wave_sum_d(acc);
+    if ((tid & (kWave - 1)) == 0) sh_red[tid / kWave] = acc;
+    if (tid == 0) { shl.last = -1; shl.slice = 0x7fffffff; }
+    __syncthreads();                                                     // also publishes the table
+    const double Z = (sh_red[0] + sh_red[1]) + (sh_red[2] + sh_red[3]);
+    Weights w;
+    w.kind = 2; w.lam = 0.0;
+    w.rp.set((double)M); w.rq.set(0.0);
+    Rows r;
+    r.trow = r.drow = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, b, k);
+    int phase = 0, token = -1;
+    if (Z > 0.0) {
+        const double target = (double)u32v * Z;
+        token = find_token<DT, DT>(w, r, a.V, a.nsl, shT, target, f0, [&](int s) { return ps[s]; }, &shl, phase);
+    }
+    if (tid == 0) {
+        if (token < 0) token = 0;
+        a.tok[row] = token;
+        if (a.logq_tok) a.logq_tok[row] = (float)((double)load_elem<DT>(r.trow, token) - lse);
+    }
 }
 
 // ---- final token over vocabulary shards ---------------------------------------------------------
@@ -1534,8 +1720,7 @@ hipError_t launch_shard_typed(const ShardFinalArgs &a, int pass, hipStream_t st)
 {
     if (pass == 0) {
         hipLaunchKernelGGL(shard_jobs_kernel, dim3((a.v.B + 63) / 64), dim3(64), 0, st, a);
-        const unsigned gy = a.v.n_jobs < 65535 ? a.v.n_jobs : 65535, gz = (a.v.n_jobs + gy - 1) / gy;
-        hipLaunchKernelGGL((verify_slices<TD, DD, false>), dim3((a.v.nsl + kWavesPerWG - 1) / kWavesPerWG, gy, gz), dim3(kVBlock), 0, st, a.v);
+        hipLaunchKernelGGL((verify_slices<TD, DD, false>), dim3((a.v.nsl + kWavesPerWG - 1) / kWavesPerWG, a.v.B), dim3(kVBlock), 0, st, a.v);
         hipLaunchKernelGGL(shard_sums_kernel, dim3((a.v.B * kSliceVals + 63) / 64), dim3(64), 0, st, a);
     } else {
         hipLaunchKernelGGL((shard_locate<TD, DD>), dim3(a.v.B), dim3(kVBlock), 0, st, a);
@@ -1554,8 +1739,7 @@ hipError_t launch_shard_dispatch(const ShardFinalArgs &a, int pass, hipStream_t 
 template <int TD, int DD>
 hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool with_fin, int pass, hipStream_t st, Timing tm)
 {
-    const unsigned gy = a.n_jobs < 65535 ? a.n_jobs : 65535, gz = (a.n_jobs + gy - 1) / gy;
-    dim3 grid12((a.nsl + kWavesPerWG - 1) / kWavesPerWG, gy, gz), block(kVBlock);
+    dim3 grid12((a.nsl + kWavesPerWG - 1) / kWavesPerWG, a.B), block(kVBlock);         // (a context holds at most 65535 sequences)
     if (pass == 1) {
         if (a.fused_head) launch_kernel(verify_slices<TD, DD, true>, grid12, block, st, tm, a);
         else launch_kernel(verify_slices<TD, DD, false>, grid12, block, st, tm, a);
@@ -1565,11 +1749,11 @@ hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool wit
         const unsigned extra = a.bandit_tail == 2 ? (unsigned)((a.B + kVBlock / 16 - 1) / (kVBlock / 16)) : 0u;
         const bool tail = a.bandit_tail == 1;
         if (with_fin) {
-            if (!tail) launch_kernel(verify_locate<TD, DD, false, true>, dim3(a.n_jobs + a.B + extra), block, st, tm, a, fin);
-            else launch_kernel(verify_locate<TD, DD, true, true>, dim3(a.n_jobs + a.B), block, st, tm, a, fin);
+            if (!tail) launch_kernel(verify_locate<TD, DD, false, true>, dim3(2 * a.B + extra), block, st, tm, a, fin);
+            else launch_kernel(verify_locate<TD, DD, true, true>, dim3(2 * a.B), block, st, tm, a, fin);
         }
-        else if (!tail) launch_kernel(verify_locate<TD, DD, false, false>, dim3(a.n_jobs + extra), block, st, tm, a, fin);
-        else launch_kernel(verify_locate<TD, DD, true, false>, dim3(a.n_jobs), block, st, tm, a, fin);
+        else if (!tail) launch_kernel(verify_locate<TD, DD, false, false>, dim3(a.B + extra), block, st, tm, a, fin);
+        else launch_kernel(verify_locate<TD, DD, true, false>, dim3(a.B), block, st, tm, a, fin);
     }
     return hipGetLastError();
 }
@@ -1579,10 +1763,27 @@ hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool wit
 hipError_t launch_shard_final_sums(const ShardFinalArgs &a, hipStream_t st) { return launch_shard_dispatch(a, 0, st); }
 hipError_t launch_shard_final_token(const ShardFinalArgs &a, hipStream_t st) { return launch_shard_dispatch(a, 1, st); }
 
-hipError_t launch_sample_head(const VerifyArgs &a, hipStream_t st, Timing tm)
+template <int DT>
+static hipError_t launch_sample_typed(SampleArgs &a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm)
 {
-    launch_kernel(sample_head_kernel, dim3((a.n_jobs + kVBlock - 1) / kVBlock), dim3(kVBlock), st, tm, a);
+    if (pass == 0) {
+        constexpr int per_wg = kSampleBlock / kWave;
+        const int64_t rows = (int64_t)a.B * a.K, want = (rows * a.nsl + per_wg - 1) / per_wg;
+        const int wgs = (int)(want < kSampleWgs ? want : kSampleWgs);
+        a.n_waves = wgs * per_wg;
+        const int step_rows = a.n_waves / a.nsl;
+        a.step_s = a.n_waves % a.nsl; a.step_b = step_rows / a.K; a.step_k = step_rows % a.K;
+        launch_kernel(sample_slices_kernel<DT>, dim3(a.B + wgs), dim3(kSampleBlock), st, tm, a, fin);
+    } else {
+        launch_kernel(sample_locate_kernel<DT>, dim3(a.B * a.K), dim3(kVBlock), st, tm, a);
+    }
     return hipGetLastError();
+}
+
+hipError_t launch_sample(SampleArgs a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm)
+{
+    if (!a.exp_table || fin.B != a.B || !fin.sampled_lse || fin.shards > 0) return hipErrorInvalidValue;
+    return a.dtype == TAPOUT_F32 ? launch_sample_typed<TAPOUT_F32>(a, fin, pass, st, tm) : launch_sample_typed<TAPOUT_BF16>(a, fin, pass, st, tm);
 }
 
 hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing tm, const DraftFinalArgs *fin)
@@ -1590,7 +1791,7 @@ hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing t
     static const DraftFinalArgs no_fin{};
     const bool with_fin = fin != nullptr;
     if (!a.exp_table) return hipErrorInvalidValue;           // every pass reads it
-    if (((a.vflags & kVerifyOwnQ) != 0) != with_fin || (fin && (a.jps != 1 || a.n_jobs != a.B || a.shards > 0 || fin->shards > 0 || fin->B != a.B)))
+    if (((a.vflags & kVerifyOwnQ) != 0) != with_fin || (fin && (a.shards > 0 || fin->shards > 0 || fin->B != a.B)))
         return hipErrorInvalidValue;
     if (!fin) fin = &no_fin;
     if (pass == 0) {

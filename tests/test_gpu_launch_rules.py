@@ -128,3 +128,38 @@ def test_token_level_bandit_at_the_edges_of_its_workgroups(policy, shared, B, K,
         ob.update(arm.cpu().numpy(), m.numpy(), n.numpy(), gamma.numpy())
     s, q, c = tp.bandit_get_state(moments=True)
     assert (c == ob.count).all() and (s == ob.sum_r).all() and (q == ob.sum_r2).all()
+
+
+@pytest.mark.parametrize("B,K,V,dt", [
+    (1, 1, 5, bf16),                  # one short slice
+    (1, 1, 2048, f32), (1, 3, 2049, bf16),
+    (3, 7, 4099, bf16),               # rows at every alignment
+    (64, 1, 131072, bf16),            # 4096 slices: one per resident wavefront
+    (65, 1, 131080, f32),             # one more row: some wavefronts take a second slice, of another row
+    (9, 16, 70001, bf16),             # steps over sequences and positions at once
+    (1400, 3, 2500, f32),             # fewer slices per row than the step
+])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_draft_token_draw_with_a_wavefront_per_slice(B, K, V, dt, ragged):
+    rnd = random_round(B, K, V, dt, seed=V + B)
+    tp = binding.Tapout(B, K, V, draft_sampling=True)
+    g = torch.Generator().manual_seed(V)
+    u = torch.rand(B, K, generator=g)
+    k_len = torch.randint(0, K + 1, (B,), generator=g, dtype=torch.int32) if ragged else None
+    n = np.full(B, K) if k_len is None else k_len.numpy()
+    rnd["draft"][B // 2, K - 1] = float("-inf")                 # a row without a finite maximum: no token
+    if dt == bf16 and V > 2048:
+        rnd["draft"][0, 0] = 90.0 + (rnd["draft"][0, 0].float() % 3)    # beyond the table of exponentials: computed
+        rnd["draft"][0, 0, 7::11] = 1e-6                        # and magnitudes below it
+        rnd["draft"][B - 1, 0, 5::13] = 0.0
+    out = tp.draft_stats(rnd["draft"], k_len=None if k_len is None else k_len.to(DEV), u_draft=u.to(DEV))
+    live = np.arange(K)[None, :] < n[:, None]
+    ref = orc.draft_sample(pu.host_logits(rnd["draft"]), u.numpy(), k_len=n.astype(np.int32), nthreads=16)
+    tok = out["sampled_tok"].cpu().numpy()
+    near = ref["icdf_margin"] <= pu.TAU_S
+    assert near[live].sum() <= 2                                # a cell edge within 1e-9 of the target: V 1e-9 per row
+    assert (tok[live & ~near] == ref["tok"][live & ~near]).all() and (tok[~live] == -1).all()
+    # log q of the token and the flags as for tokens that the caller hands in
+    given = tp.draft_stats(rnd["draft"], draft_tok=out["sampled_tok"], k_len=None if k_len is None else k_len.to(DEV))
+    a, b = (torch.nan_to_num(x["logq_tok"][torch.from_numpy(live).to(DEV)], nan=7.0) for x in (out, given))
+    assert torch.equal(a, b) and torch.equal(out["flags"], given["flags"])
