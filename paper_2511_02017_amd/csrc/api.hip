@@ -752,7 +752,7 @@ tapout_status shard_final_args(tapout_ctx *ctx, const tapout_logits *target_shar
     va.B = B; va.K = K; va.V = Vs; va.nsl = (Vs + kSampleSlice - 1) / kSampleSlice;
     va.jobs = ctx->jobs; va.part1 = ctx->part1; va.part2 = ctx->part2; va.exp_table = ctx->exp_table;
     if (!ctx->exp_lookup) va.vflags |= kVerifyNoExpTable;
-    a.jobs_in = (const SampleJob *)jobs;
+    va.final_jobs = (SampleJob *)const_cast<tapout_final_job *>(jobs);        // (read only there)
     *out = a;
     return TAPOUT_OK;
 }

@@ -182,7 +182,7 @@ struct VerifyArgs {
     int32_t nsl;                  // slices per row of the final-token passes (kSampleSlice elements each)
     int32_t shards;               // > 0: part holds records of vocabulary shards, shard-major [shards, B*(K+1)] (head kernel only)
     int32_t fused_head;           // 1: no head launch; every workgroup of the slice kernel works out its sequence's job itself
-    SampleJob *final_jobs;        // sharded head: the job of every sequence for the caller (or NULL)
+    SampleJob *final_jobs;        // sharded head: the job of every sequence for the caller (or NULL); sharded final token: the caller's jobs
     const Partial *part;
     const float *draft_lse, *logq_tok; const int32_t *draft_tok, *n_draft; const uint8_t *greedy;
     const float *u_accept, *u_sample;
@@ -241,7 +241,6 @@ hipError_t launch_sample(SampleArgs a, const DraftFinalArgs &fin, int pass, hipS
 // describe this shard's column slices (V = its width, nsl = its slices, jobs / part1 / part2 of the context).
 struct ShardFinalArgs {
     VerifyArgs v;
-    const SampleJob *jobs_in;     // [B] jobs as the caller holds them
     double *sums_out;             // [B, 5]                       (sums)
     const double *sums_all;       // [G, B, 5]                    (token)
     const double *exact_all;      // [G, B] or NULL               (token)
@@ -668,10 +667,12 @@ __device__ inline int lane_merge_shift(int rows, int nsplit)
 }
 
 // Request this thread's partials: row `t >> sh` (first pass) and row `(t >> sh) + (256 >> sh)` (second pass),
-// slice `t & (P - 1)`, of `rows` rows at `part` ([rows][nsplit]).  Threads without a partial get zeros.
+// piece `t & (P - 1)`, of `rows` rows at `part`.
 // (256-thread workgroups.)
 struct LaneRegs { StageRegs p[2]; };
-__device__ inline LaneRegs lane_merge_issue(const Partial *part, int rows, int nsplit, int sh)
+// row_stride, slice_stride: records from one row, one piece to the next (slice partials [rows][nsplit]: nsplit, 1; records
+// of vocabulary shards, shard-major: 1, rows of the whole call).
+__device__ inline LaneRegs lane_merge_issue(const Partial *part, int rows, int nsplit, int sh, int64_t row_stride, int64_t slice_stride)
 {
     // Every thread requests something (one without a partial re-reads partial 0; lane_piece ignores what it got): a
     // request under a condition is merged with the other branch's zeros, and the compiler waits for the data at the
@@ -685,7 +686,7 @@ __device__ inline LaneRegs lane_merge_issue(const Partial *part, int rows, int n
         if (q == 1 && (256 >> sh) >= rows) break;
         const int row = (threadIdx.x >> sh) + q * (256 >> sh);
         const bool mine = row < rows && sl < nsplit;
-        const u32x4 *s = (const u32x4 *)(part + (mine ? (int64_t)row * nsplit + sl : 0));
+        const u32x4 *s = (const u32x4 *)(part + (mine ? row * row_stride + sl * slice_stride : 0));
         r.p[q].w0 = s[0]; r.p[q].w1 = s[1];
     }
     return r;

@@ -33,41 +33,45 @@ __global__ __launch_bounds__(kFinalBlock) void draft_finalize_kernel(DraftFinalA
 }
 
 // ---- vocabulary shards -----------------------------------------------------------------------
-// One thread per row of the shard: merges the row's slice partials (a few dozen bytes, straight from memory)
-// into one record with the exact global argmax and, if this shard owns it, the logit of the drafted token.
-__global__ __launch_bounds__(kFinalBlock) void shard_merge_kernel(ShardMergeArgs a)
+// One record per row of the shard from its slice partials, with the exact global argmax and, if this shard owns it, the logit
+// of the drafted token.  Every slice partial gets its left-out batch back (all but the first maximum), then the slices are
+// merged; the record leaves the row slice's first maximum out of its two sums.  2^sh lanes per row, one slice each (rows of
+// more than sixteen slices: one lane that walks them; sh = 0).
+__global__ __launch_bounds__(kFinalBlock) void shard_merge_kernel(ShardMergeArgs a, int sh)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.B * a.KK) return;
+    warm_args(a);
+    const int64_t t = (int64_t)blockIdx.x * kFinalBlock + threadIdx.x;
+    const int row_i = (int)(t >> sh), sl0 = (int)threadIdx.x & ((1 << sh) - 1);
+    const bool in = row_i < a.B * a.KK;
+    const int i = in ? row_i : 0;
     const int b = i / a.KK, k = i - b * a.KK;
-    int n_live;
-    if (a.rows_mode == 0) {
-        n_live = a.len ? a.len[b] : a.KK;
-        n_live = n_live > a.KK ? a.KK : n_live;
-    } else {
-        const int n = a.len[b];
-        n_live = (n < 1 ? 1 : (n > a.KK - 1 ? a.KK - 1 : n)) + 1;
-    }
-    if (k >= n_live) return;
     const void *row = row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, k);
-    // every slice partial gets its left-out batch back (all but the first maximum), then the slices are merged; the
-    // record leaves the row slice's first maximum out of its two sums
+    const int KT = a.KK - a.rows_mode;                       // tokens per sequence (the last target row has none)
+    // first round trip: the row count, the token, the partial; second: the token's logit and the partial's left-out batch
+    const int n = a.len ? a.len[b] : a.KK;
+    int tok = -1;
+    if (a.tok && k < KT && sl0 == 0) tok = a.tok[(int64_t)b * KT + k] - a.vocab_offset;
+    const int n_live = a.rows_mode == 0 ? min(n, a.KK) : (n < 1 ? 1 : min(n, a.KK - 1)) + 1;
+    const bool live = in && k < n_live;
+    const int64_t at = (int64_t)i * a.nsplit;
     Piece acc = empty_piece();
-    for (int sl = 0; sl < a.nsplit; ++sl) {
-        Piece e = piece_from_partial(a.part[(int64_t)i * a.nsplit + sl]);
-        const BatchRegs bt = batch_issue(row, a.dtype, a.Vs, e.idx, sl, a.per, a.part);
-        batch_fix(e, bt, a.dtype);
-        acc = merge_pair<true>(acc, e);
-    }
+    if (live && sl0 < a.nsplit) acc = piece_from_partial(a.part[at + sl0]);
+    float xt = NAN;
+    if (live && tok >= 0 && tok < a.Vs) xt = load_elem_rt(row, a.dtype, tok);
+    BatchRegs bt = batch_issue(row, a.dtype, a.Vs, live && sl0 < a.nsplit ? acc.idx : -1, sl0, a.per, a.part);
+    batch_fix(acc, bt, a.dtype);
+    if (sh == 0)
+        for (int sl = 1; live && sl < a.nsplit; ++sl) {
+            Piece e = piece_from_partial(a.part[at + sl]);
+            bt = batch_issue(row, a.dtype, a.Vs, e.idx, sl, a.per, a.part);
+            batch_fix(e, bt, a.dtype);
+            acc = merge_pair<true>(acc, e);
+        }
+    acc = lane_group_merge<true>(acc, sh);
+    if (!live || sl0 != 0) return;
     Partial o;
     o.v1 = acc.M; o.S = (float)acc.S; o.T = (float)acc.T; o.v2 = acc.v2;
     o.cand = a.vocab_offset + ((acc.idx >= 0 && acc.idx < a.Vs) ? acc.idx : 0);
-    float xt = NAN;
-    const int KT = a.KK - a.rows_mode;                       // tokens per sequence (the last target row has none)
-    if (a.tok && k < KT) {
-        const int t = a.tok[(int64_t)b * KT + k] - a.vocab_offset;
-        if (t >= 0 && t < a.Vs) xt = load_elem_rt(row, a.dtype, t);
-    }
     o.pad[0] = __float_as_int(xt); o.pad[1] = o.pad[2] = 0;
     a.out[i] = o;
 }
@@ -83,8 +87,11 @@ hipError_t launch_draft_finalize(const DraftFinalArgs &a, hipStream_t st, Timing
 
 hipError_t launch_shard_merge(const ShardMergeArgs &a, hipStream_t st, Timing tm)
 {
-    const int n = a.B * a.KK;
-    launch_kernel(shard_merge_kernel, dim3((n + kFinalBlock - 1) / kFinalBlock), dim3(kFinalBlock), st, tm, a);
+    int sh = 0;
+    while ((1 << sh) < a.nsplit) ++sh;
+    if (sh > 4) sh = 0;
+    const int64_t n = ((int64_t)a.B * a.KK) << sh;
+    launch_kernel(shard_merge_kernel, dim3((unsigned)((n + kFinalBlock - 1) / kFinalBlock)), dim3(kFinalBlock), st, tm, a, sh);
     return hipGetLastError();
 }
 

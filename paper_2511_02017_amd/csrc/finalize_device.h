@@ -45,7 +45,7 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
     __shared__ uint32_t sh_flags;
     const int K = a.K;
     // few rows and slices: one partial per thread, merged across lanes (see lane_merge_commit); else staged in LDS
-    const int msh = SHARDED ? -1 : lane_merge_shift(K, a.nsplit);
+    const int msh = lane_merge_shift(K, a.nsplit);
     // The lane-parallel merge leaves the totals of all K <= 64 rows in LDS at once and row k with thread k: it is one
     // stage whatever the slice count.  The staged merge takes kStageCap partials at a time (nsplit <= kStageCap is
     // guaranteed by the host).
@@ -67,8 +67,10 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
     StageRegs st0;
     LaneRegs ln0;
     st0.w0 = st0.w1 = ln0.p[0].w0 = ln0.p[0].w1 = ln0.p[1].w0 = ln0.p[1].w1 = u32x4{0u, 0u, 0u, 0u};
-    if constexpr (SHARDED) st0 = stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K, a.nsplit, count0);
-    else if (__builtin_expect(msh >= 0, 1)) ln0 = lane_merge_issue(a.part + (int64_t)b * K * a.nsplit, K, a.nsplit, msh);
+    if (__builtin_expect(msh >= 0, 1))
+        ln0 = SHARDED ? lane_merge_issue(a.part + (int64_t)b * K, K, a.nsplit, msh, 1, (int64_t)a.B * K)
+                      : lane_merge_issue(a.part + (int64_t)b * K * a.nsplit, K, a.nsplit, msh, a.nsplit, 1);
+    else if constexpr (SHARDED) st0 = stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K, a.nsplit, count0);
     else st0 = stage_issue(a.part + (int64_t)b * K * a.nsplit, count0);
     asm volatile("" :: "v"(kb), "v"(arm), "v"(H_carry), "v"(tok0), "v"(st0.w0), "v"(st0.w1), "v"(ln0.p[0].w0), "v"(ln0.p[0].w1), "v"(ln0.p[1].w0), "v"(ln0.p[1].w1));
     kb = kb > K ? K : (kb < 0 ? 0 : kb);
@@ -79,7 +81,10 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
         if (want_tok && (int)threadIdx.x < K && tok0 >= 0 && tok0 < a.V)
             xtok_first = load_elem_rt(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, threadIdx.x), a.dtype, tok0);
     if (threadIdx.x == 0) sh_flags = 0;                       // ahead of the barrier in the commit: rows of other wavefronts OR into it
-    if (__builtin_expect(msh >= 0, 1)) {
+    if (SHARDED && __builtin_expect(msh >= 0, 1)) {
+        // a record is complete: nothing to add back
+        lane_merge_commit<true>(sh_rows, lane_piece(ln0, 0, kb, a.nsplit, msh), lane_piece(ln0, 1, kb, a.nsplit, msh), kb, msh);
+    } else if (__builtin_expect(msh >= 0, 1)) {
         Piece e[2];
         BatchRegs bt[2];
         const int sl = threadIdx.x & ((1 << msh) - 1);
@@ -205,10 +210,12 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
                 if constexpr (SHARDED) {
                     // the shard that owns the token sent its logit; the others sent NaN
                     xt = NAN;
-                    for (int g = 0; g < a.nsplit; ++g) {
-                        const float v = __int_as_float(sh_part[(k - k0) * a.nsplit + g].pad[0]);
-                        if (v == v) xt = v;
-                    }
+                    if (msh >= 0) xt = sh_rows[k].xt;
+                    else
+                        for (int g = 0; g < a.nsplit; ++g) {
+                            const float v = __int_as_float(sh_part[(k - k0) * a.nsplit + g].pad[0]);
+                            if (v == v) xt = v;
+                        }
                 } else if (k != kmine) {
                     if (t >= 0 && t < a.V) xt = load_elem_rt(row, a.dtype, t);
                 }

@@ -313,7 +313,7 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
 {
     const int K = a.K;
     // few rows and slices: one partial per thread, merged across lanes (see lane_merge_commit); else staged in LDS
-    const int msh = SHARDED ? -1 : lane_merge_shift(K + 1, a.nsplit);
+    const int msh = lane_merge_shift(K + 1, a.nsplit);
     // The lane-parallel merge leaves the totals of all K + 1 <= 64 rows in LDS at once and row k with thread k: it is
     // one stage whatever the slice count.  The staged merge takes kStageCap partials at a time.
     const int rows_per_stage = msh >= 0 ? kWave : kStageCap / a.nsplit;
@@ -343,7 +343,13 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
     if (threadIdx.x == 0) { *sh_flags = 0; sh_bcast[4] = 0; }     // ahead of the staging barrier: rows of other wavefronts OR into the flags
     RowSlot *sh_rows = (RowSlot *)sh_part;
     static_assert(sizeof(RowSlot) * 64 <= sizeof(Partial) * kStageCap, "the row totals reuse the staging buffer");
-    if constexpr (SHARDED) {
+    if (SHARDED && __builtin_expect(msh >= 0, 1)) {
+        const LaneRegs ln = lane_merge_issue(a.part + (int64_t)b * (K + 1), K + 1, a.nsplit, msh, 1, (int64_t)a.B * (K + 1));
+        more_requests();
+        lane_merge_pin(ln, K + 1, msh);
+        shT[threadIdx.x] = tv;
+        lane_merge_commit<true>(sh_rows, lane_piece(ln, 0, K + 1, a.nsplit, msh), lane_piece(ln, 1, K + 1, a.nsplit, msh), K + 1, msh);
+    } else if constexpr (SHARDED) {
         const int c0 = min(K + 1, rows_per_stage) * a.nsplit;
         const StageRegs st = stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1), a.nsplit, c0);
         more_requests();
@@ -352,7 +358,7 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
     } else if (__builtin_expect(msh >= 0, 1)) {
         // target partials run over every element of their slice: plain pieces, nothing left out
         // all requests first, then one wait for the lot (see lane_merge_pin)
-        const LaneRegs ln = lane_merge_issue(a.part + (int64_t)b * (K + 1) * a.nsplit, K + 1, a.nsplit, msh);
+        const LaneRegs ln = lane_merge_issue(a.part + (int64_t)b * (K + 1) * a.nsplit, K + 1, a.nsplit, msh, a.nsplit, 1);
         const int qsh = own_q ? lane_merge_shift(K, a.d_nsplit) : -1;            // >= 0: the host offers own_q for such shapes only
         DraftLseRegs lq;
         if (qsh >= 0) lq = draft_rows_lse_issue(a.dpart + (int64_t)b * K * a.d_nsplit, K, a.d_nsplit, qsh);
@@ -789,7 +795,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
         uint8_t *sh_dec = q;
         job = verify_head<false>(a, b, writer, sh_part, sh_dec, sh_flags, sh_bcast, sh_lse, sh_qrows, shT, request_table);
     } else {
-        job = a.jobs[b].job;
+        job = a.final_jobs ? a.final_jobs[b] : a.jobs[b].job;      // vocabulary shards: the caller's copy
     }
     WG_STAMP(g_stamps_slices, 8, wg, 1);                         // job known
     if (job.kind == 0) return;
@@ -903,6 +909,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
                         const double diff = fma(-lam, bv, av);
                         if (fabs(diff) < band * bv) {
                             U += bv;
+                            if (!FUSED && a.final_jobs) continue;             // (vocabulary shards keep no band list)
                             const int pos = atomicAdd(&a.jobs[b].band_cnt, 1);
                             if (pos < kBandCap) a.jobs[b].band_idx[pos] = base + c * kWave * kPer + i;
                         }
@@ -1568,28 +1575,22 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
 }
 
 // ---- final token over vocabulary shards ---------------------------------------------------------
-// Copies the caller's jobs into the context's job records (the slice kernel reads them there and appends band
-// elements, which the sharded path counts but does not use).
-__global__ void shard_jobs_kernel(ShardFinalArgs a)
+// This shard's five sums per sequence, one wavefront per sequence (fixed order).
+__global__ __launch_bounds__(kVBlock) void shard_sums_kernel(ShardFinalArgs a)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    const int b = blockIdx.x * kWavesPerWG + (int)(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     if (b >= a.v.B) return;
-    a.v.jobs[b].job = a.jobs_in[b];
-    a.v.jobs[b].band_cnt = 0;
-}
-
-// This shard's five sums per sequence: the slice sums in slice order (fixed order, one thread per value).
-__global__ void shard_sums_kernel(ShardFinalArgs a)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.v.B * kSliceVals) return;
-    const int b = i / kSliceVals, q = i - b * kSliceVals;
-    double s = 0.0;
-    if (a.jobs_in[b].kind != 0 && (q == 0 || a.jobs_in[b].kind == 1)) {
-        const double *ps = a.v.part1 + (int64_t)b * a.v.nsl * kSliceVals;
-        for (int sl = 0; sl < a.v.nsl; ++sl) s += ps[sl * kSliceVals + q];
+    const int kind = a.v.final_jobs[b].kind;
+    const double *ps = a.v.part1 + (int64_t)b * a.v.nsl * kSliceVals;
+    double s[kSliceVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int sl = lane; sl < a.v.nsl; sl += kWave)
+#pragma unroll
+        for (int q = 0; q < kSliceVals; ++q) s[q] += ps[sl * kSliceVals + q];       // stale where the job has no such sum: dropped below
+#pragma unroll
+    for (int q = 0; q < kSliceVals; ++q) {
+        const double t = wave_sum_d(s[q]);
+        if (lane == 0) a.sums_out[(int64_t)b * kSliceVals + q] = (kind != 0 && (q == 0 || kind == 1)) ? t : 0.0;
     }
-    a.sums_out[i] = s;
 }
 
 // One workgroup per sequence.  Every shard runs this on the same sums_all, so all of them derive the same
@@ -1599,19 +1600,34 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
 {
     __shared__ double shT[256];
     __shared__ LocateShared shl;
+    warm_args(a);
     const VerifyArgs &v = a.v;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const SampleJob job = a.jobs_in[b];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
+    // everything that does not depend on the job is requested first (one round trip): the sums of the shards (lane h of
+    // every wavefront takes shards h, h + 64, ...), the slice sums of thread tid's slice, the table
+    double mine[kSliceVals], tot[kSliceVals];
+    const double *sa = a.sums_all + ((int64_t)min(lane, a.G - 1) * v.B + b) * kSliceVals;
+#pragma unroll
+    for (int q = 0; q < kSliceVals; ++q) mine[q] = sa[q];
+    const double *ps = v.part1 + (int64_t)b * v.nsl * kSliceVals;
+    const double *pf = ps + (tid < v.nsl ? tid : 0) * kSliceVals;
+    const double f0 = pf[0], f2 = pf[2], f3 = pf[3];
+    const double tv = v.exp_table[tid];
+    const float u32v = v.u_sample[b];
+    const SampleJob job = v.final_jobs[b];
+    asm volatile("" :: "v"(mine[0]), "v"(mine[1]), "v"(mine[2]), "v"(mine[3]), "v"(mine[4]), "v"(f0), "v"(f2), "v"(f3), "v"(tv), "v"(u32v));
     if (tid == 0) { a.tok_out[b] = -1; a.need_exact[b] = 0; a.exact_mass[b] = NAN; }
     if (job.kind == 0) return;
-    shT[tid] = v.exp_table[tid];
+    shT[tid] = tv;
     if (tid == 0) { shl.last = -1; shl.slice = 0x7fffffff; }
     __syncthreads();
-    // totals over all shards, shard order
-    double tot[kSliceVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int h = 0; h < a.G; ++h)
+    // totals over all shards, in one fixed order on every shard
 #pragma unroll
-        for (int q = 0; q < kSliceVals; ++q) tot[q] += a.sums_all[((int64_t)h * v.B + b) * kSliceVals + q];
+    for (int q = 0; q < kSliceVals; ++q) {
+        double t = lane < a.G ? mine[q] : 0.0;
+        for (int h = lane + kWave; h < a.G; h += kWave) t += a.sums_all[((int64_t)h * v.B + b) * kSliceVals + q];
+        tot[q] = wave_sum_d(t);
+    }
     const double Sp = tot[0], Sq = tot[1];
     Weights w;
     w.kind = job.kind;
@@ -1620,18 +1636,9 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
     w.lam = w.kind == 1 ? Sp / Sq : 0.0;
     const double delta = w.lam - job.lam;
     const Rows r = job_rows<TD, DD>(v, b, job);
-    const double *ps = v.part1 + (int64_t)b * v.nsl * kSliceVals;
     double *zs = v.part2 + (int64_t)b * v.nsl;
     int phase = 0;
-    // mass of shard h under the current weights
     bool exact = false;                       // masses and own slice weights are exact recomputations
-    auto shard_mass = [&](int h) -> double {
-        const double *sh = a.sums_all + ((int64_t)h * v.B + b) * kSliceVals;
-        if (w.kind == 2) return sh[0];
-        if (exact) return a.exact_all[(int64_t)h * v.B + b];
-        const double m = sh[2] - delta * sh[3];
-        return m > 0.0 ? m : 0.0;
-    };
     double Z = w.kind == 2 ? Sp : tot[2] - delta * tot[3];
     if (w.kind == 1) {
         const bool certified = fabs(delta) <= kEta * job.lam && Z > 0.0 && fabs(delta) * tot[4] <= 2.0e-10 * Z;
@@ -1651,8 +1658,9 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
                 return;
             }
             exact = true;
-            Z = 0.0;
-            for (int h = 0; h < a.G; ++h) Z += a.exact_all[(int64_t)h * v.B + b];
+            double t = 0.0;
+            for (int h = lane; h < a.G; h += kWave) t += a.exact_all[(int64_t)h * v.B + b];
+            Z = wave_sum_d(t);
             if (!(Z > 0.0)) {                                                   // p == q up to rounding: draw from the target row itself
                 w.kind = 2; exact = false; Z = Sp;
             }
@@ -1662,16 +1670,26 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
         if (tid == 0 && a.g == 0) a.tok_out[b] = a.vocab_offset;
         return;
     }
-    // owner: the first shard whose inclusive prefix of masses exceeds u * Z; the last one with mass if rounding leaves none
-    const double target = (double)v.u_sample[b] * Z;
+    // owner: the first shard whose inclusive prefix of masses exceeds u * Z; the last one with mass if rounding leaves none.
+    // Every wavefront walks the shards 64 at a time, lane h the mass of the h-th of them under the current weights.
+    const double target = (double)u32v * Z;
     double prefix = 0.0, mine_prefix = 0.0;
     int owner = -1, last_pos = -1;
-    for (int h = 0; h < a.G; ++h) {
-        const double m = shard_mass(h);
-        if (h == a.g) mine_prefix = prefix;
-        if (m > 0.0) last_pos = h;
-        if (owner < 0 && prefix + m > target) owner = h;
-        prefix += m;
+    for (int h0 = 0; h0 < a.G; h0 += kWave) {
+        const int h = h0 + lane;
+        double m = 0.0;
+        if (h < a.G) {
+            const double *sh = a.sums_all + ((int64_t)h * v.B + b) * kSliceVals;
+            const double m0 = h0 == 0 ? mine[0] : sh[0], m2 = h0 == 0 ? mine[2] : sh[2], m3 = h0 == 0 ? mine[3] : sh[3];
+            m = w.kind == 2 ? m0 : (exact ? a.exact_all[(int64_t)h * v.B + b] : fmax(m2 - delta * m3, 0.0));
+        }
+        double total;
+        const double incl = wave_incl_scan_d(m, &total);
+        const uint64_t past = __builtin_amdgcn_ballot_w64(h < a.G && prefix + incl > target), pos = __builtin_amdgcn_ballot_w64(m > 0.0);
+        if (a.g >= h0 && a.g < h0 + kWave) mine_prefix = prefix + lane_d(incl - m, a.g - h0);
+        if (owner < 0 && past) owner = h0 + __builtin_ctzll(past);
+        if (pos) last_pos = h0 + 63 - __builtin_clzll(pos);
+        prefix += total;
     }
     const bool fallback = owner < 0;
     if (fallback) owner = last_pos;
@@ -1682,36 +1700,9 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
         const double x = ps[s * kSliceVals + 2] - delta * ps[s * kSliceVals + 3];
         return x > 0.0 ? x : 0.0;
     };
-    int token = -1;
-    if (!fallback) {
-        const double local = target - mine_prefix;
-        // the first thread walks the slice weights (a few hundred at most; this kernel is rare-path simple)
-        if (tid == 0) {
-            double c = 0.0; int sf = -1;
-            for (int s = 0; s < v.nsl; ++s) { const double x = slice_weight(s); if (c + x > local) { sf = s; break; } c += x; }
-            shl.bc[0] = c; shl.slice = sf;
-        }
-        __syncthreads();
-        double cum = shl.bc[0];
-        const int s_found = shl.slice;
-        __syncthreads();
-        if (s_found >= 0)
-            for (int s = s_found; s < v.nsl && token < 0; ++s) {
-                double slice_total;
-                token = locate_in_slice<TD, DD>(w, r, s, v.V, shT, cum, local, &shl, phase++, &slice_total);
-                cum += slice_total;
-            }
-    }
-    if (token < 0) {                                                            // rounding left no crossing: the last positive weight here
-        if (tid == 0) shl.last = -1;
-        __syncthreads();
-        for (int s = 0; s < v.nsl; ++s) {
-            double slice_total;
-            locate_in_slice<TD, DD>(w, r, s, v.V, shT, 0.0, INFINITY, &shl, phase++, &slice_total, true);
-        }
-        __syncthreads();
-        token = shl.last;
-    }
+    // (a fallback's target lies beyond every slice: find_token then takes the last positive weight here)
+    const double z_mine = w.kind == 2 ? f0 : (exact ? (tid < v.nsl ? zs[tid] : 0.0) : fmax(f2 - delta * f3, 0.0));
+    const int token = find_token<TD, DD>(w, r, v.V, v.nsl, shT, fallback ? INFINITY : target - mine_prefix, z_mine, slice_weight, &shl, phase);
     if (tid == 0) a.tok_out[b] = a.vocab_offset + (token < 0 ? 0 : token);
 }
 
@@ -1719,9 +1710,8 @@ template <int TD, int DD>
 hipError_t launch_shard_typed(const ShardFinalArgs &a, int pass, hipStream_t st)
 {
     if (pass == 0) {
-        hipLaunchKernelGGL(shard_jobs_kernel, dim3((a.v.B + 63) / 64), dim3(64), 0, st, a);
         hipLaunchKernelGGL((verify_slices<TD, DD, false>), dim3((a.v.nsl + kWavesPerWG - 1) / kWavesPerWG, a.v.B), dim3(kVBlock), 0, st, a.v);
-        hipLaunchKernelGGL(shard_sums_kernel, dim3((a.v.B * kSliceVals + 63) / 64), dim3(64), 0, st, a);
+        hipLaunchKernelGGL(shard_sums_kernel, dim3((a.v.B + kWavesPerWG - 1) / kWavesPerWG), dim3(kVBlock), 0, st, a);
     } else {
         hipLaunchKernelGGL((shard_locate<TD, DD>), dim3(a.v.B), dim3(kVBlock), 0, st, a);
     }

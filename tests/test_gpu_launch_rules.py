@@ -7,7 +7,7 @@ import torch
 from oracle import oracle as orc
 from paper_2511_02017_amd import binding
 from tests import parity_util as pu
-from tests.test_gpu_parity import random_arms, random_round
+from tests.test_gpu_parity import force_slices, random_arms, random_round, sharded_round
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -163,3 +163,36 @@ def test_draft_token_draw_with_a_wavefront_per_slice(B, K, V, dt, ragged):
     given = tp.draft_stats(rnd["draft"], draft_tok=out["sampled_tok"], k_len=None if k_len is None else k_len.to(DEV))
     a, b = (torch.nan_to_num(x["logq_tok"][torch.from_numpy(live).to(DEV)], nan=7.0) for x in (out, given))
     assert torch.equal(a, b) and torch.equal(out["flags"], given["flags"])
+
+
+@pytest.mark.parametrize("G,V", [(1, 3000), (3, 9001), (16, 20000), (17, 20011), (64, 40000), (70, 33000)])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_vocabulary_shards_merged_across_lanes(G, V, dt):
+    """Up to sixteen shards the records of a row are merged across lanes, beyond that one after the other; the final token's
+    shard is found 64 shards at a time."""
+    B, K = 6, 5
+    rnd = mixed_round(B, K, V, dt, dt, seed=G)
+    rnd["greedy"][1] = 1
+    for u in (2.0 ** -12, 0.5, 1.0 - 2.0 ** -24):
+        rnd["u_sample"] = torch.full((B,), u, device=DEV)
+        acc, out, _ = sharded_round(rnd, G, V)
+        _, ref, nd = pu.oracle_round(rnd)
+        ok = ~((ref["accept_margin"] <= pu.TAU) & (np.arange(K)[None, :] < nd[:, None])).any(1) & ~(ref["icdf_margin"] <= pu.TAU_S)
+        assert ok.sum() >= B - 1
+        assert (acc.cpu().numpy()[ok] == ref["accept_len"][ok]).all() and (out.cpu().numpy()[ok] == ref["out_tok"][ok]).all()
+
+
+@pytest.mark.parametrize("P", [1, 2, 3, 16, 17])
+def test_shard_records_from_any_number_of_slices(P):
+    """Sixteen slices of a shard's row are merged across lanes, seventeen one after the other: the same record."""
+    B, K, V = 3, 4, 17 * 256 + 5
+    rnd = mixed_round(B, K, V, bf16, bf16, seed=P, k_len=[4, 2, 3])
+    tp = binding.Tapout(B, K, V)
+    force_slices(tp, B * K, P)
+    rec = tp.shard_stats(rnd["draft"], 0, length=rnd["k_len"], tok=rnd["draft_tok"])
+    out = tp.draft_stats_sharded(rec[None], B, K, V, draft_tok=rnd["draft_tok"], k_len=rnd["k_len"])
+    ref, _, _ = pu.oracle_round(rnd)
+    live = np.arange(K)[None, :] < rnd["k_len"].cpu().numpy()[:, None]
+    for key in pu.STAT_KEYS:
+        pu.assert_stats_close(key, out[key].cpu().numpy(), ref[key], live)
+    assert (out["top1_id"].cpu().numpy()[live] == ref["top1_id"][live]).all()
