@@ -3,6 +3,9 @@
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  torch supplies device memory and the stream; nothing here computes.
 The binding fails loudly if the built library is missing: there is no fallback.
+The per-round methods first try _marshal.so (csrc/marshal.cpp), which takes the
+tensors apart in native code and calls the library; where it finds an argument
+that is not in order it returns None and the code here describes the error.
 """
 from __future__ import annotations
 
@@ -66,16 +69,22 @@ class TapoutError(RuntimeError):
 
 
 _lib = None
+_fast = None
 
 
 def load_library(path: str = None):
     """Load the in-tree libtapout.so; raises if it has not been built.  `path` (first call only): another build of the
     same sources, such as the one with time stamps that wg_stamps.py measures with."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         path = path or LIB_PATH
         if not os.path.exists(path):
             raise ImportError(f"{path} is missing: build it with `python -m paper_2511_02017_amd.build`")
+        if not os.path.exists(os.path.join(_PKG, "_marshal.so")):
+            raise ImportError("_marshal.so is missing: build it with `python -m paper_2511_02017_amd.build`")
+        from . import _marshal
+        _marshal.load(path)
+        _fast = _marshal
         lib = C.CDLL(path)
         vp, i32 = C.c_void_p, C.c_int32
         lib.tapout_default_config.restype = None
@@ -141,9 +150,12 @@ def _logits(t, name) -> TapoutLogits:
     return TapoutLogits(t.data_ptr(), dt, t.stride(0), t.stride(1))
 
 
+def _handle(stream):
+    return None if stream is None else stream.cuda_stream
+
+
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    return _fast.current_stream() if stream is None else stream.cuda_stream
 
 
 STATIC_MAX_PARTIALS = 131072
@@ -211,9 +223,11 @@ class Tapout:
         st = self._lib.tapout_create(C.byref(self._ctx), C.byref(cfg))
         if st != 0:
             raise TapoutError(st, self._lib.tapout_last_error(None).decode())
+        self._addr = self._ctx.value                            # for the native marshalling; 0 once closed
 
     def close(self):
         ctx = getattr(self, "_ctx", None)
+        self._addr = 0
         if ctx is not None and ctx.value:
             self._lib.tapout_destroy(ctx)
             self._ctx = None
@@ -332,7 +346,10 @@ class Tapout:
         ushape = (B, A, TS_UNIFORMS_PER_ARM) if P == 1 else (B, P, A, TS_UNIFORMS_PER_ARM)
         if arm_out is None:
             arm_out = torch.empty(ashape, dtype=torch.int32, device=self.device)
-        self._check(self._lib.tapout_bandit_select(
+        st = _fast.bandit_select(self._addr, B, P, A, u_ts, arm_out, flags, _handle(stream))
+        if st == 0:
+            return arm_out
+        self._check(st if st is not None else self._lib.tapout_bandit_select(
             self._ctx, B, _ptr(u_ts, torch.float32, ushape, "u_ts"),
             _ptr(arm_out, torch.int32, ashape, "arm_out"), _ptr(flags, torch.int32, (B,), "flags"), _stream(stream)))
         return arm_out
@@ -346,9 +363,12 @@ class Tapout:
             out = self.alloc_draft_outputs(B, K)
         if u_draft is not None and "sampled_tok" not in out:
             out["sampled_tok"] = torch.full((B, K), -1, dtype=torch.int32, device=self.device)
+        st = _fast.draft_stats(self._addr, self.positions, draft, draft_tok, k_len, arm, u_draft, out, _handle(stream))
+        if st == 0:
+            return out
         f32, i32 = torch.float32, torch.int32
         lg = _logits(draft, "draft")
-        self._check(self._lib.tapout_draft_stats(
+        self._check(st if st is not None else self._lib.tapout_draft_stats(
             self._ctx, C.byref(lg), B, K, V,
             _ptr(draft_tok, i32, (B, K), "draft_tok"), _ptr(k_len, i32, (B,), "k_len"),
             _ptr(arm, i32, (B,) if self.positions == 1 else (B, self.positions), "arm"),
@@ -369,8 +389,11 @@ class Tapout:
         B, KK, Vs = shard.shape
         if out is None:
             out = torch.zeros((B * KK, 8), dtype=torch.int32, device=self.device)
+        st = _fast.shard_stats(self._addr, shard, vocab_offset, length, rows_mode, tok, out, _handle(stream))
+        if st == 0:
+            return out
         lg = _logits(shard, "shard")
-        self._check(self._lib.tapout_shard_stats(
+        self._check(st if st is not None else self._lib.tapout_shard_stats(
             self._ctx, C.byref(lg), B, KK, Vs, int(vocab_offset), _ptr(length, torch.int32, (B,), "len"), int(rows_mode),
             _ptr(tok, torch.int32, (B, KK - rows_mode), "tok"), _ptr(out, torch.int32, (B * KK, 8), "out"), _stream(stream)))
         return out
@@ -380,8 +403,11 @@ class Tapout:
         G = stats.shape[0]
         if out is None:
             out = self.alloc_draft_outputs(B, K)
+        st = _fast.draft_stats_sharded(self._addr, self.positions, stats, B, K, V, draft_tok, k_len, arm, out, _handle(stream))
+        if st == 0:
+            return out
         f32, i32 = torch.float32, torch.int32
-        self._check(self._lib.tapout_draft_stats_sharded(
+        self._check(st if st is not None else self._lib.tapout_draft_stats_sharded(
             self._ctx, _ptr(stats, i32, (G, B * K, 8), "stats"), G, B, K, V,
             _ptr(draft_tok, i32, (B, K), "draft_tok"), _ptr(k_len, i32, (B,), "k_len"),
             _ptr(arm, i32, (B,) if self.positions == 1 else (B, self.positions), "arm"),
@@ -403,8 +429,12 @@ class Tapout:
             out = self.alloc_verify_outputs(B, K)
         if draft_lse is not None and "final_jobs" not in out:
             out["final_jobs"] = torch.zeros((B, 24), dtype=torch.uint8, device=self.device)
+        st = _fast.verify_accept_sharded(self._addr, stats, B, K, V, logq_tok, draft_tok, n_draft, u_accept, greedy, draft_lse, out,
+                                         _handle(stream))
+        if st == 0:
+            return out
         f32, i32 = torch.float32, torch.int32
-        self._check(self._lib.tapout_verify_accept_sharded(
+        self._check(st if st is not None else self._lib.tapout_verify_accept_sharded(
             self._ctx, _ptr(stats, i32, (G, B * (K + 1), 8), "stats"), G, B, K, V,
             _ptr(logq_tok, f32, (B, K), "logq_tok"), _ptr(draft_tok, i32, (B, K), "draft_tok"), _ptr(n_draft, i32, (B,), "n_draft"),
             _ptr(greedy, torch.uint8, (B,), "greedy"), _ptr(u_accept, f32, (B, K), "u_accept"), _ptr(draft_lse, f32, (B, K), "draft_lse"),
@@ -419,9 +449,12 @@ class Tapout:
     def shard_final_sums(self, target_shard, draft_shard, jobs, stream=None):
         """This shard's five double-precision sums per sequence for the final-token draw: float64 tensor [B, 5]."""
         B, K1, Vs = target_shard.shape
-        sums = torch.zeros((B, 5), dtype=torch.float64, device=self.device)
+        sums = torch.empty((B, 5), dtype=torch.float64, device=self.device)           # the call writes every entry
+        st = _fast.shard_final_sums(self._addr, target_shard, draft_shard, jobs, sums, _handle(stream))
+        if st == 0:
+            return sums
         tl, dl = _logits(target_shard, "target shard"), _logits(draft_shard, "draft shard")
-        self._check(self._lib.tapout_shard_final_sums(self._ctx, C.byref(tl), C.byref(dl), B, K1 - 1, Vs,
+        self._check(st if st is not None else self._lib.tapout_shard_final_sums(self._ctx, C.byref(tl), C.byref(dl), B, K1 - 1, Vs,
                                                       _ptr(jobs, torch.uint8, (B, 24), "jobs"), _ptr(sums, torch.float64, (B, 5), "sums"),
                                                       _stream(stream)))
         return sums
@@ -431,11 +464,15 @@ class Tapout:
         """(tok [B] int32: global id where this shard holds the draw, else -1; exact_mass [B] float64; need_exact [B] uint8)."""
         B, K1, Vs = target_shard.shape
         d = self.device
-        tok = torch.full((B,), -1, dtype=torch.int32, device=d)
-        mass = torch.zeros(B, dtype=torch.float64, device=d)
-        need = torch.zeros(B, dtype=torch.uint8, device=d)
+        tok = torch.empty(B, dtype=torch.int32, device=d)                              # the call writes every entry of the three
+        mass = torch.empty(B, dtype=torch.float64, device=d)
+        need = torch.empty(B, dtype=torch.uint8, device=d)
+        st = _fast.shard_final_token(self._addr, target_shard, draft_shard, vocab_offset, G, g, jobs, sums_all, exact_all, u_sample,
+                                     tok, mass, need, _handle(stream))
+        if st == 0:
+            return tok, mass, need
         tl, dl = _logits(target_shard, "target shard"), _logits(draft_shard, "draft shard")
-        self._check(self._lib.tapout_shard_final_token(
+        self._check(st if st is not None else self._lib.tapout_shard_final_token(
             self._ctx, C.byref(tl), C.byref(dl), B, K1 - 1, Vs, int(vocab_offset), int(G), int(g),
             _ptr(jobs, torch.uint8, (B, 24), "jobs"), _ptr(sums_all, torch.float64, (G, B, 5), "sums_all"),
             _ptr(exact_all, torch.float64, (G, B), "exact_all"), _ptr(u_sample, torch.float32, (B,), "u_sample"),
@@ -462,9 +499,13 @@ class Tapout:
             raise ValueError(f"draft logits must be {(B, K, V)}, got {tuple(draft.shape)}")
         if out is None:
             out = self.alloc_verify_outputs(B, K)
+        st = _fast.verify(self._addr, target, draft, draft_lse, logq_tok, draft_tok, n_draft, u_accept, u_sample, greedy, out,
+                          _handle(stream))
+        if st == 0:
+            return out
         f32, i32 = torch.float32, torch.int32
         tl, dl = _logits(target, "target"), _logits(draft, "draft")
-        self._check(self._lib.tapout_verify(
+        self._check(st if st is not None else self._lib.tapout_verify(
             self._ctx, C.byref(tl), C.byref(dl), B, K, V,
             _ptr(draft_lse, f32, (B, K), "draft_lse"), _ptr(logq_tok, f32, (B, K), "logq_tok"),
             _ptr(draft_tok, i32, (B, K), "draft_tok"), _ptr(n_draft, i32, (B,), "n_draft"),
@@ -490,8 +531,11 @@ class Tapout:
     # -- tapout_bandit_update ------------------------------------------------
     def bandit_update(self, arm, accept_len, n_draft, gamma, active=None, stream=None):
         B = arm.shape[0]
+        st = _fast.bandit_update(self._addr, B, self.positions, arm, accept_len, n_draft, gamma, active, _handle(stream))
+        if st == 0:
+            return
         i32 = torch.int32
-        self._check(self._lib.tapout_bandit_update(
+        self._check(st if st is not None else self._lib.tapout_bandit_update(
             self._ctx, B, _ptr(arm, i32, (B,) if self.positions == 1 else (B, self.positions), "arm"),
             _ptr(accept_len, i32, (B,), "accept_len"),
             _ptr(n_draft, i32, (B,), "n_draft"), _ptr(gamma, i32, (B,), "gamma"),
@@ -508,7 +552,10 @@ class Tapout:
         ushape = (B, A, TS_UNIFORMS_PER_ARM) if P == 1 else (B, P, A, TS_UNIFORMS_PER_ARM)
         if arm_out is None:
             arm_out = torch.empty(ashape, dtype=i32, device=self.device)
-        self._check(self._lib.tapout_bandit_update_select(
+        st = _fast.bandit_update_select(self._addr, B, P, A, arm, accept_len, n_draft, gamma, active, u_ts, arm_out, flags, _handle(stream))
+        if st == 0:
+            return arm_out
+        self._check(st if st is not None else self._lib.tapout_bandit_update_select(
             self._ctx, B, _ptr(arm, i32, ashape, "arm"), _ptr(accept_len, i32, (B,), "accept_len"),
             _ptr(n_draft, i32, (B,), "n_draft"), _ptr(gamma, i32, (B,), "gamma"), _ptr(active, torch.uint8, (B,), "active"),
             _ptr(u_ts, torch.float32, ushape, "u_ts"), _ptr(arm_out, i32, ashape, "arm_out"), _ptr(flags, i32, (B,), "flags"),

@@ -1,4 +1,4 @@
-"""Builds libtapout.so (HIP, gfx950) in-tree with hipcc.
+"""Builds libtapout.so (HIP, gfx950) in-tree with hipcc, and _marshal.so, the binding's native part, with g++.
 
 Run as `python -m paper_2511_02017_amd.build`.  hipcc cross-compiles without a
 GPU, so this works on a CPU-only machine.  With `--stamps` it builds
@@ -17,6 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(PKG, "libtapout.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 LIB_STAMPS = os.path.join(PKG, "libtapout_stamps.so")
 SOURCES = ["row_reduce.hip", "finalize.hip", "verify.hip", "bandit.hip", "api.hip"]
 
@@ -66,5 +67,26 @@ def build(verbose: bool = False, extra_flags=(), stamps: bool = False) -> str:
     return lib
 
 
+def build_marshal() -> str:
+    """_marshal.so, the native argument marshalling of binding.py: host code against torch's own headers and libraries."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))) if os.path.sep in hipcc() else "/opt/rocm"
+    if not os.path.isdir(os.path.join(rocm, "include", "hip")):
+        rocm = "/opt/rocm"
+    libs = cpp_extension.library_paths()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=" + ("1" if __import__("torch")._C._GLIBCXX_USE_CXX11_ABI else "0"),
+           "-I", os.path.join(ROOT, "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+           *(a for p in cpp_extension.include_paths() for a in ("-isystem", p)), os.path.join(CSRC, "marshal.cpp"),
+           *(a for p in libs for a in ("-L", p)), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ldl", "-o", MARSHAL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on marshal.cpp:\n{r.stdout}\n{r.stderr}")
+    return MARSHAL
+
+
 if __name__ == "__main__":
+    print(build_marshal())
     print(build(verbose="-v" in sys.argv, stamps="--stamps" in sys.argv))

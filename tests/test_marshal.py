@@ -1,0 +1,87 @@
+"""The native argument marshalling of the binding (csrc/marshal.cpp): it calls the library only when every argument is in
+order, and hands everything else to the Python code, which describes the error."""
+import pytest
+import torch
+
+from paper_2511_02017_amd import binding
+
+f32, i32, u8 = torch.float32, torch.int32, torch.uint8
+
+
+def test_arguments_that_are_not_in_order_go_to_the_python_code():
+    """No GPU needed: nothing here reaches the library (the context's address is no context)."""
+    binding.load_library()
+    fast = binding._fast
+    d, t = torch.zeros(2, 3, 8), torch.zeros(2, 4, 8)                       # not on a GPU
+    out = {}
+    assert fast.draft_stats(1, 1, d, None, None, None, None, out, None) is None
+    assert fast.draft_stats(0, 1, d, None, None, None, None, out, None) is None     # closed context
+    assert fast.draft_stats(None, 1, d, None, None, None, None, out, None) is None
+    assert fast.verify(1, t, d, None, None, None, None, None, None, None, out, 0) is None
+    assert fast.bandit_select(1, 2, 1, 3, None, None, None, 0) is None              # arm_out missing
+    assert fast.bandit_select(1, 2, 1, 3, torch.zeros(2, 3, 48), torch.zeros(2, dtype=i32), None, 0) is None
+    assert fast.shard_stats(1, d, 0, None, 0, None, None, 0) is None
+    assert fast.shard_final_sums(1, t, d, None, None, 0) is None
+    assert fast.verify(1) is None and fast.draft_stats() is None                    # wrong number of arguments
+    assert fast.draft_stats(1, 1, "x", None, None, None, None, out, None) is None
+    assert fast.draft_stats(1 << 80, 1, d, None, None, None, None, out, None) is None
+    with pytest.raises(ImportError):
+        fast.load("/nonexistent/libtapout.so")
+    assert fast.verify(1) is None                                                   # the library loaded before stays
+
+
+@pytest.mark.gpu
+def test_errors_are_those_of_the_python_code():
+    B, K, V = 2, 3, 100
+    tp = binding.Tapout(B, K, V)
+    x = torch.randn(B, K, V, device="cuda:0")
+    tok = torch.zeros(B, K, dtype=i32, device="cuda:0")
+    with pytest.raises(ValueError, match="draft_tok: expected shape"):
+        tp.draft_stats(x, tok[:, :2].contiguous())
+    with pytest.raises(ValueError, match="draft_tok: expected torch.int32"):
+        tp.draft_stats(x, tok.long())
+    with pytest.raises(ValueError, match="must live on the GPU"):
+        tp.draft_stats(x, tok.cpu())
+    with pytest.raises(ValueError, match="must be contiguous"):
+        tp.draft_stats(x, torch.zeros(K, B, dtype=i32, device="cuda:0").t())
+    with pytest.raises(ValueError, match="not supported"):
+        tp.draft_stats(x.half())
+    with pytest.raises(ValueError, match="vocabulary axis"):
+        tp.draft_stats(torch.randn(B, V, K, device="cuda:0").transpose(1, 2))
+    with pytest.raises(ValueError, match="arm: expected shape"):
+        tp.draft_stats(x, arm=torch.zeros(B + 1, dtype=i32, device="cuda:0"))
+    with pytest.raises(binding.TapoutError, match="max_k"):
+        tp.draft_stats(torch.randn(B, K + 1, V, device="cuda:0"))
+    with pytest.raises(binding.TapoutError, match="exclude each other|draft_sampling"):
+        tp.draft_stats(x, tok, u_draft=torch.rand(B, K, device="cuda:0"))
+    out = tp.alloc_draft_outputs(B, K)
+    out["lse"] = out["lse"][:, :2]
+    with pytest.raises(ValueError, match="lse: expected shape"):
+        tp.draft_stats(x, tok, out=out)
+    tp.close()
+    with pytest.raises(binding.TapoutError):
+        tp.draft_stats(x, tok)
+
+
+@pytest.mark.gpu
+def test_streams_views_and_parameters():
+    """The current stream, a stream handed in, strided views and tensors that take gradients: the same results."""
+    B, K, V = 3, 4, 5000
+    tp = binding.Tapout(B, K, V)
+    full = torch.randn(B, K + 2, V + 40, device="cuda:0")
+    tok = torch.randint(0, V, (B, K), dtype=i32, device="cuda:0")
+    view = full[:, 1:K + 1, 13:V + 13]
+    torch.cuda.synchronize()
+    want = tp.draft_stats(view.contiguous(), tok)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        a = tp.draft_stats(view, tok)
+    s.synchronize()
+    b = tp.draft_stats(view, tok, stream=s)
+    s.synchronize()
+    c = tp.draft_stats(torch.nn.Parameter(view), tok)
+    torch.cuda.synchronize()
+    for got in (a, b, c):
+        assert torch.equal(got["top1_id"], want["top1_id"])
+        assert torch.allclose(got["lse"], want["lse"], rtol=0, atol=1e-5) and torch.allclose(got["logq_tok"], want["logq_tok"], rtol=0, atol=1e-5)
