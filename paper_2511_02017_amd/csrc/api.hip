@@ -868,7 +868,7 @@ hipError_t verify_rest(tapout_ctx *ctx, const VerifyCall &c, hipStream_t st, con
     if (fin) { va.vflags |= kVerifyOwnQ; va.d_nsplit = fin_nsplit; va.dpart = fin->part; }
     if (!ctx->exp_lookup) va.vflags |= kVerifyNoExpTable;
     if (tail) {
-        va.bandit_tail = tail_kind;                 // 1: in the locate workgroups (UCB), 2: workgroups of their own (Thompson Sampling)
+        va.bandit_tail = tail_kind;
         va.bandit = bandit_args(ctx, c.B);
         va.b_arm_in = tail->arm_in; va.b_gamma = tail->gamma; va.b_active = tail->active; va.b_u_ts = tail->u_ts;
         va.b_arm_out = tail->arm_out; va.b_flags = tail->flags;
@@ -970,13 +970,12 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
         e = verify_target_pass(ctx, c, st);
         if (e != hipSuccess) return hip_fail(ctx, e, "target pass launch");
     }
-    // Sequence-level UCB bandits, one per sequence: the final-token locate kernel, one workgroup per sequence, also
-    // applies the reward and picks the next arm.  Gaussian Thompson Sampling, shared and token-level bandits take a
-    // launch of their own.
+    // Sequence-level bandits, one per sequence, UCB or Thompson Sampling with Beta posteriors: workgroups of their own in
+    // the final-token locate kernel's launch apply the rewards and pick the next arms.  Gaussian Thompson Sampling, shared
+    // and token-level bandits take a launch of their own.
     // (a shared bandit with one sequence is that sequence's own)
     const bool own = ctx->positions == 1 && (ctx->cfg.n_bandits != 1 || a->B == 1);
     const bool tail = own && (ctx->cfg.policy == TAPOUT_UCB1 || ctx->cfg.policy == TAPOUT_UCB_TUNED);
-    // Thompson Sampling with Beta posteriors: the same launch carries the end of the round as workgroups of its own
     const bool ts_tail = own && ctx->cfg.policy == TAPOUT_TS_BETA && a->u_ts_next != nullptr;
     const RoundTail rt{a->arm, a->gamma, a->active, a->u_ts_next, a->arm, a->select_flags};
     e = verify_rest(ctx, c, st, (tail || ts_tail) ? &rt : nullptr, defer ? &fin : nullptr, fin_nsplit, ts_tail ? 2 : 1);

@@ -193,10 +193,10 @@ struct VerifyArgs {
     double *part1;                // [B, nsl, 5]  A, B, R~, D, U of each slice
     double *part2;                // [B, nsl]     exact weight of each slice (slow path)
     const double *exp_table;      // 2^(k/256), k = 0..255, then the kExpBf16Doubles entries of the bfloat16 table
-    // tapout_round: the locate kernel also ends the round of its sequence: reward into the sequence's bandit
-    // (arm b_arm_in[b], accept_len, n_draft, b_gamma, b_active as tapout_bandit_update) and the arm of the next round
-    // (b_arm_out, b_flags as tapout_bandit_select).  Sequence-level UCB bandits, one per sequence.
-    int32_t bandit_tail;
+    // tapout_round: workgroups of the locate launch also end the round: rewards into the sequences' bandits
+    // (arm b_arm_in[b], accept_len, n_draft, b_gamma, b_active as tapout_bandit_update) and the arms of the next round
+    // (b_arm_out, b_flags as tapout_bandit_select).  Sequence-level bandits, one per sequence.
+    int32_t bandit_tail;          // 0: no; 1: UCB1, UCB-Tuned; 2: Thompson Sampling with Beta posteriors
     BanditArgs bandit;
     const int32_t *b_arm_in, *b_gamma; const uint8_t *b_active; const float *b_u_ts; int32_t *b_arm_out; uint32_t *b_flags;
     // tapout_round with n_draft from the caller: the accept decisions form log q(tok) and the draft rows' lse themselves

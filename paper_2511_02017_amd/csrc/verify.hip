@@ -1170,27 +1170,28 @@ __device__ __noinline__ double settle_band(const Weights &w, const Rows &r, int 
     return total;
 }
 
-// TAIL: the workgroup also ends its sequence's round for the UCB policies (a logarithm and a square root per arm, one
-// thread).  Thompson Sampling is not offered here: its Gamma / Gaussian draws are long double-precision chains that
-// want 178 registers and scratch memory, which this kernel would then pay for at every launch (measured: twice as long).
-//
 // FIN (whole-round calls whose accept decisions did not wait for the draft epilogue): the launch carries
 // that epilogue's workgroups too, one per sequence, ahead of the locate workgroups: two latency-bound kernels of a
 // few dozen workgroups each run side by side instead of one after the other.
-template <int TD, int DD, bool TAIL, bool FIN>
+template <int TD, int DD, bool FIN>
 __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFinalArgs fin)
 {
     if constexpr (FIN) warm_args(a, fin); else warm_args(a);
     static_assert(kVBlock == kFinalBlock, "the draft epilogue runs in this kernel's workgroups");
     LOCATE_STAMP(0);                                             // entry
-    // Thompson Sampling (tapout_round, bandit_tail == 2): the end of the round needs nothing of this launch, only the
-    // accepted lengths of an earlier one, so it rides along as workgroups of its own behind the others, sixteen
-    // sequences each (sixteen lanes per sequence), instead of taking a launch after this one.
-    if (a.bandit_tail == 2) {
-        const int first = (FIN ? a.B : 0) + a.B;
-        if ((int)blockIdx.x >= first) {
-            update_select_ts_lanes(a.bandit, ((int)blockIdx.x - first) * (kVBlock / 16) + (int)(threadIdx.x >> 4), threadIdx.x & 15,
-                                   a.b_arm_in, a.accept_len, a.n_draft, a.b_gamma, a.b_active, a.b_u_ts, a.b_arm_out, a.b_flags);
+    // tapout_round: the end of the round needs nothing of this launch, only the accepted lengths of an earlier one, so it
+    // rides along as workgroups of its own behind the others instead of taking a launch after this one: a few lanes per
+    // sequence (UCB: one per arm, Thompson Sampling: two).  (UCB at the end of the locate workgroups themselves, behind
+    // the token, made them 2 us longer: V = 128256, 64 sequences, up to the stop position 8.0 us, this 6.0.)
+    if (a.bandit_tail) {
+        const int wg = (int)blockIdx.x - (FIN ? 2 : 1) * a.B;
+        if (wg >= 0) {
+            if (a.bandit_tail == 2)
+                update_select_ts_lanes(a.bandit, wg * (kVBlock / 16) + (int)(threadIdx.x >> 4), threadIdx.x & 15,
+                                       a.b_arm_in, a.accept_len, a.n_draft, a.b_gamma, a.b_active, a.b_u_ts, a.b_arm_out, a.b_flags);
+            else
+                update_select_ucb_lanes(a.bandit, wg * (kVBlock / TAPOUT_MAX_ARMS) + (int)(threadIdx.x / TAPOUT_MAX_ARMS), threadIdx.x % TAPOUT_MAX_ARMS,
+                                        a.b_arm_in, a.accept_len, a.n_draft, a.b_gamma, a.b_active, a.b_arm_out, a.b_flags);
             return;
         }
     }
@@ -1223,26 +1224,10 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     const int band_n = a.jobs[b].band_cnt;
     const int band_i = a.jobs[b].band_idx[tid & (kBandCap - 1)];                                  // stale beyond band_n: unused
     const SampleJob job = a.jobs[b].job;
-    // TAIL: the first thread also requests what the end of the round reads (bandit state of the sequence, its arm,
-    // lengths; the accepted length is the head's, written by an earlier launch)
-    UcbLane ucb;
-    int32_t acc_len = 0;
-    if constexpr (TAIL)
-        if (tid < TAPOUT_MAX_ARMS) {                                  // one arm per lane
-            ucb = ucb_lane_prefetch(a.bandit, b, tid, a.b_arm_in, a.n_draft, a.b_gamma, a.b_active);
-            acc_len = a.accept_len[b];
-            asm volatile("" :: "v"(ucb.S), "v"(ucb.Q), "v"(ucb.N), "v"(ucb.arm), "v"(ucb.n_draft), "v"(ucb.gamma), "v"(acc_len));
-        }
     // the compiler would otherwise sink these loads below the early exit and pay a second round trip for them
     asm volatile("" :: "v"(f0), "v"(f1), "v"(f2), "v"(f3), "v"(f4), "v"(tv), "v"(u32v), "v"(band_n), "v"(band_i));
     shT[tid] = tv;
-    // tapout_round: this workgroup also ends the sequence's round (the accepted length is the head's, written by an
-    // earlier launch): reward into its bandit, next arm.
-    auto end_round = [&]() {
-        if constexpr (TAIL)
-            if (tid < TAPOUT_MAX_ARMS) ucb_lane_finish(a.bandit, b, tid, ucb, acc_len, a.b_arm_out, a.b_flags);
-    };
-    if (__builtin_expect(job.kind == 0, 0)) { end_round(); return; }                       // the slice sums of such a sequence are stale: unused
+    if (__builtin_expect(job.kind == 0, 0)) return;                  // the slice sums of such a sequence are stale: unused
     if (has_first) { acc[0] = f0; acc[1] = f1; acc[2] = f2; acc[3] = f3; acc[4] = f4; }
     for (int s = tid + kVBlock; s < a.nsl; s += kVBlock)              // vocabularies beyond 256 slices
 #pragma unroll
@@ -1359,8 +1344,7 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
             if (a.flags) a.flags[b] = f;
         }
     }
-    end_round();
-    LOCATE_STAMP(5);                                             // round ended (bandit update, next arm)
+    LOCATE_STAMP(5);                                             // outputs written
 }
 
 // ---- draft-token sampling: the inverse CDF of every live draft row ---------------------------
@@ -1735,15 +1719,11 @@ hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool wit
         else launch_kernel(verify_slices<TD, DD, false>, grid12, block, st, tm, a);
     }
     else {
-        // bandit_tail 1: the locate workgroups end the round (UCB); 2: workgroups of their own do (Thompson Sampling)
-        const unsigned extra = a.bandit_tail == 2 ? (unsigned)((a.B + kVBlock / 16 - 1) / (kVBlock / 16)) : 0u;
-        const bool tail = a.bandit_tail == 1;
-        if (with_fin) {
-            if (!tail) launch_kernel(verify_locate<TD, DD, false, true>, dim3(2 * a.B + extra), block, st, tm, a, fin);
-            else launch_kernel(verify_locate<TD, DD, true, true>, dim3(2 * a.B), block, st, tm, a, fin);
-        }
-        else if (!tail) launch_kernel(verify_locate<TD, DD, false, false>, dim3(a.B + extra), block, st, tm, a, fin);
-        else launch_kernel(verify_locate<TD, DD, true, false>, dim3(a.B), block, st, tm, a, fin);
+        // workgroups that end the round: 32 sequences each (UCB, bandit_tail 1) or sixteen (Thompson Sampling, 2)
+        const int per_wg = kVBlock / (a.bandit_tail == 2 ? 16 : TAPOUT_MAX_ARMS);
+        const unsigned extra = a.bandit_tail ? (unsigned)((a.B + per_wg - 1) / per_wg) : 0u;
+        if (with_fin) launch_kernel(verify_locate<TD, DD, true>, dim3(2 * a.B + extra), block, st, tm, a, fin);
+        else launch_kernel(verify_locate<TD, DD, false>, dim3(a.B + extra), block, st, tm, a, fin);
     }
     return hipGetLastError();
 }
@@ -1802,7 +1782,7 @@ hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing t
 // (0 entry, 1 job known, 2 tables in LDS and rows requested, 3..6 each wavefront's loop done, 7 sums stored);
 // table 1: accept decisions inside the slice kernel, 4 slots (0 first requests answered, 1 rows merged, 2 decisions
 // taken, 3 first rejection published); table 2: locate kernel, 8 slots by blockIdx.x (0 entry, 1 first requests
-// answered, 2 total weight known, 3 slice found, 4 token found, 5 round ended; 7: a draft epilogue workgroup is done).
+// answered, 2 total weight known, 3 slice found, 4 token found, 5 written; 7: a draft epilogue workgroup is done).
 // Units: 10 ns.  Not part of the library's interface.
 extern "C" __attribute__((visibility("default"))) int tapout_debug_wg_stamps(int table, unsigned long long *host, int n_wg)
 {

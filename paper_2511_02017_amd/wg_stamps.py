@@ -92,7 +92,7 @@ def main(argv) -> int:
     print(line("locate: -> total weight known", lo[:, 2] - lo[:, 1]))
     print(line("locate: -> slice found", (lo[:, 3] - lo[:, 2])[lo[:, 3] > 0]))
     print(line("locate: -> token found", (lo[:, 4] - np.maximum(lo[:, 3], lo[:, 2]))[lo[:, 4] > 0]))
-    print(line("locate: -> round ended", lo[:, 5] - lo[:, 4]))
+    print(line("locate: -> token written", lo[:, 5] - lo[:, 4]))
     print(line("locate: workgroup total", lo[:, 5] - lo[:, 0]))
     if with_fin:
         fi = loc[:w.B]
