@@ -370,6 +370,43 @@ __device__ inline StageRegs stage_issue_shards(const Partial *src, int64_t rows_
     return r;
 }
 
+// 2^f for |f| <= 1/2: the Taylor polynomial of exp(f ln 2) to the 13th power (remainder < 4e-18), evaluated in pairs so that
+// the chain of dependent operations is six long.
+__device__ inline double exp2_frac(double f)
+{
+    constexpr double c[14] = {1.0, 0.6931471805599453, 0.24022650695910072, 0.05550410866482158, 0.009618129107628477, 0.0013333558146428443, 0.0001540353039338161, 1.5252733804059841e-05, 1.321548679014431e-06, 1.01780860092397e-07, 7.054911620801123e-09, 4.4455382718708116e-10, 2.5678435993488206e-11, 1.3691488853904128e-12};
+    const double f2 = f * f, f4 = f2 * f2;
+    const double p0 = fma(c[1], f, c[0]), p1 = fma(c[3], f, c[2]), p2 = fma(c[5], f, c[4]), p3 = fma(c[7], f, c[6]);
+    const double p4 = fma(c[9], f, c[8]), p5 = fma(c[11], f, c[10]), p6 = fma(c[13], f, c[12]);
+    const double q0 = fma(p1, f2, p0), q1 = fma(p3, f2, p2), q2 = fma(p5, f2, p4);
+    return fma(fma(fma(p6, f4, q2), f4, q1), f4, q0);
+}
+// 2^x for x <= 0 (also -inf; underflows to 0).
+__device__ inline double exp2_neg(double x)
+{
+    x = fmax(x, -1100.0);
+    const double n = rint(x);
+    return ldexp(exp2_frac(x - n), (int)n);
+}
+// log2 x for x in the range of normal binary32 numbers: the hardware's binary32 logarithm y, then one step of Newton's method
+// in double: log2 x = y + log2(1 + d), d = x 2^-y - 1, |d| < 4e-6.  Like exp2_neg good to about two units in the last
+// place of a double; the device library's functions, which are good to one and cover every argument, take several
+// times the instructions, one after the other in a kernel that is nothing but latency.
+__device__ inline double log2_pos(double x)
+{
+    const float y = __builtin_amdgcn_logf((float)x), n = rintf(y);
+    const double d = fma(ldexp(x, -(int)n), exp2_frac((double)(n - y)), -1.0);
+    constexpr double l = 1.4426950408889634;
+    return (double)y + d * fma(d, fma(d, l / 3.0, -0.5 * l), l);
+}
+// 1 / x for normal x whose reciprocal is normal: the hardware's approximation (2^-24 or better) and two Newton steps.
+__device__ inline double rcp_pos(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
 // v[i] for a small array that lives in scalar registers (kernel arguments): selects instead of a load from
 // the argument buffer, which would be one more memory round trip.
 template <class T>
@@ -489,13 +526,13 @@ struct RowSignals { double lse, H, p1, p2, margin; };
 __device__ inline RowSignals row_signals(const RowTotal &r, bool has_second)
 {
     RowSignals o;
-    const double inv = 1.0 / r.eM, eps = r.Sx * inv;
-    const double l2 = log2(1.0 + eps);
-    o.p1 = 1.0 / (1.0 + eps);
+    const double inv = rcp_pos(r.eM), eps = r.Sx * inv;          // eM in (1/2, 1], eps below the vocabulary size
+    const double l2 = log2_pos(1.0 + eps);
+    o.p1 = rcp_pos(1.0 + eps);
     o.lse = (r.R + r.yM + l2) * kLn2;
     const double Hd = (l2 + (r.yM * eps - r.Tx * inv) * o.p1) * kLn2;
     o.H = Hd > 0.0 ? Hd : 0.0;
-    const double r2 = has_second ? exp2(((double)r.v2 - (double)r.M) * (double)kLog2e) : 0.0;
+    const double r2 = has_second ? exp2_neg(((double)r.v2 - (double)r.M) * (double)kLog2e) : 0.0;
     o.p2 = r2 * o.p1;
     o.margin = (1.0 - r2) * o.p1;
     return o;
@@ -518,9 +555,26 @@ struct BatchRegs {
 // tell), the compiler has no loaded registers to merge between branches.  With the requests inside the branches it
 // merged them with the zeros of the other paths and waited for the data right there: a second memory round trip in a
 // kernel that is nothing but round trips.
-__device__ inline BatchRegs batch_issue(const void *row, int dtype, int32_t V, int32_t cand, int split, int per, const void *safe)
+// What of it does not depend on the candidate comes apart (BatchGeom): a caller forms it while the partial travels.
+struct BatchGeom {
+    const char *row;
+    int32_t head, nvec, v0, v1e;      // the row's unaligned elements and whole vectors; the slice's vectors [v0, v1e)
+};
+__device__ inline BatchGeom batch_geom(const void *row, int dtype, int32_t V, int split, int per)
 {
     const int esz = dtype == TAPOUT_F32 ? 4 : 2, vsh = dtype == TAPOUT_F32 ? 2 : 3, VEC = 1 << vsh;
+    BatchGeom g;
+    g.row = (const char *)row;
+    const int mis = (int)(((uintptr_t)row & 15u) / (unsigned)esz);              // as row_geometry
+    g.head = min((VEC - mis) & (VEC - 1), V);
+    g.nvec = (V - g.head) >> vsh;
+    g.v0 = min(split * per, g.nvec);
+    g.v1e = min(g.v0 + per, g.nvec);
+    return g;
+}
+__device__ inline BatchRegs batch_issue(const BatchGeom &g, int dtype, int32_t V, int32_t cand, const void *safe)
+{
+    const int esz = dtype == TAPOUT_F32 ? 4 : 2, vsh = dtype == TAPOUT_F32 ? 2 : 3;
     BatchRegs b;
     b.valid = 0; b.first = 0; b.ucand = 0; b.single = 0;
     // (device memory, and said so: chosen among several pointers the compiler would otherwise treat them as generic
@@ -530,27 +584,23 @@ __device__ inline BatchRegs batch_issue(const void *row, int dtype, int32_t V, i
 #pragma unroll
     for (int u = 0; u < kStreamU; ++u) p[u] = (GlobalVec)safe;
     if (cand >= 0 && cand < V) {
-        // the row's unaligned head, 16-byte vectors and tail (as row_geometry)
-        const int mis = (int)(((uintptr_t)row & 15u) / (unsigned)esz);
-        int head = (VEC - mis) & (VEC - 1);
-        if (head > V) head = V;
-        const int nvec = (V - head) >> vsh;
-        if (cand < head || cand >= head + (nvec << vsh)) {
-            b.single = __float_as_uint(load_elem_rt(row, dtype, cand));
+        if (cand < g.head || cand >= g.head + (g.nvec << vsh)) {
+            b.single = __float_as_uint(load_elem_rt(g.row, dtype, cand));
             b.valid = 0x100u; b.first = cand;
         } else {
-            const int i = (cand - head) >> vsh;
-            const int v0 = min(split * per, nvec), v1e = min(v0 + per, nvec);
-            if (i >= v0 && i < v1e) {                                           // else: not a candidate of this slice: stale record
-                const int rel = i - v0, t = rel % kBlock, q0 = (rel / kBlock) / kStreamU * kStreamU;
-                GlobalVec vp = (GlobalVec)((const char *)row + (int64_t)head * esz);
-                b.first = head + ((v0 + t + q0 * kBlock) << vsh);
-                b.ucand = rel / kBlock - q0;
+            const int i = (cand - g.head) >> vsh, rel = i - g.v0;
+            if (rel >= 0 && i < g.v1e) {                                        // else: not a candidate of this slice: stale record
+                constexpr int kSpan = kBlock * kStreamU;                        // vectors of a batch; thread t holds every kBlock-th
+                static_assert((kSpan & (kSpan - 1)) == 0 && (kBlock & (kBlock - 1)) == 0, "masks below");
+                const int i0 = g.v0 + (rel & ~(kSpan - 1)) + (rel & (kBlock - 1));      // the thread's vector 0 of the batch
+                GlobalVec vp = (GlobalVec)(g.row + (int64_t)g.head * esz);
+                b.first = g.head + (i0 << vsh);
+                b.ucand = (rel & (kSpan - 1)) / kBlock;
 #pragma unroll
                 for (int u = 0; u < kStreamU; ++u) {
-                    const int iu = v0 + t + (q0 + u) * kBlock;
-                    p[u] = vp + min(iu, v1e - 1);                               // v0 <= i <= v1e - 1: inside the slice
-                    b.valid |= iu < v1e ? 1u << u : 0u;
+                    const int iu = i0 + u * kBlock;
+                    p[u] = vp + min(iu, g.v1e - 1);                             // v0 <= i <= v1e - 1: inside the slice
+                    b.valid |= iu < g.v1e ? 1u << u : 0u;
                 }
             }
         }
@@ -558,6 +608,11 @@ __device__ inline BatchRegs batch_issue(const void *row, int dtype, int32_t V, i
 #pragma unroll
     for (int u = 0; u < kStreamU; ++u) b.w[u] = *p[u];
     return b;
+}
+
+__device__ inline BatchRegs batch_issue(const void *row, int dtype, int32_t V, int32_t cand, int split, int per, const void *safe)
+{
+    return batch_issue(batch_geom(row, dtype, V, split, per), dtype, V, cand, safe);
 }
 
 // The elements of a piece's left-out batch, except the first one equal to the piece's maximum M: their two sums

@@ -72,6 +72,17 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
                       : lane_merge_issue(a.part + (int64_t)b * K * a.nsplit, K, a.nsplit, msh, a.nsplit, 1);
     else if constexpr (SHARDED) st0 = stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K, a.nsplit, count0);
     else st0 = stage_issue(a.part + (int64_t)b * K * a.nsplit, count0);
+    // While they travel: where the left-out batch of this thread's pieces will lie (lane path; see below).
+    BatchGeom gm[2];
+    if (!SHARDED && __builtin_expect(msh >= 0, 1)) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (q == 1 && (256 >> msh) >= K) break;               // uniform
+            const int row = (int)(threadIdx.x >> msh) + q * (256 >> msh);
+            gm[q] = batch_geom(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, row), a.dtype, a.V, threadIdx.x & ((1 << msh) - 1), a.per);
+            asm volatile("" :: "v"(gm[q].row), "v"(gm[q].head), "v"(gm[q].nvec), "v"(gm[q].v0), "v"(gm[q].v1e));
+        }
+    }
     asm volatile("" :: "v"(kb), "v"(arm), "v"(H_carry), "v"(tok0), "v"(st0.w0), "v"(st0.w1), "v"(ln0.p[0].w0), "v"(ln0.p[0].w1), "v"(ln0.p[1].w0), "v"(ln0.p[1].w1));
     kb = kb > K ? K : (kb < 0 ? 0 : kb);
     // Second round trip: the logit of the drafted token (its address needs the token, not k_len: rows up to K
@@ -94,8 +105,7 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
             e[q] = lane_piece(ln0, q, kb, a.nsplit, msh);     // rows beyond k_len hold stale partials: empty pieces
             bt[q].valid = 0;
             if (q == 0 || (256 >> msh) < kb)                      // uniform; a thread without a piece asks for nothing (candidate -1)
-                bt[q] = batch_issue(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, row), a.dtype, a.V,
-                                    (row < kb && sl < a.nsplit) ? e[q].idx : -1, sl, a.per, a.part);
+                bt[q] = batch_issue(gm[q], a.dtype, a.V, (row < kb && sl < a.nsplit) ? e[q].idx : -1, a.part);
         }
         // While the batches travel, the pieces are merged as they are.  Then every lane adds what its own batch holds
         // besides the first maximum: rescaled to the row's reference, summed over the row's lanes (binary32: small

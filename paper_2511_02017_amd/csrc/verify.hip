@@ -228,7 +228,7 @@ __device__ inline void draft_rows_lse_finish(const DraftLseRegs &r, int rows, in
         if (row < rows && sl == 0) {
             const bool bad = !(e.S > 0.0) || !(e.S < INFINITY) || !(e.M > -INFINITY && e.M < INFINITY);
             DraftRowLse o;
-            o.lse = bad ? (double)NAN : ((double)ref_of_max(e.M) + log2(e.S)) * kLn2;
+            o.lse = bad ? (double)NAN : ((double)ref_of_max(e.M) + log2_pos(e.S)) * kLn2;
             o.xt = e.xt;
             out[row] = o;
         }
@@ -419,7 +419,7 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
             uint32_t f = 0;
             double lse_d = NAN;
             if (__builtin_expect(r.bad, 0)) f |= TAPOUT_FLAG_BAD_ROW;
-            else lse_d = (r.R + log2(r.S)) * kLn2;
+            else lse_d = (r.R + log2_pos(r.S)) * kLn2;
             // greedy sequences decide on the argmax; the others only report it: they look at the window last
             if constexpr (!SHARDED)
                 if (greedy) top1 = argmax_finish(probe, row, a.t_dtype, a.V, r.cand, r.M);
@@ -523,7 +523,7 @@ __device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
         else stage_partials(sh_part, a.part + ((int64_t)b * (K + 1) + m) * a.nsplit, a.nsplit);
         RowTotal r = merge_partials<SHARDED>(sh_part, a.nsplit);
         Mm = r.M;
-        lse_m = (r.R + log2(r.S)) * kLn2;
+        lse_m = (r.R + log2_pos(r.S)) * kLn2;
         if constexpr (SHARDED) top1m = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;
         else top1m = need_top1 ? resolve_argmax(row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, m), a.t_dtype, a.V, r.cand, r.M) : 0;
         if (m < n && a.draft_lse) dl_m = a.draft_lse[(int64_t)b * K + m];
