@@ -321,6 +321,65 @@ __device__ inline const void *row_address(const void *base, int dtype, int64_t s
     return (const char *)base + off * (dtype == TAPOUT_F32 ? 4 : 2);
 }
 
+// ---- reductions over the 2^(hi - lo) lanes that differ in bits lo .. hi - 1 of the lane number ---------------
+// Commutative, every lane of a group ends with the same bits.  Steps 2 and 3 mirror half a row of sixteen lanes and a row:
+// they also flip the lower bits, in which the lanes agree by then (already reduced, or copies of one piece).
+// lo and hi are uniform.
+template <int CTRL>
+__device__ inline int dpp_mov(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ inline float dpp_mov(float v) { return __int_as_float(dpp_mov<CTRL>(__float_as_int(v))); }
+template <int CTRL>
+__device__ inline double dpp_mov(double v) { return __hiloint2double(dpp_mov<CTRL>(__double2hiint(v)), dpp_mov<CTRL>(__double2loint(v))); }
+struct IntPair { int a, b; };
+__device__ inline IntPair swap16(int v) { auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false); return {(int)r[0], (int)r[1]}; }
+__device__ inline IntPair swap32(int v) { auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false); return {(int)r[0], (int)r[1]}; }
+template <class F>
+__device__ inline int lanes_reduce_i(int v, int lo, int hi, F f)
+{
+    if (lo <= 0 && hi > 0) v = f(v, dpp_mov<0xB1>(v));
+    if (lo <= 1 && hi > 1) v = f(v, dpp_mov<0x4E>(v));
+    if (lo <= 2 && hi > 2) v = f(v, dpp_mov<0x141>(v));
+    if (lo <= 3 && hi > 3) v = f(v, dpp_mov<0x140>(v));
+    if (hi > 4) { const IntPair p = swap16(v); v = f(p.a, p.b); }          // the two values of a pair, in the same order in both lanes
+    if (hi > 5) { const IntPair p = swap32(v); v = f(p.a, p.b); }
+    return v;
+}
+__device__ inline int lanes_min(int v, int lo, int hi) { return lanes_reduce_i(v, lo, hi, [](int x, int y) { return min(x, y); }); }
+__device__ inline float lanes_max(float v, int lo, int hi)                   // of the numbers: a NaN gives way
+{
+    return __int_as_float(lanes_reduce_i(__float_as_int(v), lo, hi, [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
+}
+// largest and second largest, duplicates counted; m1, m2 of a lane: its own pair
+__device__ inline void lanes_top2(float &m1, float &m2, int lo, int hi)
+{
+    auto step = [&](float a1, float a2, float b1, float b2) {
+        m2 = fmaxf(fmaxf(fminf(a1, b1), a2), b2);
+        m1 = fmaxf(a1, b1);
+    };
+    if (lo <= 0 && hi > 0) step(m1, m2, dpp_mov<0xB1>(m1), dpp_mov<0xB1>(m2));
+    if (lo <= 1 && hi > 1) step(m1, m2, dpp_mov<0x4E>(m1), dpp_mov<0x4E>(m2));
+    if (lo <= 2 && hi > 2) step(m1, m2, dpp_mov<0x141>(m1), dpp_mov<0x141>(m2));
+    if (lo <= 3 && hi > 3) step(m1, m2, dpp_mov<0x140>(m1), dpp_mov<0x140>(m2));
+    if (hi > 4) { const IntPair p = swap16(__float_as_int(m1)), q = swap16(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
+    if (hi > 5) { const IntPair p = swap32(__float_as_int(m1)), q = swap32(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
+}
+__device__ inline double lanes_sum(double v, int lo, int hi)
+{
+    if (lo <= 0 && hi > 0) v += dpp_mov<0xB1>(v);
+    if (lo <= 1 && hi > 1) v += dpp_mov<0x4E>(v);
+    if (lo <= 2 && hi > 2) v += dpp_mov<0x141>(v);
+    if (lo <= 3 && hi > 3) v += dpp_mov<0x140>(v);
+    if (hi > 4) { const IntPair h = swap16(__double2hiint(v)), l = swap16(__double2loint(v)); v = __hiloint2double(h.a, l.a) + __hiloint2double(h.b, l.b); }
+    if (hi > 5) { const IntPair h = swap32(__double2hiint(v)), l = swap32(__double2loint(v)); v = __hiloint2double(h.a, l.a) + __hiloint2double(h.b, l.b); }
+    return v;
+}
+__device__ inline void lanes_sum2(double &s, double &t, int lo, int hi)
+{
+    s = lanes_sum(s, lo, hi);
+    t = lanes_sum(t, lo, hi);
+}
+
 constexpr int kStageCap = 256;     // partials staged in LDS at a time by an epilogue (8 KB)
 constexpr int kScanCap = 4096;     // largest K: one stop / accept decision byte per draft position fits LDS
 
@@ -615,6 +674,49 @@ __device__ inline BatchRegs batch_issue(const void *row, int dtype, int32_t V, i
     return batch_issue(batch_geom(row, dtype, V, split, per), dtype, V, cand, safe);
 }
 
+// The same split over the lanes of a piece: NV of the batch's kStreamU vectors, from vector u0 on.
+template <int NV>
+struct BatchVecs {
+    u32x4 w[NV];
+    uint32_t valid;       // bit n: vector n is wanted; bit 8: a single head / tail element, in w[0].x (the lane with u0 == 0)
+    int32_t first;        // element index of the lane's vector 0 (or of the single element)
+    int32_t search;       // which of the lane's vectors the candidate is (else outside 0 .. NV - 1)
+};
+template <int NV>
+__device__ inline BatchVecs<NV> batch_issue_vecs(const BatchGeom &g, int dtype, int32_t V, int32_t cand, int u0, const void *safe)
+{
+    const int esz = dtype == TAPOUT_F32 ? 4 : 2, vsh = dtype == TAPOUT_F32 ? 2 : 3;
+    BatchVecs<NV> b;
+    b.valid = 0; b.first = 0; b.search = -1;
+    typedef const __attribute__((address_space(1))) u32x4 *GlobalVec;          // (see batch_issue)
+    GlobalVec p[NV];
+#pragma unroll
+    for (int n = 0; n < NV; ++n) p[n] = (GlobalVec)safe;
+    uint32_t single = 0;
+    if (cand >= 0 && cand < V) {
+        const int i = (cand - g.head) >> vsh, rel = i - g.v0;
+        if (__builtin_expect(cand < g.head || i >= g.nvec, 0)) {
+            if (u0 == 0) { single = __float_as_uint(load_elem_rt(g.row, dtype, cand)); b.valid = 0x100u; b.first = cand; }
+        } else if (rel >= 0 && i < g.v1e) {                                      // else: not a candidate of this slice: stale record
+            constexpr int kSpan = kBlock * kStreamU;
+            const int i0 = g.v0 + (rel & ~(kSpan - 1)) + (rel & (kBlock - 1)) + u0 * kBlock;
+            GlobalVec vp = (GlobalVec)(g.row + (int64_t)g.head * esz);
+            b.first = g.head + (i0 << vsh);
+            b.search = (rel & (kSpan - 1)) / kBlock - u0;
+#pragma unroll
+            for (int n = 0; n < NV; ++n) {
+                const int iu = i0 + n * kBlock;
+                p[n] = vp + min(iu, g.v1e - 1);
+                b.valid |= iu < g.v1e ? 1u << n : 0u;
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NV; ++n) b.w[n] = *p[n];
+    if (b.valid & 0x100u) b.w[0].x = single;
+    return b;
+}
+
 // The elements of a piece's left-out batch, except the first one equal to the piece's maximum M: their two sums
 // relative to ref_of_max(M) (binary32 terms as in the streaming pass: they are small, or the row is not peaked) and
 // the index of that first maximum (0x7fffffff if the batch does not hold it).
@@ -668,6 +770,49 @@ __device__ inline BatchExtra batch_extra(const Piece &p, const BatchRegs &b, int
 {
     if (piece_empty(p) || !b.valid) { BatchExtra o; o.sa = 0.0f; o.ta = 0.0f; o.idx = 0x7fffffff; return o; }
     return dtype == TAPOUT_F32 ? batch_extra_t<TAPOUT_F32>(p.M, b) : batch_extra_t<TAPOUT_BF16>(p.M, b);
+}
+
+// Sums of a lane's vectors of a left-out batch in the row's reference R; excl: the piece holds the row's first maximum M,
+// which stays out and whose index is idx.  (See batch_extra_t for the search and the masked logits.)
+template <int DT, int NV>
+__device__ inline BatchExtra batch_sum(float R, float M, bool excl, const BatchVecs<NV> &b, int u0)
+{
+    constexpr int VEC = Elem<DT>::vec;
+    BatchExtra o;
+    auto sums = [&](bool clamp) {
+        float sa[2] = {0.0f, 0.0f}, ta[2] = {0.0f, 0.0f};
+        int32_t idx = 0x7fffffff;
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+            const bool on = (b.valid >> n) & 1u, search = excl && n == b.search;
+            const u32x4 w = {on ? b.w[n].x : 0u, on ? b.w[n].y : 0u, on ? b.w[n].z : 0u, on ? b.w[n].w : 0u};   // stand-in data may be anything
+            float x[VEC];
+            unpack<DT>(w, x);
+#pragma unroll
+            for (int j = VEC - 1; j >= 0; --j) idx = (search && on && x[j] == M) ? b.first + n * kBlock * VEC + j : idx;      // the lowest one stays
+            const int skip = idx - (b.first + n * kBlock * VEC);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                const float y = __builtin_fmaf(x[j], kLog2e, -R);
+                const float e = (on && j != skip) ? __builtin_amdgcn_exp2f(y) : 0.0f;
+                sa[j & 1] += e;
+                ta[j & 1] = __builtin_fmaf(e, clamp ? fmaxf(y, -200.0f) : y, ta[j & 1]);
+            }
+        }
+        if (__builtin_expect(b.valid & 0x100u, 0)) {
+            const float x = __uint_as_float(b.w[0].x);
+            if (excl) idx = b.first;
+            else {
+                const float y = __builtin_fmaf(x, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
+                sa[0] += e;
+                ta[0] = __builtin_fmaf(e, clamp ? fmaxf(y, -200.0f) : y, ta[0]);
+            }
+        }
+        o.sa = sa[0] + sa[1]; o.ta = ta[0] + ta[1]; o.idx = idx;
+    };
+    sums(false);
+    if (o.ta != o.ta) sums(true);
+    return o;
 }
 
 // Completes a piece of the draft pass: the left-out batch back in, all but the first maximum, whose index becomes idx.

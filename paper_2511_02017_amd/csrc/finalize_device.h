@@ -35,21 +35,181 @@ __device__ inline bool adaedl_fires(double g, double lambda, float H)
     return 1.0 - sqrt(g * (double)H) < lambda;
 }
 
-// The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.
-template <bool SHARDED>
-__device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
+// One row's results: the signals from its merged sums into the output arrays (i = b K + k), log q(tok) of its token t with
+// logit xt (want_tok), and its flags.
+struct RowOut { float H, p1, margin; uint32_t flags; };
+__device__ inline RowOut emit_row(const DraftFinalArgs &a, int64_t i, const RowTotal &r, bool want_tok, int32_t t, float xt)
 {
-    __shared__ Partial sh_part[kStageCap];
-    __shared__ uint8_t sh_dec[kScanCap];
-    __shared__ float sh_H[kScanCap];                           // entropies of the sequence (stateful rules only)
-    __shared__ uint32_t sh_flags;
+    RowOut o;
+    o.flags = 0;
+    float lse, p2;
+    double lse_d = NAN;
+    if (__builtin_expect(r.bad, 0)) {
+        o.flags = TAPOUT_FLAG_BAD_ROW | (a.sampled_lse ? TAPOUT_FLAG_BAD_TOKEN : 0u);
+        lse = o.H = o.p1 = p2 = o.margin = NAN;
+    } else {
+        const RowSignals g = row_signals(r, a.V > 1);
+        lse_d = g.lse;
+        lse = (float)g.lse; o.H = (float)g.H;
+        o.p1 = (float)g.p1; p2 = (float)g.p2; o.margin = (float)g.margin;
+    }
+    if (a.sampled_lse) a.sampled_lse[i] = lse_d;
+    if (a.lse) a.lse[i] = lse;
+    if (a.entropy) a.entropy[i] = o.H;
+    if (a.p_top1) a.p_top1[i] = o.p1;
+    if (a.p_top2) a.p_top2[i] = p2;
+    if (a.margin) a.margin[i] = o.margin;
+    if (a.top1_id) a.top1_id[i] = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;      // exact: the pieces carry the index of their first maximum
+    if (want_tok) {
+        if (__builtin_expect(t < 0 || t >= a.V, 0)) { o.flags |= TAPOUT_FLAG_BAD_TOKEN; a.logq_tok[i] = NAN; }
+        else a.logq_tok[i] = (float)((double)xt - lse_d);
+    }
+    if (a.round_entropy) a.round_entropy[i] = o.H;
+    return o;
+}
+
+// Decision of a rule that looks beyond the row's own signals; H_prev: the previous row's entropy (the carried one for row 0).
+__device__ inline bool stateful_fires(const DraftFinalArgs &a, int b, int arm, int rule, float threshold, float H, float H_prev)
+{
+    if (rule == TAPOUT_RULE_SVIP_DIFF) return svip_diff_fires(threshold, H, H_prev);
+    return adaedl_fires(a.adaedl_gamma, a.lambda ? a.lambda[(int64_t)b * a.n_arms + arm] : (double)threshold, H);
+}
+
+// ---- lane path: few rows and slices (see lane_merge_shift) -----------------------------------------
+// A wavefront of these small kernels executes an instruction about every nine cycles whatever it is, so what counts is
+// the number of instructions from the first request to the last store.  Every (row, slice) piece has 2^USH lanes of its
+// own, each of which takes 4 >> USH vectors of the piece's left-out batch; a row's lanes find the row's maximum first (one
+// instruction per exchange), bring every piece to the row's reference once, add the batch's elements in that reference
+// and then only sum.  Two or four lanes per piece where the workgroup has that many to spare.  No LDS between a row's
+// lanes and its signals.  (Pairwise merges of whole records, the batch by one lane, and the row totals handed to a
+// thread per row through LDS: launch 8.4 us at V = 128256, B = 64, K = 8, this 6.5; one sequence at V = 32000 6.2 / 4.7.)
+template <bool SHARDED, int USH>
+__device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b, unsigned char *lds, const int msh)
+{
+    constexpr int U = 1 << USH, NV = kStreamU >> USH;                 // lanes per piece, vectors per lane
+    float *sh_H = (float *)lds;                                       // [64] entropies of the sequence (stateful rules)
+    uint8_t *sh_dec = lds + 4 * kWave, *sh_flag = sh_dec + kWave;     // [64] each: decisions, flags
+    const int K = a.K, tid = threadIdx.x, gsh = msh + USH;            // 2^gsh lanes per row
+    const int u = tid & (U - 1), sl = (tid >> USH) & ((1 << msh) - 1), per_pass = kFinalBlock >> gsh;
+    const bool want_tok = a.draft_tok && a.logq_tok, tok_mode = a.arm_stride > 0;
+    int kb = a.k_len ? a.k_len[b] : K;
+    int arm = (a.arm && !tok_mode) ? a.arm[b] : -1;                   // sequence-level bandit: one arm for all steps
+    float H_carry = a.prev_entropy ? a.prev_entropy[b] : NAN;
+    for (int row0 = 0; row0 < K; row0 += per_pass) {                  // one pass but for long drafts of many slices
+        const int row = row0 + (tid >> gsh), row_c = min(row, K - 1);
+        const int64_t i = (int64_t)b * K + row;
+        // First memory round trip: the partial, the row's token and arm (and above the sequence's values).  A lane without a
+        // piece asks for one all the same: a request under a condition is waited for where the branches meet.
+        const Partial *pp = SHARDED ? a.part + (int64_t)min(sl, a.nsplit - 1) * a.B * K + (int64_t)b * K + row_c
+                                    : a.part + ((int64_t)b * K + row_c) * a.nsplit + min(sl, a.nsplit - 1);
+        const u32x4 w0 = ((const u32x4 *)pp)[0], w1 = ((const u32x4 *)pp)[1];
+        int32_t tok = -1, arm_k = -1;
+        if (want_tok) tok = a.draft_tok[(int64_t)b * K + row_c];
+        if (tok_mode && a.arm) arm_k = a.arm[(int64_t)b * a.arm_stride + row_c];
+        // while they travel: the row's geometry
+        BatchGeom g{};
+        const char *row_p = nullptr;
+        if constexpr (!SHARDED) {
+            row_p = (const char *)row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, row_c);
+            g = batch_geom(row_p, a.dtype, a.V, sl, a.per);
+            asm volatile("" :: "v"(g.row), "v"(g.head), "v"(g.nvec), "v"(g.v0), "v"(g.v1e));
+        }
+        asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(arm_k), "v"(kb), "v"(arm), "v"(H_carry));
+        if (row0 == 0) { kb = kb > K ? K : (kb < 0 ? 0 : kb); arm = __builtin_amdgcn_readfirstlane(arm); }
+        const bool live = row < kb, mine = live && sl < a.nsplit;     // rows beyond k_len hold stale partials
+        const float v1 = mine ? __uint_as_float(w0.x) : -INFINITY;
+        float S = __uint_as_float(w0.y), T = __uint_as_float(w0.z), v2 = __uint_as_float(w0.w);
+        int32_t cand = (int32_t)w1.x;
+        if (!mine || (v1 == -INFINITY && !(S != S))) { S = 0.0f; T = 0.0f; v2 = -INFINITY; cand = 0x7fffffff; }     // nothing in it
+        // Second round trip: the token's logit, this lane's vectors of the left-out batch.
+        float xt = NAN;
+        if constexpr (SHARDED) { if (mine) xt = __uint_as_float(w1.y); }      // the shard that owns the token sent its logit, the others NaN
+        else if (want_tok && live && tok >= 0 && tok < a.V) xt = load_elem_rt(row_p, a.dtype, tok);
+        BatchVecs<NV> bt{};
+        if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, a.dtype, a.V, cand, u * NV, a.part);
+        // the row's maximum, second maximum and the piece that holds its first maximum
+        float M = v1;
+        lanes_top2(M, v2, USH, gsh);
+        const bool holds = v1 == M && cand != 0x7fffffff;
+        const int32_t first = lanes_min(holds ? cand : 0x7fffffff, USH, gsh);
+        const bool wins = holds && cand == first;
+        const float R = ref_of_max(M);
+        const float d = R - ref_of_max(v1);                           // an integer, >= 0 for a piece that holds anything
+        const int di = (int)fminf(fmaxf(d, -4000.0f), 4000.0f);       // 2^-4000 underflows to 0 as it should
+        double Sd = u == 0 ? ldexp((double)S, -di) : 0.0;             // exact power-of-two scaling
+        double Td = u == 0 ? ldexp((double)T - (double)d * (double)S, -di) : 0.0;
+        if (S == 0.0f && T == 0.0f) { Sd = 0.0; Td = 0.0; }           // (0 * inf)
+        int32_t idx = 0x7fffffff;
+        if constexpr (SHARDED) {
+            // a record leaves its maximum out: an ordinary term here unless it is the row's first maximum
+            idx = wins ? cand : 0x7fffffff;
+            if (!wins && v1 > -INFINITY) {
+                const float y = __builtin_fmaf(v1, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
+                Sd += (double)e;
+                Td += (double)e * (double)fmaxf(y, -200.0f);
+            }
+            xt = lanes_max(xt, USH, gsh);
+        } else {
+            // the batch's elements in the row's reference, all but the row's first maximum
+            const BatchExtra x = a.dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
+            Sd += (double)x.sa; Td += (double)x.ta; idx = x.idx;
+        }
+        Piece t;
+        t.M = M; t.v2 = v2; t.xt = xt;
+        t.idx = lanes_min(idx, 0, gsh);
+        lanes_sum2(Sd, Td, 0, gsh);
+        t.S = Sd; t.T = Td;
+        if (live && (tid & ((1 << gsh) - 1)) == 0) {
+            const RowOut o = emit_row(a, i, row_total<true>(t), want_tok, tok, xt);
+            sh_flag[row] = (uint8_t)o.flags;
+            if (a.arm) {
+                if (!tok_mode) arm_k = arm;
+                const bool ok = arm_k >= 0 && arm_k < a.n_arms;
+                const int rule = ok ? pick8(a.rule, arm_k) : -1;
+                sh_H[row] = o.H;
+                if (rule == TAPOUT_RULE_SVIP_DIFF || rule == TAPOUT_RULE_ADAEDL) sh_dec[row] = (uint8_t)(2 + arm_k);    // decided below
+                else {
+                    const bool fire = ok && rule_fires(rule, pick8(a.threshold, arm_k), o.H, o.p1, o.margin);
+                    if (a.stop_fired) a.stop_fired[i] = fire ? 1 : 0;
+                    sh_dec[row] = fire ? 1 : 0;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // the sequence: rows are lanes of the first wavefront, ballots give the stop position and the flags
+    if (tid < kWave) {
+        const bool row = tid < kb;
+        const uint32_t f = row ? sh_flag[tid] : 0u;
+        uint32_t fa = 0;
+        if (__builtin_amdgcn_ballot_w64((f & TAPOUT_FLAG_BAD_ROW) != 0)) fa |= TAPOUT_FLAG_BAD_ROW;
+        if (__builtin_amdgcn_ballot_w64((f & TAPOUT_FLAG_BAD_TOKEN) != 0)) fa |= TAPOUT_FLAG_BAD_TOKEN;
+        if (tid == 0 && a.flags) a.flags[b] = fa;
+        if (a.arm) {
+            const int dec = row ? sh_dec[tid] : 0;
+            bool fire = dec == 1;
+            if (dec >= 2) {
+                const int ar = dec - 2;
+                fire = stateful_fires(a, b, ar, pick8(a.rule, ar), pick8(a.threshold, ar), sh_H[tid], tid > 0 ? sh_H[tid - 1] : H_carry);
+                if (a.stop_fired) a.stop_fired[(int64_t)b * K + tid] = fire ? 1 : 0;
+            }
+            const uint64_t fired = __builtin_amdgcn_ballot_w64(fire);
+            if (tid == 0 && a.n_stop) a.n_stop[b] = fired ? __builtin_ctzll(fired) + 1 : kb;
+        }
+    }
+}
+
+// ---- staged path: any number of rows and pieces ------------------------------------------------------
+template <bool SHARDED>
+__device__ inline void draft_finalize_staged(const DraftFinalArgs &a, const int b, unsigned char *lds)
+{
+    Partial *sh_part = (Partial *)lds;
+    float *sh_H = (float *)(lds + sizeof(Partial) * kStageCap);                 // entropies of the sequence (stateful rules only)
+    uint8_t *sh_dec = lds + sizeof(Partial) * kStageCap + 4 * kScanCap;
+    uint32_t &sh_flags = *(uint32_t *)(sh_dec + kScanCap);
     const int K = a.K;
-    // few rows and slices: one partial per thread, merged across lanes (see lane_merge_commit); else staged in LDS
-    const int msh = lane_merge_shift(K, a.nsplit);
-    // The lane-parallel merge leaves the totals of all K <= 64 rows in LDS at once and row k with thread k: it is one
-    // stage whatever the slice count.  The staged merge takes kStageCap partials at a time (nsplit <= kStageCap is
-    // guaranteed by the host).
-    const int rows_per_stage = msh >= 0 ? kWave : kStageCap / a.nsplit;
+    // kStageCap partials at a time (nsplit <= kStageCap is guaranteed by the host)
+    const int rows_per_stage = kStageCap / a.nsplit;
     const bool want_tok = a.draft_tok && a.logq_tok;
     static_assert(kFinalBlock == 256, "stage_issue / stage_commit assume 256 threads");
     // First memory round trip: k_len, the arm, the carried entropy, the drafted tokens and the partials, all
@@ -59,95 +219,13 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
     int kb = a.k_len ? a.k_len[b] : K;
     const int arm = (a.arm && !tok_mode) ? a.arm[b] : -1;     // sequence-level bandit: one arm for all steps
     float H_carry = a.prev_entropy ? a.prev_entropy[b] : NAN;
-    int32_t tok0 = -1;
-    if (want_tok && (int)threadIdx.x < K) tok0 = a.draft_tok[(int64_t)b * K + threadIdx.x];
     const int count0 = min(K, rows_per_stage) * a.nsplit;
-    RowSlot *sh_rows = (RowSlot *)sh_part;
-    static_assert(sizeof(RowSlot) * 64 <= sizeof(Partial) * kStageCap, "the row totals reuse the staging buffer");
-    StageRegs st0;
-    LaneRegs ln0;
-    st0.w0 = st0.w1 = ln0.p[0].w0 = ln0.p[0].w1 = ln0.p[1].w0 = ln0.p[1].w1 = u32x4{0u, 0u, 0u, 0u};
-    if (__builtin_expect(msh >= 0, 1))
-        ln0 = SHARDED ? lane_merge_issue(a.part + (int64_t)b * K, K, a.nsplit, msh, 1, (int64_t)a.B * K)
-                      : lane_merge_issue(a.part + (int64_t)b * K * a.nsplit, K, a.nsplit, msh, a.nsplit, 1);
-    else if constexpr (SHARDED) st0 = stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K, a.nsplit, count0);
-    else st0 = stage_issue(a.part + (int64_t)b * K * a.nsplit, count0);
-    // While they travel: where the left-out batch of this thread's pieces will lie (lane path; see below).
-    BatchGeom gm[2];
-    if (!SHARDED && __builtin_expect(msh >= 0, 1)) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (q == 1 && (256 >> msh) >= K) break;               // uniform
-            const int row = (int)(threadIdx.x >> msh) + q * (256 >> msh);
-            gm[q] = batch_geom(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, row), a.dtype, a.V, threadIdx.x & ((1 << msh) - 1), a.per);
-            asm volatile("" :: "v"(gm[q].row), "v"(gm[q].head), "v"(gm[q].nvec), "v"(gm[q].v0), "v"(gm[q].v1e));
-        }
-    }
-    asm volatile("" :: "v"(kb), "v"(arm), "v"(H_carry), "v"(tok0), "v"(st0.w0), "v"(st0.w1), "v"(ln0.p[0].w0), "v"(ln0.p[0].w1), "v"(ln0.p[1].w0), "v"(ln0.p[1].w1));
+    const StageRegs st0 = SHARDED ? stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K, a.nsplit, count0)
+                                  : stage_issue(a.part + (int64_t)b * K * a.nsplit, count0);
+    asm volatile("" :: "v"(kb), "v"(arm), "v"(H_carry), "v"(st0.w0), "v"(st0.w1));
     kb = kb > K ? K : (kb < 0 ? 0 : kb);
-    // Second round trip: the logit of the drafted token (its address needs the token, not k_len: rows up to K
-    // exist) and, on the lane path, the left-out batch of this thread's (row, slice) pieces.
-    float xtok_first = 0.0f;
-    if constexpr (!SHARDED)
-        if (want_tok && (int)threadIdx.x < K && tok0 >= 0 && tok0 < a.V)
-            xtok_first = load_elem_rt(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, threadIdx.x), a.dtype, tok0);
     if (threadIdx.x == 0) sh_flags = 0;                       // ahead of the barrier in the commit: rows of other wavefronts OR into it
-    if (SHARDED && __builtin_expect(msh >= 0, 1)) {
-        // a record is complete: nothing to add back
-        lane_merge_commit<true>(sh_rows, lane_piece(ln0, 0, kb, a.nsplit, msh), lane_piece(ln0, 1, kb, a.nsplit, msh), kb, msh);
-    } else if (__builtin_expect(msh >= 0, 1)) {
-        Piece e[2];
-        BatchRegs bt[2];
-        const int sl = threadIdx.x & ((1 << msh) - 1);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int row = (threadIdx.x >> msh) + q * (256 >> msh);
-            e[q] = lane_piece(ln0, q, kb, a.nsplit, msh);     // rows beyond k_len hold stale partials: empty pieces
-            bt[q].valid = 0;
-            if (q == 0 || (256 >> msh) < kb)                      // uniform; a thread without a piece asks for nothing (candidate -1)
-                bt[q] = batch_issue(gm[q], a.dtype, a.V, (row < kb && sl < a.nsplit) ? e[q].idx : -1, a.part);
-        }
-        // While the batches travel, the pieces are merged as they are.  Then every lane adds what its own batch holds
-        // besides the first maximum: rescaled to the row's reference, summed over the row's lanes (binary32: small
-        // terms, a fixed butterfly), together with the exact index of the row's first maximum from the lane that won.
-        const bool two = (256 >> msh) < kb;                     // uniform
-        Piece m[2];
-        m[0] = lane_group_merge<true>(e[0], msh);
-        if (two) m[1] = lane_group_merge<true>(e[1], msh);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (q == 1 && !two) break;
-            const BatchExtra x = batch_extra(e[q], bt[q], a.dtype);
-            const float d = ref_of_max(m[q].M) - ref_of_max(e[q].M);              // >= 0 for a piece that holds anything
-            const int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
-            float sa = ldexpf(x.sa, -di), ta = ldexpf(x.ta - d * x.sa, -di);
-            if (x.sa == 0.0f) { sa = 0.0f; ta = 0.0f; }                           // empty piece or empty batch (0 * inf)
-            int32_t idx = (e[q].M == m[q].M && e[q].idx == m[q].idx) ? x.idx : 0x7fffffff;
-            auto step = [&](auto ctrl) {
-                constexpr int C = decltype(ctrl)::value;
-                sa += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sa), C, 0xf, 0xf, true));
-                ta += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(ta), C, 0xf, 0xf, true));
-                idx = min(idx, __builtin_amdgcn_update_dpp(0, idx, C, 0xf, 0xf, true));
-            };
-            if (msh >= 1) step(std::integral_constant<int, 0xB1>{});
-            if (msh >= 2) step(std::integral_constant<int, 0x4E>{});
-            if (msh >= 3) step(std::integral_constant<int, 0x141>{});
-            if (msh >= 4) step(std::integral_constant<int, 0x140>{});
-            const int row = (threadIdx.x >> msh) + q * (256 >> msh);
-            if (row < kb && sl == 0) {
-                Piece f = m[q];
-                f.S += (double)sa; f.T += (double)ta; f.idx = idx;
-                RowSlot o;
-                o.r = row_total<true>(f);
-                o.xt = f.xt;
-                sh_rows[row] = o;
-            }
-        }
-        __syncthreads();
-    } else {
-        stage_commit(sh_part, st0, count0);
-    }
-    // Staged path: the `count` partials of rows k0.. lie in LDS; every thread completes some of them (left-out batch
+    // The `count` partials of rows k0.. lie in LDS; every thread completes some of them (left-out batch
     // back in, exact index of the first maximum into the cand slot) before the rows are merged one by one.
     auto complete_stage = [&](int k0, int count) {
         if constexpr (!SHARDED) {
@@ -162,20 +240,17 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
             __syncthreads();
         }
     };
-    if (__builtin_expect(msh < 0, 0)) complete_stage(0, count0);
+    stage_commit(sh_part, st0, count0);
+    complete_stage(0, count0);
     const bool arm_ok = arm >= 0 && arm < a.n_arms;
     const int rule_b = arm_ok ? pick8(a.rule, arm) : -1;
     // rows whose rule looks beyond their own signals are decided in a second sweep (uniform over the workgroup);
     // token-level bandits: the arm of step k is arm[b, k]
     const bool sweep = tok_mode ? (a.round_entropy != nullptr)
                                 : (rule_b == TAPOUT_RULE_SVIP_DIFF || rule_b == TAPOUT_RULE_ADAEDL);
-    bool fire_mine = false; uint32_t f_mine = 0;      // this thread's row: rule fired, flags (used on the lane-merge path)
     for (int k0 = 0; k0 < kb; k0 += rows_per_stage) {
         const int k1 = min(kb, k0 + rows_per_stage);
-        const int kmine = k0 + threadIdx.x;                   // first (usually only) row of this thread in the stage
-        float xtok0 = xtok_first;
-        if (__builtin_expect(k0 > 0, 0)) {                                         // further stages (K > rows_per_stage): load late
-            tok0 = (want_tok && kmine < k1) ? a.draft_tok[(int64_t)b * K + kmine] : -1;
+        if (k0 > 0) {
             __syncthreads();
             if constexpr (SHARDED) {
                 stage_commit(sh_part, stage_issue_shards(a.part, (int64_t)a.B * K, (int64_t)b * K + k0, a.nsplit, (k1 - k0) * a.nsplit),
@@ -184,101 +259,47 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
                 stage_partials(sh_part, a.part + ((int64_t)b * K + k0) * a.nsplit, (k1 - k0) * a.nsplit);
                 complete_stage(k0, (k1 - k0) * a.nsplit);
             }
-            xtok0 = 0.0f;
-            if constexpr (!SHARDED)
-                if (want_tok && kmine < k1 && tok0 >= 0 && tok0 < a.V)
-                    xtok0 = load_elem_rt(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, kmine), a.dtype, tok0);
         }
-        for (int k = kmine; k < k1; k += kFinalBlock) {
+        for (int k = k0 + threadIdx.x; k < k1; k += kFinalBlock) {
             const int64_t i = (int64_t)b * K + k;
-            const void *row = SHARDED ? nullptr : row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, k);
-            const RowTotal r = msh >= 0 ? sh_rows[k].r : merge_partials<true>(sh_part + (k - k0) * a.nsplit, a.nsplit);
-            const int32_t top1 = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;                      // exact: the pieces carry the index of their first maximum
-            uint32_t f = 0;
-            float lse, H, p1, p2, mg;
-            double lse_d = NAN;
-            if (__builtin_expect(r.bad, 0)) {
-                f |= TAPOUT_FLAG_BAD_ROW | (a.sampled_lse ? TAPOUT_FLAG_BAD_TOKEN : 0u);
-                lse = H = p1 = p2 = mg = NAN;
-            } else {
-                const RowSignals g = row_signals(r, a.V > 1);
-                lse_d = g.lse;
-                lse = (float)g.lse; H = (float)g.H;
-                p1 = (float)g.p1; p2 = (float)g.p2; mg = (float)g.margin;
-            }
-            if (a.sampled_lse) a.sampled_lse[i] = lse_d;
-            if (a.lse) a.lse[i] = lse;
-            if (a.entropy) a.entropy[i] = H;
-            if (a.p_top1) a.p_top1[i] = p1;
-            if (a.p_top2) a.p_top2[i] = p2;
-            if (a.margin) a.margin[i] = mg;
-            if (a.top1_id) a.top1_id[i] = top1;
-            if (a.draft_tok && a.logq_tok) {
-                int32_t t = tok0;
-                float xt = xtok0;
-                if (k != kmine) t = a.draft_tok[i];            // more rows than threads: load late
+            const RowTotal r = merge_partials<true>(sh_part + (k - k0) * a.nsplit, a.nsplit);
+            int32_t t = -1;
+            float xt = NAN;
+            if (want_tok) {
+                t = a.draft_tok[i];
                 if constexpr (SHARDED) {
                     // the shard that owns the token sent its logit; the others sent NaN
-                    xt = NAN;
-                    if (msh >= 0) xt = sh_rows[k].xt;
-                    else
-                        for (int g = 0; g < a.nsplit; ++g) {
-                            const float v = __int_as_float(sh_part[(k - k0) * a.nsplit + g].pad[0]);
-                            if (v == v) xt = v;
-                        }
-                } else if (k != kmine) {
-                    if (t >= 0 && t < a.V) xt = load_elem_rt(row, a.dtype, t);
+                    for (int g = 0; g < a.nsplit; ++g) {
+                        const float v = __int_as_float(sh_part[(k - k0) * a.nsplit + g].pad[0]);
+                        if (v == v) xt = v;
+                    }
+                } else if (t >= 0 && t < a.V) {
+                    xt = load_elem_rt(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, k), a.dtype, t);
                 }
-                if (t < 0 || t >= a.V) { f |= TAPOUT_FLAG_BAD_TOKEN; a.logq_tok[i] = NAN; }
-                else a.logq_tok[i] = (float)((double)xt - lse_d);
             }
-            if (a.round_entropy) a.round_entropy[i] = H;
+            const RowOut o = emit_row(a, i, r, want_tok, t, xt);
             if (a.arm) {
                 const int arm_k = tok_mode ? a.arm[(int64_t)b * a.arm_stride + k] : arm;
                 const bool ok_k = arm_k >= 0 && arm_k < a.n_arms;
                 const int rule_k = ok_k ? pick8(a.rule, arm_k) : -1;
-                if (sweep) sh_H[k] = H;
+                if (sweep) sh_H[k] = o.H;
                 if (rule_k == TAPOUT_RULE_SVIP_DIFF || rule_k == TAPOUT_RULE_ADAEDL) {
                     sh_dec[k] = 2;                             // decided below, once every row's entropy is known
                 } else {
-                    const bool fire = ok_k && rule_fires(rule_k, pick8(a.threshold, arm_k), H, p1, mg);
+                    const bool fire = ok_k && rule_fires(rule_k, pick8(a.threshold, arm_k), o.H, o.p1, o.margin);
                     if (a.stop_fired) a.stop_fired[i] = fire ? 1 : 0;
                     sh_dec[k] = fire ? 1 : 0;                  // k < K <= kScanCap
-                    fire_mine = fire;
                 }
             }
-            f_mine = f;
-            if (f) atomicOr(&sh_flags, f);
+            if (o.flags) atomicOr(&sh_flags, o.flags);
         }
-    }
-    if (__builtin_expect(msh >= 0 && !sweep, 1)) {
-        // Lane-merge path without a second sweep: row k was thread k's, so the rows are lanes of the first wavefront
-        // and ballots give the stop position and the flags; no barrier, no scan through LDS.
-        if (threadIdx.x < kWave) {
-            const uint64_t fired = __builtin_amdgcn_ballot_w64((int)threadIdx.x < kb && fire_mine);
-            uint32_t fa = 0;
-            if (__builtin_amdgcn_ballot_w64((f_mine & TAPOUT_FLAG_BAD_ROW) != 0)) fa |= TAPOUT_FLAG_BAD_ROW;
-            if (__builtin_amdgcn_ballot_w64((f_mine & TAPOUT_FLAG_BAD_TOKEN) != 0)) fa |= TAPOUT_FLAG_BAD_TOKEN;
-            if (threadIdx.x == 0) {
-                if (a.flags) a.flags[b] = fa;
-                if (a.arm && a.n_stop) a.n_stop[b] = fired ? __builtin_ctzll(fired) + 1 : kb;
-            }
-        }
-        return;
     }
     __syncthreads();                       // orders the LDS / scratch writes above before the scan
     if (__builtin_expect(sweep, 0)) {
         for (int k = threadIdx.x; k < kb; k += kFinalBlock) {
             if (sh_dec[k] != 2) continue;
             const int arm_k = tok_mode ? a.arm[(int64_t)b * a.arm_stride + k] : arm;      // in range: checked when it was marked
-            const float H = sh_H[k];
-            bool fire;
-            if (pick8(a.rule, arm_k) == TAPOUT_RULE_SVIP_DIFF) {
-                fire = svip_diff_fires(pick8(a.threshold, arm_k), H, k > 0 ? sh_H[k - 1] : H_carry);
-            } else {
-                const double lam = a.lambda ? a.lambda[(int64_t)b * a.n_arms + arm_k] : (double)pick8(a.threshold, arm_k);
-                fire = adaedl_fires(a.adaedl_gamma, lam, H);
-            }
+            const bool fire = stateful_fires(a, b, arm_k, pick8(a.rule, arm_k), pick8(a.threshold, arm_k), sh_H[k], k > 0 ? sh_H[k - 1] : H_carry);
             if (a.stop_fired) a.stop_fired[(int64_t)b * K + k] = fire ? 1 : 0;
             sh_dec[k] = fire ? 1 : 0;
         }
@@ -293,6 +314,20 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
             }
             a.n_stop[b] = ns;
         }
+    }
+}
+
+// The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.
+template <bool SHARDED>
+__device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
+{
+    __shared__ __align__(16) unsigned char lds[sizeof(Partial) * kStageCap + 5 * kScanCap + 16];
+    const int msh = lane_merge_shift(a.K, a.nsplit), pieces = msh < 0 ? 0 : a.K << msh;
+    if (__builtin_expect(msh < 0, 0)) draft_finalize_staged<SHARDED>(a, b, lds);
+    else if (SHARDED || pieces > kFinalBlock / 2) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
+    else if constexpr (!SHARDED) {
+        if (pieces > kFinalBlock / 4) draft_finalize_lanes<false, 1>(a, b, lds, msh);
+        else draft_finalize_lanes<false, 2>(a, b, lds, msh);
     }
 }
 

@@ -1392,7 +1392,7 @@ __device__ inline float row_ref_finish(RowRefRegs r, const Partial *p, int nspli
 // the rows' maxima; this, which finds them itself and carries the epilogue's workgroups (7.9 alone), 33.9; 64 rows: 4.2 + 8.4 + 8.2 against
 // 11.2.
 template <int DT>
-__global__ __launch_bounds__(kSampleBlock) void sample_slices_kernel(SampleArgs a, DraftFinalArgs fin)
+__global__ __launch_bounds__(kSampleBlock) __attribute__((amdgpu_waves_per_eu(4))) void sample_slices_kernel(SampleArgs a, DraftFinalArgs fin)
 {
     constexpr bool kTab = DT == TAPOUT_BF16;
     __shared__ double shT[256];
@@ -1738,8 +1738,15 @@ static hipError_t launch_sample_typed(SampleArgs &a, const DraftFinalArgs &fin, 
 {
     if (pass == 0) {
         constexpr int per_wg = kSampleBlock / kWave;
-        const int64_t rows = (int64_t)a.B * a.K, want = (rows * a.nsl + per_wg - 1) / per_wg;
-        const int wgs = (int)(want < kSampleWgs ? want : kSampleWgs);
+        // All wavefronts the same number of slices.  With few each, no more workgroups than are resident beside the epilogue's: one
+        // that waits for a place starts when the others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us,
+        // 252 of two slices per wavefront 10.0; with many each the places of the epilogue's are wanted back soon: K = 8,
+        // 448 workgroups of nine slices per wavefront 34.0 us, 504 of eight 33.3).
+        const int64_t slices = (int64_t)a.B * a.K * a.nsl;
+        int64_t places = (int64_t)per_wg * (a.B < kSampleWgs / 2 ? kSampleWgs - a.B : kSampleWgs / 2);
+        if (slices > 4 * places) places = (int64_t)per_wg * kSampleWgs;
+        const int64_t rounds = (slices + places - 1) / places;
+        const int wgs = (int)((slices + rounds * per_wg - 1) / (rounds * per_wg));
         a.n_waves = wgs * per_wg;
         const int step_rows = a.n_waves / a.nsl;
         a.step_s = a.n_waves % a.nsl; a.step_b = step_rows / a.K; a.step_k = step_rows % a.K;
