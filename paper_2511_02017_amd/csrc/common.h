@@ -833,16 +833,7 @@ __device__ inline RowTotal merge_partials(const Partial *p, int n, int stride = 
     return row_total<EXCL>(acc);
 }
 
-// ---- lane-parallel merge ------------------------------------------------------------------------
-// A sequential merge walks the slices of a row one after the other: eight dependent LDS reads and rescalings, about
-// 1.4 us of a per-sequence kernel whose every other step is one memory round trip.  When the rows of a sequence
-// times the slice count rounded up to a power of two (P <= 16) fit two passes of one workgroup, thread t instead
-// takes partial (row t / P, slice t % P) straight from memory (and the partial 256 / P rows further on in the
-// second pass), and the P lanes of a row combine their records with DPP exchanges in log2 P steps.  The combination
-// is commutative, so both partners of an exchange, and in the end all lanes of a group, hold the same bits; the
-// first lane of the group puts the row's total into LDS.
-struct RowSlot { RowTotal r; float xt; };
-
+// ---- records of a row's pieces on neighbouring lanes -------------------------------------------------
 template <int CTRL>
 __device__ inline Piece piece_dpp(const Piece &e)
 {
@@ -857,56 +848,14 @@ __device__ inline Piece piece_dpp(const Piece &e)
     return o;
 }
 
-// log2 of the group size P (1, 2, 4, 8 or 16) the lane-parallel merge would use for `rows` rows of `nsplit` slices,
-// or -1 if it does not apply (then the staged, sequential merge is used).
+// log2 of the lanes per row, one for each of its `nsplit` pieces (1, 2, 4, 8 or 16), that the per-sequence kernels' lane
+// paths use for `rows` rows, or -1 where they do not apply (then partials are staged in LDS and merged one by one): the
+// rows of a sequence fit two passes of one workgroup, and a wavefront's ballots.
 __device__ inline int lane_merge_shift(int rows, int nsplit)
 {
     if (nsplit > 16 || rows > 64) return -1;
     const int sh = nsplit <= 1 ? 0 : 32 - __clz(nsplit - 1);
     return (rows << sh) <= 512 ? sh : -1;
-}
-
-// Request this thread's partials: row `t >> sh` (first pass) and row `(t >> sh) + (256 >> sh)` (second pass),
-// piece `t & (P - 1)`, of `rows` rows at `part`.
-// (256-thread workgroups.)
-struct LaneRegs { StageRegs p[2]; };
-// row_stride, slice_stride: records from one row, one piece to the next (slice partials [rows][nsplit]: nsplit, 1; records
-// of vocabulary shards, shard-major: 1, rows of the whole call).
-__device__ inline LaneRegs lane_merge_issue(const Partial *part, int rows, int nsplit, int sh, int64_t row_stride, int64_t slice_stride)
-{
-    // Every thread requests something (one without a partial re-reads partial 0; lane_piece ignores what it got): a
-    // request under a condition is merged with the other branch's zeros, and the compiler waits for the data at the
-    // merge, ahead of whatever the caller wanted to request next.
-    LaneRegs r;
-    const int sl = threadIdx.x & ((1 << sh) - 1);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        // pass 2 only where one pass does not cover the rows (uniform); its registers are left unset otherwise and
-        // nothing reads them (setting them would be the merge described above)
-        if (q == 1 && (256 >> sh) >= rows) break;
-        const int row = (threadIdx.x >> sh) + q * (256 >> sh);
-        const bool mine = row < rows && sl < nsplit;
-        const u32x4 *s = (const u32x4 *)(part + (mine ? row * row_stride + sl * slice_stride : 0));
-        r.p[q].w0 = s[0]; r.p[q].w1 = s[1];
-    }
-    return r;
-}
-
-// Holds the requested partials' registers until here: placed after the caller's other requests, it keeps the compiler
-// from handing a register of a still outstanding request to something else (it would have to wait for the request
-// first); the wait for the data then happens here, behind all requests.
-__device__ inline void lane_merge_pin(const LaneRegs &r, int rows, int sh)
-{
-    asm volatile("" :: "v"(r.p[0].w0), "v"(r.p[0].w1));
-    if ((256 >> sh) < rows) asm volatile("" :: "v"(r.p[1].w0), "v"(r.p[1].w1));
-}
-
-// This thread's piece of pass q (an empty piece where the thread has none).
-__device__ inline Piece lane_piece(const LaneRegs &w, int q, int rows, int nsplit, int sh)
-{
-    const int sl = threadIdx.x & ((1 << sh) - 1), row = (threadIdx.x >> sh) + q * (256 >> sh);
-    if (q == 1 && (256 >> sh) >= rows) return empty_piece();       // uniform: no second pass was requested
-    return (row < rows && sl < nsplit) ? piece_from_words(w.p[q].w0, w.p[q].w1) : empty_piece();
 }
 
 // The pieces of the 2^sh lanes of a group combined; every lane of the group returns the same bits.
@@ -919,28 +868,6 @@ __device__ inline Piece lane_group_merge(Piece e, int sh)
     if (sh >= 3) e = merge_pair<EXCL>(e, piece_dpp<0x141>(e));
     if (sh >= 4) e = merge_pair<EXCL>(e, piece_dpp<0x140>(e));
     return e;
-}
-
-template <bool EXCL>
-__device__ inline void lane_merge_pass(RowSlot *sh_rows, const Piece &e0, int row, int rows, int sh)
-{
-    const int sl = threadIdx.x & ((1 << sh) - 1);
-    const Piece e = lane_group_merge<EXCL>(e0, sh);
-    if (row < rows && sl == 0) {
-        RowSlot o;
-        o.r = row_total<EXCL>(e);
-        o.xt = e.xt;
-        sh_rows[row] = o;
-    }
-}
-
-// Combine and publish: sh_rows[row] for row < rows; ends with a barrier.  e0, e1: this thread's pieces of the two passes.
-template <bool EXCL>
-__device__ inline void lane_merge_commit(RowSlot *sh_rows, const Piece &e0, const Piece &e1, int rows, int sh)
-{
-    lane_merge_pass<EXCL>(sh_rows, e0, threadIdx.x >> sh, rows, sh);
-    if ((256 >> sh) < rows) lane_merge_pass<EXCL>(sh_rows, e1, (threadIdx.x >> sh) + (256 >> sh), rows, sh);   // uniform
-    __syncthreads();
 }
 
 // First index j in [cand, cand + window) with x_j == M (the lowest argmax index of the row), in two steps so

@@ -152,89 +152,6 @@ __device__ inline double wave_incl_scan_d(double v, double *total)
     return v;
 }
 
-// ---- lse and token logit of the draft rows from the draft pass's partials ----------------
-// For accept decisions that do not wait for the draft epilogue.  A draft partial's S leaves out the batch with the
-// slice's first maximum; pad[1] holds that batch's own sum in the same reference, so S + pad[1] is the sum over the
-// whole slice (binary32 precision).  Same lane layout as the lane-parallel merge: thread t takes the partial of
-// (row t >> sh, slice t & (P - 1)) and of the row 256 >> sh further on; the P lanes of a row combine (max, sum) with
-// DPP exchanges (commutative: all lanes of a group end with the same bits) and the first writes the row's entry.
-struct DraftRowLse { double lse; float xt; };     // xt: the logit of the row's token (NaN: the token is out of range)
-
-struct QPiece { float M; double S; float xt; };
-
-template <int CTRL>
-__device__ inline QPiece qpiece_dpp(const QPiece &e)
-{
-    auto mv = [](int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); };
-    QPiece o;
-    o.M = __int_as_float(mv(__float_as_int(e.M)));
-    o.S = __hiloint2double(mv(__double2hiint(e.S)), mv(__double2loint(e.S)));
-    o.xt = __int_as_float(mv(__float_as_int(e.xt)));
-    return o;
-}
-__device__ inline QPiece qpiece_merge(const QPiece &a, const QPiece &b)
-{
-    QPiece o;
-    o.M = fmaxf(a.M, b.M);                                        // slice maxima are never NaN
-    const float Rw = ref_of_max(o.M);
-    const int da = (int)fminf(fmaxf(Rw - ref_of_max(a.M), -4000.0f), 4000.0f), db = (int)fminf(fmaxf(Rw - ref_of_max(b.M), -4000.0f), 4000.0f);
-    o.S = ldexp(a.S, -da) + ldexp(b.S, -db);                      // an empty piece has S = 0 whatever its shift
-    o.xt = (a.xt == a.xt) ? a.xt : b.xt;                          // at most one slice holds the token
-    return o;
-}
-// In two steps, so that the caller can put these requests beside its own and wait for all of them once: the requests ...
-struct DraftLseRegs { float pm[2], ps[2], px[2], ph[2]; };       // maximum, sum, token logit, left-out sum: the words wanted
-__device__ inline int draft_lse_tid(int rows, int sh)
-{
-    // when they fit, on the upper two wavefronts: the lower two merge the target rows meanwhile
-    return (rows << sh) <= 128 ? (int)threadIdx.x - 128 : (int)threadIdx.x;
-}
-__device__ inline DraftLseRegs draft_rows_lse_issue(const Partial *part, int rows, int nsplit, int sh)
-{
-    const int tid = draft_lse_tid(rows, sh), sl = tid & ((1 << sh) - 1);
-    DraftLseRegs r;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        if (q == 1 && (256 >> sh) >= rows) break;                              // uniform; pass 2 stays unset and unread
-        // unconditional requests (a thread without a partial re-reads partial 0 and ignores it): see lane_merge_issue
-        const int row = tid < 0 ? rows : (tid >> sh) + q * (256 >> sh);        // rows: none
-        const bool mine = row < rows && sl < nsplit;
-        const Partial *s = part + (mine ? (int64_t)row * nsplit + sl : 0);
-        r.pm[q] = s->v1; r.ps[q] = s->S; r.px[q] = __int_as_float(s->pad[0]); r.ph[q] = __int_as_float(s->pad[1]);
-    }
-    return r;
-}
-// ... and the merge, which writes out[row] for row < rows (published by the caller's next barrier).
-__device__ inline void draft_rows_lse_finish(const DraftLseRegs &r, int rows, int nsplit, int sh, DraftRowLse *out)
-{
-    const int tid = draft_lse_tid(rows, sh), sl = tid & ((1 << sh) - 1);
-    asm volatile("" :: "v"(r.pm[0]), "v"(r.ps[0]), "v"(r.px[0]), "v"(r.ph[0]));     // see lane_merge_pin
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        if (q == 1 && (256 >> sh) >= rows) break;                 // uniform
-        const int row = tid < 0 ? rows : (tid >> sh) + q * (256 >> sh);
-        QPiece e;
-        e.M = -INFINITY; e.S = 0.0; e.xt = NAN;
-        if (row < rows && sl < nsplit) {
-            e.M = r.pm[q];
-            e.S = (double)r.ps[q] + (double)r.ph[q];
-            e.xt = r.px[q];
-            if (e.M == -INFINITY && !(e.S != e.S)) e.S = 0.0;     // empty slice
-        }
-        if (sh >= 1) e = qpiece_merge(e, qpiece_dpp<0xB1>(e));
-        if (sh >= 2) e = qpiece_merge(e, qpiece_dpp<0x4E>(e));
-        if (sh >= 3) e = qpiece_merge(e, qpiece_dpp<0x141>(e));
-        if (sh >= 4) e = qpiece_merge(e, qpiece_dpp<0x140>(e));
-        if (row < rows && sl == 0) {
-            const bool bad = !(e.S > 0.0) || !(e.S < INFINITY) || !(e.M > -INFINITY && e.M < INFINITY);
-            DraftRowLse o;
-            o.lse = bad ? (double)NAN : ((double)ref_of_max(e.M) + log2_pos(e.S)) * kLn2;
-            o.xt = e.xt;
-            out[row] = o;
-        }
-    }
-}
-
 // Eight consecutive elements j .. j+7 of a row as they lie in memory (one 16-byte vector of bfloat16, two of binary32;
 // -inf beyond V), so that a kernel can hold several requests in flight in few registers and widen them, exactly, when
 // their turn comes.
@@ -290,277 +207,340 @@ __device__ inline void widen8(const Raw8<DT> &r, float (&x)[kPer])
 }
 
 // ---- head: accept decisions of one sequence -----------------------------------------
-// Called by all threads of a workgroup.  Returns the sequence's job (identical in every
-// workgroup of the sequence); with `writer` also writes the sequence's outputs.
-// Accept decisions exist for rows k < n <= K <= kScanCap, so the LDS byte buffer always holds them.
+// verify_head is called by all 256 threads of a workgroup.  It returns the sequence's job (identical in every
+// workgroup of the sequence); with `writer` it also writes the sequence's outputs.
 //
-// kVerifyOwnQ (whole-round calls, lane-merge shapes only): log q(tok) and the draft rows' lse are not read from the draft
-// epilogue's outputs, which then need not exist yet, but formed here from the draft pass's partials: the slice sums
-// with their left-out batch's own sum added back (binary32 precision, which a ratio p/q compared with a uniform
-// needs no more than) and the token's logit, which the draft pass left in the partial of the slice that holds it.
+// kVerifyOwnQ (whole-round calls, lane-path shapes only): log q(tok) and the draft rows' lse are not read from the draft
+// epilogue's outputs, which then need not exist yet, but formed here from the draft pass's partials: a draft partial's S
+// leaves out the batch with the slice's first maximum, pad[1] holds that batch's own sum in the same reference, so S +
+// pad[1] is the sum over the whole slice (binary32 precision, which a ratio p/q compared with a uniform needs no more
+// than); the token's logit was left in pad[0] of the slice that holds it.
 //
 // shT: 256 doubles of LDS for the table of exp_fast, which this function fills (each thread requests its entry with the
 // first requests and stores it ahead of the first barrier): the two exponentials on the critical path take 13
-// instructions each instead of a call into the device library.  256-thread workgroups.
+// instructions each instead of a call into the device library.
 //
-// more_requests(): called once, right after this function's own first requests are out: a caller with bulk loads of its
-// own (the slice kernel's table) puts them there, behind the few words the decisions wait for (loads return in order).
-struct NoRequests { __device__ void operator()() const {} };
-template <bool SHARDED, class MoreRequests = NoRequests>
-__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer,
-                                        Partial *sh_part, uint8_t *sh_dec, uint32_t *sh_flags, int32_t *sh_bcast, double *sh_lse,
-                                        DraftRowLse *sh_qrows, double *shT, MoreRequests more_requests = MoreRequests())
+// request_table(): called once, where the caller's copy of its table to LDS may start (the slice kernel's; it may lie over
+// `stg`): on the lane path right behind this function's own first requests (loads return in order).  The copy is complete
+// and published when this function returns.
+struct NoTable { __device__ void operator()() const {} };
+constexpr uint32_t kFatal = TAPOUT_FLAG_BAD_NDRAFT | TAPOUT_FLAG_BAD_TOKEN | TAPOUT_FLAG_BAD_ROW;
+
+// LDS of the decisions on either path.
+struct HeadRow { double lse; float M, dl; int32_t top1, tok; };             // what the job and the outputs want of a target row
+struct HeadLanes { HeadRow rows[kWave]; uint8_t dec[kWave], flag[kWave]; };
+struct HeadStaged {
+    Partial part[kStageCap];
+    uint8_t dec[kScanCap];                  // accept decisions exist for rows k < n <= K <= kScanCap
+    uint32_t flags;
+    int32_t bcast[8];
+    double lse;
+};
+
+// One row's decision: t the drafted token, u its uniform, lq its log q, xt its target logit.
+struct Accept { bool yes; float lp; uint32_t flags; };
+__device__ inline Accept accept_row(const VerifyArgs &a, bool bad, double lse, bool greedy, int32_t t, float u, float lq, float xt, int32_t top1, const double *shT)
+{
+    Accept o{false, NAN, 0u};
+    if (__builtin_expect(t < 0 || t >= a.V, 0)) o.flags = TAPOUT_FLAG_BAD_TOKEN;
+    else if (!bad) {
+        o.lp = (float)((double)xt - lse);
+        if (greedy) o.yes = t == top1;
+        else {
+            const double arg = (double)o.lp - (double)lq;
+            o.yes = arg == arg && (double)u < exp_fast_d(arg, shT);
+        }
+    }
+    return o;
+}
+
+// The sequence's job: row m, its maximum Mm and lse, the draft row's lse dl.
+__device__ inline SampleJob head_job(bool draws, int m, int n, float Mm, double lse_m, float dl_m, bool have_dl, const double *shT)
+{
+    SampleJob job;
+    job.kind = 0; job.row = 0; job.ref_p = 0.0f; job.ref_q = 0.0f; job.lam = 0.0;
+    if (draws) {
+        job.kind = m < n ? 1 : 2;
+        job.row = m;
+        job.ref_p = Mm;                          // exponent references: the target row's maximum, the draft row's lse
+        job.ref_q = (m < n && have_dl) ? dl_m : 0.0f;
+        // binary32-grade estimate of S_p / S_q in these references (S_q = sum exp(d - lse_q) = 1): lets the
+        // slice pass form the residual before the exact normalisers exist
+        job.lam = exp_fast_d(lse_m - (double)Mm, shT);
+    }
+    return job;
+}
+
+// The sequence's outputs but for the rows'; tok(k): the drafted token of row k.
+template <bool SHARDED, class Tok>
+__device__ inline void head_outputs(const VerifyArgs &a, int b, const SampleJob &job, int m, int n, bool flagged, bool greedy, uint32_t f, int32_t top1m, Tok tok)
 {
     const int K = a.K;
-    // few rows and slices: one partial per thread, merged across lanes (see lane_merge_commit); else staged in LDS
-    const int msh = lane_merge_shift(K + 1, a.nsplit);
-    // The lane-parallel merge leaves the totals of all K + 1 <= 64 rows in LDS at once and row k with thread k: it is
-    // one stage whatever the slice count.  The staged merge takes kStageCap partials at a time.
-    const int rows_per_stage = msh >= 0 ? kWave : kStageCap / a.nsplit;
+    const int32_t final_tok = (flagged || greedy) ? top1m : -1;   // sampled sequences: written by pass 3
+    if (threadIdx.x == 0) {
+        a.accept_len[b] = m;
+        a.n_out[b] = m + 1;
+        if constexpr (!SHARDED) {
+            a.jobs[b].job = job;
+            // the slice kernel appends to the sequence's band list; fused into that kernel, this workgroup
+            // cannot empty the list under the others' appends: the target pass has done it
+            if (!a.fused_head) a.jobs[b].band_cnt = 0;
+            a.flags_ws[b] = f;
+        } else if (a.final_jobs) {
+            a.final_jobs[b] = job;
+        }
+        if (a.flags) a.flags[b] = f;
+    }
+    int32_t *o = a.out_tok + (int64_t)b * (K + 1);
+    for (int k = threadIdx.x; k <= K; k += kVBlock) {
+        o[k] = k < m ? tok(k) : (k == m ? final_tok : -1);
+        if (flagged && a.logp_tok && k < n) a.logp_tok[(int64_t)b * K + k] = NAN;
+    }
+}
+
+// Few rows and slices (lane_merge_shift): 2^msh lanes per target row, one piece each; they find the row's maximum, bring
+// their sums to its reference and add them up, the draft row of the same position beside it (kVerifyOwnQ), and every
+// lane takes the row's decision: no LDS on the way to it, and one barrier behind it, after which every wavefront finds
+// the first rejection for itself.  An instruction costs a wavefront here about nine cycles whatever it is: see
+// draft_finalize_lanes.  (Pairwise merges of whole records, rows and draft rows handed to a thread per row through LDS, the
+// first rejection published by a second barrier, and the table through registers: slice kernel with the decisions, V = 128256,
+// 64 sequences, up to the stop position 17.4 us, this 15.9; head launch at 256 sequences, K = 16 7.0 / 5.6.)
+template <bool SHARDED, class Table>
+__device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool writer, HeadLanes *sh, double *shT, Table request_table, const int msh)
+{
+    const int K = a.K, tid = threadIdx.x, lane = tid & (kWave - 1), sl = tid & ((1 << msh) - 1), per_pass = kVBlock >> msh;
     // Everything whose address does not depend on n_draft is requested before n_draft is looked at, so that
     // the first memory round trip carries n_draft, the tokens, the uniforms and the partials together.
     // (Rows beyond n_draft hold stale partials and unused tokens: read, never used.)
-    int32_t tok0 = -1;
-    float u0 = 0.0f, lq0 = 0.0f, dl0 = 0.0f;
-    // n_draft and greedy are requested here too, as vector loads (the index carries a zero the compiler cannot
+    // n_draft and greedy are requested as vector loads (the index carries a zero the compiler cannot
     // see through): a scalar load would share its counter with the loads of kernel arguments, and the first wait
-    // for one of those would wait for memory.  Their first use comes after the staging barrier.
+    // for one of those would wait for memory.
     int zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
     int n = a.n_draft[b + zero];
     uint8_t greedy_raw = a.greedy ? a.greedy[b + zero] : (uint8_t)0;
-    const double tv = a.exp_table[threadIdx.x];
-    const bool own_q = !SHARDED && (a.vflags & kVerifyOwnQ) != 0 && msh >= 0 && lane_merge_shift(K, a.d_nsplit) >= 0;   // (the host offers own_q for lane-merge shapes only)
-    if ((int)threadIdx.x < K) {
-        const int64_t i = (int64_t)b * K + threadIdx.x;
-        tok0 = a.draft_tok[i];
-        u0 = a.u_accept[i];
-        if (!own_q) {
-            lq0 = a.logq_tok[i];
-            if (a.draft_lse) dl0 = a.draft_lse[i];  // the final token's job wants it for row m: no dependent load later
-        }
-    }
-    if (threadIdx.x == 0) { *sh_flags = 0; sh_bcast[4] = 0; }     // ahead of the staging barrier: rows of other wavefronts OR into the flags
-    RowSlot *sh_rows = (RowSlot *)sh_part;
-    static_assert(sizeof(RowSlot) * 64 <= sizeof(Partial) * kStageCap, "the row totals reuse the staging buffer");
-    if (SHARDED && __builtin_expect(msh >= 0, 1)) {
-        const LaneRegs ln = lane_merge_issue(a.part + (int64_t)b * (K + 1), K + 1, a.nsplit, msh, 1, (int64_t)a.B * (K + 1));
-        more_requests();
-        lane_merge_pin(ln, K + 1, msh);
-        shT[threadIdx.x] = tv;
-        lane_merge_commit<true>(sh_rows, lane_piece(ln, 0, K + 1, a.nsplit, msh), lane_piece(ln, 1, K + 1, a.nsplit, msh), K + 1, msh);
-    } else if constexpr (SHARDED) {
-        const int c0 = min(K + 1, rows_per_stage) * a.nsplit;
-        const StageRegs st = stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1), a.nsplit, c0);
-        more_requests();
-        shT[threadIdx.x] = tv;
-        stage_commit(sh_part, st, c0);
-    } else if (__builtin_expect(msh >= 0, 1)) {
-        // target partials run over every element of their slice: plain pieces, nothing left out
-        // all requests first, then one wait for the lot (see lane_merge_pin)
-        const LaneRegs ln = lane_merge_issue(a.part + (int64_t)b * (K + 1) * a.nsplit, K + 1, a.nsplit, msh, a.nsplit, 1);
-        const int qsh = own_q ? lane_merge_shift(K, a.d_nsplit) : -1;            // >= 0: the host offers own_q for such shapes only
-        DraftLseRegs lq;
-        if (qsh >= 0) lq = draft_rows_lse_issue(a.dpart + (int64_t)b * K * a.d_nsplit, K, a.d_nsplit, qsh);
-        more_requests();
-        lane_merge_pin(ln, K + 1, msh);
-        HEAD_STAMP(0);                                           // first requests answered
-        shT[threadIdx.x] = tv;
-        if (qsh >= 0) draft_rows_lse_finish(lq, K, a.d_nsplit, qsh, sh_qrows);     // published by the barrier below
-        lane_merge_commit<false>(sh_rows, lane_piece(ln, 0, K + 1, a.nsplit, msh), lane_piece(ln, 1, K + 1, a.nsplit, msh), K + 1, msh);
-        HEAD_STAMP(1);                                           // rows merged, barrier passed
-    } else {
-        const int c0 = min(K + 1, rows_per_stage) * a.nsplit;
-        const StageRegs st = stage_issue(a.part + (int64_t)b * (K + 1) * a.nsplit, c0);
-        more_requests();
-        shT[threadIdx.x] = tv;
-        stage_commit(sh_part, st, c0);
-    }
+    const double tv = a.exp_table[tid];
+    const bool own_q = !SHARDED && (a.vflags & kVerifyOwnQ) != 0;          // (the host offers it for shapes that take this path on both sides)
+    bool greedy = false;
     uint32_t f0 = 0;
-    n = __builtin_amdgcn_readfirstlane(n);
-    if (__builtin_expect(n < 1 || n > K, 0)) { f0 |= TAPOUT_FLAG_BAD_NDRAFT; n = n < 1 ? 1 : K; }
-    const bool greedy = __builtin_amdgcn_readfirstlane((int)greedy_raw) != 0;
-    SampleJob job;
-    job.kind = 0; job.row = 0; job.ref_p = 0.0f; job.ref_q = 0.0f; job.lam = 0.0;
-    if (threadIdx.x == 0 && f0) atomicOr(sh_flags, f0);
-    const bool need_top1 = writer || greedy;
-    int last_k = -1; float last_M = 0.0f, last_dl = 0.0f; int32_t last_top1 = 0; double last_lse = 0.0;   // the last row this thread merged
-    bool acc_mine = false; uint32_t f_mine = 0;      // its accept decision and flags (used on the lane-merge path)
-    for (int k0 = 0; k0 <= n; k0 += rows_per_stage) {
-        const int k1 = min(n + 1, k0 + rows_per_stage);
-        const int kmine = k0 + threadIdx.x;
-        if (__builtin_expect(k0 > 0, 0)) {                               // further stages (K + 1 > rows_per_stage): load late
-            tok0 = -1;
-            if (kmine < k1 && kmine < n) {
-                const int64_t i = (int64_t)b * K + kmine;
-                tok0 = a.draft_tok[i]; u0 = a.u_accept[i]; lq0 = a.logq_tok[i];
-                if (a.draft_lse) dl0 = a.draft_lse[i];
-            }
-            __syncthreads();
-            if constexpr (SHARDED) {
-                const int c1 = (k1 - k0) * a.nsplit;
-                stage_commit(sh_part, stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1) + k0, a.nsplit, c1), c1);
-            } else {
-                stage_partials(sh_part, a.part + ((int64_t)b * (K + 1) + k0) * a.nsplit, (k1 - k0) * a.nsplit);
+    for (int row0 = 0; row0 <= K; row0 += per_pass) {                      // one pass but for long drafts of many slices
+        const int row = row0 + (tid >> msh), row_t = min(row, K), row_d = min(row, K - 1);
+        const int64_t it = (int64_t)b * (K + 1) + row_t, i = (int64_t)b * K + row_d;
+        const u32x4 *pt = (const u32x4 *)(SHARDED ? a.part + (int64_t)min(sl, a.nsplit - 1) * a.B * (K + 1) + it : a.part + it * a.nsplit + min(sl, a.nsplit - 1));
+        const u32x4 w0 = pt[0], w1 = pt[1];
+        float qv1 = -INFINITY, qS = 0.0f, qx = NAN, qh = 0.0f;
+        const int32_t tok = a.draft_tok[i];
+        const float u = a.u_accept[i];
+        float lq = 0.0f, dl = 0.0f;
+        if (own_q) {
+            const Partial *pd = a.dpart + i * a.d_nsplit + min(sl, a.d_nsplit - 1);
+            qv1 = pd->v1; qS = pd->S; qx = __int_as_float(pd->pad[0]); qh = __int_as_float(pd->pad[1]);
+        } else {
+            lq = a.logq_tok[i];
+            if (a.draft_lse) dl = a.draft_lse[i];                          // the final token's job wants it for row m: no dependent load later
+        }
+        if (row0 == 0) request_table();
+        asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(u), "v"(qv1), "v"(qS), "v"(qx), "v"(qh));     // every request is out before the first wait
+        HEAD_STAMP(0);                                                     // first requests answered
+        if (row0 == 0) {
+            shT[tid] = tv;
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (__builtin_expect(n < 1 || n > K, 0)) { f0 = TAPOUT_FLAG_BAD_NDRAFT; n = n < 1 ? 1 : K; }
+            greedy = __builtin_amdgcn_readfirstlane((int)greedy_raw) != 0;
+            __syncthreads();                                               // the table: every row's decision reads it
+        }
+        // target row: maximum, sum and (start of the vector that holds) its first maximum.  Slice partials run over every
+        // element of their slice; shard records leave their maximum out.
+        const bool mine = sl < a.nsplit;
+        const float v1 = mine ? __uint_as_float(w0.x) : -INFINITY;
+        float S = mine ? __uint_as_float(w0.y) : 0.0f;
+        if (v1 == -INFINITY && !(S != S)) S = 0.0f;
+        Piece p;
+        p.M = lanes_max(v1, 0, msh);
+        const float R = ref_of_max(p.M);
+        p.S = ldexp((double)S, -(int)fminf(fmaxf(R - ref_of_max(v1), -4000.0f), 4000.0f));
+        if (S == 0.0f) p.S = 0.0;                                          // (0 * inf)
+        const bool holds = mine && v1 == p.M;
+        p.idx = lanes_min(holds ? (int32_t)w1.x : 0x7fffffff, 0, msh);
+        if constexpr (SHARDED)
+            if (!(holds && (int32_t)w1.x == p.idx) && v1 > -INFINITY) p.S += (double)__builtin_amdgcn_exp2f(__builtin_fmaf(v1, kLog2e, -R));
+        p.S = lanes_sum(p.S, 0, msh);
+        p.T = 0.0; p.v2 = 0.0f;
+        p.xt = lanes_max(mine ? __uint_as_float(w1.y) : NAN, 0, msh);      // the piece that holds the token put its logit there, the others NaN
+        const RowTotal r = row_total<SHARDED>(p);
+        double lse = NAN;
+        uint32_t f = 0;
+        if (__builtin_expect(r.bad, 0)) f = TAPOUT_FLAG_BAD_ROW;
+        else lse = (r.R + log2_pos(r.S)) * kLn2;
+        if (own_q) {
+            const bool has = sl < a.d_nsplit;
+            qv1 = has ? qv1 : -INFINITY;
+            float s = has ? qS + qh : 0.0f;
+            if (qv1 == -INFINITY && !(s != s)) s = 0.0f;
+            const float qM = lanes_max(qv1, 0, msh), qR = ref_of_max(qM);
+            double qs = ldexp(has ? (double)qS + (double)qh : 0.0, -(int)fminf(fmaxf(qR - ref_of_max(qv1), -4000.0f), 4000.0f));
+            if (s == 0.0f) qs = 0.0;
+            qs = lanes_sum(qs, 0, msh);
+            const float x = lanes_max(has ? qx : NAN, 0, msh);
+            const bool bad = !(qs > 0.0) || !(qs < INFINITY) || !(qM > -INFINITY && qM < INFINITY);
+            const double lse_q = bad ? (double)NAN : ((double)qR + log2_pos(qs)) * kLn2;
+            lq = (float)((double)x - lse_q);
+            dl = (float)lse_q;
+        }
+        HEAD_STAMP(1);                                                     // row merged
+        const bool lead = sl == 0 && row <= n;
+        int32_t top1 = (SHARDED && r.cand >= 0 && r.cand < a.V) ? r.cand : 0;      // a shard's argmax is exact and global
+        // Greedy sequences decide on the argmax; the others only report it: their leading lane looks at the window last.
+        const void *row_p = SHARDED ? nullptr : row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, row_t);
+        ArgmaxProbe probe;
+        if constexpr (!SHARDED) {
+            if (lead && (writer || greedy)) {
+                probe = argmax_issue(row_p, a.t_dtype, a.V, r.cand);
+                if (greedy) top1 = argmax_finish(probe, row_p, a.t_dtype, a.V, r.cand, r.M);
             }
         }
-        for (int k = kmine; k < k1; k += kVBlock) {
-            const int64_t it = (int64_t)b * (K + 1) + k;
-            const void *row = SHARDED ? nullptr : row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, k);
-            // shard records leave their first maximum out of the sums (and carry its exact index), slice partials of
-            // target rows do not
-            const RowTotal r = msh >= 0 ? sh_rows[k].r : merge_partials<SHARDED>(sh_part + (k - k0) * a.nsplit, a.nsplit);
-            // the argmax window is requested here and looked at after the logarithm (greedy sequences need the
-            // argmax for their decisions, the others only for the outputs)
-            int32_t top1 = 0;
-            ArgmaxProbe probe;
-            if constexpr (SHARDED) top1 = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;                // a shard's argmax is exact and global
-            else if (need_top1) probe = argmax_issue(row, a.t_dtype, a.V, r.cand);
-            uint32_t f = 0;
-            double lse_d = NAN;
-            if (__builtin_expect(r.bad, 0)) f |= TAPOUT_FLAG_BAD_ROW;
-            else lse_d = (r.R + log2_pos(r.S)) * kLn2;
-            // greedy sequences decide on the argmax; the others only report it: they look at the window last
+        Accept acc{false, NAN, 0u};
+        if (row < n) acc = accept_row(a, r.bad, lse, greedy, tok, u, lq, p.xt, top1, shT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // the table's copy, before this workgroup's first stores
+        if (lead) {
             if constexpr (!SHARDED)
-                if (greedy) top1 = argmax_finish(probe, row, a.t_dtype, a.V, r.cand, r.M);
-            if (k < n) {
-                const int64_t i = (int64_t)b * K + k;
-                int32_t t = tok0;
-                float u = u0, lq = lq0;
-                last_dl = dl0;
-                if (own_q) {                                   // one row per thread on this path: k == kmine
-                    const double lse_q = sh_qrows[k].lse;
-                    lq = (float)((double)sh_qrows[k].xt - lse_q);
-                    last_dl = (float)lse_q;
-                } else if (__builtin_expect(k != kmine, 0)) {                       // more rows than threads: load late
-                    t = a.draft_tok[i]; u = a.u_accept[i]; lq = a.logq_tok[i];
-                    if (a.draft_lse) last_dl = a.draft_lse[i];
-                }
-                // the slice (or vocabulary shard) that holds the token put its logit into its partial, the others NaN
-                float xt = NAN;
-                if (msh >= 0) xt = sh_rows[k].xt;
-                else
-                    for (int g = 0; g < a.nsplit; ++g) {
-                        const float v = __int_as_float(sh_part[(k - k0) * a.nsplit + g].pad[0]);
-                        if (v == v) xt = v;
-                    }
-                bool acc = false;
-                float lp = NAN;
-                if (__builtin_expect(t < 0 || t >= a.V, 0)) f |= TAPOUT_FLAG_BAD_TOKEN;
-                else if (!r.bad) {
-                    lp = (float)((double)xt - lse_d);
-                    if (greedy) acc = (t == top1);
-                    else {
-                        const double arg = (double)lp - (double)lq;
-                        acc = arg == arg && (double)u < exp_fast_d(arg, shT);
-                    }
-                }
-                if (writer && a.logp_tok) a.logp_tok[i] = lp;
-                acc_mine = acc;
-                if (msh < 0) sh_dec[k] = acc ? 1 : 0;
-            }
-            if constexpr (!SHARDED)
-                if (need_top1 && !greedy) top1 = argmax_finish(probe, row, a.t_dtype, a.V, r.cand, r.M);
+                if (writer && !greedy) top1 = argmax_finish(probe, row_p, a.t_dtype, a.V, r.cand, r.M);
+            sh->dec[row] = acc.yes ? 1 : 0;
+            sh->flag[row] = (uint8_t)(f | acc.flags);
+            HeadRow h;
+            h.lse = lse; h.M = r.M; h.dl = dl; h.top1 = top1; h.tok = tok;
+            sh->rows[row] = h;
             if (writer) {
-                if (a.target_lse) a.target_lse[it] = (float)lse_d;
+                if (row < n && a.logp_tok) a.logp_tok[i] = acc.lp;
+                if (a.target_lse) a.target_lse[it] = (float)lse;
                 if (a.target_top1) a.target_top1[it] = top1;
             }
-            last_k = k; last_M = r.M; last_top1 = top1; last_lse = lse_d;
-            f_mine = f;
-            if (msh < 0 && f) atomicOr(sh_flags, f);
         }
+        HEAD_STAMP(2);                                                     // lse, log p(tok), accept decision
     }
-    constexpr uint32_t kFatal = TAPOUT_FLAG_BAD_NDRAFT | TAPOUT_FLAG_BAD_TOKEN | TAPOUT_FLAG_BAD_ROW;
-    HEAD_STAMP(2);                                               // every row's lse, log p(tok), accept decision
-    if (__builtin_expect(msh >= 0, 1)) {
-        // Lane-merge path: row k was thread k's, so the rows are lanes of the first wavefront.  Ballots give the
-        // first rejection and the flags, lane m hands over what the job needs of row m, one barrier publishes it.
-        if (threadIdx.x < kWave) {
-            const uint64_t acc_mask = __builtin_amdgcn_ballot_w64((int)threadIdx.x < n && acc_mine);
-            uint32_t fa = f0;
-            if (__builtin_amdgcn_ballot_w64((f_mine & TAPOUT_FLAG_BAD_TOKEN) != 0)) fa |= TAPOUT_FLAG_BAD_TOKEN;
-            if (__builtin_amdgcn_ballot_w64((f_mine & TAPOUT_FLAG_BAD_ROW) != 0)) fa |= TAPOUT_FLAG_BAD_ROW;
-            // first draft position that was not accepted, n if there is none (n <= 63 here)
-            const int mm = (fa & kFatal) ? 0 : __builtin_ctzll(~acc_mask | (1ull << n));
-            const int Mb = __builtin_amdgcn_readlane(__float_as_int(last_M), mm);
-            const int tb = __builtin_amdgcn_readlane(last_top1, mm);
-            const int db = __builtin_amdgcn_readlane(__float_as_int(last_dl), mm);
-            const int lh = __builtin_amdgcn_readlane(__double2hiint(last_lse), mm);
-            const int ll = __builtin_amdgcn_readlane(__double2loint(last_lse), mm);
-            if (threadIdx.x == 0) {
-                sh_bcast[0] = mm; sh_bcast[1] = (fa & kFatal) ? 1 : 0; sh_bcast[2] = (int32_t)fa;
-                sh_bcast[4] = 1; sh_bcast[5] = Mb; sh_bcast[6] = tb; sh_bcast[7] = db;
-                *sh_lse = __hiloint2double(lh, ll);
+    __syncthreads();
+    // rows are lanes of every wavefront: ballots give the first rejection and the flags
+    const uint64_t acc_mask = __builtin_amdgcn_ballot_w64(lane < n && sh->dec[lane] != 0);
+    const uint32_t fl = lane <= n ? sh->flag[lane] : 0u;
+    uint32_t f = f0;
+    if (__builtin_amdgcn_ballot_w64((fl & TAPOUT_FLAG_BAD_TOKEN) != 0)) f |= TAPOUT_FLAG_BAD_TOKEN;
+    if (__builtin_amdgcn_ballot_w64((fl & TAPOUT_FLAG_BAD_ROW) != 0)) f |= TAPOUT_FLAG_BAD_ROW;
+    const bool flagged = (f & kFatal) != 0;
+    const int m = flagged ? 0 : __builtin_ctzll(~acc_mask | (1ull << n));  // first draft position that was not accepted, n if there is none (n <= 63 here)
+    const HeadRow h = sh->rows[m];                                         // a flagged sequence has m = 0 and emits the argmax of row 0
+    HEAD_STAMP(3);                                                         // first rejection known
+    const SampleJob job = head_job(!flagged && !greedy, m, n, h.M, h.lse, h.dl, a.draft_lse || own_q, shT);
+    if (writer) head_outputs<SHARDED>(a, b, job, m, n, flagged, greedy, f, h.top1, [&](int k) { return sh->rows[k].tok; });
+    return job;
+}
+
+// Any number of rows and pieces: kStageCap partials at a time in LDS, one row per thread.
+template <bool SHARDED, class Table>
+__device__ inline SampleJob verify_head_staged(const VerifyArgs &a, int b, bool writer, HeadStaged *sh, double *shT, Table request_table)
+{
+    const int K = a.K, rows_per_stage = kStageCap / a.nsplit;
+    int n = a.n_draft[b];
+    const bool greedy = a.greedy && a.greedy[b] != 0;
+    const double tv = a.exp_table[threadIdx.x];
+    auto stage = [&](int k0, int count) {
+        if constexpr (SHARDED) return stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1) + k0, a.nsplit, count);
+        else return stage_issue(a.part + ((int64_t)b * (K + 1) + k0) * a.nsplit, count);
+    };
+    {
+        const int c0 = min(K + 1, rows_per_stage) * a.nsplit;
+        const StageRegs st = stage(0, c0);
+        shT[threadIdx.x] = tv;
+        if (threadIdx.x == 0) { sh->flags = 0; sh->bcast[4] = 0; }         // ahead of the barrier: rows of other wavefronts OR into the flags
+        stage_commit(sh->part, st, c0);
+    }
+    if (n < 1 || n > K) {
+        if (threadIdx.x == 0) atomicOr(&sh->flags, TAPOUT_FLAG_BAD_NDRAFT);
+        n = n < 1 ? 1 : K;
+    }
+    const bool need_top1 = writer || greedy;
+    int last_k = -1; float last_M = 0.0f, last_dl = 0.0f; int32_t last_top1 = 0; double last_lse = 0.0;   // the last row this thread merged
+    for (int k0 = 0; k0 <= n; k0 += rows_per_stage) {
+        const int k1 = min(n + 1, k0 + rows_per_stage);
+        if (k0 > 0) {
+            __syncthreads();
+            stage_commit(sh->part, stage(k0, (k1 - k0) * a.nsplit), (k1 - k0) * a.nsplit);
+        }
+        for (int k = k0 + threadIdx.x; k < k1; k += kVBlock) {
+            const int64_t it = (int64_t)b * (K + 1) + k, i = (int64_t)b * K + k;
+            // shard records leave their first maximum out of the sums (and carry its exact index), slice partials of
+            // target rows do not
+            const RowTotal r = merge_partials<SHARDED>(sh->part + (k - k0) * a.nsplit, a.nsplit);
+            int32_t top1 = 0;
+            if constexpr (SHARDED) top1 = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;
+            else if (need_top1) top1 = resolve_argmax(row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, k), a.t_dtype, a.V, r.cand, r.M);
+            double lse = NAN;
+            uint32_t f = 0;
+            if (r.bad) f |= TAPOUT_FLAG_BAD_ROW;
+            else lse = (r.R + log2_pos(r.S)) * kLn2;
+            if (k < n) {
+                float xt = NAN;
+                for (int g = 0; g < a.nsplit; ++g) {
+                    const float v = __int_as_float(sh->part[(k - k0) * a.nsplit + g].pad[0]);
+                    if (v == v) xt = v;
+                }
+                const Accept acc = accept_row(a, r.bad, lse, greedy, a.draft_tok[i], a.u_accept[i], a.logq_tok[i], xt, top1, shT);
+                f |= acc.flags;
+                if (writer && a.logp_tok) a.logp_tok[i] = acc.lp;
+                sh->dec[k] = acc.yes ? 1 : 0;
+                last_dl = a.draft_lse ? a.draft_lse[i] : 0.0f;
             }
+            if (writer) {
+                if (a.target_lse) a.target_lse[it] = (float)lse;
+                if (a.target_top1) a.target_top1[it] = top1;
+            }
+            last_k = k; last_M = r.M; last_top1 = top1; last_lse = lse;
+            if (f) atomicOr(&sh->flags, f);
         }
-        __syncthreads();
-    } else {
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t f = *sh_flags;
-            int m = 0;
-            if (!(f & kFatal))
-                while (m < n && sh_dec[m] != 0) ++m;
-            sh_bcast[0] = m;
-            sh_bcast[1] = (f & kFatal) ? 1 : 0;
-            sh_bcast[2] = (int32_t)f;
-        }
-        __syncthreads();
-        // maximum and argmax of row m: from the thread that merged it, if it still holds them
-        if (last_k == sh_bcast[0]) { sh_bcast[4] = 1; sh_bcast[5] = __float_as_int(last_M); sh_bcast[6] = last_top1; sh_bcast[7] = __float_as_int(last_dl); *sh_lse = last_lse; }
-        __syncthreads();
     }
-    HEAD_STAMP(3);                                               // first rejection published
-    const int m = sh_bcast[0];                   // a flagged sequence has m = 0 and emits the argmax of row 0
-    const bool flagged = sh_bcast[1] != 0;
-    const uint32_t f = (uint32_t)sh_bcast[2];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t f = sh->flags;
+        int m = 0;
+        if (!(f & kFatal))
+            while (m < n && sh->dec[m] != 0) ++m;
+        sh->bcast[0] = m;
+    }
+    __syncthreads();
+    const int m = sh->bcast[0];                  // a flagged sequence has m = 0 and emits the argmax of row 0
+    const uint32_t f = sh->flags;
+    const bool flagged = (f & kFatal) != 0;
+    // maximum and argmax of row m: from the thread that merged it, if it still holds them
+    if (last_k == m) { sh->bcast[4] = 1; sh->bcast[5] = __float_as_int(last_M); sh->bcast[6] = last_top1; sh->bcast[7] = __float_as_int(last_dl); sh->lse = last_lse; }
+    __syncthreads();
     float Mm, dl_m = 0.0f; int32_t top1m; double lse_m;
-    if (__builtin_expect(sh_bcast[4] != 0, 1)) {
-        Mm = __int_as_float(sh_bcast[5]); top1m = sh_bcast[6]; dl_m = __int_as_float(sh_bcast[7]); lse_m = *sh_lse;
+    if (sh->bcast[4] != 0) {
+        Mm = __int_as_float(sh->bcast[5]); top1m = sh->bcast[6]; dl_m = __int_as_float(sh->bcast[7]); lse_m = sh->lse;
     } else {                                     // more rows than threads: merge row m once more
         __syncthreads();
-        if constexpr (SHARDED) stage_commit(sh_part, stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1) + m, a.nsplit, a.nsplit), a.nsplit);
-        else stage_partials(sh_part, a.part + ((int64_t)b * (K + 1) + m) * a.nsplit, a.nsplit);
-        RowTotal r = merge_partials<SHARDED>(sh_part, a.nsplit);
+        stage_commit(sh->part, stage(m, a.nsplit), a.nsplit);
+        const RowTotal r = merge_partials<SHARDED>(sh->part, a.nsplit);
         Mm = r.M;
         lse_m = (r.R + log2_pos(r.S)) * kLn2;
         if constexpr (SHARDED) top1m = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;
         else top1m = need_top1 ? resolve_argmax(row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, m), a.t_dtype, a.V, r.cand, r.M) : 0;
         if (m < n && a.draft_lse) dl_m = a.draft_lse[(int64_t)b * K + m];
     }
-    if (!flagged && !greedy) {
-        job.kind = m < n ? 1 : 2;
-        job.row = m;
-        job.ref_p = Mm;                          // exponent references: the target row's maximum, the draft row's lse
-        job.ref_q = (m < n && (a.draft_lse || own_q)) ? dl_m : 0.0f;
-        // binary32-grade estimate of S_p / S_q in these references (S_q = sum exp(d - lse_q) = 1): lets the
-        // slice pass form the residual before the exact normalisers exist
-        job.lam = exp_fast_d(lse_m - (double)Mm, shT);
-    }
-    if (writer) {
-        const int32_t final_tok = (flagged || greedy) ? top1m : -1;   // sampled sequences: written by pass 3
-        if (threadIdx.x == 0) {
-            a.accept_len[b] = m;
-            a.n_out[b] = m + 1;
-            if constexpr (!SHARDED) {
-                a.jobs[b].job = job;
-                // the slice kernel appends to the sequence's band list; fused into that kernel, this workgroup
-                // cannot empty the list under the others' appends: the target pass has done it
-                if (!a.fused_head) a.jobs[b].band_cnt = 0;
-                a.flags_ws[b] = f;
-            } else if (a.final_jobs) {
-                a.final_jobs[b] = job;
-            }
-            if (a.flags) a.flags[b] = f;
-        }
-        int32_t *o = a.out_tok + (int64_t)b * (K + 1);
-        for (int k = threadIdx.x; k <= K; k += kVBlock) {
-            // (lane-merge path: thread k still holds row k's token from the first round trip)
-            o[k] = k < m ? ((msh >= 0 && k == (int)threadIdx.x) ? tok0 : a.draft_tok[(int64_t)b * K + k]) : (k == m ? final_tok : -1);
-            if (flagged && a.logp_tok && k < n) a.logp_tok[(int64_t)b * K + k] = NAN;
-        }
-    }
+    const SampleJob job = head_job(!flagged && !greedy, m, n, Mm, lse_m, dl_m, a.draft_lse != nullptr, shT);
+    if (writer) head_outputs<SHARDED>(a, b, job, m, n, flagged, greedy, f, top1m, [&](int k) { return a.draft_tok[(int64_t)b * K + k]; });
+    __syncthreads();                             // every thread is done with `sh`
+    request_table();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     return job;
+}
+
+template <bool SHARDED, class Table = NoTable>
+__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer, HeadStaged *stg, HeadLanes *lanes, double *shT, Table request_table = Table())
+{
+    int msh = lane_merge_shift(a.K + 1, a.nsplit);
+    if (__builtin_expect(msh < 0, 0)) return verify_head_staged<SHARDED>(a, b, writer, stg, shT, request_table);
+    if (!SHARDED && (a.vflags & kVerifyOwnQ)) msh = max(msh, lane_merge_shift(a.K, a.d_nsplit));        // both tensors' slices on the same lanes
+    return verify_head_lanes<SHARDED>(a, b, writer, lanes, shT, request_table, msh);
 }
 
 struct Rows {
@@ -581,15 +561,11 @@ template <bool SHARDED>
 __global__ __launch_bounds__(kVBlock) void verify_head_kernel(VerifyArgs a)
 {
     warm_args(a);
-    __shared__ Partial sh_part[kStageCap];
-    __shared__ uint8_t sh_dec[kScanCap];
-    __shared__ uint32_t sh_flags;
-    __shared__ int32_t sh_bcast[8];
-    __shared__ double sh_lse;
-    __shared__ DraftRowLse sh_qrows[SHARDED ? 1 : kWave];
+    __shared__ HeadStaged stg;
+    __shared__ HeadLanes lanes;
     __shared__ double shT[256];
     static_assert(kVBlock == 256, "one table entry per thread");
-    verify_head<SHARDED>(a, blockIdx.x, true, sh_part, sh_dec, &sh_flags, sh_bcast, &sh_lse, sh_qrows, shT);
+    verify_head<SHARDED>(a, blockIdx.x, true, &stg, &lanes, shT);
 }
 
 // ---- slice kernel -----------------------------------------------------------------------
@@ -737,6 +713,23 @@ __device__ inline double chunk_one_tab(const u32x4 &wt, const double *shE)
     return cA;
 }
 
+// N 16-byte vectors from memory to LDS, without passing through registers, by a 256-thread workgroup.  The copy is complete
+// when every wavefront has waited for its loads (vmcnt) and a barrier has been passed.
+template <int N>
+__device__ inline void copy_to_lds(const void *src, void *dst)
+{
+    typedef const __attribute__((address_space(1))) void *Global;
+    typedef __attribute__((address_space(3))) void *Lds;
+    constexpr int kRounds = N / kVBlock;
+    static_assert(N % kVBlock == 0, "whole rounds of the workgroup");
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+        const int first = (q * (kVBlock / kWave) + wave) * kWave;              // the wavefront's 64 vectors: lane l's goes to first + l
+        __builtin_amdgcn_global_load_lds((Global)((const char *)src + (int64_t)(first + lane) * 16), (Lds)((char *)dst + first * 16), 16, 0, 0);
+    }
+}
+
 // One wavefront per slice, four slices per workgroup.  A wavefront takes its slice in chunks of one 8-element run per
 // lane; its five sums need no LDS and no barrier.  The requests run ahead of the arithmetic (see kAhead): with one
 // chunk ahead the launch was bound by memory latency.  Four wavefronts per SIMD: the bfloat16 table limits a CU to
@@ -749,12 +742,13 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     // inside the loop (V = 256000, 512 sequences, binary32 target rows: 210 us against 139 us all computed; at three
     // wavefronts per SIMD, 154 registers and no spills, 147 us).
     constexpr bool kTabT = TD == TAPOUT_BF16 && DD == TAPOUT_BF16, kTabD = kTabT;
-    // LDS: the accept decisions' buffers (FUSED) are dead once the job is known; the table takes their place
-    constexpr size_t kHeadBytes = sizeof(Partial) * kStageCap + sizeof(DraftRowLse) * kWave + 8 + 32 + 8 + kScanCap;
-    constexpr size_t kTabBytes = (kTabT || kTabD) ? sizeof(double) * kTabDoubles : 0;
-    constexpr size_t kRaw = (FUSED && kHeadBytes > kTabBytes) ? kHeadBytes : (kTabBytes > 0 ? kTabBytes : 16);
+    // LDS: the table lies over the staged accept decisions' buffers (FUSED), which are dead once the job is known
+    constexpr size_t kTabBytes = kTabT ? sizeof(double) * kTabDoubles : 16;
+    constexpr size_t kRaw = (FUSED && sizeof(HeadStaged) > kTabBytes) ? sizeof(HeadStaged) : kTabBytes;
     __shared__ double shT[256];
     __shared__ __align__(16) unsigned char sh_raw[kRaw];
+    __shared__ HeadLanes sh_lanes[1];
+    static_assert(sizeof shT + sizeof sh_raw + sizeof sh_lanes <= 32 * 1280, "four workgroups' LDS per compute unit");
     warm_args(a);
     [[maybe_unused]] const int wg = WG_LINEAR();
     WG_STAMP(g_stamps_slices, 8, wg, 0);                         // entry
@@ -764,38 +758,25 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     // takes the group's last slice: most often none at all, or the row's short last one
     const bool writer = FUSED && (int)blockIdx.x == (a.nsl + kWavesPerWG - 1) / kWavesPerWG - 1;
     const int s = blockIdx.x * kWavesPerWG + (writer ? kWavesPerWG - 1 - wave : wave);
-    // The tables are requested early: nothing of them depends on the job, and a wavefront's loads return in order, so
-    // requested after the rows they would hold the barrier below until the whole slice has arrived.  When the accept
-    // decisions run in this kernel they fill the small table themselves and the large one is requested right behind
-    // their own first requests; else both are requested here.
+    // The table goes from memory to LDS directly, no registers in between, while the accept decisions are taken (FUSED) or the
+    // job's record travels.  (Through registers it held 36 of them over the decisions: spills, and the wait for the table
+    // in front of the decisions; 20.5 us where this takes 15.9.)
     static_assert(kVBlock == 256, "one entry of the small table per thread");
-    constexpr int kRounds = (kTabT || kTabD) ? kTabVecs / kVBlock : 1;
-    u32x4 tw[kRounds];
-    double tv = 0.0;
-    if constexpr (!FUSED) tv = a.exp_table[threadIdx.x];
     auto request_table = [&]() {
-        if constexpr (kTabT || kTabD) {
-            const u32x4 *src = (const u32x4 *)(a.exp_table + 256);
-#pragma unroll
-            for (int q = 0; q < kRounds; ++q) tw[q] = src[q * kVBlock + threadIdx.x];
-        }
+        if constexpr (kTabT) copy_to_lds<kTabVecs>(a.exp_table + 256, sh_raw);
     };
-    if constexpr (!FUSED) request_table();
     SampleJob job;
     if constexpr (FUSED) {
         // Small batches: a head launch of its own costs more (launch, hand-over of the job record through
         // memory) than taking the accept decisions again in each of the sequence's workgroups.  All of them run
         // the same code on the same inputs and reach the same job; one of them writes the sequence's outputs.
-        unsigned char *q = sh_raw;
-        Partial *sh_part = (Partial *)q;            q += sizeof(Partial) * kStageCap;
-        DraftRowLse *sh_qrows = (DraftRowLse *)q;   q += sizeof(DraftRowLse) * kWave;
-        double *sh_lse = (double *)q;               q += 8;
-        int32_t *sh_bcast = (int32_t *)q;           q += 32;
-        uint32_t *sh_flags = (uint32_t *)q;         q += 8;
-        uint8_t *sh_dec = q;
-        job = verify_head<false>(a, b, writer, sh_part, sh_dec, sh_flags, sh_bcast, sh_lse, sh_qrows, shT, request_table);
+        job = verify_head<false>(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table);
     } else {
+        const double tv = a.exp_table[threadIdx.x];
         job = a.final_jobs ? a.final_jobs[b] : a.jobs[b].job;      // vocabulary shards: the caller's copy
+        request_table();
+        shT[threadIdx.x] = tv;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // before the rows are requested: nothing younger to wait for
     }
     WG_STAMP(g_stamps_slices, 8, wg, 1);                         // job known
     if (job.kind == 0) return;
@@ -811,15 +792,6 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     const bool tab_ok = (kTabT || kTabD) && !(a.vflags & kVerifyNoExpTable) && tab_job_ok(job);
     const bool tab_t = kTabT && tab_ok, tab_d = kTabD && tab_ok && resid;
     const double *shE = (const double *)sh_raw;
-    // the tables into LDS before the rows are requested: the wait for them then has nothing younger behind it
-    if constexpr (!FUSED) shT[threadIdx.x] = tv;
-    if constexpr (kTabT || kTabD) {
-        if constexpr (FUSED) __syncthreads();                    // every thread is done with the accept decisions' LDS
-        if (tab_t || tab_d) {
-#pragma unroll
-            for (int q = 0; q < kRounds; ++q) ((u32x4 *)sh_raw)[q * kVBlock + threadIdx.x] = tw[q];
-        }
-    }
     Raw8<TD> qt[kChunks];
     Raw8<DD> qd[kChunks];
     // A slice that lies wholly inside the rows (all but a row's last one) is requested in straight-line code:
@@ -855,7 +827,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
             }
         }
     }
-    __syncthreads();
+    if constexpr (!FUSED) __syncthreads();                       // (FUSED: the decisions' last barrier has published the tables)
     WG_STAMP(g_stamps_slices, 8, wg, 2);                         // tables in LDS, rows requested
     if (!live) return;
     ExpRef rp, rq;
