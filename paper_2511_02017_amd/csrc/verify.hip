@@ -991,9 +991,8 @@ __device__ inline void thread_weights(const Weights &w, const Rows &r, int s, in
 
 struct LocateShared {
     double scan[2][4];      // alternating buffers of block_excl_scan_d
-    double bc[4];           // broadcasts
     int hits[2][4];         // alternating per-wavefront results of locate_in_slice
-    int last, slice;
+    int last;
     int band_key[kBandCap];     // band elements of the sequence, sorted by index ...
     double band_val[kBandCap];  // ... and their residual weights with the exact L
 };
@@ -1046,53 +1045,53 @@ __device__ inline int locate_in_slice(const Weights &w, const Rows &r, int s, in
     return h == 0x7fffffff ? -1 : h;
 }
 
-// Token of a draw: the first element whose running sum over the row exceeds `target`; whole workgroup.  z_mine: the weight
-// of slice threadIdx.x (rows of at most kVBlock slices; others call slice_weight, one thread).
-template <int TD, int DD, class SliceWeight>
-__device__ inline int find_token(const Weights &w, const Rows &r, int V, int nsl, const double *T, double target, double z_mine,
-                                 SliceWeight slice_weight, LocateShared *sh, int &phase)
+// A row's slices over the lanes of a wavefront: lane l has slices [l n, (l + 1) n), n = slices_per_lane.  Every wavefront of a
+// workgroup does this for itself, on the same numbers: no LDS and no barrier before the slice is known.
+__device__ inline int slices_per_lane(int nsl) { return (nsl + kWave - 1) / kWave; }
+
+// The first slice whose inclusive prefix of weights exceeds `target`, and the prefix ahead of it; -1: none.
+// weight(s, q): of slice s, the q-th of the lane's.
+template <class Weight>
+__device__ __forceinline__ int find_slice(int nsl, double target, Weight weight, double *ahead)
 {
-    const int tid = threadIdx.x;
-    // slice whose inclusive prefix (slice order) first exceeds the target
-    double cum_at = 0.0;
-    int s_found = -1;
-    if (__builtin_expect(nsl <= kVBlock, 1)) {
-        if (tid >= nsl) z_mine = 0.0;
-        double ztot;
-        const double excl = block_excl_scan_d(z_mine, sh->scan[phase++ & 1], &ztot);
-        const int cand = wave_min_i32((tid < nsl && excl + z_mine > target) ? tid : 0x7fffffff);
-        if ((tid & (kWave - 1)) == 0) sh->hits[phase & 1][tid / kWave] = cand;
-        __syncthreads();
-        const int *hh = sh->hits[phase & 1];
-        const int sf = min(min(hh[0], hh[1]), min(hh[2], hh[3]));
-        ++phase;
-        s_found = sf == 0x7fffffff ? -1 : sf;
-        if (tid == s_found) sh->bc[0] = excl;
-        __syncthreads();
-        if (s_found >= 0) cum_at = sh->bc[0];
-    } else {
-        // very large vocabularies: the first thread walks the slice weights
-        if (tid == 0) {
-            double c = 0.0; int sf = -1;
-            for (int s = 0; s < nsl; ++s) { const double v = slice_weight(s); if (c + v > target) { sf = s; break; } c += v; }
-            sh->bc[0] = c; sh->slice = sf;
+    const int n = slices_per_lane(nsl), first = (int)(threadIdx.x & (kWave - 1)) * n;
+    double z = 0.0;
+    for (int q = 0; q < n; ++q)
+        if (first + q < nsl) z += weight(first + q, q);
+    double total;
+    const double incl = wave_incl_scan_d(z, &total);
+    const uint64_t past = __builtin_amdgcn_ballot_w64(incl > target);
+    if (!past) { *ahead = 0.0; return -1; }
+    const int l = __builtin_ctzll(past);
+    // that lane's slices one by one (added in another order than the scan's: if none crosses, the next lane's first one)
+    double c = incl - z;
+    int found = first + n;
+    for (int q = 0; q < n; ++q)
+        if (found == first + n && first + q < nsl) {
+            const double w = weight(first + q, q);
+            if (c + w > target) found = first + q; else c += w;
         }
-        __syncthreads();
-        cum_at = sh->bc[0]; s_found = sh->slice;
-        __syncthreads();
-    }
+    found = __builtin_amdgcn_readlane(found, l);
+    *ahead = lane_d(c, l);
+    return found < nsl ? found : -1;
+}
+
+// Token of a draw: the first element whose running sum over the row exceeds `target`; whole workgroup (weight as find_slice).
+template <int TD, int DD, class Weight>
+__device__ __forceinline__ int find_token(const Weights &w, const Rows &r, int V, int nsl, const double *T, double target, Weight weight, LocateShared *sh, int &phase)
+{
+    double cum;
+    const int s_found = find_slice(nsl, target, weight, &cum);
     LOCATE_STAMP(3);                                             // slice found
     // slice sums and the in-slice scan round differently: if the crossing is not inside the chosen
     // slice, continue into the following ones
     int token = -1;
-    if (s_found >= 0) {
-        double cum = cum_at;
+    if (s_found >= 0)
         for (int s = s_found; s < nsl && token < 0; ++s) {
             double slice_total;
             token = locate_in_slice<TD, DD>(w, r, s, V, T, cum, target, sh, phase++, &slice_total);
             cum += slice_total;
         }
-    }
     if (__builtin_expect(token < 0, 0)) {
         // rounding left no crossing: the largest index with positive weight
         for (int s = 0; s < nsl; ++s) {
@@ -1177,7 +1176,6 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
             return;
         }
     __shared__ double shT[256];
-    __shared__ double sh_red[kSliceVals][kVBlock / kWave];
     __shared__ LocateShared shl;
     const int b = FIN ? blockIdx.x - a.B : blockIdx.x;
     const int tid = threadIdx.x;
@@ -1185,39 +1183,35 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     const double *ps = a.part1 + (int64_t)b * a.nsl * kSliceVals;
     double *zs = a.part2 + (int64_t)b * a.nsl;                       // exact slice weights (slow path only)
     // First all loads that do not depend on each other, then their uses: written so that no wait separates the
-    // requests (the first slice of each thread without a loop; 256 threads fetch the 256 table entries).
+    // requests (the first two slices of each lane without a loop; 256 threads fetch the 256 table entries).
     static_assert(kVBlock == 256, "one table entry per thread");
-    double acc[kSliceVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    const bool has_first = tid < a.nsl;
-    const double *pf = ps + (has_first ? tid : 0) * kSliceVals;
-    const double f0 = pf[0], f1 = pf[1], f2 = pf[2], f3 = pf[3], f4 = pf[4];     // slot 0 always exists: harmless when unused
+    const int lane = tid & (kWave - 1), npl = slices_per_lane(a.nsl), s0 = lane * npl;
+    const double *p0 = ps + (int64_t)min(s0, a.nsl - 1) * kSliceVals, *p1 = ps + (int64_t)min(s0 + 1, a.nsl - 1) * kSliceVals;
+    double f[2][kSliceVals];
+#pragma unroll
+    for (int q = 0; q < kSliceVals; ++q) f[0][q] = p0[q];
     const double tv = a.exp_table[tid];
     const float u32v = a.u_sample[b];
     const int band_n = a.jobs[b].band_cnt;
     const int band_i = a.jobs[b].band_idx[tid & (kBandCap - 1)];                                  // stale beyond band_n: unused
     const SampleJob job = a.jobs[b].job;
+#pragma unroll
+    for (int q = 0; q < kSliceVals; ++q) f[1][q] = npl > 1 ? p1[q] : 0.0;
     // the compiler would otherwise sink these loads below the early exit and pay a second round trip for them
-    asm volatile("" :: "v"(f0), "v"(f1), "v"(f2), "v"(f3), "v"(f4), "v"(tv), "v"(u32v), "v"(band_n), "v"(band_i));
+    asm volatile("" :: "v"(f[0][0]), "v"(f[0][1]), "v"(f[0][2]), "v"(f[0][3]), "v"(f[0][4]), "v"(tv), "v"(u32v), "v"(band_n), "v"(band_i));
     shT[tid] = tv;
+    if (tid == 0) shl.last = -1;
     if (__builtin_expect(job.kind == 0, 0)) return;                  // the slice sums of such a sequence are stale: unused
-    if (has_first) { acc[0] = f0; acc[1] = f1; acc[2] = f2; acc[3] = f3; acc[4] = f4; }
-    for (int s = tid + kVBlock; s < a.nsl; s += kVBlock)              // vocabularies beyond 256 slices
-#pragma unroll
-        for (int q = 0; q < kSliceVals; ++q) acc[q] += ps[s * kSliceVals + q];
-    if (tid == 0) { shl.last = -1; shl.slice = 0x7fffffff; }
-
+    __syncthreads();                                                   // publishes the table and the inits
     LOCATE_STAMP(1);                                             // first requests answered
-    // totals of the five slice quantities, fixed order
+    // totals of the five slice quantities, every wavefront for itself, fixed order
     double tot[kSliceVals];
-    {
 #pragma unroll
-        for (int q = 0; q < kSliceVals; ++q) acc[q] = wave_sum_d(acc[q]);
-        if ((tid & (kWave - 1)) == 0)
-#pragma unroll
-            for (int q = 0; q < kSliceVals; ++q) sh_red[q][tid / kWave] = acc[q];
-        __syncthreads();                                               // also publishes the table and the inits
-#pragma unroll
-        for (int q = 0; q < kSliceVals; ++q) tot[q] = (sh_red[q][0] + sh_red[q][1]) + (sh_red[q][2] + sh_red[q][3]);
+    for (int q = 0; q < kSliceVals; ++q) {
+        double acc = s0 < a.nsl ? f[0][q] : 0.0;
+        if (npl > 1) acc += s0 + 1 < a.nsl ? f[1][q] : 0.0;
+        for (int k = 2; k < npl; ++k) acc += s0 + k < a.nsl ? ps[(int64_t)(s0 + k) * kSliceVals + q] : 0.0;      // vocabularies beyond 128 slices
+        tot[q] = lanes_sum(acc, 0, 6);
     }
     const double Sp = tot[0], Sq = tot[1];
     Weights w;
@@ -1279,33 +1273,21 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
             __syncthreads();
         }
     }
-    auto slice_weight = [&](int s) -> double {
+    const double z0 = w.kind == 2 ? f[0][0] : f[0][2] - delta * f[0][3], z1 = w.kind == 2 ? f[1][0] : f[1][2] - delta * f[1][3];
+    auto slice_weight = [&](int s, int q) -> double {
         if (exact_sums) return zs[s];
-        if (w.kind == 2) return ps[s * kSliceVals + 0];
-        double v = ps[s * kSliceVals + 2] - delta * ps[s * kSliceVals + 3];
+        const double *at = ps + (int64_t)s * kSliceVals;
+        double v = q == 0 ? z0 : (q == 1 ? z1 : (w.kind == 2 ? at[0] : at[2] - delta * at[3]));
+        if (w.kind == 2) return v;
         v = v > 0.0 ? v : 0.0;
-        for (int q = 0; q < n_band; ++q)
-            if (shl.band_key[q] / kSampleSlice == s) v += shl.band_val[q];
+        for (int k = 0; k < n_band; ++k)
+            if (shl.band_key[k] / kSampleSlice == s) v += shl.band_val[k];
         return v;
     };
 
     LOCATE_STAMP(2);                                             // total weight known (certified, settled or recomputed)
     int token = -1;
-    if (Z > 0.0) {
-        // this thread's slice is the one whose sums it fetched with the first round trip: no second look at memory
-        double z_mine = 0.0;
-        if (tid < a.nsl && a.nsl <= kVBlock) {
-            if (exact_sums) z_mine = zs[tid];
-            else if (w.kind == 2) z_mine = f0;
-            else {
-                z_mine = f2 - delta * f3;
-                z_mine = z_mine > 0.0 ? z_mine : 0.0;
-                for (int q = 0; q < n_band; ++q)
-                    if (shl.band_key[q] / kSampleSlice == tid) z_mine += shl.band_val[q];
-            }
-        }
-        token = find_token<TD, DD>(w, r, a.V, a.nsl, shT, u * Z, z_mine, slice_weight, &shl, phase);
-    }
+    if (Z > 0.0) token = find_token<TD, DD>(w, r, a.V, a.nsl, shT, u * Z, slice_weight, &shl, phase);
     LOCATE_STAMP(4);                                             // token found
     if (tid == 0) {
         if (token < 0) token = 0;
@@ -1486,19 +1468,20 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
 {
     warm_args(a);
     __shared__ double shT[256];
-    __shared__ double sh_red[kVBlock / kWave];
     __shared__ LocateShared shl;
     const int row = blockIdx.x, b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
     const double *ps = a.sums + (int64_t)row * a.nsl;
     // everything is requested before anything is looked at: one round trip
-    const double f0 = ps[min(tid, a.nsl - 1)];
+    const int npl = slices_per_lane(a.nsl), s0 = (tid & (kWave - 1)) * npl;
+    const double f0 = ps[min(s0, a.nsl - 1)], f1 = ps[min(s0 + 1, a.nsl - 1)];
     const double tv = a.exp_table[tid];
     const float u32v = a.u[row];
     const RowRefRegs rr = row_ref_issue(a.part + (int64_t)row * a.nsplit, a.nsplit);
     const int kl = a.k_len ? a.k_len[b] : a.K;
     const double lse = a.lse[row];
-    asm volatile("" :: "v"(f0), "v"(tv), "v"(u32v), "v"(rr.v1), "v"(rr.S), "v"(lse));
+    asm volatile("" :: "v"(f0), "v"(f1), "v"(tv), "v"(u32v), "v"(rr.v1), "v"(rr.S), "v"(lse));
     shT[tid] = tv;
+    if (tid == 0) shl.last = -1;
     if (k >= kl) return;
     bool bad;
     const float M = row_ref_finish(rr, a.part + (int64_t)row * a.nsplit, a.nsplit, &bad);
@@ -1506,23 +1489,19 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
         if (tid == 0) { a.tok[row] = -1; if (a.logq_tok) a.logq_tok[row] = NAN; }
         return;
     }
-    double acc = tid < a.nsl ? f0 : 0.0;
-    for (int s = tid + kVBlock; s < a.nsl; s += kVBlock) acc += ps[s];   // vocabularies beyond 256 slices
-    acc = wave_sum_d(acc);
-    if ((tid & (kWave - 1)) == 0) sh_red[tid / kWave] = acc;
-    if (tid == 0) { shl.last = -1; shl.slice = 0x7fffffff; }
-    __syncthreads();                                                     // also publishes the table
-    const double Z = (sh_red[0] + sh_red[1]) + (sh_red[2] + sh_red[3]);
+    __syncthreads();                                                     // publishes the table
+    double z = s0 < a.nsl ? f0 : 0.0;
+    if (npl > 1) z += s0 + 1 < a.nsl ? f1 : 0.0;
+    for (int q = 2; q < npl; ++q) z += s0 + q < a.nsl ? ps[s0 + q] : 0.0;
+    const double Z = lanes_sum(z, 0, 6);
     Weights w;
     w.kind = 2; w.lam = 0.0;
     w.rp.set((double)M); w.rq.set(0.0);
     Rows r;
     r.trow = r.drow = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, b, k);
     int phase = 0, token = -1;
-    if (Z > 0.0) {
-        const double target = (double)u32v * Z;
-        token = find_token<DT, DT>(w, r, a.V, a.nsl, shT, target, f0, [&](int s) { return ps[s]; }, &shl, phase);
-    }
+    if (Z > 0.0)
+        token = find_token<DT, DT>(w, r, a.V, a.nsl, shT, (double)u32v * Z, [&](int s, int q) { return q == 0 ? f0 : (q == 1 ? f1 : ps[s]); }, &shl, phase);
     if (tid == 0) {
         if (token < 0) token = 0;
         a.tok[row] = token;
@@ -1560,13 +1539,13 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
     const VerifyArgs &v = a.v;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
     // everything that does not depend on the job is requested first (one round trip): the sums of the shards (lane h of
-    // every wavefront takes shards h, h + 64, ...), the slice sums of thread tid's slice, the table
+    // every wavefront takes shards h, h + 64, ...), the slice sums of the lane's first slice, the table
     double mine[kSliceVals], tot[kSliceVals];
     const double *sa = a.sums_all + ((int64_t)min(lane, a.G - 1) * v.B + b) * kSliceVals;
 #pragma unroll
     for (int q = 0; q < kSliceVals; ++q) mine[q] = sa[q];
     const double *ps = v.part1 + (int64_t)b * v.nsl * kSliceVals;
-    const double *pf = ps + (tid < v.nsl ? tid : 0) * kSliceVals;
+    const double *pf = ps + (int64_t)min(lane * slices_per_lane(v.nsl), v.nsl - 1) * kSliceVals;
     const double f0 = pf[0], f2 = pf[2], f3 = pf[3];
     const double tv = v.exp_table[tid];
     const float u32v = v.u_sample[b];
@@ -1575,7 +1554,7 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
     if (tid == 0) { a.tok_out[b] = -1; a.need_exact[b] = 0; a.exact_mass[b] = NAN; }
     if (job.kind == 0) return;
     shT[tid] = tv;
-    if (tid == 0) { shl.last = -1; shl.slice = 0x7fffffff; }
+    if (tid == 0) shl.last = -1;
     __syncthreads();
     // totals over all shards, in one fixed order on every shard
 #pragma unroll
@@ -1650,15 +1629,14 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
     const bool fallback = owner < 0;
     if (fallback) owner = last_pos;
     if (owner != a.g) return;
-    auto slice_weight = [&](int s) -> double {
-        if (w.kind == 2) return ps[s * kSliceVals + 0];
+    auto slice_weight = [&](int s, int q) -> double {
+        const double *at = ps + (int64_t)s * kSliceVals;
+        if (w.kind == 2) return q == 0 ? f0 : at[0];
         if (exact) return zs[s];
-        const double x = ps[s * kSliceVals + 2] - delta * ps[s * kSliceVals + 3];
-        return x > 0.0 ? x : 0.0;
+        return q == 0 ? fmax(f2 - delta * f3, 0.0) : fmax(at[2] - delta * at[3], 0.0);
     };
     // (a fallback's target lies beyond every slice: find_token then takes the last positive weight here)
-    const double z_mine = w.kind == 2 ? f0 : (exact ? (tid < v.nsl ? zs[tid] : 0.0) : fmax(f2 - delta * f3, 0.0));
-    const int token = find_token<TD, DD>(w, r, v.V, v.nsl, shT, fallback ? INFINITY : target - mine_prefix, z_mine, slice_weight, &shl, phase);
+    const int token = find_token<TD, DD>(w, r, v.V, v.nsl, shT, fallback ? INFINITY : target - mine_prefix, slice_weight, &shl, phase);
     if (tid == 0) a.tok_out[b] = a.vocab_offset + (token < 0 ? 0 : token);
 }
 

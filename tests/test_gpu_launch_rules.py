@@ -104,6 +104,20 @@ def test_final_token_on_rows_at_every_alignment(V, dt, tt, fuse):
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("V", [131072, 131073, 262144, 262145])
+@pytest.mark.parametrize("dt,tt", [(bf16, bf16), (f32, bf16)])
+def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
+    """64 and 128 slices fill one and two per lane; one element more makes it two and three, with most lanes' last one empty."""
+    B, K = 5, 2
+    rnd = mixed_round(B, K, V, dt, tt, seed=V)
+    rnd["target"][1, :, :-3] = float("-inf")                    # everything in the last slices: no weight before them
+    rnd["draft"][2] = rnd["target"][2, :K].to(dt)               # equal distributions
+    tp = binding.Tapout(B, K, V)
+    for u in (2.0 ** -12, 0.5, 1.0 - 2.0 ** -24):
+        rnd["u_sample"] = torch.full((B,), u, device=DEV)
+        assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
+
+
 @pytest.mark.parametrize("policy", [binding.TS_BETA, binding.UCB_TUNED])
 @pytest.mark.parametrize("shared", [False, True])
 @pytest.mark.parametrize("B,K,A", [(3, 2, 8), (5, 16, 1), (67, 17, 3), (2, 65, 5)])
