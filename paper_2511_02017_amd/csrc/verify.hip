@@ -713,20 +713,21 @@ __device__ inline double chunk_one_tab(const u32x4 &wt, const double *shE)
     return cA;
 }
 
-// N 16-byte vectors from memory to LDS, without passing through registers, by a 256-thread workgroup.  The copy is complete
-// when every wavefront has waited for its loads (vmcnt) and a barrier has been passed.
-template <int N>
+// N 16-byte vectors (a multiple of 64) from memory to LDS, without passing through registers, by a workgroup of kThreads.
+// The copy is complete when every wavefront has waited for its loads (vmcnt) and a barrier has been passed.
+template <int N, int kThreads>
 __device__ inline void copy_to_lds(const void *src, void *dst)
 {
     typedef const __attribute__((address_space(1))) void *Global;
     typedef __attribute__((address_space(3))) void *Lds;
-    constexpr int kRounds = N / kVBlock;
-    static_assert(N % kVBlock == 0, "whole rounds of the workgroup");
+    constexpr int kWaves = kThreads / kWave, kTurns = N / kWave;
+    static_assert(N % kWave == 0, "whole wavefronts");
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x & (kWave - 1);
 #pragma unroll
-    for (int q = 0; q < kRounds; ++q) {
-        const int first = (q * (kVBlock / kWave) + wave) * kWave;              // the wavefront's 64 vectors: lane l's goes to first + l
-        __builtin_amdgcn_global_load_lds((Global)((const char *)src + (int64_t)(first + lane) * 16), (Lds)((char *)dst + first * 16), 16, 0, 0);
+    for (int q = 0; q < (kTurns + kWaves - 1) / kWaves; ++q) {
+        const int turn = q * kWaves + wave, first = turn * kWave;              // the wavefront's 64 vectors: lane l's goes to first + l
+        if ((q + 1) * kWaves <= kTurns || turn < kTurns)
+            __builtin_amdgcn_global_load_lds((Global)((const char *)src + (int64_t)(first + lane) * 16), (Lds)((char *)dst + first * 16), 16, 0, 0);
     }
 }
 
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(4))) vo
     // in front of the decisions; 20.5 us where this takes 15.9.)
     static_assert(kVBlock == 256, "one entry of the small table per thread");
     auto request_table = [&]() {
-        if constexpr (kTabT) copy_to_lds<kTabVecs>(a.exp_table + 256, sh_raw);
+        if constexpr (kTabT) copy_to_lds<kTabVecs, kVBlock>(a.exp_table + 256, sh_raw);
     };
     SampleJob job;
     if constexpr (FUSED) {
@@ -1358,14 +1359,8 @@ __global__ __launch_bounds__(kSampleBlock) __attribute__((amdgpu_waves_per_eu(4)
         return;
     }
     const int lane = threadIdx.x & (kWave - 1);
-    const u32x4 *src = (const u32x4 *)(a.exp_table + 256);
-    constexpr int kRounds = kTab ? (kTabVecs + kSampleBlock - 1) / kSampleBlock : 1;
-    u32x4 tw[kRounds];
     const double tv = a.exp_table[threadIdx.x & 255];
-    if constexpr (kTab) {
-#pragma unroll
-        for (int q = 0; q < kRounds; ++q) tw[q] = src[min(q * kSampleBlock + (int)threadIdx.x, kTabVecs - 1)];
-    }
+    if constexpr (kTab) copy_to_lds<kTabVecs, kSampleBlock>(a.exp_table + 256, shE);
     struct Slice { int b, k, s; };
     const int first = __builtin_amdgcn_readfirstlane((int)((blockIdx.x - a.B) * (kSampleBlock / kWave) + threadIdx.x / kWave));
     Slice cur;
@@ -1404,11 +1399,7 @@ __global__ __launch_bounds__(kSampleBlock) __attribute__((amdgpu_waves_per_eu(4)
     Regs at{};
     if (on) at = request(cur);
     if (threadIdx.x < 256) shT[threadIdx.x] = tv;
-    if constexpr (kTab) {
-#pragma unroll
-        for (int q = 0; q < kRounds; ++q)
-            if (q * kSampleBlock + (int)threadIdx.x < kTabVecs) ((u32x4 *)shE)[q * kSampleBlock + threadIdx.x] = tw[q];
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
     __syncthreads();
     while (cur.b < a.B) {
         const Slice nxt = advance(cur);
@@ -1688,13 +1679,11 @@ static hipError_t launch_sample_typed(SampleArgs &a, const DraftFinalArgs &fin, 
 {
     if (pass == 0) {
         constexpr int per_wg = kSampleBlock / kWave;
-        // All wavefronts the same number of slices.  With few each, no more workgroups than are resident beside the epilogue's: one
-        // that waits for a place starts when the others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us,
-        // 252 of two slices per wavefront 10.0; with many each the places of the epilogue's are wanted back soon: K = 8,
-        // 448 workgroups of nine slices per wavefront 34.0 us, 504 of eight 33.3).
+        // All wavefronts the same number of slices, and no more workgroups than are resident beside the epilogue's: one that
+        // waits for a place starts when others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us, 252 of
+        // two slices per wavefront 10.0; K = 8: 504 of eight slices 37.8, 448 of nine 34.0).
         const int64_t slices = (int64_t)a.B * a.K * a.nsl;
-        int64_t places = (int64_t)per_wg * (a.B < kSampleWgs / 2 ? kSampleWgs - a.B : kSampleWgs / 2);
-        if (slices > 4 * places) places = (int64_t)per_wg * kSampleWgs;
+        const int64_t places = (int64_t)per_wg * (a.B < kSampleWgs / 2 ? kSampleWgs - a.B : kSampleWgs / 2);
         const int64_t rounds = (slices + places - 1) / places;
         const int wgs = (int)((slices + rounds * per_wg - 1) / (rounds * per_wg));
         a.n_waves = wgs * per_wg;
