@@ -963,11 +963,10 @@ __device__ inline double block_excl_scan_d(double v, double *sh4, double *total)
     return base + (inc - v);
 }
 
-// Weights of the kThreadPer consecutive elements this thread owns in slice s.
+// Weights of the kThreadPer consecutive elements from j0 on.
 template <int TD, int DD>
-__device__ inline void thread_weights(const Weights &w, const Rows &r, int s, int V, const double *T, double (&wv)[kThreadPer])
+__device__ inline void thread_weights(const Weights &w, const Rows &r, int j0, int V, const double *T, double (&wv)[kThreadPer])
 {
-    const int j0 = s * kSampleSlice + threadIdx.x * kThreadPer;
 #pragma unroll
     for (int g = 0; g < kThreadPer / kPer; ++g) {
         // both rows' requests side by side where the run lies inside the rows (the usual case): the checks of the
@@ -1031,7 +1030,7 @@ __device__ inline int locate_in_slice(const Weights &w, const Rows &r, int s, in
                                       bool track_last = false)
 {
     double wv[kThreadPer];
-    thread_weights<TD, DD>(w, r, s, V, T, wv);
+    thread_weights<TD, DD>(w, r, s * kSampleSlice + (int)threadIdx.x * kThreadPer, V, T, wv);
     double sum = 0.0;
 #pragma unroll
     for (int i = 0; i < kThreadPer; ++i) sum += wv[i];
@@ -1116,6 +1115,36 @@ __device__ __forceinline__ int find_token(const Weights &w, const Rows &r, int V
         token = sh->last;
     }
     return token;
+}
+
+// Exact weights of all slices of a row, zs[s], and their total; whole workgroup.  A wavefront per slice, no barrier until all
+// are done.  (By the whole workgroup, slice after slice with a scan each, every slice waited for its loads
+// and two barriers.  Rounds with a few such sequences: V = 256000, 512 sequences 1426.9 us, this 1417.6; V = 32000, 32 sequences
+// 35.6 / 34.0.)
+template <int TD, int DD>
+__device__ inline double slice_weights(const Weights &w, const Rows &r, int V, int nsl, const double *T, double *zs)
+{
+    constexpr int kWaves = kVBlock / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int s = threadIdx.x / kWave; s < nsl; s += kWaves) {
+        double sum = 0.0;
+#pragma unroll 2
+        for (int c = 0; c < kWaves; ++c) {
+            double wv[kThreadPer];
+            thread_weights<TD, DD>(w, r, s * kSampleSlice + (c * kWave + lane) * kThreadPer, V, T, wv);
+#pragma unroll
+            for (int i = 0; i < kThreadPer; ++i) sum += wv[i];
+        }
+        sum = wave_sum_d(sum);
+        if (lane == 0) zs[s] = sum;
+    }
+    __threadfence_block();
+    __syncthreads();
+    const int n = slices_per_lane(nsl);
+    double z = 0.0;
+    for (int q = 0; q < n; ++q)
+        if (lane * n + q < nsl) z += zs[lane * n + q];
+    return lanes_sum(z, 0, 6);
 }
 
 // Band elements of a sequence (see the slice kernel).  Each listed element is evaluated with the exact L; what it
@@ -1261,25 +1290,12 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
         if (__builtin_expect(!certified, 0)) {
             n_band = 0;
             // slow path: exact slice weights with the exact L (also the p == q case: then Z may vanish)
-            double ztot = 0.0;
-            for (int s = 0; s < a.nsl; ++s) {
-                double st;
-                locate_in_slice<TD, DD>(w, r, s, a.V, shT, 0.0, INFINITY, &shl, phase++, &st);
-                if (tid == 0) zs[s] = st;
-                ztot += st;
-            }
-            Z = ztot;
+            Z = slice_weights<TD, DD>(w, r, a.V, a.nsl, shT, zs);
             if (!(Z > 0.0)) {
                 // the residual vanished (p == q up to rounding): draw from the target row itself
                 w.kind = 2;
-                ztot = 0.0;
-                for (int s = 0; s < a.nsl; ++s) {
-                    double st;
-                    locate_in_slice<TD, DD>(w, r, s, a.V, shT, 0.0, INFINITY, &shl, phase++, &st);
-                    if (tid == 0) zs[s] = st;
-                    ztot += st;
-                }
-                Z = ztot;
+                __syncthreads();                                       // zs has been read
+                Z = slice_weights<TD, DD>(w, r, a.V, a.nsl, shT, zs);
             }
             exact_sums = true;
             if (tid == 0) shl.last = -1;

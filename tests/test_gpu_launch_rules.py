@@ -118,6 +118,33 @@ def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("V", [2047, 2048, 8193, 10240, 133001])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_exact_slice_weights_a_wavefront_per_slice(V, dt):
+    """p = q to 1e-5 for every token but four, which hold the residual: the list of undecided elements overflows and all slices
+    are weighed again, with fewer slices than wavefronts, one more than a multiple of them, and two or more per lane."""
+    B, K = 5, 2
+    g = torch.Generator().manual_seed(V)
+    d = (torch.randn(B, K, V, generator=g) * 0.5).to(dt)
+    tok = torch.randint(0, V, (B, K), generator=g, dtype=torch.int32)
+    hot = torch.stack([torch.tensor([0, V // 3, V // 2 + 1, V - 1])] * B)
+    for b in range(B):
+        tok[b][(tok[b][:, None] == hot[b][None, :]).any(1)] += 2
+        d[b, :, tok[b].long()] = -20.0                                    # q of the drafted tokens: below 1e-10
+    t = torch.cat([d.float(), torch.randn(B, 1, V, generator=g)], 1)
+    for b in range(B):
+        t[b, :K, tok[b].long()] = -23.0                                   # p / q = 1 / 20: rejected, u is nearly 1
+        t[b, :, hot[b]] += 1e-3                                           # L moves by less than 4e-3 e / V: inside the band of 1e-5
+    rnd = dict(draft=d.to(DEV), target=t.to(DEV), draft_tok=tok.to(DEV), u_accept=torch.full((B, K), 1.0 - 2.0 ** -24, device=DEV),
+               u_sample=torch.linspace(0.03, 0.97, B).to(DEV), k_len=torch.full((B,), K, dtype=torch.int32, device=DEV),
+               greedy=torch.zeros(B, dtype=torch.uint8, device=DEV))
+    tp = binding.Tapout(B, K, V)
+    c = pu.check_round(tp, rnd)
+    assert c["accept_flagged"] == 0 and c["icdf_flagged"] == 0
+    _, vf, _ = pu.gpu_round(tp, rnd)
+    assert (vf["accept_len"].cpu() == 0).all() and all(int(vf["out_tok"][b, 0]) in hot[b].tolist() for b in range(B))
+
+
 @pytest.mark.parametrize("policy", [binding.TS_BETA, binding.UCB_TUNED])
 @pytest.mark.parametrize("shared", [False, True])
 @pytest.mark.parametrize("B,K,A", [(3, 2, 8), (5, 16, 1), (67, 17, 3), (2, 65, 5)])
