@@ -103,10 +103,12 @@ __device__ inline double exp_fast(float x, double neg_ref_c, float lo, const dou
     return __hiloint2double(hi, __double2loint(e));
 }
 
-// exp(x) for a double argument (not NaN; clamped to [-700, 700]), same table and polynomial: relative error < 2e-13.
+// exp(x) for a double argument, same table and polynomial: relative error < 2e-13, underflowing like exp: to denormal numbers and,
+// below log(2^-1075) = -745.13, to 0 (arguments are clamped to [-746, 700], NaN to -746): a token of probability 0 has the
+// ratio 0, which a uniform of 0 is not below.  ([-700, ..] made that ratio 1e-304, and u = 0 accepted the token.)
 __device__ inline double exp_fast_d(double x, const double *T)
 {
-    const double t = fmin(fmax(x, -700.0), 700.0) * kExpC;
+    const double t = fmin(fmax(x, -746.0), 700.0) * kExpC;
     const double tm = t + kMagic;
     const int ni = __double2loint(tm);
     const double rs = t - (tm - kMagic);
@@ -247,8 +249,8 @@ __device__ inline Accept accept_row(const VerifyArgs &a, bool bad, double lse, b
         o.lp = (float)((double)xt - lse);
         if (greedy) o.yes = t == top1;
         else {
-            const double arg = (double)o.lp - (double)lq;
-            o.yes = arg == arg && (double)u < exp_fast_d(arg, shT);
+            // (NaN: the ratio is then 0, which no uniform is below)
+            o.yes = (double)u < exp_fast_d((double)o.lp - (double)lq, shT);
         }
     }
     return o;

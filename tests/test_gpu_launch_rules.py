@@ -237,3 +237,35 @@ def test_shard_records_from_any_number_of_slices(P):
     for key in pu.STAT_KEYS:
         pu.assert_stats_close(key, out[key].cpu().numpy(), ref[key], live)
     assert (out["top1_id"].cpu().numpy()[live] == ref["top1_id"][live]).all()
+
+
+@pytest.mark.parametrize("K", [5, 70])
+@pytest.mark.parametrize("dt", [f32, bf16])
+@pytest.mark.parametrize("fuse", [0, 1])
+def test_uniform_of_zero_accepts_no_token_of_probability_zero(K, dt, fuse):
+    """u_accept = 0 < p/q as the oracle has it, in double: never where p = 0 (masked target logit, or a ratio below half the
+    smallest double), always where the ratio is a number above that, however small.  K = 5 merges rows across lanes, 70 staged."""
+    B, V, at = 4, 3000, 3
+    rnd = mixed_round(B, K, V, dt, dt, seed=K)
+    rnd["target"][:, :at] = rnd["draft"][:, :at]
+    rnd["u_accept"][:] = 0.0
+    bidx, tok = torch.arange(B, device=DEV), rnd["draft_tok"][:, at].long()
+    rnd["target"][bidx, at, tok] = torch.tensor([float("-inf"), -720.0, -1000.0, -100.0], device=DEV).to(dt)    # p/q: 0, e^-720 or so, 0, e^-100
+    rnd["u_accept"][:, at + 1:] = 0.5                                # the next position is rejected by an ordinary ratio
+    rnd["target"][bidx, at + 1, rnd["draft_tok"][:, at + 1].long()] = -30.0
+    want = [at, at + 1, at, at + 1]
+    _, ref, _ = pu.oracle_round(rnd)
+    assert ref["accept_len"].tolist() == want
+    tp = binding.Tapout(B, K, V)
+    tp.set_option("fuse_head", fuse)
+    ds, vf, nd = pu.gpu_round(tp, rnd)
+    assert vf["accept_len"].cpu().tolist() == want
+    ds["logq_tok"][:, 1] = float("nan")                              # a ratio that is no number accepts nothing either
+    vf = tp.verify(rnd["target"], rnd["draft"], ds["lse"], ds["logq_tok"], rnd["draft_tok"], nd, rnd["u_accept"], rnd["u_sample"])
+    assert vf["accept_len"].cpu().tolist() == [1] * B
+    args, out = tp.round_args(rnd, torch.zeros(B, dtype=torch.int32, device=DEV), False)
+    tp.round(args)
+    assert out["verify"]["accept_len"].cpu().tolist() == want
+    for G in (2, 17):                                               # records merged across lanes, and one after the other
+        acc, _, _ = sharded_round(rnd, G, V)
+        assert acc.cpu().tolist() == want
