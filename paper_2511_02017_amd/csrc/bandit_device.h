@@ -197,6 +197,9 @@ __device__ inline void update_select_ucb_lanes(const BanditArgs &a, int b, int l
     const uint64_t unplayed = (__ballot(on && N == 0) >> ((threadIdx.x & (kWave - 1)) & ~7u)) & 0xffull;
     int best = on ? lane : 0x7fffffff;
     if (!on) v = -INFINITY;
+    // an index that is no number (UCB-Tuned on a restored state whose sums of squares allow no variance) is never larger than
+    // another, but stays where it is the first one's, as in the loop over the arms
+    if (v != v) v = lane == 0 ? INFINITY : -INFINITY;
 #pragma unroll
     for (int d = 1; d < TAPOUT_MAX_ARMS; d <<= 1) {
         const double ov = __shfl_xor(v, d);

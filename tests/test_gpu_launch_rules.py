@@ -269,3 +269,31 @@ def test_uniform_of_zero_accepts_no_token_of_probability_zero(K, dt, fuse):
     for G in (2, 17):                                               # records merged across lanes, and one after the other
         acc, _, _ = sharded_round(rnd, G, V)
         assert acc.cpu().tolist() == want
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_ucb_tuned_of_a_restored_state_without_a_variance(shared):
+    """A restored state may hold sums of squares that no rewards have (sum_r2 = 0 beside sum_r > 0): the bonus of such an arm is
+    the root of a negative number.  tapout_round chooses what the separate calls and the oracle choose: an index that is no
+    number is never larger, but stays if it is the first."""
+    g = torch.Generator().manual_seed(5)
+    for trial in range(24):
+        A = 3 + trial % 6
+        N = torch.randint(200, 3000, (1, A), generator=g).numpy().astype(np.int64)
+        S = np.round(N * (0.3 + 0.6 * torch.rand(1, A, generator=g).double().numpy()), 1)
+        Q = S * S / N
+        for a in range(A):
+            if torch.rand(1, generator=g).item() < 0.5:
+                Q[0, a] = 0.0
+        rnd = mixed_round(1, 4, 3000, bf16, bf16, seed=trial)
+        rnd["draft_tok"][0, 0] = 3000                                # nothing accepted
+        tps = [binding.Tapout(1, 4, 3000, policy=binding.UCB_TUNED, shared_bandit=shared, rules=(0,) * A, thresholds=(0.6,) * A) for _ in range(2)]
+        for tp in tps:
+            tp.bandit_set_state(S, N, sum_r2=Q)
+        arm = torch.zeros(1, dtype=torch.int32, device=DEV)
+        inactive = torch.zeros(1, dtype=torch.uint8, device=DEV)     # no reward: the state as it was restored decides
+        args, _ = tps[0].round_args(rnd, arm, False, active=inactive)
+        tps[0].round(args)
+        want = orc.ucb_tuned_select(S[0], Q[0], N[0])[0]
+        assert tps[1].bandit_select(1).item() == want
+        assert arm.item() == want, f"trial {trial}"
