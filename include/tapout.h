@@ -558,9 +558,10 @@ TAPOUT_API tapout_status tapout_rule_state_set(tapout_ctx *ctx, const float *pre
  *                 many workgroups (long rows are still cut), default 65536,
  *                 at least 16384; for bfloat16 rows, binary32 rows take slices
  *                 of as many elements (twice the bytes)
- *   "min_slice"   smallest slice of a row, in elements; unless it is set a slice
- *                 is at least one batch of the streaming kernel's loads (16 KB),
- *                 and rows are cut no finer than the epilogues merge quickly
+ *   "min_slice"   smallest slice of a row, in elements, at least 256; 0 (default):
+ *                 a slice is at least one batch of the streaming kernel's loads
+ *                 (16 KB), and rows are cut no finer than the epilogues merge
+ *                 quickly
  *   "fuse_head"   tapout_verify only: 1 = no launch of its own for the accept
  *                 decisions, every workgroup of the final-token slice kernel
  *                 takes them again for its sequence (pays while that kernel

@@ -418,7 +418,7 @@ tapout_status tapout_set_option(tapout_ctx *ctx, const char *name, int32_t value
         if (value < kMinSliceBytes) return fail(ctx, TAPOUT_EINVAL, "slice_bytes below %d", kMinSliceBytes);
         ctx->slice_bytes = value;
     } else if (!strcmp(name, "min_slice")) {
-        if (value < 256) return fail(ctx, TAPOUT_EINVAL, "min_slice below 256 elements");
+        if (value < 256 && value != 0) return fail(ctx, TAPOUT_EINVAL, "min_slice below 256 elements (0: the default rule)");
         ctx->min_slice = value;
     } else if (!strcmp(name, "profile_stride")) {
         if (value < 1) return fail(ctx, TAPOUT_EINVAL, "profile_stride below 1");

@@ -297,3 +297,19 @@ def test_ucb_tuned_of_a_restored_state_without_a_variance(shared):
         want = orc.ucb_tuned_select(S[0], Q[0], N[0])[0]
         assert tps[1].bandit_select(1).item() == want
         assert arm.item() == want, f"trial {trial}"
+
+
+@pytest.mark.parametrize("B,K,V,dt", [(1, 8, 128256, bf16), (3, 5, 9001, f32), (40, 2, 20000, bf16)])
+def test_default_slices_can_be_had_back(B, K, V, dt):
+    """"min_slice" 0 is the default rule: after any other value the same bits as a context on which it was never set."""
+    rnd = mixed_round(B, K, V, dt, dt, seed=V)
+    fresh, tp = binding.Tapout(B, K, V), binding.Tapout(B, K, V)
+    for v in (256, 4096, 0):
+        tp.set_option("min_slice", v)
+    for bad in (-1, 1, 255):
+        with pytest.raises(binding.TapoutError, match="min_slice"):
+            tp.set_option("min_slice", bad)
+    (da, va, _), (db, vb, _) = pu.gpu_round(fresh, rnd), pu.gpu_round(tp, rnd)
+    for a, b in ((da, db), (va, vb)):
+        for k in a:
+            assert torch.equal(torch.nan_to_num(a[k].float(), nan=7.0), torch.nan_to_num(b[k].float(), nan=7.0)), k
