@@ -205,7 +205,7 @@ def test_slice_counts_do_not_change_decisions():
     ref = None
     # slices per row 1 .. 125: one to sixteen take the lane-parallel merge of the per-sequence kernels (groups of
     # 1, 2, 4, 8, 16 lanes, also with empty lanes: 3, 5, 11 slices), more than sixteen the staged sequential one
-    for wgs, min_slice in ((1, 4096), (64, 256), (100, 256), (150, 256), (270, 256), (600, 256), (864, 256), (920, 256),
+    for wgs, min_slice in ((4096, 0), (65536, 0), (1, 4096), (64, 256), (100, 256), (150, 256), (270, 256), (600, 256), (864, 256), (920, 256),
                            (4096, 256), (65536, 256), (4096, 1 << 20)):
         tp.set_option("wgs_target", wgs)
         tp.set_option("min_slice", min_slice)
@@ -561,7 +561,7 @@ def test_scattered_masked_logits(dtype):
                u_accept=torch.rand(B, K, generator=g, device=DEV), u_sample=torch.rand(B, generator=g, device=DEV),
                k_len=torch.full((B,), K, dtype=torch.int32, device=DEV), greedy=torch.zeros(B, dtype=torch.uint8, device=DEV))
     tp = binding.Tapout(B, K, V)
-    for wgs, min_slice in ((4096, 4096), (65536, 256)):
+    for wgs, min_slice in ((4096, 0), (4096, 4096), (65536, 256)):
         tp.set_option("wgs_target", wgs)
         tp.set_option("min_slice", min_slice)
         c = pu.check_round(tp, rnd)
@@ -605,7 +605,8 @@ def test_random_configurations(seed):
                u_sample=torch.rand(B, generator=g, device=DEV), k_len=k_len, greedy=greedy)
     tp = binding.Tapout(B, K, V)
     tp.set_option("wgs_target", int(rs.choice([1, 64, 300, 4096, 65536])))
-    tp.set_option("min_slice", int(rs.choice([256, 1024, 4096])))
+    min_slice = int(rs.choice([256, 1024, 4096]))
+    tp.set_option("min_slice", min_slice if seed % 3 else 0)                # 0: the default rule
     tp.set_option("fuse_head", int(rs.randint(-1, 2)))
     announce(f"random configuration {seed}: B={B} K={K} V={V} {dt_d}/{dt_t} offsets {off_d}/{off_t} greedy={greedy.cpu().tolist()} k_len={k_len.cpu().tolist()}")
     c = pu.check_round(tp, rnd)
@@ -1429,7 +1430,8 @@ def test_random_draft_token_sampling(seed):
     u = torch.rand(B, K, generator=g, device=DEV)
     tp = binding.Tapout(B, K, V, draft_sampling=True)
     tp.set_option("wgs_target", int(rs.choice([1, 64, 4096, 65536])))
-    tp.set_option("min_slice", int(rs.choice([256, 4096])))
+    min_slice = int(rs.choice([256, 4096]))
+    tp.set_option("min_slice", min_slice if seed % 3 else 0)              # 0: the default rule
     announce(f"random sampling {seed}: B={B} K={K} V={V} {dt} offset {off} k_len={k_len.tolist()}")
     kl = torch.from_numpy(k_len).to(DEV)
     arm = random_arms(B, seed=seed)
