@@ -34,6 +34,12 @@ f32, bf16 = torch.float32, torch.bfloat16
     (1, 32, 70001, bf16, bf16),      # 33 target rows: groups of eight lanes
     (1, 64, 40003, f32, f32),        # 65 target rows: the staged merge, as many slices as there are batches
     (300, 2, 12289, bf16, bf16),     # 1500 rows of both tensors together: a batch and a half
+    (50, 5, 4100, f32, f32),         # a batch of binary32 and one vector: two slices for 250 draft rows, one for 300 target rows
+    (55, 5, 5000, f32, bf16),
+    (2, 33, 17000, f32, f32),        # four batches and a bit: three slices, not five in groups of eight lanes
+    (2, 80, 8003, f32, f32),         # staged: one slice of nearly two batches
+    (2, 80, 30522, bf16, f32),       # staged: four slices of two batches of binary32 rows, of one of bfloat16 rows
+    (16, 70, 9001, bf16, bf16),
 ])
 def test_slices_of_whole_batches(B, K, V, dt, tt):
     rnd = mixed_round(B, K, V, dt, tt, seed=V + K)
