@@ -140,7 +140,7 @@ Slices cut_in_batches(int n, int V, int dtype)
     const int even = (vecs + n - 1) / n, whole = (even + kBatchVecs - 1) / kBatchVecs * kBatchVecs;
     if (n <= 1 || even > 2 * kBatchVecs) return cut_evenly(n, V, dtype);
     // Level where two batches save no slice (V = 9001, binary32, 40 sequences, K = 90, two slices of 1152 vectors instead of
-    // 2048 and 202: four calls 91.5 -> 84.0 us; 200 sequences, K = 5 40.6 / 38.0).
+    // 2048 and 202: four calls 92.1 -> 84.7 us; 200 sequences, K = 5, round 40.8 -> 38.2).
     return Slices{n, whole > kBatchVecs && (vecs + whole - 1) / whole == n ? (even + 63) & ~63 : whole};
 }
 
@@ -167,11 +167,11 @@ Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t row
     const int64_t vecs = V / (dtype == TAPOUT_F32 ? 4 : 8), whole = vecs < kBatchVecs ? 1 : vecs / kBatchVecs;      // whole batches in a row
     const int64_t nb = V <= kBatchVecs * (dtype == TAPOUT_F32 ? 4 : 8) ? 1 : (vecs + kBatchVecs - 1) / kBatchVecs;  // with the part of one behind them
     // A slice of its own for the part of a batch at a row's end loses beside a single batch where what is missing from it, over
-    // all rows, is more than a batch per compute unit (round without / with it: binary32 V = 4100, 60 sequences, K = 33 33.0 /
-    // 36.6 us, 1 sequence 18.7 / 18.0; V = 7000, 120 sequences, K = 8 29.5 / 31.1, 40 sequences 23.2 / 22.1).  For binary32, whose batch is
+    // all rows, is more than a batch per compute unit (round without / with it: binary32 V = 4100, 60 sequences, K = 33 30.6 /
+    // 36.6 us, 1 sequence 18.7 / 18.0; V = 7000, 120 sequences, K = 8 27.6 / 31.1, 40 sequences 23.2 / 22.1).  For binary32, whose batch is
     // 4096 elements, it is also one more than slices of at least 4096 elements would be, and loses where it takes the merges
-    // across lanes to twice the lanes and a second pass over the rows (V = 17000, 6 sequences, K = 33 25.7 / 27.7), and where
-    // the partials are walked one after the other (V = 8000, 4 sequences, K = 256 38.7 / 45.2).
+    // across lanes to twice the lanes and a second pass over the rows (V = 17000, 6 sequences, K = 33 22.3 / 27.8), and where
+    // the partials are walked one after the other (V = 8000, 4 sequences, K = 256 36.4 / 45.3).
     const bool part_loses = whole == 1 && rows * (2 * kBatchVecs - vecs) > 256 * kBatchVecs;
     const bool part_loses_f32 = dtype == TAPOUT_F32 && (staged || (whole > 1 && lanes(nb) > lanes(whole) && KK * lanes(nb) > 256));
     if (nb > whole && (part_loses || part_loses_f32) && lane_cap > whole) lane_cap = whole;
@@ -180,7 +180,7 @@ Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t row
     if (want < 1) want = 1;
     if (want > nb) want = nb;
     // batches per slice, rounded to nearest; up where the partials are walked one after the other (V = 32000, 16 sequences,
-    // K = 100, two slices of two batches instead of four of one: draft epilogue 13.6 -> 7.6 us, accept decisions 16.0 -> 11.1)
+    // K = 100, two slices of two batches instead of four of one: draft epilogue 13.9 -> 7.7 us, accept decisions 15.9 -> 11.2)
     int64_t pb = staged ? (nb + want - 1) / want : (2 * nb + want) / (2 * want);
     if ((nb + pb - 1) / pb > cap) pb = (nb + cap - 1) / cap;
     if (pb <= 2) want = (nb + pb - 1) / pb;
