@@ -208,16 +208,18 @@ static_assert(sizeof(VerifyArgs) <= 512, "see the note above the struct");
 // fin: the draft epilogue's arguments when kVerifyOwnQ is set (pass 2 then runs it too), else NULL.
 hipError_t launch_verify(const VerifyArgs &a, int pass /*0 head, 1 slices, 2 locate*/, hipStream_t st, Timing tm,
                          const DraftFinalArgs *fin = nullptr);
+// The per-sequence kernels take their lane paths for `rows` rows of `nsplit` pieces (lane_merge_shift >= 0, for the host).
+inline bool lane_merge_fits(int rows, int nsplit)
+{
+    if (nsplit > 16 || rows > 64) return false;
+    int sh = 0;
+    while ((1 << sh) < nsplit) ++sh;
+    return (rows << sh) <= 512;
+}
 // The accept decisions can take log q(tok) from the draft partials themselves (kVerifyOwnQ) for these shapes.
 inline bool own_q_shape(int K, int nsplit_target, int nsplit_draft)
 {
-    auto fits = [](int rows, int nsplit) {
-        if (nsplit > 16 || rows > 64) return false;
-        int sh = 0;
-        while ((1 << sh) < nsplit) ++sh;
-        return (rows << sh) <= 512;
-    };
-    return fits(K + 1, nsplit_target) && fits(K, nsplit_draft);
+    return lane_merge_fits(K + 1, nsplit_target) && lane_merge_fits(K, nsplit_draft);
 }
 
 // Draft-token sampling (Algorithm 1, the sampling step of the draft loop): the inverse CDF of every live draft row, from

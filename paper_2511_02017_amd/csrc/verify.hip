@@ -209,8 +209,8 @@ __device__ inline void widen8(const Raw8<DT> &r, float (&x)[kPer])
 }
 
 // ---- head: accept decisions of one sequence -----------------------------------------
-// verify_head is called by all 256 threads of a workgroup.  It returns the sequence's job (identical in every
-// workgroup of the sequence); with `writer` it also writes the sequence's outputs.
+// verify_head_lanes and verify_head_staged are called by all 256 threads of a workgroup.  They return the sequence's job
+// (identical in every workgroup of the sequence); with `writer` they also write the sequence's outputs.
 //
 // kVerifyOwnQ (whole-round calls, lane-path shapes only): log q(tok) and the draft rows' lse are not read from the draft
 // epilogue's outputs, which then need not exist yet, but formed here from the draft pass's partials: a draft partial's S
@@ -436,25 +436,44 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
     return job;
 }
 
-// Any number of rows and pieces: kStageCap partials at a time in LDS, one row per thread.
+// Any number of rows and pieces: kStageCap partials at a time in LDS, one row per thread.  In a launch of its own the first memory
+// round trip carries, as on the lane path, all that does not depend on n_draft: the first stage's partials, and token, uniform,
+// log q and lse of the thread's first row; further stages ask for these ahead of their partials, and the argmax window travels
+// while the logarithm is formed.  (Asked for row by row behind the merge, as the slice kernel does: V = 50257, 200 sequences,
+// K = 66 6.2 us, this 5.5; in the slice kernel itself the early requests' registers cost the lane path scalar spills: one
+// sequence, V = 32000, round 20.0 us without them, 20.5 with them.)
 template <bool SHARDED, class Table>
 __device__ inline SampleJob verify_head_staged(const VerifyArgs &a, int b, bool writer, HeadStaged *sh, double *shT, Table request_table)
 {
+    constexpr bool kOwnLaunch = std::is_same_v<Table, NoTable>;
     const int K = a.K, rows_per_stage = kStageCap / a.nsplit;
-    int n = a.n_draft[b];
-    const bool greedy = a.greedy && a.greedy[b] != 0;
+    int zero = 0;
+    if constexpr (kOwnLaunch) asm volatile("v_mov_b32 %0, 0" : "=v"(zero));          // (vector loads: see verify_head_lanes)
+    int n = a.n_draft[b + zero];
+    const uint8_t greedy_raw = a.greedy ? a.greedy[b + zero] : (uint8_t)0;
     const double tv = a.exp_table[threadIdx.x];
+    int32_t tok0 = -1;                                                               // kOwnLaunch: of row k0 + threadIdx.x of the stage in LDS
+    float u0 = 0.0f, lq0 = 0.0f, dl0 = 0.0f;
+    auto request_row = [&](int k) {
+        if (k >= K) return;
+        const int64_t i = (int64_t)b * K + k;
+        tok0 = a.draft_tok[i]; u0 = a.u_accept[i]; lq0 = a.logq_tok[i];
+        if (a.draft_lse) dl0 = a.draft_lse[i];
+    };
     auto stage = [&](int k0, int count) {
         if constexpr (SHARDED) return stage_issue_shards(a.part, (int64_t)a.B * (K + 1), (int64_t)b * (K + 1) + k0, a.nsplit, count);
         else return stage_issue(a.part + ((int64_t)b * (K + 1) + k0) * a.nsplit, count);
     };
     {
         const int c0 = min(K + 1, rows_per_stage) * a.nsplit;
+        if constexpr (kOwnLaunch) request_row(threadIdx.x);
         const StageRegs st = stage(0, c0);
         shT[threadIdx.x] = tv;
         if (threadIdx.x == 0) { sh->flags = 0; sh->bcast[4] = 0; }         // ahead of the barrier: rows of other wavefronts OR into the flags
         stage_commit(sh->part, st, c0);
     }
+    if constexpr (kOwnLaunch) n = __builtin_amdgcn_readfirstlane(n);
+    const bool greedy = kOwnLaunch ? __builtin_amdgcn_readfirstlane((int)greedy_raw) != 0 : greedy_raw != 0;
     if (n < 1 || n > K) {
         if (threadIdx.x == 0) atomicOr(&sh->flags, TAPOUT_FLAG_BAD_NDRAFT);
         n = n < 1 ? 1 : K;
@@ -464,6 +483,7 @@ __device__ inline SampleJob verify_head_staged(const VerifyArgs &a, int b, bool 
     for (int k0 = 0; k0 <= n; k0 += rows_per_stage) {
         const int k1 = min(n + 1, k0 + rows_per_stage);
         if (k0 > 0) {
+            if constexpr (kOwnLaunch) request_row(k0 + threadIdx.x);
             __syncthreads();
             stage_commit(sh->part, stage(k0, (k1 - k0) * a.nsplit), (k1 - k0) * a.nsplit);
         }
@@ -472,25 +492,38 @@ __device__ inline SampleJob verify_head_staged(const VerifyArgs &a, int b, bool 
             // shard records leave their first maximum out of the sums (and carry its exact index), slice partials of
             // target rows do not
             const RowTotal r = merge_partials<SHARDED>(sh->part + (k - k0) * a.nsplit, a.nsplit);
+            const void *row_p = SHARDED ? nullptr : row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, k);
             int32_t top1 = 0;
+            ArgmaxProbe probe;
             if constexpr (SHARDED) top1 = (r.cand >= 0 && r.cand < a.V) ? r.cand : 0;
-            else if (need_top1) top1 = resolve_argmax(row_address(a.tbase, a.t_dtype, a.t_stride_b, a.t_stride_k, b, k), a.t_dtype, a.V, r.cand, r.M);
+            else if (need_top1) {
+                if constexpr (kOwnLaunch) probe = argmax_issue(row_p, a.t_dtype, a.V, r.cand);
+                else top1 = resolve_argmax(row_p, a.t_dtype, a.V, r.cand, r.M);
+            }
             double lse = NAN;
             uint32_t f = 0;
             if (r.bad) f |= TAPOUT_FLAG_BAD_ROW;
             else lse = (r.R + log2_pos(r.S)) * kLn2;
+            if constexpr (!SHARDED && kOwnLaunch)                                    // greedy sequences decide on it, the others only report it
+                if (greedy) top1 = argmax_finish(probe, row_p, a.t_dtype, a.V, r.cand, r.M);
             if (k < n) {
                 float xt = NAN;
                 for (int g = 0; g < a.nsplit; ++g) {
                     const float v = __int_as_float(sh->part[(k - k0) * a.nsplit + g].pad[0]);
                     if (v == v) xt = v;
                 }
-                const Accept acc = accept_row(a, r.bad, lse, greedy, a.draft_tok[i], a.u_accept[i], a.logq_tok[i], xt, top1, shT);
+                Accept acc;
+                if constexpr (kOwnLaunch) {
+                    if (__builtin_expect(k != k0 + (int)threadIdx.x, 0)) request_row(k);      // more rows than threads
+                    acc = accept_row(a, r.bad, lse, greedy, tok0, u0, lq0, xt, top1, shT);
+                } else acc = accept_row(a, r.bad, lse, greedy, a.draft_tok[i], a.u_accept[i], a.logq_tok[i], xt, top1, shT);
                 f |= acc.flags;
                 if (writer && a.logp_tok) a.logp_tok[i] = acc.lp;
                 sh->dec[k] = acc.yes ? 1 : 0;
-                last_dl = a.draft_lse ? a.draft_lse[i] : 0.0f;
+                if constexpr (kOwnLaunch) last_dl = dl0; else last_dl = a.draft_lse ? a.draft_lse[i] : 0.0f;
             }
+            if constexpr (!SHARDED && kOwnLaunch)
+                if (!greedy) top1 = argmax_finish(probe, row_p, a.t_dtype, a.V, r.cand, r.M);
             if (writer) {
                 if (a.target_lse) a.target_lse[it] = (float)lse;
                 if (a.target_top1) a.target_top1[it] = top1;
@@ -529,20 +562,28 @@ __device__ inline SampleJob verify_head_staged(const VerifyArgs &a, int b, bool 
     }
     const SampleJob job = head_job(!flagged && !greedy, m, n, Mm, lse_m, dl_m, a.draft_lse != nullptr, shT);
     if (writer) head_outputs<SHARDED>(a, b, job, m, n, flagged, greedy, f, top1m, [&](int k) { return a.draft_tok[(int64_t)b * K + k]; });
-    __syncthreads();                             // every thread is done with `sh`
-    request_table();
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
+    if constexpr (!kOwnLaunch) {
+        __syncthreads();                         // every thread is done with `sh`
+        request_table();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
     return job;
 }
 
-template <bool SHARDED, class Table = NoTable>
-__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer, HeadStaged *stg, HeadLanes *lanes, double *shT, Table request_table = Table())
+// Lanes per target row (log2): both tensors' slices on the same lanes where the draft rows are merged too.
+template <bool SHARDED>
+__device__ inline int head_lanes_shift(const VerifyArgs &a)
 {
-    int msh = lane_merge_shift(a.K + 1, a.nsplit);
-    if (__builtin_expect(msh < 0, 0)) return verify_head_staged<SHARDED>(a, b, writer, stg, shT, request_table);
-    if (!SHARDED && (a.vflags & kVerifyOwnQ)) msh = max(msh, lane_merge_shift(a.K, a.d_nsplit));        // both tensors' slices on the same lanes
-    return verify_head_lanes<SHARDED>(a, b, writer, lanes, shT, request_table, msh);
+    const int msh = lane_merge_shift(a.K + 1, a.nsplit);
+    return !SHARDED && (a.vflags & kVerifyOwnQ) ? max(msh, lane_merge_shift(a.K, a.d_nsplit)) : msh;
+}
+// In the slice kernel: either path.
+template <class Table>
+__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer, HeadStaged *stg, HeadLanes *lanes, double *shT, Table request_table)
+{
+    if (__builtin_expect(lane_merge_shift(a.K + 1, a.nsplit) < 0, 0)) return verify_head_staged<false>(a, b, writer, stg, shT, request_table);
+    return verify_head_lanes<false>(a, b, writer, lanes, shT, request_table, head_lanes_shift<false>(a));
 }
 
 struct Rows {
@@ -559,15 +600,17 @@ __device__ inline Rows job_rows(const VerifyArgs &a, int b, const SampleJob &job
 }
 
 // ---- head kernel: one workgroup per sequence ------------------------------------------
-template <bool SHARDED>
+// A kernel for each path: compiled as the unlikely side of the lane path the staged one kept its values in spilled scalars
+// (64 shard records a row, 8 sequences, K = 4: 48.7 us, apart 47.1; V = 32000, one sequence, K = 100, slice kernel with the decisions 14.0 / 13.7).
+template <bool SHARDED, bool STAGED>
 __global__ __launch_bounds__(kVBlock) void verify_head_kernel(VerifyArgs a)
 {
     warm_args(a);
-    __shared__ HeadStaged stg;
-    __shared__ HeadLanes lanes;
+    __shared__ std::conditional_t<STAGED, HeadStaged, HeadLanes> sh;
     __shared__ double shT[256];
     static_assert(kVBlock == 256, "one table entry per thread");
-    verify_head<SHARDED>(a, blockIdx.x, true, &stg, &lanes, shT);
+    if constexpr (STAGED) verify_head_staged<SHARDED>(a, blockIdx.x, true, &sh, shT, NoTable());
+    else verify_head_lanes<SHARDED>(a, blockIdx.x, true, &sh, shT, NoTable(), head_lanes_shift<SHARDED>(a));
 }
 
 // ---- slice kernel -----------------------------------------------------------------------
@@ -775,7 +818,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
         // Small batches: a head launch of its own costs more (launch, hand-over of the job record through
         // memory) than taking the accept decisions again in each of the sequence's workgroups.  All of them run
         // the same code on the same inputs and reach the same job; one of them writes the sequence's outputs.
-        job = verify_head<false>(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table);
+        job = verify_head(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table);
     } else {
         const double tv = a.exp_table[threadIdx.x];
         job = a.final_jobs ? a.final_jobs[b] : a.jobs[b].job;      // vocabulary shards: the caller's copy
@@ -1743,8 +1786,9 @@ hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing t
     if (!fin) fin = &no_fin;
     if (pass == 0) {
         if (a.fused_head) return hipErrorInvalidValue;       // the slice kernel is the head then
-        if (a.shards > 0) launch_kernel(verify_head_kernel<true>, dim3(a.B), dim3(kVBlock), st, tm, a);
-        else launch_kernel(verify_head_kernel<false>, dim3(a.B), dim3(kVBlock), st, tm, a);
+        const bool staged = !lane_merge_fits(a.K + 1, a.nsplit);
+        if (a.shards > 0) launch_kernel(staged ? verify_head_kernel<true, true> : verify_head_kernel<true, false>, dim3(a.B), dim3(kVBlock), st, tm, a);
+        else launch_kernel(staged ? verify_head_kernel<false, true> : verify_head_kernel<false, false>, dim3(a.B), dim3(kVBlock), st, tm, a);
         return hipGetLastError();
     }
     if (a.t_dtype == TAPOUT_F32)
