@@ -115,15 +115,24 @@ struct Args {
     }
 };
 
-// The library call without the interpreter lock (as ctypes does), its status as the Python result.
+// The library call without the interpreter lock (as ctypes does), its status as the Python result.  An exception out of the
+// library is a Python exception, raised with the lock held; None would have the Python code make the call a second time.
 template <class F>
 PyObject *call(const Args &a, F f)
 {
     if (!a.ok) Py_RETURN_NONE;
-    tapout_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
+    tapout_status st = TAPOUT_OK;
+    char thrown[256] = "";
+    PyThreadState *ts = PyEval_SaveThread();
+    try {
+        st = f();
+    } catch (const std::exception &e) {
+        snprintf(thrown, sizeof thrown, "%s", *e.what() ? e.what() : "C++ exception");
+    } catch (...) {
+        snprintf(thrown, sizeof thrown, "C++ exception");
+    }
+    PyEval_RestoreThread(ts);
+    if (*thrown) { PyErr_SetString(PyExc_RuntimeError, thrown); return nullptr; }
     return PyLong_FromLong((long)st);
 }
 

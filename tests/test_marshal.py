@@ -1,5 +1,9 @@
 """The native argument marshalling of the binding (csrc/marshal.cpp): it calls the library only when every argument is in
 order, and hands everything else to the Python code, which describes the error."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -28,6 +32,36 @@ def test_arguments_that_are_not_in_order_go_to_the_python_code():
     with pytest.raises(ImportError):
         fast.load("/nonexistent/libtapout.so")
     assert fast.verify(1) is None                                                   # the library loaded before stays
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_an_exception_out_of_the_library_becomes_a_python_one(tmp_path):
+    """The library is called without the interpreter lock; an exception that leaves it is raised with the lock held, and the call
+    is not made a second time.  A stand-in library throws (a process of its own: a fault here would end the interpreter)."""
+    names = ("bandit_select", "draft_stats", "verify", "bandit_update", "bandit_update_select", "shard_stats", "draft_stats_sharded",
+             "verify_accept_sharded", "shard_final_sums", "shard_final_token")
+    src = tmp_path / "stand_in.cpp"
+    src.write_text("#include <cstdio>\n#include <stdexcept>\n" + "".join(
+        f'extern "C" int tapout_{n}() {{ std::puts("called {n}"); std::fflush(stdout); throw std::runtime_error("out of {n}"); }}\n' for n in names))
+    lib = tmp_path / "stand_in.so"
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(lib), str(src)], check=True)
+    code = f"""
+import sys, threading, torch
+sys.path.insert(0, {ROOT!r})
+from paper_2511_02017_amd import _marshal
+_marshal.load({str(lib)!r})
+for _ in range(3):
+    try:
+        print(_marshal.bandit_update(1, 1, 1, None, None, None, None, None, 0))
+    except RuntimeError as e:
+        print("raised", e)
+t = threading.Thread(target=print, args=("alive",)); t.start(); t.join()
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert r.stdout.split("\n")[:-1] == ["called bandit_update", "raised out of bandit_update"] * 3 + ["alive"]
 
 
 @pytest.mark.gpu
