@@ -59,7 +59,7 @@ for _ in range(3):
         print("raised", e)
 t = threading.Thread(target=print, args=("alive",)); t.start(); t.join()
 """
-    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    r = subprocess.run([sys.executable, "-u", "-c", code], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.split("\n")[:-1] == ["called bandit_update", "raised out of bandit_update"] * 3 + ["alive"]
 
