@@ -6,11 +6,14 @@ The binding fails loudly if the built library is missing: there is no fallback.
 The per-round methods first try _marshal.so (csrc/marshal.cpp), which takes the
 tensors apart in native code and calls the library; where it finds an argument
 that is not in order it returns None and the code here describes the error.
+Without it (it is built against one Python and torch, the library against
+neither) the code here makes every call, 12 to 20 us later.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 
 import torch
 
@@ -68,6 +71,17 @@ class TapoutError(RuntimeError):
         self.status = status
 
 
+class _PythonOnly:
+    """Stands in for _marshal: no call can be made natively."""
+
+    @staticmethod
+    def current_stream():
+        return torch.cuda.current_stream().cuda_stream
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 _lib = None
 _fast = None
 
@@ -80,12 +94,15 @@ def load_library(path: str = None):
         path = path or LIB_PATH
         if not os.path.exists(path):
             raise ImportError(f"{path} is missing: build it with `python -m paper_2511_02017_amd.build`")
-        if not os.path.exists(os.path.join(_PKG, "_marshal.so")):
-            raise ImportError("_marshal.so is missing: build it with `python -m paper_2511_02017_amd.build`")
-        from . import _marshal
-        _marshal.load(path)
-        _fast = _marshal
         lib = C.CDLL(path)
+        try:
+            from . import _marshal
+            _marshal.load(path)
+            _fast = _marshal
+        except ImportError as e:
+            warnings.warn(f"without _marshal.so (build it with `python -m paper_2511_02017_amd.build`) calls take longer: {e}", RuntimeWarning,
+                          stacklevel=2)
+            _fast = _PythonOnly()
         vp, i32 = C.c_void_p, C.c_int32
         lib.tapout_default_config.restype = None
         lib.tapout_default_config.argtypes = [C.POINTER(TapoutConfig), i32, i32, i32]

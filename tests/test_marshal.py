@@ -64,6 +64,63 @@ t = threading.Thread(target=print, args=("alive",)); t.start(); t.join()
     assert r.stdout.split("\n")[:-1] == ["called bandit_update", "raised out of bandit_update"] * 3 + ["alive"]
 
 
+@pytest.fixture
+def python_only(monkeypatch):
+    """The binding as it loads where _marshal.so is missing or does not fit this Python or torch."""
+    import paper_2511_02017_amd as pkg
+    binding.load_library()
+    native = binding._fast
+    monkeypatch.setitem(sys.modules, "paper_2511_02017_amd._marshal", None)         # an import of it fails
+    monkeypatch.delattr(pkg, "_marshal", raising=False)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_fast", None)
+    with pytest.warns(RuntimeWarning, match="_marshal"):
+        binding.load_library()
+    return native
+
+
+def test_the_library_loads_without_the_native_part(python_only):
+    assert binding._fast is not python_only
+    assert binding._fast.verify(1, 2, 3) is None and binding._fast.bandit_select() is None      # every call goes the Python way
+    cfg = binding.default_config(4, 3, 100)
+    assert (cfg.max_batch, cfg.max_k, cfg.vocab) == (4, 3, 100)
+
+
+@pytest.mark.gpu
+def test_the_native_part_changes_no_result(python_only, monkeypatch):
+    """The calls of a round and of a round over vocabulary shards, on the current stream and on one handed in: the same bits."""
+    def calls(stream):
+        g = torch.Generator(device="cuda:0").manual_seed(1)
+        B, K, V = 5, 4, 9001
+        d, t = torch.randn(B, K, V, generator=g, device="cuda:0") * 3, torch.randn(B, K + 1, V, generator=g, device="cuda:0") * 3
+        tok, ua = d.argmax(-1).to(i32), torch.rand(B, K, generator=g, device="cuda:0")
+        us, n = torch.rand(B, generator=g, device="cuda:0"), torch.full((B,), K, dtype=i32, device="cuda:0")
+        torch.cuda.synchronize()
+        tp = binding.Tapout(B, K, V, draft_sampling=True)
+        st = dict(stream=stream)
+        arm = tp.bandit_select(B, **st)
+        ds = tp.draft_stats(d, tok, n, arm, **st)
+        smp = tp.draft_stats(d, k_len=n, u_draft=ua, **st)
+        vf = tp.verify(t, d, ds["lse"], ds["logq_tok"], tok, n, ua, us, **st)
+        tp.bandit_update(arm, vf["accept_len"], n, n, **st)
+        nxt = tp.bandit_update_select(arm, vf["accept_len"], n, n, **st)
+        r0, r1 = tp.shard_stats(d, 0, length=n, tok=tok, **st), tp.shard_stats(t, 0, length=n, rows_mode=1, tok=tok, **st)
+        dss = tp.draft_stats_sharded(r0[None], B, K, V, draft_tok=tok, k_len=n, arm=arm, **st)
+        acc = tp.verify_accept_sharded(r1[None], B, K, V, dss["logq_tok"], tok, n, ua, draft_lse=dss["lse"], **st)
+        sums = tp.shard_final_sums(t, d, acc["final_jobs"], **st)
+        fin = tp.shard_final_token(t, d, 0, 1, 0, acc["final_jobs"], sums[None], us, **st)
+        torch.cuda.synchronize()
+        return [arm, nxt, r0, r1, sums, *fin, *ds.values(), *smp.values(), *vf.values(), *dss.values(), *acc.values()]
+
+    for stream in (None, torch.cuda.Stream()):
+        without = calls(stream)
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_fast", python_only)                # the native part
+            native = calls(stream)
+        for a, b in zip(without, native):
+            assert torch.equal(torch.nan_to_num(a.double(), nan=-7.0), torch.nan_to_num(b.double(), nan=-7.0))
+
+
 @pytest.mark.gpu
 def test_errors_are_those_of_the_python_code():
     B, K, V = 2, 3, 100
