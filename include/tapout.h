@@ -497,7 +497,12 @@ TAPOUT_API tapout_status tapout_bandit_update_select(tapout_ctx *ctx, int32_t B,
  *   draft [B,K,V], target [B,K+1,V]
  *   draft_tok [B,K];  k_len [B] or NULL;  greedy [B] or NULL
  *   n_draft   [B] tokens submitted to verification, or NULL: this round's stop
- *             position n_stop (Algorithm 1 as written; then nothing overlaps)
+ *             position n_stop (Algorithm 1 as written).  The target pass then
+ *             waits for it, except where k_len is given and the target rows are
+ *             at most 24 MiB in all: those are streamed with the draft rows, rows
+ *             0..k_len[b] of every sequence, before the stop position is known.
+ *             Rows beyond the stop position may hold anything (they change no
+ *             result and raise no flag) but must be addressable
  *   arm       [B] IN: the arms of this round (from tapout_bandit_select or the
  *             previous tapout_round); OUT: the arms of the next round.
  *             SEQUENCE_LEVEL contexts; TOKEN_LEVEL: [B, max_k]
@@ -607,13 +612,15 @@ TAPOUT_API tapout_status tapout_set_option(tapout_ctx *ctx, const char *name, in
 enum {
     TAPOUT_PROFILE_SELECT = 0,          /* bandit select                                            */
     TAPOUT_PROFILE_DRAFT_PASS = 1,      /* streaming pass over the draft logits                     */
-    TAPOUT_PROFILE_DRAFT_FINALIZE = 2,  /* signals + stop scan                                      */
+    TAPOUT_PROFILE_DRAFT_FINALIZE = 2,  /* signals + stop scan, where it is a launch of its own: it */
+                                        /* rides in SAMPLE_SLICES where tokens are drawn, and in    */
+                                        /* VERIFY_LOCATE where tapout_round defers it               */
     TAPOUT_PROFILE_TARGET_PASS = 3,     /* streaming pass over the target logits                    */
     TAPOUT_PROFILE_VERIFY_HEAD = 4,     /* accept tests, first rejection, emitted prefix            */
     TAPOUT_PROFILE_VERIFY_SLICES = 5,   /* final token: slice sums of the row pair                  */
     TAPOUT_PROFILE_VERIFY_LOCATE = 6,   /* final token: normalisers, slice, token                   */
     TAPOUT_PROFILE_UPDATE = 7,          /* bandit update                                            */
-    TAPOUT_PROFILE_SAMPLE_HEAD = 8,     /* not launched (the slice kernel does this)                */
+    TAPOUT_PROFILE_SAMPLE_HEAD = 8,     /* no such launch any more: always 0 launches               */
     TAPOUT_PROFILE_SAMPLE_SLICES = 9,   /* draft-token sampling: slice sums of every draft row;     */
                                         /* signals + stop scan                                      */
     TAPOUT_PROFILE_SAMPLE_LOCATE = 10,  /* draft-token sampling: slice, token                       */

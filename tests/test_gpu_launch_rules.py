@@ -319,3 +319,27 @@ def test_default_slices_can_be_had_back(B, K, V, dt):
     for a, b in ((da, db), (va, vb)):
         for k in a:
             assert torch.equal(torch.nan_to_num(a[k].float(), nan=7.0), torch.nan_to_num(b[k].float(), nan=7.0)), k
+
+
+@pytest.mark.parametrize("B,V,dt", [(5, 32000, f32), (5, 9001, bf16), (64, 50257, f32)])       # the last: beyond 24 MB, a pass of its own
+def test_round_up_to_the_stop_position_ignores_target_rows_beyond_it(B, V, dt):
+    """Target rows between the stop position and k_len may be read before the stop position is known: whatever they hold (NaN
+    here), the results are those of the separate calls, bit for bit, which read rows up to the stop position only."""
+    K = 6
+    rnd = mixed_round(B, K, V, dt, dt, seed=V, k_len=[1 + b % K for b in range(B)])
+    for arm in range(3):
+        tp = binding.Tapout(B, K, V, thresholds=(2.0, 0.3, 0.1))
+        arms = torch.full((B,), arm, dtype=torch.int32, device=DEV)
+        n = tp.draft_stats(rnd["draft"], draft_tok=rnd["draft_tok"], k_len=rnd["k_len"], arm=arms)["n_stop"]
+        poisoned = dict(rnd, target=rnd["target"].clone())
+        rows = torch.arange(K + 1, device=DEV)[None, :] > n[:, None]
+        poisoned["target"][rows] = float("nan")
+        _, want, _ = pu.gpu_round(tp, rnd, arm=arms)
+        args, out = tp.round_args(poisoned, arms.clone(), True)
+        tp.round(args)
+        got = out["verify"]
+        assert torch.equal(out["n_draft"], n) and not got["flags"].any()
+        for k in ("accept_len", "out_tok", "n_out", "target_lse", "logp_tok", "target_top1", "flags"):
+            a, b = (torch.nan_to_num(x[k].float(), nan=7.0) for x in (got, want))
+            assert torch.equal(a, b), k
+        assert (rows & (torch.arange(K + 1, device=DEV)[None, :] <= rnd["k_len"][:, None])).sum() >= B      # (some of them up to k_len)
