@@ -24,8 +24,10 @@ f32, bf16 = torch.float32, torch.bfloat16
 
 @pytest.mark.parametrize("B,K,V,dt,tt", [
     (3, 2, 8192, bf16, bf16),        # one batch of 16 KB exactly: one slice
-    (3, 2, 8193, bf16, bf16),        # one element more: two slices, rows at every alignment
-    (2, 3, 8199, bf16, f32),         # three and a bit batches of binary32 rows beside one and a bit of bfloat16 rows
+    (3, 2, 8193, bf16, bf16),        # one element more: still one, rows at every alignment
+    (3, 2, 8199, bf16, bf16),        # no whole vector more: still one
+    (3, 2, 8200, bf16, bf16),        # one vector more: two slices
+    (2, 3, 8199, bf16, f32),         # two and a bit batches of binary32 rows beside one of bfloat16 rows
     (2, 3, 4096, f32, f32),
     (2, 3, 4101, f32, bf16),
     (1, 8, 131072, bf16, bf16),      # sixteen batches: as many slices as are merged across lanes
