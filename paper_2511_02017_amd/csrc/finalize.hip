@@ -11,14 +11,17 @@
 // term.  That is what keeps the entropy of a peaked row (a small number made
 // of small terms) accurate to binary32 relative precision.
 //
-// One workgroup per sequence, one thread per row.  The kernel is latency bound
-// (O(K * nsplit) work), so it is written to keep dependent memory round trips
-// few: the partials are requested by all threads at once, the token gather and
-// the left-out batches travel together in a second round trip, and every row decides "fires / does not fire" for itself so that
-// the sequential part is a scan over bytes in LDS.  The two rules that look at
-// more than the current row's signals (SVIP-Difference: previous row's entropy;
-// AdaEDL: the sequence's adaptive threshold) decide in a second sweep, after all
-// entropies of the sequence are in LDS.
+// One workgroup per sequence.  The kernel is latency bound (O(K * nsplit)
+// work), so it is written to keep dependent memory round trips few: the partials
+// are requested by all threads at once, the token gather and the left-out batches
+// travel together in a second round trip, and every row decides "fires / does not
+// fire" for itself.  Few rows and slices: lanes of their own for every (row,
+// slice) piece, a row's first lane emits it, and ballots over the rows give the
+// stop position.  Long drafts and many pieces: partials staged in LDS, one thread
+// per row, a scan over decision bytes.  The two rules that look at more than the
+// current row's signals (SVIP-Difference: previous row's entropy; AdaEDL: the
+// sequence's adaptive threshold) decide once all entropies of the sequence are
+// in LDS.
 #include "finalize_device.h"
 
 namespace tapout {

@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 // Draft rows and target rows of a round in ONE launch: grid = (slice, row, 2 * sequences), the first half of the
 // z range takes the draft tensor, the second half the target tensor (one more row per sequence).  A launch over a
 // few hundred rows spends a fifth of its time filling and draining the chip; one launch over both tensors pays
-// that once.  Both passes are cut into the same number of slices.
+// that once.  The grid has the larger of the two slice counts.
 template <int DD, int TD>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void stream_pair_kernel(RowReduceArgs d, RowReduceArgs t, int n_seq)
 {

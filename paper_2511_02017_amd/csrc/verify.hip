@@ -780,8 +780,9 @@ __device__ inline void copy_to_lds(const void *src, void *dst)
 // lane; its five sums need no LDS and no barrier.  The requests run ahead of the arithmetic (see kAhead): with one
 // chunk ahead the launch was bound by memory latency.  Four wavefronts per SIMD: the bfloat16 table limits a CU to
 // four workgroups anyway, and under a tighter register limit the loop spills.  Pairs of one bfloat16 and one binary32 row
-// have no table and fit five (96 registers, no spills; two binary32 rows spill): V = 256000, 512 sequences, round 1399.5 ->
-// 1394.2 us, of which the straight-line requests in the loop are about 1.
+// have no table and fit five (96 registers, no spills; two binary32 rows spill).  Launch at five / four, V = 256000, 512
+// sequences, K = 4: binary32 draft rows 164.8 / 167.7 us, bfloat16 draft rows the same within its spread of 3; V = 128256, 128
+// sequences 27.7 / 27.3.
 template <int TD, int DD, bool FUSED>
 __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != DD && !FUSED ? 5 : 4))) void verify_slices(VerifyArgs a)
 {
@@ -1753,8 +1754,9 @@ static hipError_t launch_sample_typed(SampleArgs &a, const DraftFinalArgs &fin, 
 {
     if (pass == 0) {
         constexpr int per_wg = kSampleBlock / kWave;
-        // All wavefronts the same number of slices, and no more workgroups than are resident beside the epilogue's: one that
-        // waits for a place starts when others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us, 252 of
+        // All wavefronts the same number of slices, and no more workgroups than are resident beside the epilogue's (from 256
+        // sequences on half the places, behind an epilogue that takes more than the other half): one that waits for a place
+        // starts when others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us, 252 of
         // two slices per wavefront 10.0; K = 8: 504 of eight slices 37.8, 448 of nine 34.0).
         const int64_t slices = (int64_t)a.B * a.K * a.nsl;
         const int64_t places = (int64_t)per_wg * (a.B < kSampleWgs / 2 ? kSampleWgs - a.B : kSampleWgs / 2);
