@@ -581,6 +581,7 @@ __device__ inline RowTotal row_total(const Piece &p)
 //   H / ln 2 = log2(1 + eps) + (yM eps - Tx / eM) / (1 + eps)
 //   p_top1 = 1 / (1 + eps),  p_top2 = r2 p_top1,  margin = (1 - r2) p_top1,  r2 = 2^((v2 - M) log2e)  (double: a margin
 //   between near-tied logits is the small difference 1 - r2)
+// (log2(1 + eps) comes from the rounded 1 + eps: 6e-16 absolute, below binary32's relative rounding of H down to H = 1e-8.)
 struct RowSignals { double lse, H, p1, p2, margin; };
 __device__ inline RowSignals row_signals(const RowTotal &r, bool has_second)
 {
