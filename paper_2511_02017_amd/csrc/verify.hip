@@ -776,16 +776,19 @@ __device__ inline void copy_to_lds(const void *src, void *dst)
     }
 }
 
-// One wavefront per slice, four slices per workgroup.  A wavefront takes its slice in chunks of one 8-element run per
-// lane; its five sums need no LDS and no barrier.  The requests run ahead of the arithmetic (see kAhead): with one
+// One wavefront per slice, four slices per workgroup; in small launches two or four wavefronts per slice (SPLIT; see
+// slice_split), whose sums meet in LDS.  A wavefront takes its slice in chunks of one 8-element run per
+// lane; its five sums need no LDS and no barrier of their own.  The requests run ahead of the arithmetic (see kAhead): with one
 // chunk ahead the launch was bound by memory latency.  Four wavefronts per SIMD: the bfloat16 table limits a CU to
 // four workgroups anyway, and under a tighter register limit the loop spills.  Pairs of one bfloat16 and one binary32 row
 // have no table and fit five (96 registers, no spills; two binary32 rows spill).  Launch at five / four, V = 256000, 512
 // sequences, K = 4: binary32 draft rows 164.8 / 167.7 us, bfloat16 draft rows the same within its spread of 3; V = 128256, 128
 // sequences 27.7 / 27.3.
-template <int TD, int DD, bool FUSED>
+template <int TD, int DD, bool FUSED, int SPLIT>
 __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != DD && !FUSED ? 5 : 4))) void verify_slices(VerifyArgs a)
 {
+    constexpr int kSliceChunks = kChunks / SPLIT;                // of a wavefront
+
     // The table serves row pairs of bfloat16 only: with one row computed and one looked up the compiler's schedule
     // of the mixed loop wants 160-170 registers (two wavefronts per SIMD), and held to four wavefronts it spills
     // inside the loop (V = 256000, 512 sequences, binary32 target rows: 210 us against 139 us all computed; at three
@@ -797,7 +800,8 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     __shared__ double shT[256];
     __shared__ __align__(16) unsigned char sh_raw[kRaw];
     __shared__ HeadLanes sh_lanes[1];
-    static_assert(sizeof shT + sizeof sh_raw + sizeof sh_lanes <= 32 * 1280, "four workgroups' LDS per compute unit");
+    __shared__ double sh_sums[SPLIT > 1 ? kWavesPerWG : 1][kSliceVals];
+    static_assert(sizeof shT + sizeof sh_raw + sizeof sh_lanes + sizeof sh_sums <= 32 * 1280, "four workgroups' LDS per compute unit");
     warm_args(a);
     [[maybe_unused]] const int wg = WG_LINEAR();
     WG_STAMP(g_stamps_slices, 8, wg, 0);                         // entry
@@ -805,8 +809,9 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     // FUSED: the sequence's last workgroup writes the sequence's outputs, from its first wavefront, which therefore
     // takes the group's last slice: most often none at all, or the row's short last one
-    const bool writer = FUSED && (int)blockIdx.x == (a.nsl + kWavesPerWG - 1) / kWavesPerWG - 1;
-    const int s = blockIdx.x * kWavesPerWG + (writer ? kWavesPerWG - 1 - wave : wave);
+    const bool writer = FUSED && (int)blockIdx.x == (a.nsl * SPLIT + kWavesPerWG - 1) / kWavesPerWG - 1;
+    const int piece = blockIdx.x * kWavesPerWG + (writer ? kWavesPerWG - 1 - wave : wave);
+    const int s = piece / SPLIT, part = piece % SPLIT;
     // The table goes from memory to LDS directly, no registers in between, while the accept decisions are taken (FUSED) or the
     // job's record travels.  (Through registers it held 36 of them over the decisions: spills, and the wait for the table
     // in front of the decisions; 20.5 us where this takes 15.9.)
@@ -832,26 +837,26 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     const Rows r = job_rows<TD, DD>(a, b, job);
     const bool live = s < a.nsl;
     const bool resid = job.kind == 1;
-    const int base = s * kSampleSlice + lane * kPer;
+    const int first = s * kSampleSlice + part * (kSliceChunks * kWave * kPer), base = first + lane * kPer;
     // The wavefront's requests run kAhead chunks ahead of its arithmetic.  With one chunk ahead the kernel was bound by
     // memory latency, not by arithmetic: 2 KB in flight per wavefront, 8 MB over the chip, is 2.5 TB/s at 3 us.
     // bfloat16 pairs request the whole slice at once (32 registers), others two chunks ahead.
-    constexpr int kAhead = (TD == TAPOUT_BF16 && DD == TAPOUT_BF16) ? kChunks : 2;
+    constexpr int kAhead = (TD == TAPOUT_BF16 && DD == TAPOUT_BF16) || kSliceChunks < 2 ? kSliceChunks : 2;
     // whole workgroup, uniform: which rows take their exponentials from the table
     const bool tab_ok = (kTabT || kTabD) && !(a.vflags & kVerifyNoExpTable) && tab_job_ok(job);
     const bool tab_t = kTabT && tab_ok, tab_d = kTabD && tab_ok && resid;
     const double *shE = (const double *)sh_raw;
-    Raw8<TD> qt[kChunks];
-    Raw8<DD> qd[kChunks];
+    Raw8<TD> qt[kSliceChunks];
+    Raw8<DD> qd[kSliceChunks];
     // A slice that lies wholly inside the rows (all but a row's last one) is requested in straight-line code:
     // the per-request checks of the general path are branches, and across branches the compiler waits for every
     // outstanding request where the first chunk's would do.
-    const bool whole = live && (s + 1) * kSampleSlice <= a.V;       // wavefront-uniform
+    const bool whole = live && first + kSliceChunks * kWave * kPer <= a.V;       // wavefront-uniform
     if (__builtin_expect(whole, 1)) {
         const char *tp = r.trow + (int64_t)base * Elem<TD>::size;
         const char *dp = r.drow + (int64_t)base * Elem<DD>::size;
 #pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
+        for (int c = 0; c < kSliceChunks; ++c) {
             qt[c] = Raw8<TD>{}; qd[c] = Raw8<DD>{};
             if (c < kAhead) {
 #pragma unroll
@@ -868,7 +873,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
         }
     } else {
 #pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
+        for (int c = 0; c < kSliceChunks; ++c) {
             qt[c] = Raw8<TD>{}; qd[c] = Raw8<DD>{};
             if (c < kAhead && live) {
                 qt[c] = load_raw8<TD>(r.trow, base + c * kWave * kPer, a.V);
@@ -895,8 +900,8 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     auto pass = [&](auto tt, auto td, auto inside) {
         constexpr bool TT = decltype(tt)::value, TD_ = decltype(td)::value;
 #pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-            if (c + kAhead < kChunks) {
+        for (int c = 0; c < kSliceChunks; ++c) {
+            if (c + kAhead < kSliceChunks) {
                 const int jn = base + (c + kAhead) * kWave * kPer;
                 if constexpr (decltype(inside)::value) {
 #pragma unroll
@@ -977,9 +982,19 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     double D = 0.5 * (Bs + Ds);
     A = wave_sum_d(A) * sc.ct;
     if (resid) { Bs = wave_sum_d(Bs) * sc.cd; R = wave_sum_d(R) * sc.ct; D = wave_sum_d(D) * sc.cd; U = wave_sum_d(U) * sc.cd; }
-    if (lane == 0) {
-        double *o = a.part1 + ((int64_t)b * a.nsl + s) * kSliceVals;
-        o[0] = A; o[1] = Bs; o[2] = R; o[3] = D; o[4] = U;
+    double *o = a.part1 + ((int64_t)b * a.nsl + s) * kSliceVals;
+    if constexpr (SPLIT == 1) {
+        if (lane == 0) { o[0] = A; o[1] = Bs; o[2] = R; o[3] = D; o[4] = U; }
+    } else {
+        if (lane == 0) { double *m = sh_sums[wave]; m[0] = A; m[1] = Bs; m[2] = R; m[3] = D; m[4] = U; }
+        __syncthreads();                                         // (wavefronts without a slice have left)
+        if (part == 0 && lane < kSliceVals) {
+            // the slice's other wavefronts: the next ones, or in the writer's workgroup the ones before
+            double sum = sh_sums[wave][lane];
+#pragma unroll
+            for (int q = 1; q < SPLIT; ++q) sum += sh_sums[writer ? wave - q : wave + q][lane];
+            o[lane] = sum;
+        }
     }
     WG_STAMP(g_stamps_slices, 8, wg, 7);                         // first wavefront's sums stored
 }
@@ -1706,11 +1721,38 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
     if (tid == 0) a.tok_out[b] = a.vocab_offset + (token < 0 ? 0 : token);
 }
 
+// Wavefronts that share a slice, and so workgroups of the slice launch.  Few slices leave the chip idle while single wavefronts
+// walk four chunks each: one chunk per wavefront, or two, then shorten the launch until its workgroups, each of which takes the
+// accept decisions again, get in each other's way.  One chunk up to two workgroups per compute unit, or where it adds none; two
+// up to two and a half.  Rows of more than 32 slices don't share two ways: they gain nothing there, and the rounds of binary32 rows lose.
+// Measured, us per round with one / two / four wavefronts per slice: V = 32000, one sequence, binary32, up to the stop position
+// 21.0 / 20.3 / 18.9; 32 sequences, bfloat16 26.1 / 24.8 / 24.1;
+// V = 8000, 128 sequences, binary32 24.2 / 22.9 / 21.6; V = 128256, 8 sequences, bfloat16 22.9 / 21.2 / 20.9.  Beyond 512
+// workgroups: V = 32000, 64 sequences, binary32 31.7 / 29.1 / 31.2; V = 50257, 48 sequences 34.9 / 34.0 / -; V = 128256, 16
+// sequences 28.7 / 29.8 / 30.7.  Beyond 640: V = 32000, bfloat16, 96 sequences 29.7 / 29.7 / 33.6, 128 sequences 33.4 / 34.5 / 39.9.
+inline int slice_split(int B, int nsl)
+{
+    auto wgs = [&](int split) { return (int64_t)B * ((nsl * split + kWavesPerWG - 1) / kWavesPerWG); };
+    if (wgs(4) <= 512 || wgs(4) == wgs(1)) return 4;
+    if ((wgs(2) <= 640 && nsl <= 32) || wgs(2) == wgs(1)) return 2;
+    return 1;
+}
+
+template <int TD, int DD, bool FUSED>
+void launch_slices(const VerifyArgs &a, hipStream_t st, Timing tm)
+{
+    const int split = slice_split(a.B, a.nsl);
+    const dim3 grid((a.nsl * split + kWavesPerWG - 1) / kWavesPerWG, a.B), block(kVBlock);         // (a context holds at most 65535 sequences)
+    if (split == 4) launch_kernel(verify_slices<TD, DD, FUSED, 4>, grid, block, st, tm, a);
+    else if (split == 2) launch_kernel(verify_slices<TD, DD, FUSED, 2>, grid, block, st, tm, a);
+    else launch_kernel(verify_slices<TD, DD, FUSED, 1>, grid, block, st, tm, a);
+}
+
 template <int TD, int DD>
 hipError_t launch_shard_typed(const ShardFinalArgs &a, int pass, hipStream_t st)
 {
     if (pass == 0) {
-        hipLaunchKernelGGL((verify_slices<TD, DD, false>), dim3((a.v.nsl + kWavesPerWG - 1) / kWavesPerWG, a.v.B), dim3(kVBlock), 0, st, a.v);
+        launch_slices<TD, DD, false>(a.v, st, Timing{});
         hipLaunchKernelGGL(shard_sums_kernel, dim3((a.v.B + kWavesPerWG - 1) / kWavesPerWG), dim3(kVBlock), 0, st, a);
     } else {
         hipLaunchKernelGGL((shard_locate<TD, DD>), dim3(a.v.B), dim3(kVBlock), 0, st, a);
@@ -1729,10 +1771,10 @@ hipError_t launch_shard_dispatch(const ShardFinalArgs &a, int pass, hipStream_t 
 template <int TD, int DD>
 hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool with_fin, int pass, hipStream_t st, Timing tm)
 {
-    dim3 grid12((a.nsl + kWavesPerWG - 1) / kWavesPerWG, a.B), block(kVBlock);         // (a context holds at most 65535 sequences)
+    const dim3 block(kVBlock);
     if (pass == 1) {
-        if (a.fused_head) launch_kernel(verify_slices<TD, DD, true>, grid12, block, st, tm, a);
-        else launch_kernel(verify_slices<TD, DD, false>, grid12, block, st, tm, a);
+        if (a.fused_head) launch_slices<TD, DD, true>(a, st, tm);
+        else launch_slices<TD, DD, false>(a, st, tm);
     }
     else {
         // workgroups that end the round: 32 sequences each (UCB, bandit_tail 1) or sixteen (Thompson Sampling, 2)

@@ -126,6 +126,25 @@ def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("B,V", [
+    (128, 8191), (129, 8191), (320, 8191), (321, 8191),          # four slices a row: four wavefronts share one, two, two, none
+    (102, 8200), (103, 8200),                                    # five: the last workgroup of two-way sharing has half its wavefronts idle
+    (16, 65536), (17, 65537), (17, 65535), (16, 66001),          # 32 and 33 slices
+    (600, 2048), (600, 2049), (700, 4096),                       # one and two slices: shared wherever that adds no workgroup
+])
+@pytest.mark.parametrize("dt,tt", [(bf16, bf16), (bf16, f32), (f32, f32)])
+def test_final_token_with_slices_shared_by_wavefronts(B, V, dt, tt):
+    K = 2 if B < 200 else 1
+    rnd = mixed_round(B, K, V, dt, tt, seed=B + V)
+    rnd["u_sample"][:3] = torch.tensor([2.0 ** -12, 0.5, 1.0 - 2.0 ** -24], device=DEV)
+    tp = binding.Tapout(B, K, V)
+    for fuse in (0, 1):
+        tp.set_option("fuse_head", fuse)
+        c = pu.check_round(tp, rnd)
+        # near ties: a few per thousand decisions at the tolerance of 1e-5; a cell edge within 1e-9 is a chance of about V 1e-9
+        assert c["icdf_flagged"] <= 1 and c["accept_flagged"] + c["stop_flagged"] <= 2 + 4 * B * K // 500
+
+
 @pytest.mark.parametrize("V", [2047, 2048, 8193, 10240, 133001])
 @pytest.mark.parametrize("dt", [f32, bf16])
 def test_exact_slice_weights_a_wavefront_per_slice(V, dt):
