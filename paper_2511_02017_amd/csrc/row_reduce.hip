@@ -210,57 +210,42 @@ struct ThreadState {
 };
 
 // ---- wavefront reductions with DPP -------------------------------------------
-// quad_perm [1,0,3,2] = 0xB1, quad_perm [2,3,0,1] = 0x4E, row_half_mirror = 0x141,
-// row_mirror = 0x140: after the four steps every lane of a 16-lane row holds the
-// row's result; the four rows are then combined through readlane.
-template <int CTRL>
-__device__ inline float dpp_f(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
-__device__ inline float lane_f(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-
+// quad_perm [1,0,3,2] = 0xB1, quad_perm [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140: after the four steps every
+// lane of a 16-lane row holds the row's result; row_bcast15 and row_bcast31 carry it on from row to row.
+template <int CTRL, int ROWS>
+__device__ inline float dpp_rows(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true)); }
+// Maximum over the 64 lanes, in a scalar register (bare instructions: see max3; a DPP operand is read two wait states after it was written).
 __device__ inline float wave_max(float v)
 {
-    v = fmaxf(v, dpp_f<0xB1>(v)); v = fmaxf(v, dpp_f<0x4E>(v));
-    v = fmaxf(v, dpp_f<0x141>(v)); v = fmaxf(v, dpp_f<0x140>(v));
-    return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
+        : "+v"(v));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
-__device__ inline float wave_sum(float v)
+// Sum over the 64 lanes; valid in the last lane.
+__device__ inline float wave_sum_last(float v)
 {
-    v += dpp_f<0xB1>(v); v += dpp_f<0x4E>(v); v += dpp_f<0x141>(v); v += dpp_f<0x140>(v);
-    return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
+    v += dpp_rows<0xB1, 0xf>(v); v += dpp_rows<0x4E, 0xf>(v); v += dpp_rows<0x141, 0xf>(v); v += dpp_rows<0x140, 0xf>(v);
+    v += dpp_rows<0x142, 0xa>(v);
+    v += dpp_rows<0x143, 0xc>(v);
+    return v;
 }
 __device__ inline int wave_min_i(int v)
 {
-    v = min(v, dpp_i<0xB1>(v)); v = min(v, dpp_i<0x4E>(v)); v = min(v, dpp_i<0x141>(v)); v = min(v, dpp_i<0x140>(v));
+    v = min(v, dpp_mov<0xB1>(v)); v = min(v, dpp_mov<0x4E>(v)); v = min(v, dpp_mov<0x141>(v)); v = min(v, dpp_mov<0x140>(v));
     return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
                min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
-// (largest, second largest counting duplicates) of the union of two such pairs
-__device__ inline void top2_merge(float &a1, float &a2, float b1, float b2)
-{
-    a2 = max3(fminf(a1, b1), a2, b2);
-    a1 = fmaxf(a1, b1);
-}
-__device__ inline void wave_top2(float &a1, float &a2)
-{
-    top2_merge(a1, a2, dpp_f<0xB1>(a1), dpp_f<0xB1>(a2));
-    top2_merge(a1, a2, dpp_f<0x4E>(a1), dpp_f<0x4E>(a2));
-    top2_merge(a1, a2, dpp_f<0x141>(a1), dpp_f<0x141>(a2));
-    top2_merge(a1, a2, dpp_f<0x140>(a1), dpp_f<0x140>(a2));
-    float r1 = lane_f(a1, 0), r2 = lane_f(a2, 0);
-    top2_merge(r1, r2, lane_f(a1, 16), lane_f(a2, 16));
-    top2_merge(r1, r2, lane_f(a1, 32), lane_f(a2, 32));
-    top2_merge(r1, r2, lane_f(a1, 48), lane_f(a2, 48));
-    a1 = r1; a2 = r2;
 }
 
 template <int DT> struct NegInfVec;
 template <> struct NegInfVec<TAPOUT_F32>  { static constexpr uint32_t word = 0xff800000u; };
 template <> struct NegInfVec<TAPOUT_BF16> { static constexpr uint32_t word = 0xff80ff80u; };
+
+__device__ inline float quad_sum(float v) { v += dpp_mov<0xB1>(v); return v + dpp_mov<0x4E>(v); }
 
 template <int DT, int U, bool CHECKED>
 __device__ inline void load_batch(u32x4 (&w)[U], const u32x4 *vp, int i, int end)
@@ -289,8 +274,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
     // and six wavefronts per SIMD instead of eight, which still beats two vectors at full occupancy
     // (measured; three, six and eight vectors and an explicit prefetch of the next batch are all slower).
     constexpr int U = kStreamU;
-    __shared__ float sh_f[6][kBlock / kWave];
-    __shared__ int sh_i[kBlock / kWave];
+    __shared__ u32x4 sh_rec[kBlock / kWave][2];
 
     const int row = b * a.KK + k;
     const int tid = threadIdx.x;
@@ -345,23 +329,39 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         }
         __builtin_amdgcn_s_setprio(3);      // finish the reduction promptly: the slot is wanted by the next workgroup
     }
+    // The token's logit, if this slice holds it (elements [e0, e1); every index of the row lies in exactly one slice): the first
+    // wavefront asks for it now and looks at it last (as the bits they are: widened in this branch, they would be waited for here).
+    uint32_t tok_bits = 0;
+    bool holds_tok = false;
+    {
+        const int t = __builtin_amdgcn_readfirstlane(tid < kWave ? tk : -1);
+        const int e0 = split == 0 ? 0 : head + v0 * VEC, e1 = split == a.nsplit - 1 ? a.V : head + v1e * VEC;
+        if (t >= e0 && t < e1) {
+            // the row's address once more, from scalar registers (the zero is opaque to the compiler): holding the
+            // one from the top of the kernel in vector registers through the loop costs the draft pass a wavefront per SIMD
+            int zero;
+            asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+            const char *rp = (const char *)a.base + ((int64_t)(b + zero) * a.stride_b + (int64_t)k * a.stride_k) * Elem<DT>::size;
+            if constexpr (DT == TAPOUT_F32) tok_bits = ((const uint32_t *)rp)[t]; else tok_bits = ((const uint16_t *)rp)[t];
+            holds_tok = true;
+        }
+    }
     if (split == a.nsplit - 1 && tid < tail) {
         int32_t j = head + nvec * VEC + tid;
         st.fold_single(load_elem<DT>(rowp, j), j);
     }
 
     // ---- workgroup reduction ----
+    // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
+    // What a slice costs besides its loads is this chain of instructions (a wavefront issues one in about nine cycles here), in
+    // every workgroup of a launch and, in small ones, in the open: us per pass, with the reduction
+    // it replaces (every thread to the workgroup maximum first, three barriers, one thread merging) and with this: V = 128256, 64 sequences,
+    // K = 8 up to the stop position 61.7 / 60.4, V = 50257, 48 sequences 57.9 / 56.5, V = 32000, one sequence 19.7 / 19.4.
     const int wave = tid / kWave, lane = tid % kWave;
-    float wm = wave_max(st.v1);
-    if (lane == 0) sh_f[0][wave] = wm;
-    __syncthreads();
-    float M = fmaxf(fmaxf(sh_f[0][0], sh_f[0][1]), fmaxf(sh_f[0][2], sh_f[0][3]));
-    __syncthreads();
-    // bring the thread sums to the workgroup reference (exact scaling), then plain sums
-    float Rb = ref_of_max(M);
-    float d = Rb - st.R;
-    int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
-    float s = ldexpf(st.s, -di);
+    const float Mw = wave_max(st.v1), Rw = ref_of_max(Mw);
+    const float d = Rw - st.R;
+    const int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
+    float s = ldexpf(st.s, -di);                                // exact scaling
     float t = 0.0f, s_hi = 0.0f, t_hi = 0.0f;
     if constexpr (FULL) {
         t = ldexpf(st.t - d * st.s, -di);
@@ -369,65 +369,67 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         t_hi = ldexpf(st.t_hi - d * st.s_hi, -di);
     }
     if (st.v1 == -INFINITY && !(st.s != st.s)) { s = 0.0f; t = 0.0f; s_hi = 0.0f; t_hi = 0.0f; }   // thread saw nothing finite
-    float a1 = st.v1, a2 = st.v2;
-    if constexpr (FULL) wave_top2(a1, a2);
-    // the wavefront's vector with the first maximum; FULL: the thread that met it keeps its set-apart batch out of
-    // the wavefront's sums and publishes it on its own (every other thread's set-apart batch is ordinary data)
-    const int cw = wave_min_i(st.v1 == M ? st.cand : 0x7fffffff);
-    float hs = 0.0f, ht = 0.0f;
-    if constexpr (FULL) {
-        const bool owner = st.v1 == M && st.cand == cw && cw != 0x7fffffff;
-        hs = wave_sum(owner ? s_hi : 0.0f);              // one term and zeros: exact
-        ht = wave_sum(owner ? t_hi : 0.0f);
-        s += owner ? 0.0f : s_hi;
-        t += owner ? 0.0f : t_hi;
+    // the wavefront's vector with its first maximum: one thread's, unless several met that value
+    const uint64_t met = __builtin_amdgcn_ballot_w64(st.v1 == Mw);
+    int owner = __builtin_ctzll(met), cw = __builtin_amdgcn_readlane(st.cand, owner);
+    if (met & (met - 1)) {
+        cw = wave_min_i(st.v1 == Mw ? st.cand : 0x7fffffff);
+        owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(st.v1 == Mw && st.cand == cw));
     }
-    s = wave_sum(s);
-    if constexpr (FULL) t = wave_sum(t);
-    if (lane == 0) {
-        sh_f[0][wave] = s; sh_f[1][wave] = t; sh_f[2][wave] = a1; sh_f[3][wave] = a2; sh_f[4][wave] = hs; sh_f[5][wave] = ht;
-        sh_i[wave] = cw;
+    // FULL: that thread's set-apart batch stays out of the wavefront's sums and goes into the record on its own (every other
+    // thread's is ordinary data); its second maximum counts, of the others the maximum does
+    float hs = 0.0f, ht = 0.0f, v2w = -INFINITY;
+    if constexpr (FULL) {
+        hs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s_hi), owner));
+        ht = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t_hi), owner));
+        s += lane == owner ? 0.0f : s_hi;
+        t += lane == owner ? 0.0f : t_hi;
+        v2w = wave_max(lane == owner ? st.v2 : st.v1);
+        t = wave_sum_last(t);
+    }
+    s = wave_sum_last(s);
+    if (lane == kWave - 1) {
+        sh_rec[wave][0] = u32x4{__float_as_uint(Mw), __float_as_uint(s), (uint32_t)cw, __float_as_uint(v2w)};
+        if constexpr (FULL) sh_rec[wave][1] = u32x4{__float_as_uint(t), __float_as_uint(hs), __float_as_uint(ht), 0u};
     }
     __syncthreads();
-    if (tid == 0) {
+    if (wave == 0) {
+        constexpr int kBits = 2;                                // four records, one on each lane of a quad
+        static_assert(kBlock / kWave == 1 << kBits, "a record per wavefront");
+        const u32x4 r0 = sh_rec[lane & 3][0];
+        const float Ml = __uint_as_float(r0.x), M = lanes_max(Ml, 0, kBits);
+        const bool met_it = Ml == M;
+        const float dl = ref_of_max(M) - ref_of_max(Ml);
+        const int dil = (int)fminf(fmaxf(dl, -1.0e9f), 1.0e9f);
         Partial p;
         p.v1 = M;
-        p.S = (sh_f[0][0] + sh_f[0][1]) + (sh_f[0][2] + sh_f[0][3]);
-        p.T = (sh_f[1][0] + sh_f[1][1]) + (sh_f[1][2] + sh_f[1][3]);
-        float b1 = sh_f[2][0], b2 = sh_f[3][0];
-#pragma unroll
-        for (int w = 1; w < kBlock / kWave; ++w) top2_merge(b1, b2, sh_f[2][w], sh_f[3][w]);
-        p.v2 = b2;
-        p.cand = min(min(sh_i[0], sh_i[1]), min(sh_i[2], sh_i[3]));
+        p.cand = lanes_min(met_it ? (int)r0.z : 0x7fffffff, 0, kBits);
+        float S = ldexpf(__uint_as_float(r0.y), -dil);
+        p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0; p.pad[2] = 0;
         if constexpr (FULL) {
+            const u32x4 r1 = sh_rec[lane & 3][1];
+            const float hs0 = __uint_as_float(r1.y), Hs = ldexpf(hs0, -dil), Ht = ldexpf(__uint_as_float(r1.z) - dl * hs0, -dil);
+            float T = ldexpf(__uint_as_float(r1.x) - dl * __uint_as_float(r0.y), -dil);
+            if (Ml == -INFINITY) T = 0.0f;                      // (a record without a finite maximum: d is no distance)
             // The batch with the slice's first maximum stays out (the epilogue adds its elements back from the
             // logits); the set-apart batches of the other wavefronts are ordinary data.  A NaN or an infinity
             // inside the left-out batch must still poison the sums: x - x is 0 for finite x only.
-            float left_out = 0.0f;
-#pragma unroll
-            for (int w = 0; w < kBlock / kWave; ++w) {
-                const bool holds = sh_i[w] == p.cand;
-                p.S += holds ? (sh_f[4][w] - sh_f[4][w]) : sh_f[4][w];
-                p.T += holds ? 0.0f : sh_f[5][w];
-                left_out = holds ? sh_f[4][w] : left_out;
-            }
+            const bool holds = met_it && (int)r0.z == p.cand;
+            S += holds ? Hs - Hs : Hs;
+            T += holds || Ml == -INFINITY ? 0.0f : Ht;
+            p.v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, 0, kBits);
+            p.T = quad_sum(T);
             // the left-out batch's own sum (same reference): S + this is the slice's sum over every element, to
             // binary32 precision, for a reader that wants the row's lse before the epilogue has run
-            p.pad[1] = __float_as_int(left_out);
+            p.pad[1] = __float_as_int(quad_sum(holds ? Hs : 0.0f));
         }
-        p.pad[0] = 0x7fc00000; if constexpr (!FULL) p.pad[1] = 0;
-        p.pad[2] = 0;
-        // elements of this slice: [e0, e1); every index of the row lies in exactly one slice
-        const int e0 = split == 0 ? 0 : head + v0 * VEC, e1 = split == a.nsplit - 1 ? a.V : head + v1e * VEC;
-        if (tk >= e0 && tk < e1) {
-            // the row's address once more, from scalar registers (the zero is opaque to the compiler): holding the
-            // one from the top of the kernel in vector registers through the loop costs the draft pass a wavefront per SIMD
-            int zero;
-            asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
-            const char *rp = (const char *)a.base + ((int64_t)(b + zero) * a.stride_b + (int64_t)k * a.stride_k) * Elem<DT>::size;
-            p.pad[0] = __float_as_int(load_elem<DT>(rp, tk));
+        p.S = quad_sum(S);
+        p.pad[0] = holds_tok ? (int)(DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000;
+        if (tid == 0) {
+            u32x4 *o = (u32x4 *)(a.out + (int64_t)row * a.nsplit + split);
+            o[0] = u32x4{__float_as_uint(p.v1), __float_as_uint(p.S), __float_as_uint(p.T), __float_as_uint(p.v2)};
+            o[1] = u32x4{(uint32_t)p.cand, (uint32_t)p.pad[0], (uint32_t)p.pad[1], 0u};
         }
-        a.out[(int64_t)row * a.nsplit + split] = p;
     }
 }
 

@@ -126,6 +126,28 @@ def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("dt,vec", [(f32, 4), (bf16, 8)])
+@pytest.mark.parametrize("off", [0, 3])
+def test_maxima_met_by_several_threads(dt, vec, off):
+    """The first maximum, its batch and the second maximum when a value is met twice: inside a vector, by neighbouring threads, by two
+    wavefronts, in two batches of a thread, in two slices; and rows with no other finite element."""
+    wave, batch = 64 * vec, 1024 * vec
+    V = 3 * batch + 5
+    pairs = [(0, 1), (vec, 2 * vec), (5, wave + 2), (7, 3 * wave), (6, batch + 6), (vec + 1, 2 * batch + vec), (V - 1, V - 2), (3, 70 * vec)]
+    B = len(pairs)
+    rnd = mixed_round(B, 2, V + off, dt, dt, seed=off)
+    rnd["draft"], rnd["target"] = rnd["draft"][:, :, off:], rnd["target"][:, :, off:]          # rows that start off a vector
+    for b, (i, j) in enumerate(pairs):
+        for t in (rnd["draft"], rnd["target"]):
+            t[b, 0, [i, j]] = 9.0
+            t[b, 1] = float("-inf")
+            t[b, 1, [i, j]] = torch.tensor([2.0, 2.0 if b & 1 else 1.5], dtype=dt, device=DEV)
+        rnd["draft_tok"][b] = torch.tensor([i, j], dtype=torch.int32)
+    rnd["u_accept"] = torch.full((B, 2), 0.3, device=DEV)                                      # p / q is about 1 at these tokens: no near tie
+    c = pu.check_round(binding.Tapout(B, 2, V), rnd)
+    assert c["accept_flagged"] == 0 and c["icdf_flagged"] <= 1
+
+
 @pytest.mark.parametrize("B,V", [
     (128, 8191), (129, 8191), (320, 8191), (321, 8191),          # four slices a row: four wavefronts share one, two, two, none
     (102, 8200), (103, 8200),                                    # five: the last workgroup of two-way sharing has half its wavefronts idle
