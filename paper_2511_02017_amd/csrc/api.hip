@@ -18,6 +18,7 @@ struct tapout_ctx {
     Partial *part = nullptr;      size_t part_cap = 0;       // slice partials of the draft pass (and of a shard pass)
     Partial *part_t = nullptr;                                 // slice partials of the target pass (same capacity)
     double *part1 = nullptr, *part2 = nullptr;                // slice sums of the inverse CDFs
+    double *draw_sums = nullptr;  size_t draw_cap = 0;         // sums of exponentials of the draft-token draw (see draw_sums_needed)
     double *sampled_lse = nullptr;                             // [max_batch, max_k] lse of the draft rows (draft-token sampling only)
     JobRecord *jobs = nullptr;                                 // per sequence: what its final token is drawn from, and its band list
     uint32_t *flags_ws = nullptr;
@@ -193,6 +194,13 @@ Slices choose_slices(const tapout_ctx *ctx, int64_t rows, int KK, int V, int dty
     return choose_slices(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, KK, V, dtype);
 }
 
+// Sums that the draft pass leaves for the draft-token draw, and how many a context has room for: a sum per wavefront, vector
+// of a batch and batch of every slice; n slices of `per` vectors are no more than vecs / kBatchVecs + 2 n + 1 batches, since
+// `per` exceeds an even share by less than a batch and 64 vectors.
+constexpr size_t kDrawSumsPerBatch = kStreamU * (kBlock / kWave);
+size_t draw_sums_needed(int64_t rows, int nsplit, int per) { return (size_t)rows * nsplit * draw_batches(per) * kDrawSumsPerBatch; }
+size_t draw_sums_room(size_t rows, size_t partials, int V) { return (rows * ((size_t)V / 4 / kBatchVecs + 2) + 3 * partials) * kDrawSumsPerBatch; }
+
 // ---- device address of the static scratch, per device ------------------------------------------------
 constexpr size_t kStaticPartials = TAPOUT_STATIC_MAX_PARTIALS;
 constexpr int kMaxDevices = 64;
@@ -345,10 +353,10 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     by_bytes_max = by_bytes_max < 1 ? 1 : (by_bytes_max > kStageCap ? kStageCap : by_bytes_max);
     c->part_cap = rows * (size_t)by_bytes_max + kMaxWgsTarget;   // rows * nsplit under either rule of choose_slices
     c->positions = cfg->granularity == TAPOUT_TOKEN_LEVEL ? cfg->max_k : 1;
+    if (cfg->draft_sampling) c->draw_cap = draw_sums_room((size_t)cfg->max_batch * cfg->max_k, c->part_cap, cfg->vocab);
     const size_t nstate = (size_t)cfg->n_bandits * c->positions * cfg->n_arms;
     c->nsl_max = (cfg->vocab + kSampleSlice - 1) / kSampleSlice;
-    // slice sums: five per slice of a sequence's row pair (verification), or one per slice of a draft row (draft-token sampling)
-    const size_t nsums = (size_t)cfg->max_batch * (cfg->draft_sampling && cfg->max_k > 5 ? cfg->max_k : 5);
+    const size_t nsums = (size_t)cfg->max_batch * 5;             // five per slice of a sequence's row pair
     // 2^(k/256), then exp(x) of every bfloat16 x with 2^-12 <= |x| < 63.5: entry idx (x > 0) or pairs + idx (x < 0),
     // idx = 1 + (magnitude bits - (115 << 7)); idx 0 stands for all smaller magnitudes and holds NaN (the kernels
     // notice and compute), the last idx for all larger ones and holds zeros
@@ -373,6 +381,7 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
            && hipMalloc(&c->part_t, c->part_cap * sizeof(Partial)) == hipSuccess
            && hipMalloc(&c->part1, nsums * c->nsl_max * sizeof(double)) == hipSuccess
            && hipMalloc(&c->part2, (size_t)cfg->max_batch * c->nsl_max * sizeof(double)) == hipSuccess
+           && (!cfg->draft_sampling || hipMalloc(&c->draw_sums, c->draw_cap * sizeof(double)) == hipSuccess)
            && (!cfg->draft_sampling || hipMalloc(&c->sampled_lse, (size_t)cfg->max_batch * cfg->max_k * sizeof(double)) == hipSuccess)
            && hipMalloc(&c->exp_table, table.size() * sizeof(double)) == hipSuccess
            && hipMemcpy(c->exp_table, table.data(), table.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess
@@ -416,7 +425,7 @@ tapout_status tapout_destroy(tapout_ctx *ctx)
     profile_release(ctx);
     (void)hipFree(ctx->part); (void)hipFree(ctx->part_t); (void)hipFree(ctx->part1); (void)hipFree(ctx->part2);
     (void)hipFree(ctx->jobs); (void)hipFree(ctx->flags_ws); (void)hipFree(ctx->arm_played);
-    (void)hipFree(ctx->exp_table); (void)hipFree(ctx->sampled_lse);
+    (void)hipFree(ctx->exp_table); (void)hipFree(ctx->sampled_lse); (void)hipFree(ctx->draw_sums);
     (void)hipFree(ctx->sum_r); (void)hipFree(ctx->sum_r2); (void)hipFree(ctx->count);
     (void)hipFree(ctx->prev_entropy); (void)hipFree(ctx->accept_rate); (void)hipFree(ctx->lambda); (void)hipFree(ctx->round_entropy);
     delete ctx;
@@ -545,17 +554,24 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
         // the round was drafted under from a copy that the streaming pass, two launches earlier, leaves here.
         if (arm && ctx->positions == 1) { r.arm_src = arm; r.arm_dst = ctx->arm_played; }
     }
-    hipError_t e = pair ? stream_pair(ctx, r, draft->dtype, *pair, st)
-                        : timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_row_reduce(r, draft->dtype, true, st, tm); });
-    if (e != hipSuccess) return hip_fail(ctx, e, "draft pass launch");
+    hipError_t e;
     SampleArgs sa{};
     if (u_draft) {
+        DrawArgs d{};
+        d.sums = ctx->draw_sums; d.exp_table = ctx->exp_table; d.nb = draw_batches(r.per);
+        d.vflags = ctx->exp_lookup ? 0 : kVerifyNoExpTable;
+        if (draw_sums_needed(rows, nsplit, r.per) > ctx->draw_cap) return fail(ctx, TAPOUT_EINVAL, "internal: draw buffer too small");
         sa.base = draft->ptr; sa.dtype = draft->dtype; sa.stride_b = draft->stride_b; sa.stride_k = draft->stride_k;
-        sa.vflags = ctx->exp_lookup ? 0 : kVerifyNoExpTable;
-        sa.B = B; sa.K = K; sa.V = V; sa.nsplit = nsplit; sa.nsl = (V + kSampleSlice - 1) / kSampleSlice;
+        sa.vflags = d.vflags;
+        sa.B = B; sa.K = K; sa.V = V; sa.nsplit = nsplit; sa.per = r.per; sa.nb = d.nb;
         sa.part = ctx->part; sa.k_len = k_len; sa.u = u_draft; sa.tok = sampled_tok; sa.logq_tok = logq_tok;
-        sa.sums = ctx->part1; sa.lse = ctx->sampled_lse; sa.exp_table = ctx->exp_table;
+        sa.sums = ctx->draw_sums; sa.exp_table = ctx->exp_table;
+        e = timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_stream_draw(r, draft->dtype, d, st, tm); });
+    } else {
+        e = pair ? stream_pair(ctx, r, draft->dtype, *pair, st)
+                 : timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_row_reduce(r, draft->dtype, true, st, tm); });
     }
+    if (e != hipSuccess) return hip_fail(ctx, e, "draft pass launch");
     DraftFinalArgs f{};
     f.base = draft->ptr; f.dtype = draft->dtype; f.stride_b = draft->stride_b; f.stride_k = draft->stride_k;
     f.B = B; f.K = K; f.V = V; f.nsplit = nsplit; f.per = r.per; f.part = ctx->part;
@@ -572,10 +588,15 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
     }
     if (defer) { *defer = f; *defer_nsplit = nsplit; return TAPOUT_OK; }
     if (u_draft) {
-        // the epilogue waits for no token (their log q is formed where they are found) and rides in the slice launch
-        f.draft_tok = nullptr; f.logq_tok = nullptr; f.sampled_lse = ctx->sampled_lse;
-        e = timed(ctx, TAPOUT_PROFILE_SAMPLE_SLICES, [&](Timing tm) { return launch_sample(sa, f, 0, st, tm); });
-        if (e == hipSuccess) e = timed(ctx, TAPOUT_PROFILE_SAMPLE_LOCATE, [&](Timing tm) { return launch_sample(sa, f, 1, st, tm); });
+        // The epilogue waits for no token (their log q is formed where they are found): it rides in their launch, whose
+        // workgroups form their rows' lse themselves.  Many rows, and very many slices: a launch of its own, which leaves the lse.
+        f.draft_tok = nullptr; f.logq_tok = nullptr; f.sampling = 1;
+        const bool own = sample_own_lse(B, K, nsplit);
+        if (!own) {
+            f.sampled_lse = ctx->sampled_lse; sa.lse = ctx->sampled_lse;
+            e = timed(ctx, TAPOUT_PROFILE_DRAFT_FINALIZE, [&](Timing tm) { return launch_draft_finalize(f, st, tm); });
+        }
+        if (e == hipSuccess) e = timed(ctx, TAPOUT_PROFILE_SAMPLE_LOCATE, [&](Timing tm) { return launch_sample(sa, own ? &f : nullptr, st, tm); });
         return e == hipSuccess ? TAPOUT_OK : hip_fail(ctx, e, "draft sampling launch");
     }
     e = timed(ctx, TAPOUT_PROFILE_DRAFT_FINALIZE, [&](Timing tm) { return launch_draft_finalize(f, st, tm); });

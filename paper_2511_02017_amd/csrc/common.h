@@ -113,8 +113,9 @@ struct DraftFinalArgs {
     const double *lambda;         // [B, n_arms] AdaEDL thresholds
     double adaedl_gamma;
     float *round_entropy;         // [B, K] entropies of this draft, kept for the state update
-    // the library draws the draft tokens after this epilogue: it leaves each row's lse here (in double) for their log q, and a
-    // bad row gets no token (BAD_TOKEN with BAD_ROW); else NULL
+    // the library draws the draft tokens: a bad row gets none (BAD_TOKEN with BAD_ROW); sampled_lse, or NULL: where to leave each
+    // row's lse, in double, for their log q
+    int32_t sampling;
     double *sampled_lse;
     // vocabulary-sharded input: part holds the records of `shards` vocabulary shards, shard-major [shards, B*K], instead
     // of slice partials [B*K, nsplit] (then nsplit = shards; the argmax of a record is exact and global, the logit of
@@ -218,22 +219,37 @@ inline bool own_q_shape(int K, int nsplit_target, int nsplit_draft)
     return lane_merge_fits(K + 1, nsplit_target) && lane_merge_fits(K, nsplit_draft);
 }
 
-// Draft-token sampling (Algorithm 1, the sampling step of the draft loop): the inverse CDF of every live draft row, from
-// the partials of the draft pass (the rows' maxima) and the logits.
+// Draft-token sampling (Algorithm 1, the sampling step of the draft loop): the inverse CDF of every live draft row.  The draft
+// pass leaves the sums of exponentials it runs over beside its partials; a launch behind it finds the tokens.
+// Sums of exp(x) in the logits' own scale are good for rows whose maximum lies in these bounds (bfloat16 rows, whose values from
+// -63.5 down count as 0, from kDrawLowTab on); others are summed again where their token is drawn.
+constexpr float kDrawLow = -700.0f, kDrawHigh = 700.0f, kDrawLowTab = -14.0f;
+// Draw slices of a streaming slice of `per` vectors: kStreamU, of kBlock vectors each, in every batch it takes.
+inline int draw_batches(int per) { return (per + kBlock * kStreamU - 1) / (kBlock * kStreamU); }
+struct DrawArgs {
+    double *sums;                 // [B * K, nsplit, nb, kStreamU, wavefronts of a workgroup]
+    const double *exp_table;
+    int32_t vflags;               // kVerifyNoExpTable
+    int32_t nb;                   // batches per slice
+    int32_t turns, step_b, step_k, step_s;      // (filled in by the launcher) slices per workgroup part, and the step from one to the next
+};
+// The draft pass (launch_row_reduce, full) with these sums.
+hipError_t launch_stream_draw(const RowReduceArgs &a, int dtype, DrawArgs d, hipStream_t st, Timing tm);
 struct SampleArgs {
-    const void *base; int32_t dtype; int32_t vflags; int64_t stride_b, stride_k;      // vflags: kVerifyNoExpTable
-    int32_t B, K, V, nsplit;      // nsplit: slices per row of the streaming pass
-    int32_t nsl;                  // slices per row of this pass (kSampleSlice elements each)
-    int32_t n_waves;              // wavefronts of the slice launch, and the step from one of a wavefront's slices to its next:
-    int32_t step_b, step_k, step_s;   // n_waves = (step_b * K + step_k) * nsl + step_s
+    const void *base; int32_t dtype; int32_t vflags; int64_t stride_b, stride_k;
+    int32_t B, K, V, nsplit, per, nb;      // how the draft pass cut the rows
     const Partial *part; const int32_t *k_len; const float *u;
     int32_t *tok; float *logq_tok;    // [B, K] token of each live row (-1: bad row) and its log q (or NULL)
-    double *sums;                 // [B * K, nsl]  sum of exp(x - row maximum) over each slice
-    const double *lse;            // [B * K] from the epilogue
+    double *sums;                 // DrawArgs::sums
+    const double *lse;            // [B * K] from the epilogue, or NULL: it runs beside this launch, and each row forms its own
     const double *exp_table;
 };
-// pass 0: slice sums (fills in n_waves and the steps), and the draft epilogue `fin` beside them in one launch; 1: tokens.
-hipError_t launch_sample(SampleArgs a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm);
+// Tokens.  fin: the draft epilogue, to run in the same launch (a.lse NULL; where sample_own_lse holds), or NULL.
+hipError_t launch_sample(const SampleArgs &a, const DraftFinalArgs *fin, hipStream_t st, Timing tm);
+// Every row forms its lse itself while that costs no second round of workgroups (three are resident per compute unit: the epilogue's
+// LDS and registers), and its pieces fit a wavefront.  (us: 512 rows 7.4 in one launch; 2400 rows 22.7, apart 5.4 + 13.1; one sequence of
+// 100 rows 11.5, apart 11.4 + 4.2.)
+inline bool sample_own_lse(int B, int K, int nsplit) { return (int64_t)B * (K + 1) <= 768 && nsplit <= kWave; }
 
 // Final token over vocabulary shards (see tapout_shard_final_sums / tapout_shard_final_token).  The VerifyArgs
 // describe this shard's column slices (V = its width, nsl = its slices, jobs / part1 / part2 of the context).

@@ -45,7 +45,7 @@ __device__ inline RowOut emit_row(const DraftFinalArgs &a, int64_t i, const RowT
     float lse, p2;
     double lse_d = NAN;
     if (__builtin_expect(r.bad, 0)) {
-        o.flags = TAPOUT_FLAG_BAD_ROW | (a.sampled_lse ? TAPOUT_FLAG_BAD_TOKEN : 0u);
+        o.flags = TAPOUT_FLAG_BAD_ROW | (a.sampling ? TAPOUT_FLAG_BAD_TOKEN : 0u);
         lse = o.H = o.p1 = p2 = o.margin = NAN;
     } else {
         const RowSignals g = row_signals(r, a.V > 1);
@@ -75,6 +75,55 @@ __device__ inline bool stateful_fires(const DraftFinalArgs &a, int b, int arm, i
     return adaedl_fires(a.adaedl_gamma, a.lambda ? a.lambda[(int64_t)b * a.n_arms + arm] : (double)threshold, H);
 }
 
+// A row on its lanes: from the partial (w0, w1) of this lane's piece, if it has one (mine), to the statistics of the row, the
+// same bits in every one of the row's 2^gsh lanes.  u: which of the piece's lanes this is, g: the piece's place in its row.  The
+// second memory round trip: token_logit() and this lane's vectors of the left-out batch.
+template <bool SHARDED, int USH, class TokenLogit>
+__device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, bool mine, int u, int gsh, TokenLogit token_logit)
+{
+    constexpr int NV = kStreamU >> USH;                               // vectors per lane
+    const float v1 = mine ? __uint_as_float(w0.x) : -INFINITY;
+    float S = __uint_as_float(w0.y), T = __uint_as_float(w0.z), v2 = __uint_as_float(w0.w);
+    int32_t cand = (int32_t)w1.x;
+    if (!mine || (v1 == -INFINITY && !(S != S))) { S = 0.0f; T = 0.0f; v2 = -INFINITY; cand = 0x7fffffff; }     // nothing in it
+    float xt = token_logit();
+    BatchVecs<NV> bt{};
+    if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, a.dtype, a.V, cand, u * NV, a.part);
+    // the row's maximum, second maximum and the piece that holds its first maximum
+    float M = v1;
+    lanes_top2(M, v2, USH, gsh);
+    const bool holds = v1 == M && cand != 0x7fffffff;
+    const int32_t first = lanes_min(holds ? cand : 0x7fffffff, USH, gsh);
+    const bool wins = holds && cand == first;
+    const float R = ref_of_max(M);
+    const float d = R - ref_of_max(v1);                           // an integer, >= 0 for a piece that holds anything
+    const int di = (int)fminf(fmaxf(d, -4000.0f), 4000.0f);       // 2^-4000 underflows to 0 as it should
+    double Sd = u == 0 ? ldexp((double)S, -di) : 0.0;             // exact power-of-two scaling
+    double Td = u == 0 ? ldexp((double)T - (double)d * (double)S, -di) : 0.0;
+    if (S == 0.0f && T == 0.0f) { Sd = 0.0; Td = 0.0; }           // (0 * inf)
+    int32_t idx = 0x7fffffff;
+    if constexpr (SHARDED) {
+        // a record leaves its maximum out: an ordinary term here unless it is the row's first maximum
+        idx = wins ? cand : 0x7fffffff;
+        if (!wins && v1 > -INFINITY) {
+            const float y = __builtin_fmaf(v1, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
+            Sd += (double)e;
+            Td += (double)e * (double)fmaxf(y, -200.0f);
+        }
+        xt = lanes_max(xt, USH, gsh);
+    } else {
+        // the batch's elements in the row's reference, all but the row's first maximum
+        const BatchExtra x = a.dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
+        Sd += (double)x.sa; Td += (double)x.ta; idx = x.idx;
+    }
+    Piece t;
+    t.M = M; t.v2 = v2; t.xt = xt;
+    t.idx = lanes_min(idx, 0, gsh);
+    lanes_sum2(Sd, Td, 0, gsh);
+    t.S = Sd; t.T = Td;
+    return t;
+}
+
 // ---- lane path: few rows and slices (see lane_merge_shift) -----------------------------------------
 // A wavefront of these small kernels executes an instruction about every nine cycles whatever it is, so what counts is
 // the number of instructions from the first request to the last store.  Every (row, slice) piece has 2^USH lanes of its
@@ -86,7 +135,7 @@ __device__ inline bool stateful_fires(const DraftFinalArgs &a, int b, int arm, i
 template <bool SHARDED, int USH>
 __device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b, unsigned char *lds, const int msh)
 {
-    constexpr int U = 1 << USH, NV = kStreamU >> USH;                 // lanes per piece, vectors per lane
+    constexpr int U = 1 << USH;                                       // lanes per piece
     float *sh_H = (float *)lds;                                       // [64] entropies of the sequence (stateful rules)
     uint8_t *sh_dec = lds + 4 * kWave, *sh_flag = sh_dec + kWave;     // [64] each: decisions, flags
     const int K = a.K, tid = threadIdx.x, gsh = msh + USH;            // 2^gsh lanes per row
@@ -117,50 +166,12 @@ __device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b
         asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(arm_k), "v"(kb), "v"(arm), "v"(H_carry));
         if (row0 == 0) { kb = kb > K ? K : (kb < 0 ? 0 : kb); arm = __builtin_amdgcn_readfirstlane(arm); }
         const bool live = row < kb, mine = live && sl < a.nsplit;     // rows beyond k_len hold stale partials
-        const float v1 = mine ? __uint_as_float(w0.x) : -INFINITY;
-        float S = __uint_as_float(w0.y), T = __uint_as_float(w0.z), v2 = __uint_as_float(w0.w);
-        int32_t cand = (int32_t)w1.x;
-        if (!mine || (v1 == -INFINITY && !(S != S))) { S = 0.0f; T = 0.0f; v2 = -INFINITY; cand = 0x7fffffff; }     // nothing in it
-        // Second round trip: the token's logit, this lane's vectors of the left-out batch.
-        float xt = NAN;
-        if constexpr (SHARDED) { if (mine) xt = __uint_as_float(w1.y); }      // the shard that owns the token sent its logit, the others NaN
-        else if (want_tok && live && tok >= 0 && tok < a.V) xt = load_elem_rt(row_p, a.dtype, tok);
-        BatchVecs<NV> bt{};
-        if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, a.dtype, a.V, cand, u * NV, a.part);
-        // the row's maximum, second maximum and the piece that holds its first maximum
-        float M = v1;
-        lanes_top2(M, v2, USH, gsh);
-        const bool holds = v1 == M && cand != 0x7fffffff;
-        const int32_t first = lanes_min(holds ? cand : 0x7fffffff, USH, gsh);
-        const bool wins = holds && cand == first;
-        const float R = ref_of_max(M);
-        const float d = R - ref_of_max(v1);                           // an integer, >= 0 for a piece that holds anything
-        const int di = (int)fminf(fmaxf(d, -4000.0f), 4000.0f);       // 2^-4000 underflows to 0 as it should
-        double Sd = u == 0 ? ldexp((double)S, -di) : 0.0;             // exact power-of-two scaling
-        double Td = u == 0 ? ldexp((double)T - (double)d * (double)S, -di) : 0.0;
-        if (S == 0.0f && T == 0.0f) { Sd = 0.0; Td = 0.0; }           // (0 * inf)
-        int32_t idx = 0x7fffffff;
-        if constexpr (SHARDED) {
-            // a record leaves its maximum out: an ordinary term here unless it is the row's first maximum
-            idx = wins ? cand : 0x7fffffff;
-            if (!wins && v1 > -INFINITY) {
-                const float y = __builtin_fmaf(v1, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
-                Sd += (double)e;
-                Td += (double)e * (double)fmaxf(y, -200.0f);
-            }
-            xt = lanes_max(xt, USH, gsh);
-        } else {
-            // the batch's elements in the row's reference, all but the row's first maximum
-            const BatchExtra x = a.dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
-            Sd += (double)x.sa; Td += (double)x.ta; idx = x.idx;
-        }
-        Piece t;
-        t.M = M; t.v2 = v2; t.xt = xt;
-        t.idx = lanes_min(idx, 0, gsh);
-        lanes_sum2(Sd, Td, 0, gsh);
-        t.S = Sd; t.T = Td;
+        const Piece t = row_on_lanes<SHARDED, USH>(a, g, w0, w1, mine, u, gsh, [&]() {
+            if constexpr (SHARDED) return mine ? __uint_as_float(w1.y) : NAN;     // the shard that owns the token sent its logit, the others NaN
+            else return want_tok && live && tok >= 0 && tok < a.V ? load_elem_rt(row_p, a.dtype, tok) : NAN;
+        });
         if (live && (tid & ((1 << gsh) - 1)) == 0) {
-            const RowOut o = emit_row(a, i, row_total<true>(t), want_tok, tok, xt);
+            const RowOut o = emit_row(a, i, row_total<true>(t), want_tok, tok, t.xt);
             sh_flag[row] = (uint8_t)o.flags;
             if (a.arm) {
                 if (!tok_mode) arm_k = arm;
@@ -317,6 +328,9 @@ __device__ inline void draft_finalize_staged(const DraftFinalArgs &a, const int 
     }
 }
 
+// log2 of the lanes per piece of a sequence of so many (row, slice) pieces.
+__device__ inline int draft_lanes_shift(int pieces) { return pieces > kFinalBlock / 2 ? 0 : (pieces > kFinalBlock / 4 ? 1 : 2); }
+
 // The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.
 template <bool SHARDED>
 __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
@@ -324,9 +338,9 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
     __shared__ __align__(16) unsigned char lds[sizeof(Partial) * kStageCap + 5 * kScanCap + 16];
     const int msh = lane_merge_shift(a.K, a.nsplit), pieces = msh < 0 ? 0 : a.K << msh;
     if (__builtin_expect(msh < 0, 0)) draft_finalize_staged<SHARDED>(a, b, lds);
-    else if (SHARDED || pieces > kFinalBlock / 2) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
+    else if (SHARDED || draft_lanes_shift(pieces) == 0) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
     else if constexpr (!SHARDED) {
-        if (pieces > kFinalBlock / 4) draft_finalize_lanes<false, 1>(a, b, lds, msh);
+        if (draft_lanes_shift(pieces) == 1) draft_finalize_lanes<false, 1>(a, b, lds, msh);
         else draft_finalize_lanes<false, 2>(a, b, lds, msh);
     }
 }

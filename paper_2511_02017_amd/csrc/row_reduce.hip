@@ -34,6 +34,7 @@
 // on this chip every cross-workgroup hand-over costs a memory round trip of
 // about 3 us under streaming load and four of them chain up.
 #include "common.h"
+#include "exp_device.h"
 
 namespace tapout {
 
@@ -143,8 +144,9 @@ struct ThreadState {
     // maximum), reference check, sums.  The entropy sum of a vector is formed without looking at the terms; a masked
     // (-inf) logit gives 0 * -inf = NaN there, and only then the vector is summed again with the exponent clamped (one
     // comparison per vector instead of one clamp per element).
-    template <int U, int N>
-    __device__ inline void fold_batch(const u32x4 (&w)[U], int32_t first, int32_t stride)
+    // each(u): called when vector u has been folded.
+    template <int U, int N, class Each>
+    __device__ inline void fold_batch(const u32x4 (&w)[U], int32_t first, int32_t stride, Each each)
     {
         bool grew = false;                                    // a lane mask in scalar registers
         float sb = 0.0f, tb = 0.0f;
@@ -189,6 +191,7 @@ struct ThreadState {
             } else {
                 s += sv;
             }
+            each(u);
         }
         if constexpr (FULL) {
             // If the running maximum grew inside the batch, its sums become the set-apart ones and the batch that held
@@ -205,7 +208,7 @@ struct ThreadState {
     {
         u32x4 w[1];
         w[0] = u32x4{__float_as_uint(x0), 0u, 0u, 0u};
-        fold_batch<1, 1>(w, j, 0);
+        fold_batch<1, 1>(w, j, 0, [](int) {});
     }
 };
 
@@ -258,11 +261,189 @@ __device__ inline void load_batch(u32x4 (&w)[U], const u32x4 *vp, int i, int end
     }
 }
 
-template <int DT, bool FULL, int U>
-__device__ inline void fold_batch(ThreadState<FULL> &st, const u32x4 (&w)[U], int i, int head)
+struct NoMore { __device__ void operator()(int) const {} };
+template <int DT, bool FULL, int U, class Each = NoMore>
+__device__ inline void fold_batch(ThreadState<FULL> &st, const u32x4 (&w)[U], int i, int head, Each each = Each())
 {
     constexpr int VEC = Elem<DT>::vec;
-    st.template fold_batch<U, VEC>(w, head + i * VEC, kBlock * VEC);
+    st.template fold_batch<U, VEC>(w, head + i * VEC, kBlock * VEC, each);
+}
+
+// ---- slice sums of the draft-token draw, on the way ------------------------------------------------
+// The inverse CDF of a draft row runs over sums of exponentials in double.  They need no row maximum if they are kept in the
+// logits' own scale: exp(x) as it is, from the table for bfloat16 values, computed for binary32 ones, is in range for every logit in
+// (-600, 700), and a row that holds larger ones is summed again where its token is drawn.  So the pass that reads the rows for
+// their statistics forms these sums too.  A draw slice is one vector per thread, kBlock vectors: a batch holds kStreamU of them,
+// each wavefront leaves its own sums, [draw slice][wavefront].
+// Slices a workgroup works on side by side, and workgroups of a compute unit.  bfloat16: two slices share a copy of the table, so that
+// four copies in LDS serve eight wavefronts per SIMD (64 registers); binary32: no table, six wavefronts (72 registers).  The kernel
+// is bound by vector instructions (rocprofv3: 34 of its 43 us at V = 128256, 512 rows, bfloat16): us per call with four / six / eight wavefronts per
+// SIMD 53.5 / 53.9 / 49.5, 64 rows 14.9 / 14.8 / 15.4; a batch asked for ahead of the one at hand changed nothing.
+template <int DT> struct DrawShape;
+template <> struct DrawShape<TAPOUT_BF16> { static constexpr int parts = 2, per_cu = 4; };
+template <> struct DrawShape<TAPOUT_F32>  { static constexpr int parts = 1, per_cu = 6; };
+template <int DT>
+struct DrawSums {
+    const double *T, *E;             // tables in LDS: 2^(k/256) and, for bfloat16, exp(x)
+    bool table;                      // bfloat16: look exponentials up
+    double *out;                     // of the slice the workgroup is at
+
+    __device__ inline double computed(float x) const { return exp_fast(x, 0.0, kDrawLow, T, kExpC2, kDrawHigh); }
+    __device__ inline double computed(const u32x4 &w) const
+    {
+        constexpr int VEC = Elem<DT>::vec;
+        float x[VEC];
+        unpack<DT>(w, x);
+        double e = 0.0;
+#pragma unroll
+        for (int i = 0; i < VEC; i += 2) {                   // two at a time: all of them side by side want sixty registers more
+            e += computed(x[i]) + computed(x[i + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return e;
+    }
+    __device__ inline double looked_up(const u32x4 &w) const
+    {
+        const char *at = (const char *)E;
+        double e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t o = tab_offsets2(w[i]);
+            e[i] = *(const double *)(at + (o & 0xffffu)) + *(const double *)(at + (o >> 16));
+        }
+        return (e[0] + e[1]) + (e[2] + e[3]);
+    }
+    // The four sums of a batch over the wavefront: the first two steps halve the number of values, so that each sixteen
+    // lanes end with one of them.
+    __device__ inline void store(const double (&v)[kStreamU], int bi) const
+    {
+        static_assert(kStreamU == 4, "one value for each sixteen lanes");
+        auto both = [](double a, double b, auto swap) {
+            const auto h = swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b)), l = swap((unsigned)__double2loint(a), (unsigned)__double2loint(b));
+            return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+        };
+        auto swap32 = [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); };
+        auto swap16 = [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); };
+        double x = both(both(v[0], v[1], swap32), both(v[2], v[3], swap32), swap16);       // rows of sixteen lanes: v[0], v[2], v[1], v[3]
+        x += dpp_d<0xB1>(x); x += dpp_d<0x4E>(x); x += dpp_d<0x141>(x); x += dpp_d<0x140>(x);
+        const int lane = threadIdx.x & (kWave - 1), row = lane >> 4, wave = (threadIdx.x & (kBlock - 1)) / kWave;
+        const int q = ((row & 1) << 1) | (row >> 1);
+        if ((lane & 15) == 0) out[(bi * kStreamU + q) * (kBlock / kWave) + wave] = x;
+    }
+    // One vector's sum.
+    __device__ inline double vector(const u32x4 &w) const
+    {
+        double e = DT == TAPOUT_BF16 ? looked_up(w) : computed(w);
+        asm volatile("" : "+v"(e));                          // summed here and now: else the terms, two registers each, wait for the end of the batch
+        return e;
+    }
+    // Which of a batch's sums v have to be formed again (again()), a bit each: those of vectors that hold a value which is not in
+    // the table.  v1: the thread's maximum so far, this batch included.
+    __device__ inline uint32_t missing(const double (&v)[kStreamU], float v1) const
+    {
+        if constexpr (DT != TAPOUT_BF16) return 0u;
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < kStreamU; ++u) m |= __builtin_amdgcn_ballot_w64(v[u] != v[u]) != 0 ? 1u << u : 0u;
+        return __builtin_amdgcn_ballot_w64(v1 >= 63.5f) != 0 || !table ? (1u << kStreamU) - 1 : m;
+    }
+    // The sum of vector u of batch bi once more, computed, with a thread's lone element (its exponential) beside it.  The lane that
+    // stored the first one stores it.
+    __device__ inline void again(const u32x4 &w, double lone, int bi, int u) const
+    {
+        const double x = wave_sum_d(computed(w) + lone);
+        const int lane = threadIdx.x & (kWave - 1), row = ((u & 1) << 1) | (u >> 1), wave = (threadIdx.x & (kBlock - 1)) / kWave;
+        if (lane == row * 16) out[(bi * kStreamU + u) * (kBlock / kWave) + wave] = x;
+    }
+};
+
+// What a workgroup leaves of slice `split` of a row: the threads' sums reduced, its Partial written.  tok_bits: the logit of the row's
+// token, if the slice holds it.  set: which of kSets copies of the records in LDS; on: there is a slice (all threads come to the barrier).
+template <int DT, bool FULL, int kSets = 1, int PARTS = 1>
+__device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FULL> &st, const int split, const int row, const uint32_t tok_bits,
+                                    const bool holds_tok, const int set = 0, const bool on = true)
+{
+    __shared__ u32x4 sh_rec[kSets][kBlock / kWave][2];
+    const int tid = PARTS > 1 ? threadIdx.x & (kBlock - 1) : threadIdx.x;
+    // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
+    // What a slice costs besides its loads is this chain of instructions (a wavefront issues one in about nine cycles here), in
+    // every workgroup of a launch and, in small ones, in the open: us per pass, with the reduction
+    // it replaces (every thread to the workgroup maximum first, three barriers, one thread merging) and with this: V = 128256, 64 sequences,
+    // K = 8 up to the stop position 61.7 / 60.4, V = 50257, 48 sequences 57.9 / 56.5, V = 32000, one sequence 19.7 / 19.4.
+    const int wave = tid / kWave, lane = tid % kWave;
+    const float Mw = wave_max(st.v1), Rw = ref_of_max(Mw);
+    const float d = Rw - st.R;
+    const int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
+    float s = ldexpf(st.s, -di);                                // exact scaling
+    float t = 0.0f, s_hi = 0.0f, t_hi = 0.0f;
+    if constexpr (FULL) {
+        t = ldexpf(st.t - d * st.s, -di);
+        s_hi = ldexpf(st.s_hi, -di);
+        t_hi = ldexpf(st.t_hi - d * st.s_hi, -di);
+    }
+    if (st.v1 == -INFINITY && !(st.s != st.s)) { s = 0.0f; t = 0.0f; s_hi = 0.0f; t_hi = 0.0f; }   // thread saw nothing finite
+    // the wavefront's vector with its first maximum: one thread's, unless several met that value
+    const uint64_t met = __builtin_amdgcn_ballot_w64(st.v1 == Mw);
+    int owner = __builtin_ctzll(met), cw = __builtin_amdgcn_readlane(st.cand, owner);
+    if (met & (met - 1)) {
+        cw = wave_min_i(st.v1 == Mw ? st.cand : 0x7fffffff);
+        owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(st.v1 == Mw && st.cand == cw));
+    }
+    // FULL: that thread's set-apart batch stays out of the wavefront's sums and goes into the record on its own (every other
+    // thread's is ordinary data); its second maximum counts, of the others the maximum does
+    float hs = 0.0f, ht = 0.0f, v2w = -INFINITY;
+    if constexpr (FULL) {
+        hs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s_hi), owner));
+        ht = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t_hi), owner));
+        s += lane == owner ? 0.0f : s_hi;
+        t += lane == owner ? 0.0f : t_hi;
+        v2w = wave_max(lane == owner ? st.v2 : st.v1);
+        t = wave_sum_last(t);
+    }
+    s = wave_sum_last(s);
+    if (lane == kWave - 1) {
+        sh_rec[set][wave][0] = u32x4{__float_as_uint(Mw), __float_as_uint(s), (uint32_t)cw, __float_as_uint(v2w)};
+        if constexpr (FULL) sh_rec[set][wave][1] = u32x4{__float_as_uint(t), __float_as_uint(hs), __float_as_uint(ht), 0u};
+    }
+    __syncthreads();
+    if (wave == 0) {
+        constexpr int kBits = 2;                                // four records, one on each lane of a quad
+        static_assert(kBlock / kWave == 1 << kBits, "a record per wavefront");
+        const u32x4 r0 = sh_rec[set][lane & 3][0];
+        const float Ml = __uint_as_float(r0.x), M = lanes_max(Ml, 0, kBits);
+        const bool met_it = Ml == M;
+        const float dl = ref_of_max(M) - ref_of_max(Ml);
+        const int dil = (int)fminf(fmaxf(dl, -1.0e9f), 1.0e9f);
+        Partial p;
+        p.v1 = M;
+        p.cand = lanes_min(met_it ? (int)r0.z : 0x7fffffff, 0, kBits);
+        float S = ldexpf(__uint_as_float(r0.y), -dil);
+        p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0; p.pad[2] = 0;
+        if constexpr (FULL) {
+            const u32x4 r1 = sh_rec[set][lane & 3][1];
+            const float hs0 = __uint_as_float(r1.y), Hs = ldexpf(hs0, -dil), Ht = ldexpf(__uint_as_float(r1.z) - dl * hs0, -dil);
+            float T = ldexpf(__uint_as_float(r1.x) - dl * __uint_as_float(r0.y), -dil);
+            if (Ml == -INFINITY) T = 0.0f;                      // (a record without a finite maximum: d is no distance)
+            // The batch with the slice's first maximum stays out (the epilogue adds its elements back from the
+            // logits); the set-apart batches of the other wavefronts are ordinary data.  A NaN or an infinity
+            // inside the left-out batch must still poison the sums: x - x is 0 for finite x only.
+            const bool holds = met_it && (int)r0.z == p.cand;
+            S += holds ? Hs - Hs : Hs;
+            T += holds || Ml == -INFINITY ? 0.0f : Ht;
+            p.v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, 0, kBits);
+            p.T = quad_sum(T);
+            // the left-out batch's own sum (same reference): S + this is the slice's sum over every element, to
+            // binary32 precision, for a reader that wants the row's lse before the epilogue has run
+            p.pad[1] = __float_as_int(quad_sum(holds ? Hs : 0.0f));
+        }
+        p.S = quad_sum(S);
+        p.pad[0] = holds_tok ? (int)(DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000;
+        if (tid == 0 && on) {
+            u32x4 *o = (u32x4 *)(a.out + (int64_t)row * a.nsplit + split);
+            o[0] = u32x4{__float_as_uint(p.v1), __float_as_uint(p.S), __float_as_uint(p.T), __float_as_uint(p.v2)};
+            o[1] = u32x4{(uint32_t)p.cand, (uint32_t)p.pad[0], (uint32_t)p.pad[1], 0u};
+        }
+    }
 }
 
 // The work of one workgroup: slice `split` of row k of sequence b.
@@ -274,9 +455,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
     // and six wavefronts per SIMD instead of eight, which still beats two vectors at full occupancy
     // (measured; three, six and eight vectors and an explicit prefetch of the next batch are all slower).
     constexpr int U = kStreamU;
-    __shared__ u32x4 sh_rec[kBlock / kWave][2];
 
-    const int row = b * a.KK + k;
     const int tid = threadIdx.x;
     int n_active;                                   // rows of sequence b this pass reads
     if (a.len_mode == 0) {                          // draft rows: k < k_len[b]
@@ -351,86 +530,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         st.fold_single(load_elem<DT>(rowp, j), j);
     }
 
-    // ---- workgroup reduction ----
-    // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
-    // What a slice costs besides its loads is this chain of instructions (a wavefront issues one in about nine cycles here), in
-    // every workgroup of a launch and, in small ones, in the open: us per pass, with the reduction
-    // it replaces (every thread to the workgroup maximum first, three barriers, one thread merging) and with this: V = 128256, 64 sequences,
-    // K = 8 up to the stop position 61.7 / 60.4, V = 50257, 48 sequences 57.9 / 56.5, V = 32000, one sequence 19.7 / 19.4.
-    const int wave = tid / kWave, lane = tid % kWave;
-    const float Mw = wave_max(st.v1), Rw = ref_of_max(Mw);
-    const float d = Rw - st.R;
-    const int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
-    float s = ldexpf(st.s, -di);                                // exact scaling
-    float t = 0.0f, s_hi = 0.0f, t_hi = 0.0f;
-    if constexpr (FULL) {
-        t = ldexpf(st.t - d * st.s, -di);
-        s_hi = ldexpf(st.s_hi, -di);
-        t_hi = ldexpf(st.t_hi - d * st.s_hi, -di);
-    }
-    if (st.v1 == -INFINITY && !(st.s != st.s)) { s = 0.0f; t = 0.0f; s_hi = 0.0f; t_hi = 0.0f; }   // thread saw nothing finite
-    // the wavefront's vector with its first maximum: one thread's, unless several met that value
-    const uint64_t met = __builtin_amdgcn_ballot_w64(st.v1 == Mw);
-    int owner = __builtin_ctzll(met), cw = __builtin_amdgcn_readlane(st.cand, owner);
-    if (met & (met - 1)) {
-        cw = wave_min_i(st.v1 == Mw ? st.cand : 0x7fffffff);
-        owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(st.v1 == Mw && st.cand == cw));
-    }
-    // FULL: that thread's set-apart batch stays out of the wavefront's sums and goes into the record on its own (every other
-    // thread's is ordinary data); its second maximum counts, of the others the maximum does
-    float hs = 0.0f, ht = 0.0f, v2w = -INFINITY;
-    if constexpr (FULL) {
-        hs = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s_hi), owner));
-        ht = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t_hi), owner));
-        s += lane == owner ? 0.0f : s_hi;
-        t += lane == owner ? 0.0f : t_hi;
-        v2w = wave_max(lane == owner ? st.v2 : st.v1);
-        t = wave_sum_last(t);
-    }
-    s = wave_sum_last(s);
-    if (lane == kWave - 1) {
-        sh_rec[wave][0] = u32x4{__float_as_uint(Mw), __float_as_uint(s), (uint32_t)cw, __float_as_uint(v2w)};
-        if constexpr (FULL) sh_rec[wave][1] = u32x4{__float_as_uint(t), __float_as_uint(hs), __float_as_uint(ht), 0u};
-    }
-    __syncthreads();
-    if (wave == 0) {
-        constexpr int kBits = 2;                                // four records, one on each lane of a quad
-        static_assert(kBlock / kWave == 1 << kBits, "a record per wavefront");
-        const u32x4 r0 = sh_rec[lane & 3][0];
-        const float Ml = __uint_as_float(r0.x), M = lanes_max(Ml, 0, kBits);
-        const bool met_it = Ml == M;
-        const float dl = ref_of_max(M) - ref_of_max(Ml);
-        const int dil = (int)fminf(fmaxf(dl, -1.0e9f), 1.0e9f);
-        Partial p;
-        p.v1 = M;
-        p.cand = lanes_min(met_it ? (int)r0.z : 0x7fffffff, 0, kBits);
-        float S = ldexpf(__uint_as_float(r0.y), -dil);
-        p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0; p.pad[2] = 0;
-        if constexpr (FULL) {
-            const u32x4 r1 = sh_rec[lane & 3][1];
-            const float hs0 = __uint_as_float(r1.y), Hs = ldexpf(hs0, -dil), Ht = ldexpf(__uint_as_float(r1.z) - dl * hs0, -dil);
-            float T = ldexpf(__uint_as_float(r1.x) - dl * __uint_as_float(r0.y), -dil);
-            if (Ml == -INFINITY) T = 0.0f;                      // (a record without a finite maximum: d is no distance)
-            // The batch with the slice's first maximum stays out (the epilogue adds its elements back from the
-            // logits); the set-apart batches of the other wavefronts are ordinary data.  A NaN or an infinity
-            // inside the left-out batch must still poison the sums: x - x is 0 for finite x only.
-            const bool holds = met_it && (int)r0.z == p.cand;
-            S += holds ? Hs - Hs : Hs;
-            T += holds || Ml == -INFINITY ? 0.0f : Ht;
-            p.v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, 0, kBits);
-            p.T = quad_sum(T);
-            // the left-out batch's own sum (same reference): S + this is the slice's sum over every element, to
-            // binary32 precision, for a reader that wants the row's lse before the epilogue has run
-            p.pad[1] = __float_as_int(quad_sum(holds ? Hs : 0.0f));
-        }
-        p.S = quad_sum(S);
-        p.pad[0] = holds_tok ? (int)(DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000;
-        if (tid == 0) {
-            u32x4 *o = (u32x4 *)(a.out + (int64_t)row * a.nsplit + split);
-            o[0] = u32x4{__float_as_uint(p.v1), __float_as_uint(p.S), __float_as_uint(p.T), __float_as_uint(p.v2)};
-            o[1] = u32x4{(uint32_t)p.cand, (uint32_t)p.pad[0], (uint32_t)p.pad[1], 0u};
-        }
-    }
+    finish_slice<DT, FULL>(a, st, split, b * a.KK + k, tok_bits, holds_tok);
 }
 
 // grid = (slice, row of the sequence, sequence): no index arithmetic ahead of the first load.
@@ -455,6 +555,92 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
         if ((int)blockIdx.y < d.KK && (int)blockIdx.x < d.nsplit) stream_pass_body<DD, true>(d, blockIdx.x, blockIdx.y, z);
     } else {
         if ((int)blockIdx.x < t.nsplit) stream_pass_body<TD, false>(t, blockIdx.x, blockIdx.y, z - n_seq);
+    }
+}
+
+// The draft pass with the slice sums of the draft-token draw (see DrawSums).  As many workgroups as are resident at once, so that the
+// 36 KB table of bfloat16 exponentials is copied to LDS once per workgroup; every slice is as long as the next, and a fixed stride
+// keeps them level.
+template <int DT>
+__global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgpu_waves_per_eu(DrawShape<DT>::parts * DrawShape<DT>::per_cu))) void stream_draw_kernel(RowReduceArgs a, DrawArgs d)
+{
+    constexpr bool kTab = DT == TAPOUT_BF16;
+    constexpr int VEC = Elem<DT>::vec, U = kStreamU, kParts = DrawShape<DT>::parts;
+    __shared__ double shT[256];
+    __shared__ __align__(16) double shE[kTab ? kTabDoubles : 2];
+    warm_args(a, d);
+    const int tid = threadIdx.x & (kBlock - 1), part = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock);
+    const double tv = d.exp_table[tid];
+    if constexpr (kTab) copy_to_lds<kTabVecs, kBlock * kParts>(d.exp_table + 256, shE);
+    struct Slice { int b, k, s; const char *row; int head, nvec, tail, v0, v1e, nbatch, on; } at;
+    const int n_seq = a.n_rows / a.KK;
+    {
+        const int first = (int)blockIdx.x * kParts + part, row = first / a.nsplit;
+        at.s = first - row * a.nsplit;
+        at.b = row / a.KK;
+        at.k = row - at.b * a.KK;
+    }
+    if (part == 0) shT[tid] = tv;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
+    __syncthreads();
+    DrawSums<DT> draw;
+    draw.T = shT; draw.E = shE;
+    draw.table = kTab && !(d.vflags & kVerifyNoExpTable);
+    for (int turn = 0; turn < d.turns; ++turn) {
+        at.on = at.b < n_seq;
+        at.on = at.on && (!a.len || at.k < a.len[at.b]);
+        at.row = (const char *)a.base + ((int64_t)(at.on ? at.b : 0) * a.stride_b + (int64_t)at.k * a.stride_k) * Elem<DT>::size;
+        row_geometry<DT>(at.row, a.V, at.head, at.nvec, at.tail);
+        at.v0 = min(at.s * a.per, at.nvec);
+        at.v1e = min(at.v0 + a.per, at.nvec);
+        at.nbatch = (at.v1e - at.v0 + U * kBlock - 1) / (U * kBlock);
+        const u32x4 *vp = (const u32x4 *)(at.row + (int64_t)at.head * Elem<DT>::size);
+        draw.out = d.sums + ((int64_t)(at.b * a.KK + at.k) * a.nsplit + at.s) * ((int64_t)d.nb * U * (kBlock / kWave));
+        ThreadState<true> st;
+        if (at.on && at.s == 0 && tid < at.head) st.fold_single(load_elem<DT>(at.row, tid), tid);
+        const bool heads = at.on && at.s == 0 && at.head > 0, tails = at.on && at.s == a.nsplit - 1 && at.tail > 0;
+        for (int b0 = 0; at.on && b0 < d.nb; b0 += 16) {                     // sixteen batches, then what is missing of their sums
+            const int b1 = min(b0 + 16, d.nb), b1d = min(b1, at.nbatch);
+            uint64_t missing = 0;
+#pragma unroll 1
+            for (int bi = b0; bi < b1d; ++bi) {
+                const int i = at.v0 + bi * (U * kBlock) + tid;
+                u32x4 w[U];
+                if (at.v0 + (bi + 1) * (U * kBlock) <= at.v1e) load_batch<DT, U, false>(w, vp, i, at.v1e);
+                else load_batch<DT, U, true>(w, vp, i, at.v1e);
+                double v[U];
+                fold_batch<DT, true, U>(st, w, i, at.head, [&](int u) { v[u] = draw.vector(w[u]); });
+                missing |= (uint64_t)draw.missing(v, st.v1) << ((bi - b0) * U);
+                draw.store(v, bi);
+            }
+            for (int bi = max(b0, at.nbatch); bi < b1; ++bi) {               // a slice shorter than the others
+                const double v[U] = {0.0, 0.0, 0.0, 0.0};
+                draw.store(v, bi);
+            }
+            // (the elements ahead of the row's vectors and behind them go with its first and its last draw slice)
+            if (heads && b0 == 0) missing |= 1u;
+            if (tails && b1 == d.nb) missing |= 1ull << ((b1 - b0) * U - 1);
+            while (__builtin_expect(missing != 0, 0)) {
+                const int at_bit = __builtin_ctzll(missing), bi = b0 + at_bit / U, u = at_bit % U;
+                missing &= missing - 1;
+                const int i = at.v0 + bi * (U * kBlock) + u * kBlock + tid;
+                constexpr uint32_t ni = NegInfVec<DT>::word;
+                u32x4 w = u32x4{ni, ni, ni, ni};
+                if (i < at.v1e) w = vp[i];
+                int32_t j = -1;
+                if (heads && bi == 0 && u == 0 && tid < at.head) j = tid;
+                if (tails && bi == d.nb - 1 && u == U - 1 && tid < at.tail) j = at.head + at.nvec * VEC + tid;
+                draw.again(w, j >= 0 ? draw.computed(load_elem<DT>(at.row, j)) : 0.0, bi, u);
+            }
+        }
+        if (at.on && at.s == a.nsplit - 1 && tid < at.tail) {
+            const int32_t j = at.head + at.nvec * VEC + tid;
+            st.fold_single(load_elem<DT>(at.row, j), j);
+        }
+        finish_slice<DT, true, 2 * kParts, kParts>(a, st, at.s, at.b * a.KK + at.k, 0u, false, (turn & 1) * kParts + part, at.on);
+        at.s += d.step_s; at.k += d.step_k; at.b += d.step_b;
+        if (at.s >= a.nsplit) { at.s -= a.nsplit; ++at.k; }
+        if (at.k >= a.KK) { at.k -= a.KK; ++at.b; }
     }
 }
 
@@ -484,6 +670,25 @@ hipError_t launch_row_reduce_pair(const RowReduceArgs &d, int d_dtype, const Row
     if (d_dtype == TAPOUT_F32)
         return t_dtype == TAPOUT_F32 ? launch_pair<TAPOUT_F32, TAPOUT_F32>(d, t, st, tm) : launch_pair<TAPOUT_F32, TAPOUT_BF16>(d, t, st, tm);
     return t_dtype == TAPOUT_F32 ? launch_pair<TAPOUT_BF16, TAPOUT_F32>(d, t, st, tm) : launch_pair<TAPOUT_BF16, TAPOUT_BF16>(d, t, st, tm);
+}
+
+template <int DT>
+static hipError_t launch_draw(const RowReduceArgs &a, DrawArgs d, hipStream_t st, Timing tm)
+{
+    // every part of every workgroup the same number of slices, and no more workgroups than are resident
+    constexpr int kParts = DrawShape<DT>::parts;
+    const int64_t units = (int64_t)a.n_rows * a.nsplit, slots = 256 * DrawShape<DT>::per_cu * kParts;
+    d.turns = (int)((units + slots - 1) / slots);
+    const int wgs = (int)((units + (int64_t)d.turns * kParts - 1) / ((int64_t)d.turns * kParts)), step = wgs * kParts;
+    d.step_s = step % a.nsplit; d.step_k = step / a.nsplit % a.KK; d.step_b = step / a.nsplit / a.KK;
+    launch_kernel(stream_draw_kernel<DT>, dim3(wgs), dim3(kBlock * kParts), st, tm, a, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_stream_draw(const RowReduceArgs &a, int dtype, DrawArgs d, hipStream_t st, Timing tm)
+{
+    if (!d.exp_table || !d.sums || a.tok || a.clear_jobs || a.arm_dst || a.len_mode != 0) return hipErrorInvalidValue;
+    return dtype == TAPOUT_F32 ? launch_draw<TAPOUT_F32>(a, d, st, tm) : launch_draw<TAPOUT_BF16>(a, d, st, tm);
 }
 
 hipError_t launch_row_reduce(const RowReduceArgs &a, int dtype, bool full, hipStream_t st, Timing tm)

@@ -42,6 +42,7 @@
 // exp(x) itself from a table of all bfloat16 values a softmax row can hold.
 #include "common.h"
 #include "bandit_device.h"
+#include "exp_device.h"
 #include "finalize_device.h"
 
 namespace tapout {
@@ -74,85 +75,6 @@ static_assert(kVBlock == kBlock, "stage_partials strides by kBlock");
 constexpr int kPer = 8;                       // elements per 16-byte (bf16) / 32-byte (f32) run
 
 
-
-// ---- double-precision helpers ---------------------------------------------------
-constexpr double kExpC = 369.3299304675746;            // 256 / ln 2
-constexpr double kExpC1 = 0.0027076061740622863;       // ln2/256
-constexpr double kExpC2 = kExpC1 * kExpC1 / 2.0;
-constexpr double kExpC3 = kExpC1 * kExpC1 * kExpC1 / 6.0;
-constexpr double kMagic = 6755399441055744.0;          // 1.5 * 2^52: adding it rounds to an integer held in the low mantissa bits
-
-// exp(x - ref) for x <= ref + small.  neg_ref_c = -ref * 256/ln2; lo = ref - 700 as binary32: inputs
-// below it (masked -inf logits, NaN) are treated as ref - 700, i.e. as weight 1e-304.
-// c2 is kExpC2 and top is +inf: a caller with many exponentials in a row keeps them in vector registers (an
-// instruction takes one scalar constant only, and the compiler would otherwise move c2 into a register before
-// every use; with a top it cannot see through, the clamp stays a med3, which unlike fmaxf needs no quieting of
-// its input first).
-__device__ inline double exp_fast(float x, double neg_ref_c, float lo, const double *T, double c2 = kExpC2, float top = INFINITY)
-{
-    const double xd = (double)__builtin_amdgcn_fmed3f(x, lo, top);      // max(x, lo) for numbers, lo for NaN
-    const double t = fma(xd, kExpC, neg_ref_c);          // (x - ref) * 256/ln2
-    const double tm = t + kMagic;
-    const int ni = __double2loint(tm);                   // round(t) in two's complement
-    const double rs = t - (tm - kMagic);                 // remainder in units of ln2/256, |rs| <= 1/2
-    const double q = rs * fma(rs, fma(rs, kExpC3, c2), kExpC1);
-    const double tk = T[ni & 255];
-    const double e = fma(tk, q, tk);                     // in [1, 2): scale by 2^(ni >> 8) through the exponent field
-    int hi;                                              // high word + ((ni >> 8) << 20), as mask and one shift-add
-    asm("v_lshl_add_u32 %0, %1, 12, %2" : "=v"(hi) : "v"(ni & (int)0xffffff00), "v"(__double2hiint(e)));
-    return __hiloint2double(hi, __double2loint(e));
-}
-
-// exp(x) for a double argument, same table and polynomial: relative error < 2e-13, underflowing like exp: to denormal numbers and,
-// below log(2^-1075) = -745.13, to 0 (arguments are clamped to [-746, 700], NaN to -746): a token of probability 0 has the
-// ratio 0, which a uniform of 0 is not below.  ([-700, ..] made that ratio 1e-304, and u = 0 accepted the token.)
-__device__ inline double exp_fast_d(double x, const double *T)
-{
-    const double t = fmin(fmax(x, -746.0), 700.0) * kExpC;
-    const double tm = t + kMagic;
-    const int ni = __double2loint(tm);
-    const double rs = t - (tm - kMagic);
-    const double q = rs * fma(rs, fma(rs, kExpC3, kExpC2), kExpC1);
-    const double tk = T[ni & 255];
-    return ldexp(fma(tk, q, tk), ni >> 8);
-}
-
-struct ExpRef {
-    double neg_ref_c; float lo;
-    __device__ inline void set(double ref) { neg_ref_c = -ref * kExpC; lo = (float)(ref - 700.0); }
-};
-
-// ---- wavefront reductions and scans of doubles with DPP (no LDS round trips) ---------------
-// quad_perm [1,0,3,2] = 0xB1, quad_perm [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140,
-// row_shr:n = 0x110 + n (lanes without a source inside their 16-lane row read 0).
-template <int CTRL>
-__device__ inline double dpp_d(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-__device__ inline double lane_d(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-// Sum over the 64 lanes, same value in every lane, fixed order.
-__device__ inline double wave_sum_d(double v)
-{
-    v += dpp_d<0xB1>(v); v += dpp_d<0x4E>(v); v += dpp_d<0x141>(v); v += dpp_d<0x140>(v);
-    return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
-// Inclusive prefix sum over the 64 lanes (lane order); *total = sum of all lanes.
-__device__ inline double wave_incl_scan_d(double v, double *total)
-{
-    v += dpp_d<0x111>(v); v += dpp_d<0x112>(v); v += dpp_d<0x114>(v); v += dpp_d<0x118>(v);   // inside each 16-lane row
-    const double t0 = lane_d(v, 15), t1 = lane_d(v, 31), t2 = lane_d(v, 47), t3 = lane_d(v, 63);
-    const int rowid = (threadIdx.x & (kWave - 1)) >> 4;
-    const double t01 = t0 + t1, t012 = t01 + t2;
-    v += rowid == 0 ? 0.0 : (rowid == 1 ? t0 : (rowid == 2 ? t01 : t012));
-    *total = t012 + t3;
-    return v;
-}
 
 // Eight consecutive elements j .. j+7 of a row as they lie in memory (one 16-byte vector of bfloat16, two of binary32;
 // -inf beyond V), so that a kernel can hold several requests in flight in few registers and widen them, exactly, when
@@ -621,65 +543,6 @@ constexpr int kSliceVals = 5;          // A, B, R~, D, U
 constexpr int kWavesPerWG = kVBlock / kWave;                    // 4 slices per workgroup, one per wavefront
 constexpr int kChunks = kSampleSlice / (kWave * kPer);          // a wavefront takes its slice in 4 chunks of 512 elements
 
-// ---- exponentials of bfloat16 logits from a table -----------------------------------------
-// A bfloat16 logit has 2^16 possible values, and those between 2^-12 and 2^6 in magnitude (all a softmax row holds
-// besides masked entries and the odd tiny one) are 2 * 2302 of them: exp(x) itself, correctly rounded on the host,
-// comes from a table of 36 KB in LDS with four integer instructions and one LDS read instead of the thirteen
-// instructions of exp_fast.  The row's exponent reference is applied once per slice, to the sums:
-//   a_j = exp(t_j - ref_p) = E[t_j] c_t,  b_j = exp(d_j - ref_q) = E[d_j] c_d,   c_t = exp(-ref_p), c_d = exp(-ref_q)
-//   a_j - L~ b_j = c_t (E[t_j] - L' E[d_j]),  L' = L~ c_d / c_t
-// so the slice kernel sums E[t], E[d], max(0, E[t] - L' E[d]), ... and scales A, R~ by c_t and B, D, U by c_d at the
-// end.  A row of another element type keeps exp_fast and c = 1.
-// Layout: T[idx] for positive values, T[kTabTop + 1 + idx] for negative ones (kept apart: with the two signs of a
-// magnitude side by side a wavefront's 64 reads fall on half as many LDS banks).  Entry idx = 1 .. kTabTop - 1 is
-// the magnitude with bfloat16 bits kTabLo15 + idx - 1.
-// Entry kTabTop stands for every magnitude from 63.5 up (and NaN): 0 for either sign.  That is exact for -inf (a
-// masked entry) and an error below e^-49 of the row's largest term for any other logit <= -63.5 given the condition
-// on the references that tab_job_ok checks (row maxima in [-14, 63)); a job outside it takes the computed
-// exponentials.  Entry 0 stands for the magnitudes below 2^-12 (and zeros), which are not in the table, and holds
-// NaN: a chunk's sums show that it met one, and the slice kernel forms that chunk again with tab_exp_any, which
-// evaluates 1 + x + x^2/2 + x^3/6 for them (error < 2e-16).
-constexpr int kTabTop = 18 * 128 - 1;
-constexpr uint32_t kTabLo15 = (uint32_t)(127 - 12) << 7;            // bfloat16 magnitude bits of 2^-12
-constexpr int kTabDoubles = 2 * (kTabTop + 1);                       // 4608 doubles = 36,864 bytes
-constexpr int kTabVecs = kTabDoubles / 2;                            // 16-byte vectors
-static_assert(kTabVecs % kVBlock == 0, "the table is copied to LDS in whole rounds of the workgroup");
-static_assert(kTabDoubles == kExpBf16Doubles, "the host builds the table");
-static_assert(8 * (2 * kTabTop + 1) < 65536, "an entry's byte offset fits sixteen bits");
-
-// Two bfloat16 values as they lie in one word -> the byte offsets of their entries, again as two halves of a word.
-// Both halves are worked on at once with the packed 16-bit integer instructions: eight instructions for two
-// look-ups, the two that take the word apart included (one value at a time it was nine each).
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t tab_offsets2(uint32_t w)
-{
-    const uint32_t mag = w & 0x7fff7fffu;
-    u16x2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, mag), (u16x2)(unsigned short)(kTabLo15 - 1));   // 0: below the table
-    d = __builtin_elementwise_min(d, (u16x2)(unsigned short)kTabTop);
-    d = d << (u16x2)(unsigned short)3;
-    typedef short i16x2 __attribute__((ext_vector_type(2)));
-    const i16x2 neg = __builtin_bit_cast(i16x2, w) >> (i16x2)(short)15;           // all ones in the half of a negative value
-    d += __builtin_bit_cast(u16x2, neg) & (u16x2)(unsigned short)(8 * (kTabTop + 1));
-    return __builtin_bit_cast(uint32_t, d);
-}
-// x: a bfloat16 value widened to binary32 (low 16 bits zero); same entry as tab_offsets2 finds.
-__device__ inline double tab_lookup(float x, const double *T)
-{
-    const uint32_t u = __float_as_uint(x);
-    const uint32_t m = (u >> 16) & 0x7fffu;
-    const uint32_t d = min(max(m, kTabLo15 - 1) - (kTabLo15 - 1), (uint32_t)kTabTop);
-    return T[d + (u >> 31) * (uint32_t)(kTabTop + 1)];
-}
-// Any binary32-widened bfloat16 value, with the same bits as the table wherever it applies.
-__device__ inline double tab_exp_any(float x, const double *T)
-{
-    const uint32_t u = __float_as_uint(x);
-    if (((u >> 16) & 0x7fffu) < kTabLo15) {
-        const double t = (double)x;
-        return fma(t, fma(t, fma(t, 1.0 / 6.0, 0.5), 1.0), 1.0);
-    }
-    return tab_lookup(x, T);
-}
 __device__ inline bool tab_job_ok(const SampleJob &job)
 {
     // ref_p: the target row's maximum; ref_q: the draft row's lse, at most ln V above its maximum
@@ -744,38 +607,6 @@ __device__ inline void chunk_pair_tab(const u32x4 &wt, const u32x4 &wd, const do
         }
     }
 }
-// One row alone: the sum of its exponentials over a chunk.
-__device__ inline double chunk_one_tab(const u32x4 &wt, const double *shE)
-{
-    const char *E = (const char *)shE;
-    double cA = 0.0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t ot = tab_offsets2(wt[k]);
-        cA += *(const double *)(E + (ot & 0xffffu));
-        cA += *(const double *)(E + (ot >> 16));
-    }
-    return cA;
-}
-
-// N 16-byte vectors (a multiple of 64) from memory to LDS, without passing through registers, by a workgroup of kThreads.
-// The copy is complete when every wavefront has waited for its loads (vmcnt) and a barrier has been passed.
-template <int N, int kThreads>
-__device__ inline void copy_to_lds(const void *src, void *dst)
-{
-    typedef const __attribute__((address_space(1))) void *Global;
-    typedef __attribute__((address_space(3))) void *Lds;
-    constexpr int kWaves = kThreads / kWave, kTurns = N / kWave;
-    static_assert(N % kWave == 0, "whole wavefronts");
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int q = 0; q < (kTurns + kWaves - 1) / kWaves; ++q) {
-        const int turn = q * kWaves + wave, first = turn * kWave;              // the wavefront's 64 vectors: lane l's goes to first + l
-        if ((q + 1) * kWaves <= kTurns || turn < kTurns)
-            __builtin_amdgcn_global_load_lds((Global)((const char *)src + (int64_t)(first + lane) * 16), (Lds)((char *)dst + first * 16), 16, 0, 0);
-    }
-}
-
 // One wavefront per slice, four slices per workgroup; in small launches two or four wavefronts per slice (SPLIT; see
 // slice_split), whose sums meet in LDS.  A wavefront takes its slice in chunks of one 8-element run per
 // lane; its five sums need no LDS and no barrier of their own.  The requests run ahead of the arithmetic (see kAhead): with one
@@ -1081,22 +912,22 @@ __device__ inline int wave_min_i32(int v)
                min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
-// First element of slice s whose running sum (starting at cum) exceeds target, or -1.
+// First of the kSampleSlice elements from `from` on (a slice, most often) whose running sum (starting at cum) exceeds target, or -1.
 // With track_last, sh->last collects the largest index with positive weight seen (fallback only).
-// *slice_total: the slice's weight as scanned.  `phase` alternates between calls so that consecutive
+// *slice_total: their weight as scanned.  `phase` alternates between calls so that consecutive
 // scans use different LDS buffers.
 template <int TD, int DD>
-__device__ inline int locate_in_slice(const Weights &w, const Rows &r, int s, int V, const double *T,
+__device__ inline int locate_in_slice(const Weights &w, const Rows &r, int from, int V, const double *T,
                                       double cum, double target, LocateShared *sh, int phase, double *slice_total,
                                       bool track_last = false)
 {
     double wv[kThreadPer];
-    thread_weights<TD, DD>(w, r, s * kSampleSlice + (int)threadIdx.x * kThreadPer, V, T, wv);
+    thread_weights<TD, DD>(w, r, from + (int)threadIdx.x * kThreadPer, V, T, wv);
     double sum = 0.0;
 #pragma unroll
     for (int i = 0; i < kThreadPer; ++i) sum += wv[i];
     const double excl = block_excl_scan_d(sum, sh->scan[phase & 1], slice_total);
-    const int j0 = s * kSampleSlice + threadIdx.x * kThreadPer;
+    const int j0 = from + threadIdx.x * kThreadPer;
     double c = cum + excl;
     int hit = 0x7fffffff, lp = -1;
 #pragma unroll
@@ -1150,33 +981,35 @@ __device__ __forceinline__ int find_slice(int nsl, double target, Weight weight,
     return found < nsl ? found : -1;
 }
 
-// Token of a draw: the first element whose running sum over the row exceeds `target`; whole workgroup (weight as find_slice).
-template <int TD, int DD, class Weight>
-__device__ __forceinline__ int find_token(const Weights &w, const Rows &r, int V, int nsl, const double *T, double target, Weight weight, LocateShared *sh, int &phase)
+// Token of a draw: the first element whose running sum over the row exceeds `target`; whole workgroup (weight as find_slice;
+// start(s): the element at which slice s starts).
+template <int TD, int DD, class Weight, class Start>
+__device__ __forceinline__ int find_token(const Weights &w, const Rows &r, int V, int nsl, const double *T, double target, Weight weight, Start start, LocateShared *sh, int &phase)
 {
     double cum;
     const int s_found = find_slice(nsl, target, weight, &cum);
     LOCATE_STAMP(3);                                             // slice found
     // slice sums and the in-slice scan round differently: if the crossing is not inside the chosen
-    // slice, continue into the following ones
+    // slice, continue into the elements behind it
     int token = -1;
     if (s_found >= 0)
-        for (int s = s_found; s < nsl && token < 0; ++s) {
+        for (int j = start(s_found); j < V && token < 0; j += kSampleSlice) {
             double slice_total;
-            token = locate_in_slice<TD, DD>(w, r, s, V, T, cum, target, sh, phase++, &slice_total);
+            token = locate_in_slice<TD, DD>(w, r, j, V, T, cum, target, sh, phase++, &slice_total);
             cum += slice_total;
         }
     if (__builtin_expect(token < 0, 0)) {
         // rounding left no crossing: the largest index with positive weight
-        for (int s = 0; s < nsl; ++s) {
+        for (int j = 0; j < V; j += kSampleSlice) {
             double slice_total;
-            locate_in_slice<TD, DD>(w, r, s, V, T, 0.0, INFINITY, sh, phase++, &slice_total, true);
+            locate_in_slice<TD, DD>(w, r, j, V, T, 0.0, INFINITY, sh, phase++, &slice_total, true);
         }
         __syncthreads();
         token = sh->last;
     }
     return token;
 }
+__device__ inline int whole_slice_start(int s) { return s * kSampleSlice; }
 
 // Exact weights of all slices of a row, zs[s], and their total; whole workgroup.  A wavefront per slice, no barrier until all
 // are done.  (By the whole workgroup, slice after slice with a scan each, every slice waited for its loads
@@ -1378,7 +1211,7 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
 
     LOCATE_STAMP(2);                                             // total weight known (certified, settled or recomputed)
     int token = -1;
-    if (Z > 0.0) token = find_token<TD, DD>(w, r, a.V, a.nsl, shT, u * Z, slice_weight, &shl, phase);
+    if (Z > 0.0) token = find_token<TD, DD>(w, r, a.V, a.nsl, shT, u * Z, slice_weight, whole_slice_start, &shl, phase);
     LOCATE_STAMP(4);                                             // token found
     if (tid == 0) {
         if (token < 0) token = 0;
@@ -1393,9 +1226,6 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
 }
 
 // ---- draft-token sampling: the inverse CDF of every live draft row ---------------------------
-constexpr int kSampleBlock = 512;
-constexpr int kSampleWgs = 512;      // two per CU: what the kernel's registers let be resident at once
-
 __device__ inline float wave_max_f(float v)
 {
     auto mv = [](float x, auto ctrl) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
@@ -1427,140 +1257,74 @@ __device__ inline float row_ref_finish(RowRefRegs r, const Partial *p, int nspli
     return M;
 }
 
-// Slice sums of every live row: sums[row, s] = sum of exp(x - M) over slice s, M the row's maximum, in double and with the
-// arithmetic of the final-token slice kernel.  A wavefront per slice; the workgroups are as many as are resident at once
-// and each wavefront takes every n_waves-th slice, so that the table of bfloat16 exponentials is copied to LDS once per
-// workgroup: with a workgroup per four slices its 37 KB were twice the logits they served (and the slices here are all
-// alike, so a fixed stride keeps the wavefronts level).  A wavefront requests its next slice and that row's partials
-// before it works on the one at hand.  Bound by the look-ups' LDS reads and the second reading of the logits.
-// Measured at V = 128256, 512 rows, bfloat16: 42.1 us with a workgroup per four slices, behind a launch of 4.8 that found
-// the rows' maxima; this, which finds them itself and carries the epilogue's workgroups (7.9 alone), 33.9; 64 rows: 4.2 + 8.4 + 8.2 against
-// 11.2.
-template <int DT>
-__global__ __launch_bounds__(kSampleBlock) __attribute__((amdgpu_waves_per_eu(4))) void sample_slices_kernel(SampleArgs a, DraftFinalArgs fin)
+// The row's lse in double, the same bits in every lane as the draft epilogue leaves in its outputs: its lane path's arithmetic on
+// the same lanes (see draft_finalize_body), every group of a row's lanes with the same row.
+template <int USH>
+__device__ inline double row_lse_lanes(const DraftFinalArgs &a, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, int msh)
 {
-    constexpr bool kTab = DT == TAPOUT_BF16;
-    __shared__ double shT[256];
-    __shared__ __align__(16) double shE[kTab ? kTabDoubles : 2];
-    warm_args(a, fin);
-    if ((int)blockIdx.x < a.B) {
-        // the draft epilogue of one sequence, by the first wavefronts (whole wavefronts leave: barriers do not wait for them)
-        if (threadIdx.x < kFinalBlock) draft_finalize_body<false>(fin, blockIdx.x);
-        return;
-    }
-    const int lane = threadIdx.x & (kWave - 1);
-    const double tv = a.exp_table[threadIdx.x & 255];
-    if constexpr (kTab) copy_to_lds<kTabVecs, kSampleBlock>(a.exp_table + 256, shE);
-    struct Slice { int b, k, s; };
-    const int first = __builtin_amdgcn_readfirstlane((int)((blockIdx.x - a.B) * (kSampleBlock / kWave) + threadIdx.x / kWave));
-    Slice cur;
-    {
-        const int row = first / a.nsl;
-        cur.s = first - row * a.nsl;
-        cur.b = row / a.K;
-        cur.k = row - cur.b * a.K;
-    }
-    auto advance = [&](Slice t) {
-        t.s += a.step_s; t.k += a.step_k; t.b += a.step_b;
-        if (t.s >= a.nsl) { t.s -= a.nsl; ++t.k; }
-        if (t.k >= a.K) { t.k -= a.K; ++t.b; }
-        return t;
-    };
-    auto live = [&](const Slice &t) { return t.b < a.B && (!a.k_len || t.k < a.k_len[t.b]); };
-    struct Regs { Raw8<DT> q[kChunks]; RowRefRegs r; };
-    auto request = [&](const Slice &t) {
-        Regs o;
-        const char *row = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, t.b, t.k);
-        const int base = t.s * kSampleSlice + lane * kPer;
-        o.r = row_ref_issue(a.part + ((int64_t)t.b * a.K + t.k) * a.nsplit, a.nsplit);
-        if (__builtin_expect((t.s + 1) * kSampleSlice <= a.V, 1)) {          // straight-line requests (see the final-token slice kernel)
-#pragma unroll
-            for (int c = 0; c < kChunks; ++c)
-#pragma unroll
-                for (int h = 0; h < (DT == TAPOUT_F32 ? 2 : 1); ++h)
-                    o.q[c].w[h] = load16<DT>(row + (int64_t)(base + c * kWave * kPer) * Elem<DT>::size + 16 * h);
-        } else {
-#pragma unroll
-            for (int c = 0; c < kChunks; ++c) o.q[c] = load_raw8<DT>(row, base + c * kWave * kPer, a.V);
-        }
-        return o;
-    };
-    bool on = live(cur);
-    Regs at{};
-    if (on) at = request(cur);
-    if (threadIdx.x < 256) shT[threadIdx.x] = tv;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
-    __syncthreads();
-    while (cur.b < a.B) {
-        const Slice nxt = advance(cur);
-        const bool nxt_on = live(nxt);
-        Regs ahead{};
-        if (nxt_on) ahead = request(nxt);
-        if (on) {
-            const int64_t row = (int64_t)cur.b * a.K + cur.k;
-            bool bad;
-            const float M = row_ref_finish(at.r, a.part + row * a.nsplit, a.nsplit, &bad);
-            if (!bad) {
-                SampleJob job;
-                job.kind = 2; job.row = cur.k; job.ref_p = M; job.ref_q = 0.0f; job.lam = 0.0;
-                double A = 0.0, scale = 1.0;
-                if (kTab && !(a.vflags & kVerifyNoExpTable) && tab_job_ok(job)) {
-                    scale = exp_fast_d(-(double)M, shT);
-#pragma unroll
-                    for (int c = 0; c < kChunks; ++c) {
-                        double cA = chunk_one_tab(at.q[c].w[0], shE);
-                        if (__builtin_expect(__builtin_amdgcn_ballot_w64(cA != cA) != 0, 0)) {        // a magnitude below the table
-                            asm volatile("" ::: "memory");
-                            float x[kPer];
-                            widen8<DT>(at.q[c], x);
-                            cA = 0.0;
-#pragma unroll
-                            for (int i = 0; i < kPer; ++i) cA += tab_exp_any(x[i], shE);
-                        }
-                        A += cA;
-                    }
-                } else {
-                    ExpRef ref;
-                    ref.set((double)M);
-                    double c2 = kExpC2;
-                    float top = INFINITY;
-                    asm volatile("" : "+v"(c2), "+v"(top));               // stay in vector registers
-#pragma unroll
-                    for (int c = 0; c < kChunks; ++c) {
-                        float x[kPer];
-                        widen8<DT>(at.q[c], x);
-                        double cA = 0.0;
-#pragma unroll
-                        for (int i = 0; i < kPer; ++i) cA += exp_fast(x[i], ref.neg_ref_c, ref.lo, shT, c2, top);
-                        A += cA;
-                    }
-                }
-                A = wave_sum_d(A) * scale;
-                if (lane == 0) a.sums[row * a.nsl + cur.s] = A;
-            }
-        }
-        cur = nxt; at = ahead; on = nxt_on;
-    }
+    const int sl = (int)(threadIdx.x >> USH) & ((1 << msh) - 1);
+    const Piece t = row_on_lanes<false, USH>(a, g, w0, w1, sl < a.nsplit, threadIdx.x & ((1 << USH) - 1), msh + USH, []() { return NAN; });
+    return row_signals(row_total<true>(t), a.V > 1).lse;
 }
 
-// Tokens: one workgroup per draft row finds the slice and the element that hold u * Z, and forms log q(tok).
-template <int DT>
-__global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
+// The same of the epilogue's staged path (see draft_finalize_staged): every piece completed and rounded by a lane, then merged one
+// by one; at most a wavefront of pieces.
+__device__ inline double row_lse_staged(const DraftFinalArgs &a, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1)
 {
-    warm_args(a);
+    const int sl = threadIdx.x & (kWave - 1);
+    Piece e = piece_from_words(w0, w1);
+    batch_fix(e, batch_issue(g, a.dtype, a.V, sl < a.nsplit ? e.idx : -1, a.part), a.dtype);
+    Piece acc = empty_piece();
+    for (int s = 0; s < a.nsplit; ++s) {
+        auto at = [&](int v) { return (uint32_t)__builtin_amdgcn_readlane(v, s); };
+        acc = merge_pair<true>(acc, piece_from_words(u32x4{at(__float_as_int(e.M)), at(__float_as_int((float)e.S)), at(__float_as_int((float)e.T)), at(__float_as_int(e.v2))},
+                                                     u32x4{at(e.idx), at(__float_as_int(e.xt)), 0u, 0u}));
+    }
+    return row_signals(row_total<true>(acc), a.V > 1).lse;
+}
+
+// Tokens: one workgroup per draft row finds the draw slice (see DrawSums) and the element that hold u * Z, and forms log q(tok).
+// OWN: the draft epilogue's workgroups ride in this launch, ahead of the others, and every row forms its lse itself, from the
+// partials, while the elements travel; else the epilogue has run and left it.
+template <int DT, bool OWN>
+__global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, DraftFinalArgs fin)
+{
+    if constexpr (OWN) {
+        warm_args(a, fin);
+        if ((int)blockIdx.x < a.B) { draft_finalize_body<false>(fin, blockIdx.x); return; }
+    } else warm_args(a);
     __shared__ double shT[256];
     __shared__ LocateShared shl;
-    const int row = blockIdx.x, b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
-    const double *ps = a.sums + (int64_t)row * a.nsl;
+    constexpr int kParts = kBlock / kWave, kVec = Elem<DT>::vec;
+    const int row = (int)blockIdx.x - (OWN ? a.B : 0), b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
+    const int per_split = a.nb * kStreamU, n_slices = a.nsplit * per_split;
+    double *ps = a.sums + (int64_t)row * n_slices * kParts;
     // everything is requested before anything is looked at: one round trip
-    const int npl = slices_per_lane(a.nsl), s0 = (tid & (kWave - 1)) * npl;
-    const double f0 = ps[min(s0, a.nsl - 1)], f1 = ps[min(s0 + 1, a.nsl - 1)];
+    const int npl = slices_per_lane(n_slices), s0 = (tid & (kWave - 1)) * npl;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    static_assert(kParts == 4, "two loads a slice");
+    auto request = [&](int s, d2 &lo, d2 &hi) { const d2 *p = (const d2 *)(ps + (int64_t)min(s, n_slices - 1) * kParts); lo = p[0]; hi = p[1]; };
+    d2 x0, y0, x1, y1;
+    request(s0, x0, y0);
+    request(s0 + 1, x1, y1);
     const double tv = a.exp_table[tid];
     const float u32v = a.u[row];
     const RowRefRegs rr = row_ref_issue(a.part + (int64_t)row * a.nsplit, a.nsplit);
     const int kl = a.k_len ? a.k_len[b] : a.K;
-    const double lse = a.lse[row];
-    asm volatile("" :: "v"(f0), "v"(f1), "v"(tv), "v"(u32v), "v"(rr.v1), "v"(rr.S), "v"(lse));
+    const char *rowp = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, b, k);
+    double lse = 0.0;
+    [[maybe_unused]] BatchGeom g{};
+    [[maybe_unused]] u32x4 w0{}, w1{};
+    [[maybe_unused]] int msh = 0, ush = 0;
+    if constexpr (OWN) {
+        msh = lane_merge_shift(a.K, a.nsplit);
+        ush = msh < 0 ? 0 : draft_lanes_shift(a.K << msh);
+        const int sl = msh < 0 ? tid & (kWave - 1) : (tid >> ush) & ((1 << msh) - 1);
+        const u32x4 *pp = (const u32x4 *)(a.part + (int64_t)row * a.nsplit + min(sl, a.nsplit - 1));
+        w0 = pp[0]; w1 = pp[1];
+        g = batch_geom(rowp, DT, a.V, sl, a.per);
+    } else lse = a.lse[row];
+    asm volatile("" :: "v"(x0), "v"(y0), "v"(x1), "v"(y1), "v"(tv), "v"(u32v), "v"(rr.v1), "v"(rr.S), "v"(lse), "v"(w0), "v"(w1));
     shT[tid] = tv;
     if (tid == 0) shl.last = -1;
     if (k >= kl) return;
@@ -1571,18 +1335,47 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a)
         return;
     }
     __syncthreads();                                                     // publishes the table
-    double z = s0 < a.nsl ? f0 : 0.0;
-    if (npl > 1) z += s0 + 1 < a.nsl ? f1 : 0.0;
-    for (int q = 2; q < npl; ++q) z += s0 + q < a.nsl ? ps[s0 + q] : 0.0;
-    const double Z = lanes_sum(z, 0, 6);
     Weights w;
     w.kind = 2; w.lam = 0.0;
     w.rp.set((double)M); w.rq.set(0.0);
     Rows r;
-    r.trow = r.drow = (const char *)row_address(a.base, DT, a.stride_b, a.stride_k, b, k);
+    r.trow = r.drow = rowp;
     int phase = 0, token = -1;
-    if (Z > 0.0)
-        token = find_token<DT, DT>(w, r, a.V, a.nsl, shT, (double)u32v * Z, [&](int s, int q) { return q == 0 ? f0 : (q == 1 ? f1 : ps[s]); }, &shl, phase);
+    const bool tab = DT == TAPOUT_BF16 && !(a.vflags & kVerifyNoExpTable);
+    if (__builtin_expect(M >= (tab ? kDrawLowTab : kDrawLow + 100.0f) && M < kDrawHigh, 1)) {
+        // the sums in the reference of the row's maximum
+        const double scale = exp_fast_d(-(double)M, shT);
+        auto sum4 = [&](const d2 &lo, const d2 &hi) { return ((lo.x + lo.y) + (hi.x + hi.y)) * scale; };
+        const double f0 = sum4(x0, y0), f1 = sum4(x1, y1);
+        auto weight = [&](int s, int q) -> double {
+            if (q == 0) return f0;
+            if (q == 1) return f1;
+            d2 lo, hi;
+            request(s, lo, hi);
+            return sum4(lo, hi);
+        };
+        double z = s0 < n_slices ? f0 : 0.0;
+        if (npl > 1) z += s0 + 1 < n_slices ? f1 : 0.0;
+        for (int q = 2; q < npl; ++q) z += s0 + q < n_slices ? weight(s0 + q, q) : 0.0;
+        const double Z = lanes_sum(z, 0, 6);
+        int head, nvec, tail;
+        row_geometry<DT>(rowp, a.V, head, nvec, tail);
+        auto start = [&](int s) {
+            const int split = s / per_split;
+            return s == 0 ? 0 : head + min(split * a.per + min((s - split * per_split) * kBlock, a.per), nvec) * kVec;
+        };
+        if (Z > 0.0) token = find_token<DT, DT>(w, r, a.V, n_slices, shT, (double)u32v * Z, weight, start, &shl, phase);
+    } else {
+        // logits beyond the range of the sums: all over again in the reference of the row's maximum (the sums' place holds them)
+        const int nsl = (a.V + kSampleSlice - 1) / kSampleSlice;
+        __syncthreads();                                                 // every wavefront has its sums
+        const double Z = slice_weights<DT, DT>(w, r, a.V, nsl, shT, ps);
+        if (Z > 0.0) token = find_token<DT, DT>(w, r, a.V, nsl, shT, (double)u32v * Z, [&](int s, int) { return ps[s]; }, whole_slice_start, &shl, phase);
+    }
+    if constexpr (OWN) {
+        if (__builtin_expect(msh < 0, 0)) lse = row_lse_staged(fin, g, w0, w1);
+        else lse = ush == 0 ? row_lse_lanes<0>(fin, g, w0, w1, msh) : (ush == 1 ? row_lse_lanes<1>(fin, g, w0, w1, msh) : row_lse_lanes<2>(fin, g, w0, w1, msh));
+    }
     if (tid == 0) {
         if (token < 0) token = 0;
         a.tok[row] = token;
@@ -1663,7 +1456,7 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
             double ztot = 0.0;
             for (int s = 0; s < v.nsl; ++s) {
                 double st;
-                locate_in_slice<TD, DD>(w, r, s, v.V, shT, 0.0, INFINITY, &shl, phase++, &st);
+                locate_in_slice<TD, DD>(w, r, s * kSampleSlice, v.V, shT, 0.0, INFINITY, &shl, phase++, &st);
                 if (tid == 0) zs[s] = st;
                 ztot += st;
             }
@@ -1717,7 +1510,7 @@ __global__ __launch_bounds__(kVBlock) void shard_locate(ShardFinalArgs a)
         return q == 0 ? fmax(f2 - delta * f3, 0.0) : fmax(at[2] - delta * at[3], 0.0);
     };
     // (a fallback's target lies beyond every slice: find_token then takes the last positive weight here)
-    const int token = find_token<TD, DD>(w, r, v.V, v.nsl, shT, fallback ? INFINITY : target - mine_prefix, slice_weight, &shl, phase);
+    const int token = find_token<TD, DD>(w, r, v.V, v.nsl, shT, fallback ? INFINITY : target - mine_prefix, slice_weight, whole_slice_start, &shl, phase);
     if (tid == 0) a.tok_out[b] = a.vocab_offset + (token < 0 ? 0 : token);
 }
 
@@ -1791,33 +1584,15 @@ hipError_t launch_typed(const VerifyArgs &a, const DraftFinalArgs &fin, bool wit
 hipError_t launch_shard_final_sums(const ShardFinalArgs &a, hipStream_t st) { return launch_shard_dispatch(a, 0, st); }
 hipError_t launch_shard_final_token(const ShardFinalArgs &a, hipStream_t st) { return launch_shard_dispatch(a, 1, st); }
 
-template <int DT>
-static hipError_t launch_sample_typed(SampleArgs &a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm)
+hipError_t launch_sample(const SampleArgs &a, const DraftFinalArgs *fin, hipStream_t st, Timing tm)
 {
-    if (pass == 0) {
-        constexpr int per_wg = kSampleBlock / kWave;
-        // All wavefronts the same number of slices, and no more workgroups than are resident beside the epilogue's (from 256
-        // sequences on half the places, behind an epilogue that takes more than the other half): one that waits for a place
-        // starts when others are done (V = 128256, B = 64, K = 1: 504 workgroups beside 64 11.8 us, 252 of
-        // two slices per wavefront 10.0; K = 8: 504 of eight slices 37.8, 448 of nine 34.0).
-        const int64_t slices = (int64_t)a.B * a.K * a.nsl;
-        const int64_t places = (int64_t)per_wg * (a.B < kSampleWgs / 2 ? kSampleWgs - a.B : kSampleWgs / 2);
-        const int64_t rounds = (slices + places - 1) / places;
-        const int wgs = (int)((slices + rounds * per_wg - 1) / (rounds * per_wg));
-        a.n_waves = wgs * per_wg;
-        const int step_rows = a.n_waves / a.nsl;
-        a.step_s = a.n_waves % a.nsl; a.step_b = step_rows / a.K; a.step_k = step_rows % a.K;
-        launch_kernel(sample_slices_kernel<DT>, dim3(a.B + wgs), dim3(kSampleBlock), st, tm, a, fin);
-    } else {
-        launch_kernel(sample_locate_kernel<DT>, dim3(a.B * a.K), dim3(kVBlock), st, tm, a);
-    }
+    static const DraftFinalArgs no_fin{};
+    if (!a.exp_table || (fin != nullptr) != (a.lse == nullptr)) return hipErrorInvalidValue;
+    if (fin && (fin->B != a.B || fin->shards > 0 || !sample_own_lse(a.B, a.K, a.nsplit))) return hipErrorInvalidValue;
+    const dim3 grid(a.B * a.K + (fin ? a.B : 0)), block(kVBlock);
+    if (a.dtype == TAPOUT_F32) launch_kernel(fin ? sample_locate_kernel<TAPOUT_F32, true> : sample_locate_kernel<TAPOUT_F32, false>, grid, block, st, tm, a, fin ? *fin : no_fin);
+    else launch_kernel(fin ? sample_locate_kernel<TAPOUT_BF16, true> : sample_locate_kernel<TAPOUT_BF16, false>, grid, block, st, tm, a, fin ? *fin : no_fin);
     return hipGetLastError();
-}
-
-hipError_t launch_sample(SampleArgs a, const DraftFinalArgs &fin, int pass, hipStream_t st, Timing tm)
-{
-    if (!a.exp_table || fin.B != a.B || !fin.sampled_lse || fin.shards > 0) return hipErrorInvalidValue;
-    return a.dtype == TAPOUT_F32 ? launch_sample_typed<TAPOUT_F32>(a, fin, pass, st, tm) : launch_sample_typed<TAPOUT_BF16>(a, fin, pass, st, tm);
 }
 
 hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing tm, const DraftFinalArgs *fin)

@@ -255,6 +255,38 @@ def test_draft_token_draw_with_a_wavefront_per_slice(B, K, V, dt, ragged):
     assert torch.equal(a, b) and torch.equal(out["flags"], given["flags"])
 
 
+@pytest.mark.parametrize("V,K,off,options", [
+    (9001, 2, 0, {}), (9001, 2, 3, {"exp_lookup": 0}), (2055, 70, 1, {}),           # 70 rows: the epilogue in a launch of its own
+    (7, 2, 1, {}), (40000, 2, 0, {"wgs_target": 1, "slice_bytes": 1 << 22}),        # no whole vector in some rows; slices of many batches
+    (150001, 1, 5, {"wgs_target": 1, "slice_bytes": 1 << 22}),                      # more than sixteen of them
+    (9001, 2, 0, {"min_slice": 256}),                                               # draw slices shorter than their batch
+])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_draft_token_draw_at_every_magnitude(V, K, off, options, dt):
+    """The sums of the draw are kept in the logits' own scale: inside its range, beyond the table of bfloat16 exponentials, beyond the
+    range on either side, and with values too small for the table; every other output as without a draw."""
+    g = torch.Generator().manual_seed(V + K)
+    moves = [lambda x: x, lambda x: x + 70, lambda x: x - 40, lambda x: x * 40, lambda x: x + 800, lambda x: x - 900, lambda x: x * 1e-4, lambda x: x * 0,
+             lambda x: torch.where(x > 0, x * 1e-5, -torch.inf), lambda x: torch.where(x > 3, x + 62, torch.finfo(torch.float32).min)]
+    B = len(moves)
+    x = torch.randn(B, K, V + off, generator=g) * 2
+    x[:, :, off + V // 2] = 4.0
+    draft = torch.stack([m(x[b]) for b, m in enumerate(moves)]).to(dt).to(DEV)[:, :, off:]
+    u = torch.rand(B, K, generator=g)
+    tp = binding.Tapout(B, K, V, draft_sampling=True)
+    for name, value in options.items():
+        tp.set_option(name, value)
+    arm = random_arms(B, seed=V)
+    o = tp.draft_stats(draft, arm=arm, u_draft=u.to(DEV))
+    osm = orc.draft_sample(pu.host_logits(draft), u.numpy(), nthreads=16)
+    tok, near = o["sampled_tok"].cpu().numpy(), osm["icdf_margin"] <= pu.TAU_S
+    # cell edges lie 1/V apart: a uniform within 1e-9 of one is a chance of about V 1e-9, more where few tokens hold all the mass
+    assert near.sum() <= 1 and (tok[~near] == osm["tok"][~near]).all()
+    again = tp.draft_stats(draft, draft_tok=o["sampled_tok"], arm=arm)
+    for key in (*pu.STAT_KEYS, "top1_id", "n_stop", "flags"):
+        assert torch.equal(o[key], again[key]), key
+
+
 @pytest.mark.parametrize("G,V", [(1, 3000), (3, 9001), (16, 20000), (17, 20011), (64, 40000), (70, 33000)])
 @pytest.mark.parametrize("dt", [f32, bf16])
 def test_vocabulary_shards_merged_across_lanes(G, V, dt):
