@@ -144,14 +144,16 @@ struct ThreadState {
     // maximum), reference check, sums.  The entropy sum of a vector is formed without looking at the terms; a masked
     // (-inf) logit gives 0 * -inf = NaN there, and only then the vector is summed again with the exponent clamped (one
     // comparison per vector instead of one clamp per element).
-    // each(u): called when vector u has been folded.
+    // n: the vectors behind the n-th hold nothing in the whole wavefront and are passed over.  each(u): called when vector u has been
+    // folded.
     template <int U, int N, class Each>
-    __device__ inline void fold_batch(const u32x4 (&w)[U], int32_t first, int32_t stride, Each each)
+    __device__ inline void fold_batch(const u32x4 (&w)[U], int n, int32_t first, int32_t stride, Each each)
     {
         bool grew = false;                                    // a lane mask in scalar registers
         float sb = 0.0f, tb = 0.0f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (U > 1 && u >= n) continue;
             float x[N];
             if constexpr (N == 8) unpack<TAPOUT_BF16>(w[u], x);
             else if constexpr (N == 4) unpack<TAPOUT_F32>(w[u], x);
@@ -208,7 +210,7 @@ struct ThreadState {
     {
         u32x4 w[1];
         w[0] = u32x4{__float_as_uint(x0), 0u, 0u, 0u};
-        fold_batch<1, 1>(w, j, 0, [](int) {});
+        fold_batch<1, 1>(w, 1, j, 0, [](int) {});
     }
 };
 
@@ -263,10 +265,21 @@ __device__ inline void load_batch(u32x4 (&w)[U], const u32x4 *vp, int i, int end
 
 struct NoMore { __device__ void operator()(int) const {} };
 template <int DT, bool FULL, int U, class Each = NoMore>
-__device__ inline void fold_batch(ThreadState<FULL> &st, const u32x4 (&w)[U], int i, int head, Each each = Each())
+__device__ inline void fold_batch(ThreadState<FULL> &st, const u32x4 (&w)[U], int n, int i, int head, Each each = Each())
 {
     constexpr int VEC = Elem<DT>::vec;
-    st.template fold_batch<U, VEC>(w, head + i * VEC, kBlock * VEC, each);
+    st.template fold_batch<U, VEC>(w, n, head + i * VEC, kBlock * VEC, each);
+}
+
+// How many of its vectors of a batch a wavefront has to fold (first: the batch's first vector, end: behind the slice's last one), where
+// the vector ALU is what bounds the pass: the draw's.  (Its launch, 1024 rows of V = 50257, bfloat16 48.5 us with the whole batch
+// folded at the end of a row, 41.7 so, and 0.3 of 41 us the other way where batches are whole; the passes without a draw wait for memory,
+// 0.3 % longer with it.)
+template <int U>
+__device__ inline int wave_vectors(int first, int end)
+{
+    const int left = end - __builtin_amdgcn_readfirstlane(first + ((int)threadIdx.x & (kBlock - 1) & -kWave));
+    return max(min((left + kBlock - 1) / kBlock, U), 0);
 }
 
 // ---- slice sums of the draft-token draw, on the way ------------------------------------------------
@@ -504,7 +517,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
             u32x4 w[U];
             if (bi < nfull) load_batch<DT, U, false>(w, vp, i, v1e);      // every vector of the batch lies inside the slice
             else load_batch<DT, U, true>(w, vp, i, v1e);
-            fold_batch<DT, FULL, U>(st, w, i, head);
+            fold_batch<DT, FULL, U>(st, w, U, i, head);
         }
         __builtin_amdgcn_s_setprio(3);      // finish the reduction promptly: the slot is wanted by the next workgroup
     }
@@ -606,10 +619,11 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
             for (int bi = b0; bi < b1d; ++bi) {
                 const int i = at.v0 + bi * (U * kBlock) + tid;
                 u32x4 w[U];
+                int n = U;
                 if (at.v0 + (bi + 1) * (U * kBlock) <= at.v1e) load_batch<DT, U, false>(w, vp, i, at.v1e);
-                else load_batch<DT, U, true>(w, vp, i, at.v1e);
-                double v[U];
-                fold_batch<DT, true, U>(st, w, i, at.head, [&](int u) { v[u] = draw.vector(w[u]); });
+                else { load_batch<DT, U, true>(w, vp, i, at.v1e); n = wave_vectors<U>(at.v0 + bi * (U * kBlock), at.v1e); }
+                double v[U] = {0.0, 0.0, 0.0, 0.0};
+                fold_batch<DT, true, U>(st, w, n, i, at.head, [&](int u) { v[u] = draw.vector(w[u]); });
                 missing |= (uint64_t)draw.missing(v, st.v1) << ((bi - b0) * U);
                 draw.store(v, bi);
             }
