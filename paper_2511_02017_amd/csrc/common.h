@@ -95,6 +95,9 @@ struct RowReduceArgs {
 };
 // Streaming pass: one Partial per (row, slice).  Returns hipGetLastError() after enqueueing.
 hipError_t launch_row_reduce(const RowReduceArgs &a, int dtype, bool full, hipStream_t st, Timing tm);
+// The records of a vocabulary shard's rows in one launch: `out` is [n_rows], nsplit 1; tok holds global indices, of which the shard's
+// first is vocab_offset.
+hipError_t launch_shard_records(const RowReduceArgs &a, int vocab_offset, int dtype, hipStream_t st, Timing tm);
 // Draft pass (all statistics) and target pass of the same sequences in one launch.
 hipError_t launch_row_reduce_pair(const RowReduceArgs &d, int d_dtype, const RowReduceArgs &t, int t_dtype, hipStream_t st, Timing tm);
 
@@ -189,7 +192,7 @@ struct VerifyArgs {
     uint32_t *flags_ws;           // internal copy of the flags (always present)
     JobRecord *jobs;              // [B]
     double *part1;                // [B, nsl, 5]  A, B, R~, D, U of each slice
-    double *part2;                // [B, nsl]     exact weight of each slice (slow path)
+    double *part2;                // [B, nsl]     exact weight of each slice (slow path); slice launch of a shard: [B, 5] the sequences' sums
     const double *exp_table;      // 2^(k/256), k = 0..255, then the kExpBf16Doubles entries of the bfloat16 table
     // tapout_round: workgroups of the locate launch also end the round: rewards into the sequences' bandits
     // (arm b_arm_in[b], accept_len, n_draft, b_gamma, b_active as tapout_bandit_update) and the arms of the next round

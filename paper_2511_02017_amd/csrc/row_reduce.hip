@@ -372,10 +372,13 @@ struct DrawSums {
 
 // What a workgroup leaves of slice `split` of a row: the threads' sums reduced, its Partial written.  tok_bits: the logit of the row's
 // token, if the slice holds it.  set: which of kSets copies of the records in LDS; on: there is a slice (all threads come to the barrier).
-template <int DT, bool FULL, int kSets = 1, int PARTS = 1>
+// RECORD: the slice is the whole row, rowp, and what is left is the row's shard record: the left-out batch back in, all but the
+// first maximum, whose index is exact and global.
+template <int DT, bool FULL, int kSets = 1, int PARTS = 1, bool RECORD = false>
 __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FULL> &st, const int split, const int row, const uint32_t tok_bits,
-                                    const bool holds_tok, const int set = 0, const bool on = true)
+                                    const bool holds_tok, const int set = 0, const bool on = true, const char *rowp = nullptr, const int vocab_offset = 0)
 {
+    static_assert(!RECORD || FULL, "a record holds all statistics");
     __shared__ u32x4 sh_rec[kSets][kBlock / kWave][2];
     const int tid = PARTS > 1 ? threadIdx.x & (kBlock - 1) : threadIdx.x;
     // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
@@ -451,6 +454,17 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
         }
         p.S = quad_sum(S);
         p.pad[0] = holds_tok ? (int)(DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000;
+        if constexpr (RECORD) {
+            // a vector of the batch per lane of the quad (no finite maximum: nothing is left out)
+            const int u = lane & 3;
+            const BatchVecs<1> bt = batch_issue_vecs<1>(batch_geom(rowp, DT, a.V, 0, a.per), DT, a.V, p.cand, u, a.out);
+            const BatchExtra x = batch_sum<DT>(ref_of_max(M), M, true, bt, u);
+            const int idx = lanes_min(x.idx, 0, kBits);
+            p.S = (float)((double)p.S + lanes_sum((double)x.sa, 0, kBits));
+            p.T = (float)((double)p.T + lanes_sum((double)x.ta, 0, kBits));
+            p.cand = vocab_offset + (idx >= 0 && idx < a.V ? idx : 0);
+            p.pad[1] = 0;
+        }
         if (tid == 0 && on) {
             u32x4 *o = (u32x4 *)(a.out + (int64_t)row * a.nsplit + split);
             o[0] = u32x4{__float_as_uint(p.v1), __float_as_uint(p.S), __float_as_uint(p.T), __float_as_uint(p.v2)};
@@ -460,8 +474,8 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
 }
 
 // The work of one workgroup: slice `split` of row k of sequence b.
-template <int DT, bool FULL>
-__device__ inline void stream_pass_body(const RowReduceArgs &a, const int split, const int k, const int b)
+template <int DT, bool FULL, bool RECORD = false>
+__device__ inline void stream_pass_body(const RowReduceArgs &a, const int split, const int k, const int b, const int vocab_offset = 0)
 {
     constexpr int VEC = Elem<DT>::vec;
     // vectors in flight per thread.  Four is best for both passes: for the draft pass that means 77 registers
@@ -489,6 +503,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         int zero;
         asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
         tk = a.tok[(int64_t)b * a.tok_rows + k + zero];
+        if constexpr (RECORD) tk -= vocab_offset;
     }
     const char *rowp = (const char *)a.base + ((int64_t)b * a.stride_b + (int64_t)k * a.stride_k) * Elem<DT>::size;
     int head, nvec, tail;
@@ -543,7 +558,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         st.fold_single(load_elem<DT>(rowp, j), j);
     }
 
-    finish_slice<DT, FULL>(a, st, split, b * a.KK + k, tok_bits, holds_tok);
+    finish_slice<DT, FULL, 1, 1, RECORD>(a, st, split, b * a.KK + k, tok_bits, holds_tok, 0, true, rowp, vocab_offset);
 }
 
 // grid = (slice, row of the sequence, sequence): no index arithmetic ahead of the first load.
@@ -553,6 +568,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 {
     warm_args(a);
     stream_pass_body<DT, FULL>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// A workgroup per row of a vocabulary shard: the row's record, with no launch behind this one to merge slices.
+template <int DT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void stream_record_kernel(RowReduceArgs a, int vocab_offset)
+{
+    warm_args(a);
+    stream_pass_body<DT, true, true>(a, 0, blockIdx.x, blockIdx.y, vocab_offset);
 }
 
 // Draft rows and target rows of a round in ONE launch: grid = (slice, row, 2 * sequences), the first half of the
@@ -666,6 +689,13 @@ hipError_t launch(const RowReduceArgs &a, hipStream_t st, Timing tm)
     return hipGetLastError();
 }
 
+template <int DT>
+hipError_t launch_record(const RowReduceArgs &a, int vocab_offset, hipStream_t st, Timing tm)
+{
+    launch_kernel(stream_record_kernel<DT>, dim3((unsigned)a.KK, (unsigned)(a.n_rows / a.KK)), dim3(kBlock), st, tm, a, vocab_offset);
+    return hipGetLastError();
+}
+
 template <int DD, int TD>
 hipError_t launch_pair(const RowReduceArgs &d, const RowReduceArgs &t, hipStream_t st, Timing tm)
 {
@@ -709,6 +739,12 @@ hipError_t launch_row_reduce(const RowReduceArgs &a, int dtype, bool full, hipSt
 {
     if (dtype == TAPOUT_F32) return full ? launch<TAPOUT_F32, true>(a, st, tm) : launch<TAPOUT_F32, false>(a, st, tm);
     return full ? launch<TAPOUT_BF16, true>(a, st, tm) : launch<TAPOUT_BF16, false>(a, st, tm);
+}
+
+hipError_t launch_shard_records(const RowReduceArgs &a, int vocab_offset, int dtype, hipStream_t st, Timing tm)
+{
+    if (a.nsplit != 1) return hipErrorInvalidValue;
+    return dtype == TAPOUT_F32 ? launch_record<TAPOUT_F32>(a, vocab_offset, st, tm) : launch_record<TAPOUT_BF16>(a, vocab_offset, st, tm);
 }
 
 }  // namespace tapout

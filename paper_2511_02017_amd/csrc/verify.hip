@@ -615,9 +615,13 @@ __device__ inline void chunk_pair_tab(const u32x4 &wt, const u32x4 &wd, const do
 // have no table and fit five (96 registers, no spills; two binary32 rows spill).  Launch at five / four, V = 256000, 512
 // sequences, K = 4: binary32 draft rows 164.8 / 167.7 us, bfloat16 draft rows the same within its spread of 3; V = 128256, 128
 // sequences 27.7 / 27.3.
-template <int TD, int DD, bool FUSED, int SPLIT>
-__global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != DD && !FUSED ? 5 : 4))) void verify_slices(VerifyArgs a)
+// WAVES: four, or in the sums of a vocabulary shard sixteen, a workgroup for all slices of a sequence, which leaves the sequence's
+// sums too (a.part2).
+template <int TD, int DD, bool FUSED, int SPLIT, int WAVES = kWavesPerWG>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(TD != DD && !FUSED && WAVES == kWavesPerWG ? 5 : 4))) void verify_slices(VerifyArgs a)
 {
+    constexpr bool kTotals = WAVES > kWavesPerWG;                // one workgroup per sequence
+    static_assert(!kTotals || !FUSED, "the accept decisions are taken by 256 threads");
     constexpr int kSliceChunks = kChunks / SPLIT;                // of a wavefront
 
     // The table serves row pairs of bfloat16 only: with one row computed and one looked up the compiler's schedule
@@ -631,8 +635,8 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     __shared__ double shT[256];
     __shared__ __align__(16) unsigned char sh_raw[kRaw];
     __shared__ HeadLanes sh_lanes[1];
-    __shared__ double sh_sums[SPLIT > 1 ? kWavesPerWG : 1][kSliceVals];
-    static_assert(sizeof shT + sizeof sh_raw + sizeof sh_lanes + sizeof sh_sums <= 32 * 1280, "four workgroups' LDS per compute unit");
+    __shared__ double sh_sums[SPLIT > 1 || kTotals ? WAVES : 1][kSliceVals];
+    static_assert(kTotals || sizeof shT + sizeof sh_raw + sizeof sh_lanes + sizeof sh_sums <= 32 * 1280, "four workgroups' LDS per compute unit");
     warm_args(a);
     [[maybe_unused]] const int wg = WG_LINEAR();
     WG_STAMP(g_stamps_slices, 8, wg, 0);                         // entry
@@ -640,15 +644,15 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     // FUSED: the sequence's last workgroup writes the sequence's outputs, from its first wavefront, which therefore
     // takes the group's last slice: most often none at all, or the row's short last one
-    const bool writer = FUSED && (int)blockIdx.x == (a.nsl * SPLIT + kWavesPerWG - 1) / kWavesPerWG - 1;
-    const int piece = blockIdx.x * kWavesPerWG + (writer ? kWavesPerWG - 1 - wave : wave);
+    const bool writer = FUSED && (int)blockIdx.x == (a.nsl * SPLIT + WAVES - 1) / WAVES - 1;
+    const int piece = blockIdx.x * WAVES + (writer ? WAVES - 1 - wave : wave);
     const int s = piece / SPLIT, part = piece % SPLIT;
     // The table goes from memory to LDS directly, no registers in between, while the accept decisions are taken (FUSED) or the
     // job's record travels.  (Through registers it held 36 of them over the decisions: spills, and the wait for the table
     // in front of the decisions; 20.5 us where this takes 15.9.)
     static_assert(kVBlock == 256, "one entry of the small table per thread");
     auto request_table = [&]() {
-        if constexpr (kTabT) copy_to_lds<kTabVecs, kVBlock>(a.exp_table + 256, sh_raw);
+        if constexpr (kTabT) copy_to_lds<kTabVecs, WAVES * kWave>(a.exp_table + 256, sh_raw);
     };
     SampleJob job;
     if constexpr (FUSED) {
@@ -657,14 +661,18 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
         // the same code on the same inputs and reach the same job; one of them writes the sequence's outputs.
         job = verify_head(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table);
     } else {
-        const double tv = a.exp_table[threadIdx.x];
+        const double tv = a.exp_table[threadIdx.x & 255];
         job = a.final_jobs ? a.final_jobs[b] : a.jobs[b].job;      // vocabulary shards: the caller's copy
         request_table();
-        shT[threadIdx.x] = tv;
+        if (!kTotals || threadIdx.x < 256) shT[threadIdx.x] = tv;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // before the rows are requested: nothing younger to wait for
     }
     WG_STAMP(g_stamps_slices, 8, wg, 1);                         // job known
-    if (job.kind == 0) return;
+    if (job.kind == 0) {
+        if constexpr (kTotals)
+            if (threadIdx.x < kSliceVals) a.part2[(int64_t)b * kSliceVals + threadIdx.x] = 0.0;
+        return;
+    }
     const Rows r = job_rows<TD, DD>(a, b, job);
     const bool live = s < a.nsl;
     const bool resid = job.kind == 1;
@@ -714,7 +722,13 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     }
     if constexpr (!FUSED) __syncthreads();                       // (FUSED: the decisions' last barrier has published the tables)
     WG_STAMP(g_stamps_slices, 8, wg, 2);                         // tables in LDS, rows requested
-    if (!live) return;
+    if (!live) {
+        if constexpr (kTotals) {
+            if (lane < kSliceVals) sh_sums[wave][lane] = 0.0;
+            __syncthreads();
+        }
+        return;
+    }
     ExpRef rp, rq;
     rp.set((double)job.ref_p); rq.set((double)job.ref_q);
     const TabScale sc = tab_scale(job, tab_t, tab_d, shT);
@@ -814,7 +828,7 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
     A = wave_sum_d(A) * sc.ct;
     if (resid) { Bs = wave_sum_d(Bs) * sc.cd; R = wave_sum_d(R) * sc.ct; D = wave_sum_d(D) * sc.cd; U = wave_sum_d(U) * sc.cd; }
     double *o = a.part1 + ((int64_t)b * a.nsl + s) * kSliceVals;
-    if constexpr (SPLIT == 1) {
+    if constexpr (SPLIT == 1 && !kTotals) {
         if (lane == 0) { o[0] = A; o[1] = Bs; o[2] = R; o[3] = D; o[4] = U; }
     } else {
         if (lane == 0) { double *m = sh_sums[wave]; m[0] = A; m[1] = Bs; m[2] = R; m[3] = D; m[4] = U; }
@@ -826,6 +840,13 @@ __global__ __launch_bounds__(kVBlock) __attribute__((amdgpu_waves_per_eu(TD != D
             for (int q = 1; q < SPLIT; ++q) sum += sh_sums[writer ? wave - q : wave + q][lane];
             o[lane] = sum;
         }
+        if constexpr (kTotals)
+            if (wave == 0 && lane < kSliceVals) {                // (what the job has no sum of is 0)
+                double sum = 0.0;
+#pragma unroll
+                for (int q = 0; q < WAVES; ++q) sum += sh_sums[q][lane];
+                a.part2[(int64_t)b * kSliceVals + lane] = sum;
+            }
     }
     WG_STAMP(g_stamps_slices, 8, wg, 7);                         // first wavefront's sums stored
 }
@@ -1541,10 +1562,23 @@ void launch_slices(const VerifyArgs &a, hipStream_t st, Timing tm)
     else launch_kernel(verify_slices<TD, DD, FUSED, 1>, grid, block, st, tm, a);
 }
 
+// A shard's sums: all slices of a sequence in one workgroup of sixteen wavefronts, which adds them up itself, where that workgroup has
+// but one slice or the sequences alone fill the chip; else the slices spread over the chip and a launch behind them adds up (us per call apart
+// / together, bfloat16: V = 2000, 64 sequences 7.2 / 5.3; V = 8016, 64 and 256 sequences 7.2 / 7.5, 10.0 / 8.1; V = 16032 8.1 / 9.7, 12.8 / 10.6;
+// V = 32064 9.7 / 14.6, 19.5 / 16.5).
+constexpr int kShardWaves = 16;
+inline bool shard_totals(int B, int nsl) { return nsl == 1 || (B >= 192 && nsl <= kShardWaves); }
 template <int TD, int DD>
 hipError_t launch_shard_typed(const ShardFinalArgs &a, int pass, hipStream_t st)
 {
-    if (pass == 0) {
+    if (pass == 0 && shard_totals(a.v.B, a.v.nsl)) {
+        VerifyArgs v = a.v;
+        v.part2 = a.sums_out;
+        const dim3 grid(1, v.B), block(kShardWaves * kWave);
+        if (v.nsl <= kShardWaves / 4) launch_kernel(verify_slices<TD, DD, false, 4, kShardWaves>, grid, block, st, Timing{}, v);
+        else if (v.nsl <= kShardWaves / 2) launch_kernel(verify_slices<TD, DD, false, 2, kShardWaves>, grid, block, st, Timing{}, v);
+        else launch_kernel(verify_slices<TD, DD, false, 1, kShardWaves>, grid, block, st, Timing{}, v);
+    } else if (pass == 0) {
         launch_slices<TD, DD, false>(a.v, st, Timing{});
         hipLaunchKernelGGL(shard_sums_kernel, dim3((a.v.B + kWavesPerWG - 1) / kWavesPerWG), dim3(kVBlock), 0, st, a);
     } else {

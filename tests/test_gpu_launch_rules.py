@@ -304,6 +304,37 @@ def test_vocabulary_shards_merged_across_lanes(G, V, dt):
         assert (acc.cpu().numpy()[ok] == ref["accept_len"][ok]).all() and (out.cpu().numpy()[ok] == ref["out_tok"][ok]).all()
 
 
+@pytest.mark.parametrize("B,K,V,G,dt", [
+    (5, 3, 65536, 2, bf16), (5, 3, 65538, 2, bf16), (5, 3, 32768, 2, f32), (5, 3, 32771, 2, f32),      # four batches a row and one element more
+    (7, 4, 13, 3, bf16), (7, 4, 30, 2, f32),                    # rows without a whole vector, rows that start off one
+    (191, 1, 8200, 2, bf16), (192, 1, 8200, 2, bf16),           # three slices of a sequence in workgroups of their own, in one
+    (192, 1, 65560, 2, f32), (200, 1, 65600, 2, bf16),          # seventeen and sixteen slices
+    (200, 2, 20000, 3, f32), (65, 2, 4000, 2, bf16),            # four, one
+])
+def test_shard_rows_and_sums_by_one_workgroup(B, K, V, G, dt):
+    rnd = mixed_round(B, K, V, dt, dt, seed=V)
+    rnd["greedy"][1] = 1
+    rnd["u_sample"][2:5] = torch.tensor([2.0 ** -12, 0.5, 1.0 - 2.0 ** -24], device=DEV)
+    for t in (rnd["draft"], rnd["target"]):                     # a maximum met twice, in one shard and in two; a shard without a finite logit
+        t[0, 0, [1, V // 4]] = 12.0
+        t[3, 0, [2, V - 2]] = 12.0
+        t[4, 0, :(V + G - 1) // G] = float("-inf")
+    acc, out, _ = sharded_round(rnd, G, V)
+    _, ref, nd = pu.oracle_round(rnd)
+    ok = ~((ref["accept_margin"] <= pu.TAU) & (np.arange(K)[None, :] < nd[:, None])).any(1) & ~(ref["icdf_margin"] <= pu.TAU_S)
+    assert ok.sum() >= B - 1 - B * K // 100                      # near ties: a few per thousand decisions; two planted maxima
+    assert (acc.cpu().numpy()[ok] == ref["accept_len"][ok]).all() and (out.cpu().numpy()[ok] == ref["out_tok"][ok]).all()
+    tps = binding.Tapout(B, K, V)
+    rec = torch.stack([tps.shard_stats(rnd["draft"][:, :, round(g * V / G):round((g + 1) * V / G)], round(g * V / G), length=rnd["k_len"],
+                                       tok=rnd["draft_tok"]).clone() for g in range(G)])
+    got = tps.draft_stats_sharded(rec, B, K, V, draft_tok=rnd["draft_tok"], k_len=rnd["k_len"])
+    ods, _, _ = pu.oracle_round(rnd)
+    live = np.arange(K)[None, :] < rnd["k_len"].cpu().numpy()[:, None]
+    for key in pu.STAT_KEYS:
+        pu.assert_stats_close(key, got[key].cpu().numpy(), ods[key], live)
+    assert (got["top1_id"].cpu().numpy()[live] == ods["top1_id"][live]).all()
+
+
 @pytest.mark.parametrize("P", [1, 2, 3, 16, 17])
 def test_shard_records_from_any_number_of_slices(P):
     """Sixteen slices of a shard's row are merged across lanes, seventeen one after the other: the same record."""
