@@ -230,9 +230,13 @@ __device__ inline void head_outputs(const VerifyArgs &a, int b, const SampleJob 
 // first rejection published by a second barrier, and the table through registers: slice kernel with the decisions, V = 128256,
 // 64 sequences, up to the stop position 17.4 us, this 15.9; head launch at 256 sequences, K = 16 7.0 / 5.6.)
 template <bool SHARDED, class Table>
-__device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool writer, HeadLanes *sh, double *shT, Table request_table, const int msh)
+__device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool writer, HeadLanes *sh, double *shT, Table request_table, const int msh, const int turn)
 {
     const int K = a.K, tid = threadIdx.x, lane = tid & (kWave - 1), sl = tid & ((1 << msh) - 1), per_pass = kVBlock >> msh;
+    // The rows go to the wavefronts from the `turn`-th on, and a wavefront without a row waits at the barrier: the workgroups of a compute
+    // unit put their wavefronts on the same four SIMDs, and one wavefront or two is all that most drafts need.  (us per round, rows clamped to the
+    // last one in all wavefronts / this: V = 32000, 32 sequences 24.06 / 23.81, V = 128256, 64 sequences 68.4 / 68.2.)
+    const int wave0 = __builtin_amdgcn_readfirstlane(((tid / kWave - turn) & (kVBlock / kWave - 1)) * kWave), vt = wave0 + lane;
     // Everything whose address does not depend on n_draft is requested before n_draft is looked at, so that
     // the first memory round trip carries n_draft, the tokens, the uniforms and the partials together.
     // (Rows beyond n_draft hold stale partials and unused tokens: read, never used.)
@@ -248,20 +252,24 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
     bool greedy = false;
     uint32_t f0 = 0;
     for (int row0 = 0; row0 <= K; row0 += per_pass) {                      // one pass but for long drafts of many slices
-        const int row = row0 + (tid >> msh), row_t = min(row, K), row_d = min(row, K - 1);
+        const bool busy = row0 + (wave0 >> msh) <= K;
+        const int row = row0 + (vt >> msh), row_t = min(row, K), row_d = min(row, K - 1);
         const int64_t it = (int64_t)b * (K + 1) + row_t, i = (int64_t)b * K + row_d;
-        const u32x4 *pt = (const u32x4 *)(SHARDED ? a.part + (int64_t)min(sl, a.nsplit - 1) * a.B * (K + 1) + it : a.part + it * a.nsplit + min(sl, a.nsplit - 1));
-        const u32x4 w0 = pt[0], w1 = pt[1];
-        float qv1 = -INFINITY, qS = 0.0f, qx = NAN, qh = 0.0f;
-        const int32_t tok = a.draft_tok[i];
-        const float u = a.u_accept[i];
-        float lq = 0.0f, dl = 0.0f;
-        if (own_q) {
-            const Partial *pd = a.dpart + i * a.d_nsplit + min(sl, a.d_nsplit - 1);
-            qv1 = pd->v1; qS = pd->S; qx = __int_as_float(pd->pad[0]); qh = __int_as_float(pd->pad[1]);
-        } else {
-            lq = a.logq_tok[i];
-            if (a.draft_lse) dl = a.draft_lse[i];                          // the final token's job wants it for row m: no dependent load later
+        u32x4 w0{}, w1{};
+        float qv1 = -INFINITY, qS = 0.0f, qx = NAN, qh = 0.0f, u = 0.0f, lq = 0.0f, dl = 0.0f;
+        int32_t tok = -1;
+        if (busy) {
+            const u32x4 *pt = (const u32x4 *)(SHARDED ? a.part + (int64_t)min(sl, a.nsplit - 1) * a.B * (K + 1) + it : a.part + it * a.nsplit + min(sl, a.nsplit - 1));
+            w0 = pt[0]; w1 = pt[1];
+            tok = a.draft_tok[i];
+            u = a.u_accept[i];
+            if (own_q) {
+                const Partial *pd = a.dpart + i * a.d_nsplit + min(sl, a.d_nsplit - 1);
+                qv1 = pd->v1; qS = pd->S; qx = __int_as_float(pd->pad[0]); qh = __int_as_float(pd->pad[1]);
+            } else {
+                lq = a.logq_tok[i];
+                if (a.draft_lse) dl = a.draft_lse[i];                      // the final token's job wants it for row m: no dependent load later
+            }
         }
         if (row0 == 0) request_table();
         asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(u), "v"(qv1), "v"(qS), "v"(qx), "v"(qh));     // every request is out before the first wait
@@ -273,6 +281,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
             greedy = __builtin_amdgcn_readfirstlane((int)greedy_raw) != 0;
             __syncthreads();                                               // the table: every row's decision reads it
         }
+        if (!busy) continue;
         // target row: maximum, sum and (start of the vector that holds) its first maximum.  Slice partials run over every
         // element of their slice; shard records leave their maximum out.
         const bool mine = sl < a.nsplit;
@@ -325,7 +334,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
         }
         Accept acc{false, NAN, 0u};
         if (row < n) acc = accept_row(a, r.bad, lse, greedy, tok, u, lq, p.xt, top1, shT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // the table's copy, before this workgroup's first stores
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // (the table's copy, before this wavefront's first stores)
         if (lead) {
             if constexpr (!SHARDED)
                 if (writer && !greedy) top1 = argmax_finish(probe, row_p, a.t_dtype, a.V, r.cand, r.M);
@@ -342,6 +351,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
         }
         HEAD_STAMP(2);                                                     // lse, log p(tok), accept decision
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the table's copy
     __syncthreads();
     // rows are lanes of every wavefront: ballots give the first rejection and the flags
     const uint64_t acc_mask = __builtin_amdgcn_ballot_w64(lane < n && sh->dec[lane] != 0);
@@ -502,10 +512,11 @@ __device__ inline int head_lanes_shift(const VerifyArgs &a)
 }
 // In the slice kernel: either path.
 template <class Table>
-__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer, HeadStaged *stg, HeadLanes *lanes, double *shT, Table request_table)
+__device__ inline SampleJob verify_head(const VerifyArgs &a, int b, bool writer, HeadStaged *stg, HeadLanes *lanes, double *shT, Table request_table, int wgs)
 {
     if (__builtin_expect(lane_merge_shift(a.K + 1, a.nsplit) < 0, 0)) return verify_head_staged<false>(a, b, writer, stg, shT, request_table);
-    return verify_head_lanes<false>(a, b, writer, lanes, shT, request_table, head_lanes_shift<false>(a));
+    // (a compute unit's workgroups follow each other by about the number of units)
+    return verify_head_lanes<false>(a, b, writer, lanes, shT, request_table, head_lanes_shift<false>(a), (int)((blockIdx.y * (unsigned)wgs + blockIdx.x) >> 8));
 }
 
 struct Rows {
@@ -532,7 +543,7 @@ __global__ __launch_bounds__(kVBlock) void verify_head_kernel(VerifyArgs a)
     __shared__ double shT[256];
     static_assert(kVBlock == 256, "one table entry per thread");
     if constexpr (STAGED) verify_head_staged<SHARDED>(a, blockIdx.x, true, &sh, shT, NoTable());
-    else verify_head_lanes<SHARDED>(a, blockIdx.x, true, &sh, shT, NoTable(), head_lanes_shift<SHARDED>(a));
+    else verify_head_lanes<SHARDED>(a, blockIdx.x, true, &sh, shT, NoTable(), head_lanes_shift<SHARDED>(a), 0);
 }
 
 // ---- slice kernel -----------------------------------------------------------------------
@@ -659,7 +670,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(T
         // Small batches: a head launch of its own costs more (launch, hand-over of the job record through
         // memory) than taking the accept decisions again in each of the sequence's workgroups.  All of them run
         // the same code on the same inputs and reach the same job; one of them writes the sequence's outputs.
-        job = verify_head(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table);
+        job = verify_head(a, b, writer, (HeadStaged *)sh_raw, sh_lanes, shT, request_table, (a.nsl * SPLIT + WAVES - 1) / WAVES);
     } else {
         const double tv = a.exp_table[threadIdx.x & 255];
         job = a.final_jobs ? a.final_jobs[b] : a.jobs[b].job;      // vocabulary shards: the caller's copy
