@@ -357,7 +357,7 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     const size_t nstate = (size_t)cfg->n_bandits * c->positions * cfg->n_arms;
     c->nsl_max = (cfg->vocab + kSampleSlice - 1) / kSampleSlice;
     const size_t nsums = (size_t)cfg->max_batch * 5;             // five per slice of a sequence's row pair
-    // 2^(k/256), then exp(x) of every bfloat16 x with 2^-12 <= |x| < 63.5: entry idx (x > 0) or pairs + idx (x < 0),
+    // 2^(k/256), then exp(x) of every bfloat16 x with 2^-12 <= |x| < 63.5: entry 2 idx (x > 0) or 2 idx + 1 (x < 0),
     // idx = 1 + (magnitude bits - (115 << 7)); idx 0 stands for all smaller magnitudes and holds NaN (the kernels
     // notice and compute), the last idx for all larger ones and holds zeros
     std::vector<double> table(256 + kExpBf16Doubles);
@@ -374,8 +374,8 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
             pos = std::exp((double)x);
             neg = std::exp(-(double)x);
         }
-        table[256 + idx] = pos;
-        table[256 + pairs + idx] = neg;
+        table[256 + 2 * idx] = pos;
+        table[256 + 2 * idx + 1] = neg;
     }
     bool ok = hipMalloc(&c->part, c->part_cap * sizeof(Partial)) == hipSuccess
            && hipMalloc(&c->part_t, c->part_cap * sizeof(Partial)) == hipSuccess

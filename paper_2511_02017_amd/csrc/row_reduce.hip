@@ -321,8 +321,8 @@ struct DrawSums {
         double e[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t o = tab_offsets2(w[i]);
-            e[i] = *(const double *)(at + (o & 0xffffu)) + *(const double *)(at + (o >> 16));
+            const TabOffsets o = tab_offsets2(w[i]);
+            e[i] = *(const double *)(at + o.lo) + *(const double *)(at + o.hi);
         }
         return (e[0] + e[1]) + (e[2] + e[3]);
     }

@@ -604,11 +604,11 @@ __device__ inline void chunk_pair_tab(const u32x4 &wt, const u32x4 &wd, const do
     const char *E = (const char *)shE;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const uint32_t ot = tab_offsets2(wt[k]), od = tab_offsets2(wd[k]);
+        const TabOffsets ot = tab_offsets2(wt[k]), od = tab_offsets2(wd[k]);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const double av = *(const double *)(E + (h ? ot >> 16 : ot & 0xffffu));
-            const double bv = *(const double *)(E + (h ? od >> 16 : od & 0xffffu));
+            const double av = *(const double *)(E + (h ? ot.hi : ot.lo));
+            const double bv = *(const double *)(E + (h ? od.hi : od.lo));
             const double diff = fma(-Lp, bv, av);
             cA += av;
             cB += bv;
