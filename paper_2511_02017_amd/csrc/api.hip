@@ -514,11 +514,13 @@ namespace {
 struct VerifyCall;
 hipError_t stream_pair(tapout_ctx *ctx, const RowReduceArgs &d, int d_dtype, const VerifyCall &c, hipStream_t st);
 RowReduceArgs target_pass_args(tapout_ctx *ctx, const VerifyCall &c);
+int target_dtype(const VerifyCall &c);
 
 // tapout_draft_stats.  pair != NULL (tapout_round): the streaming pass is one launch over the draft rows and the target
 // rows of *pair.  slices.n > 0 (tapout_round): how the draft rows are cut; else chosen here.  defer != NULL (tapout_round): the epilogue is not launched;
 // its arguments go to *defer for the caller to run later, the slice count to *defer_nsplit, and the streaming pass
 // leaves the logits of the drafted tokens in its partials.
+// behind != NULL (tapout_round up to the stop position): the epilogue and the target pass of *behind follow in two launches.
 tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
                                  int32_t B, int32_t K, int32_t V,
                                  const int32_t *draft_tok, const int32_t *k_len, const int32_t *arm,
@@ -526,7 +528,7 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
                                  float *lse, float *entropy, float *p_top1, float *p_top2, float *margin,
                                  int32_t *top1_id, float *logq_tok, int32_t *sampled_tok,
                                  int32_t *n_stop, uint8_t *stop_fired, uint32_t *flags, void *stream,
-                                 const VerifyCall *pair, Slices slices, DraftFinalArgs *defer = nullptr, int *defer_nsplit = nullptr)
+                                 const VerifyCall *pair, Slices slices, DraftFinalArgs *defer = nullptr, int *defer_nsplit = nullptr, const VerifyCall *behind = nullptr)
 {
     if (!ctx) return TAPOUT_EINVAL;
     tapout_status s = check_shape(ctx, B, K, V);
@@ -587,6 +589,13 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
         ctx->round_K = K;
     }
     if (defer) { *defer = f; *defer_nsplit = nsplit; return TAPOUT_OK; }
+    if (behind) {
+        const RowReduceArgs t = target_pass_args(ctx, *behind);
+        const int t_dtype = target_dtype(*behind);
+        e = timed(ctx, TAPOUT_PROFILE_DRAFT_FINALIZE, [&](Timing tm) { return launch_epilogue_stream(f, t, t_dtype, st, tm); });
+        if (e == hipSuccess && K + 1 > kFirstRows) e = timed(ctx, TAPOUT_PROFILE_TARGET_PASS, [&](Timing tm) { return launch_stream_rest(t, t_dtype, st, tm); });
+        return e == hipSuccess ? TAPOUT_OK : hip_fail(ctx, e, "draft finalize and target pass launch");
+    }
     if (u_draft) {
         // The epilogue waits for no token (their log q is formed where they are found): it rides in their launch, whose
         // workgroups form their rows' lse themselves.  Many rows, and very many slices: a launch of its own, which leaves the lse.
@@ -890,6 +899,8 @@ RowReduceArgs target_pass_args(tapout_ctx *ctx, const VerifyCall &c)
                          c.fused ? ctx->jobs : nullptr, c.draft_tok, c.K};     // the pass also picks up the logits of the drafted tokens
 }
 
+int target_dtype(const VerifyCall &c) { return c.target->dtype; }
+
 hipError_t verify_target_pass(tapout_ctx *ctx, const VerifyCall &c, hipStream_t st)
 {
     const RowReduceArgs r = target_pass_args(ctx, c);
@@ -1006,15 +1017,17 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
                                   : ctx->min_slice > 0 ? cut_evenly(c.slices.n, a->V, a->draft->dtype) : cut_in_batches(c.slices.n, a->V, a->draft->dtype);
     const bool defer = given && !ctx->stateful && ctx->defer_epilogue &&
                        own_q_shape(a->K, c.slices.n, d_slices.n);
+    // Up to the stop position, target rows that the draft rows' launch does not stream: the first two beside the epilogue.
+    const bool behind = !given && !pair && epilogue_streams(a->B, a->K, d_slices.n, c.slices.n);
     DraftFinalArgs fin{};
     int fin_nsplit = 0;
     s = draft_stats_impl(ctx, a->draft, a->B, a->K, a->V, a->draft_tok, a->k_len, a->arm, nullptr,
                          a->lse, a->entropy, a->p_top1, a->p_top2, a->margin, a->top1_id, a->logq_tok, nullptr,
                          a->n_stop, a->stop_fired, a->draft_flags, stream, pair ? &c : nullptr, d_slices,
-                         defer ? &fin : nullptr, &fin_nsplit);
+                         defer ? &fin : nullptr, &fin_nsplit, behind ? &c : nullptr);
     if (s != TAPOUT_OK) return s;
     hipError_t e = hipSuccess;
-    if (!pair) {
+    if (!pair && !behind) {
         e = verify_target_pass(ctx, c, st);
         if (e != hipSuccess) return hip_fail(ctx, e, "target pass launch");
     }

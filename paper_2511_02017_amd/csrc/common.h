@@ -127,6 +127,25 @@ struct DraftFinalArgs {
 };
 hipError_t launch_draft_finalize(const DraftFinalArgs &a, hipStream_t st, Timing tm);
 
+// The draft epilogue and the target pass up to the stop position it finds, in two launches: the first streams target rows 0 and 1, which
+// are wanted whatever that position is, beside the epilogue, the second the rows behind them (not to be launched for K = 1).
+constexpr int kFirstRows = 2;
+hipError_t launch_epilogue_stream(const DraftFinalArgs &f, RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm);
+hipError_t launch_stream_rest(RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm);
+
+// A sequence's draft rows are so few pieces that the epilogue has four lanes for each (draft_lanes_shift).
+inline bool few_pieces(int K, int nsplit)
+{
+    int p = 1;
+    while (p < nsplit) p *= 2;
+    return p <= 16 && K * p <= 64;
+}
+// The epilogue streams the first target rows beside it while that is about one round of workgroups (six are resident per compute unit).
+// us per round up to the stop position, V = 128256, bfloat16, 64 sequences, K = 8, apart / together 60.9 / 59.3 (92.0 / 89.1 diffuse rows,
+// 57.6 / 54.1 Zipf-like ones), 24 sequences, K = 4 34.9 / 33.9 (36.4 / 33.9, 32.9 / 30.1); V = 256000, binary32, 32 sequences, K = 3
+// 64.0 / 61.6 (63.4 / 56.6, 61.4 / 55.6); beyond 1280 workgroups V = 100001, 100 sequences 63.5 / 64.4, V = 151936, 200 sequences 185 / 189.
+inline bool epilogue_streams(int B, int K, int d_nsplit, int t_nsplit) { return few_pieces(K, d_nsplit) && (int64_t)B * (1 + kFirstRows * t_nsplit) <= 1280; }
+
 // One record per live row of a vocabulary shard from its slice partials (see tapout_shard_stats).
 struct ShardMergeArgs {
     const void *base; int32_t dtype; int64_t stride_b, stride_k;

@@ -345,4 +345,11 @@ __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
     }
 }
 
+// The same where few_pieces holds, for a kernel that needs the registers for something else (80 instead of 140).
+__device__ inline void draft_finalize_few(const DraftFinalArgs &a, const int b)
+{
+    __shared__ __align__(16) unsigned char lds[6 * kWave];
+    draft_finalize_lanes<false, 2>(a, b, lds, lane_merge_shift(a.K, a.nsplit));
+}
+
 }  // namespace tapout

@@ -35,6 +35,7 @@
 // about 3 us under streaming load and four of them chain up.
 #include "common.h"
 #include "exp_device.h"
+#include "finalize_device.h"
 
 namespace tapout {
 
@@ -570,6 +571,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     stream_pass_body<DT, FULL>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
+// The draft epilogue's workgroups and, behind them, target rows 0 and 1 of every sequence: up to the stop position those two are read
+// whatever it turns out to be, and the epilogue alone leaves the chip idle.
+template <int TD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void epilogue_stream_kernel(DraftFinalArgs f, RowReduceArgs t, int n_seq)
+{
+    static_assert(kBlock == kFinalBlock, "the epilogue runs in this kernel's workgroups");
+    warm_args(f, t);
+    if ((int)blockIdx.x < n_seq) { draft_finalize_few(f, blockIdx.x); return; }
+    const int i = (int)blockIdx.x - n_seq, row = i / t.nsplit, b = row / kFirstRows;
+    stream_pass_body<TD, false>(t, i - row * t.nsplit, row - b * kFirstRows, b);
+}
+// The target rows behind them.
+template <int TD>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void stream_rest_kernel(RowReduceArgs a)
+{
+    warm_args(a);
+    stream_pass_body<TD, false>(a, blockIdx.x, blockIdx.y + kFirstRows, blockIdx.z);
+}
+
 // A workgroup per row of a vocabulary shard: the row's record, with no launch behind this one to merge slices.
 template <int DT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void stream_record_kernel(RowReduceArgs a, int vocab_offset)
@@ -739,6 +759,26 @@ hipError_t launch_row_reduce(const RowReduceArgs &a, int dtype, bool full, hipSt
 {
     if (dtype == TAPOUT_F32) return full ? launch<TAPOUT_F32, true>(a, st, tm) : launch<TAPOUT_F32, false>(a, st, tm);
     return full ? launch<TAPOUT_BF16, true>(a, st, tm) : launch<TAPOUT_BF16, false>(a, st, tm);
+}
+
+hipError_t launch_epilogue_stream(const DraftFinalArgs &f, RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm)
+{
+    const int n_seq = t.n_rows / t.KK;
+    if (!epilogue_streams(f.B, f.K, f.nsplit, t.nsplit) || f.shards > 0 || f.B != n_seq || f.K + 1 != t.KK || t.arm_dst) return hipErrorInvalidValue;
+    t.len = nullptr; t.len_mode = 0;                          // rows 0 and 1 whatever the stop position
+    const dim3 grid((unsigned)(n_seq + n_seq * kFirstRows * t.nsplit)), block(kBlock);
+    if (t_dtype == TAPOUT_F32) launch_kernel(epilogue_stream_kernel<TAPOUT_F32>, grid, block, st, tm, f, t, n_seq);
+    else launch_kernel(epilogue_stream_kernel<TAPOUT_BF16>, grid, block, st, tm, f, t, n_seq);
+    return hipGetLastError();
+}
+hipError_t launch_stream_rest(RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm)
+{
+    if (t.KK <= kFirstRows || t.len_mode != 1 || t.arm_dst) return hipErrorInvalidValue;
+    t.clear_jobs = nullptr;                                   // (done with row 0)
+    const dim3 grid((unsigned)t.nsplit, (unsigned)(t.KK - kFirstRows), (unsigned)(t.n_rows / t.KK)), block(kBlock);
+    if (t_dtype == TAPOUT_F32) launch_kernel(stream_rest_kernel<TAPOUT_F32>, grid, block, st, tm, t);
+    else launch_kernel(stream_rest_kernel<TAPOUT_BF16>, grid, block, st, tm, t);
+    return hipGetLastError();
 }
 
 hipError_t launch_shard_records(const RowReduceArgs &a, int vocab_offset, int dtype, hipStream_t st, Timing tm)

@@ -126,6 +126,27 @@ def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
         assert pu.check_round(tp, rnd)["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("B,K,V,dt,tt", [
+    (64, 6, 32001, bf16, bf16),      # the first two target rows beside the epilogue, the others behind them; rows at every alignment
+    (32, 1, 256000, bf16, bf16),     # no others
+    (142, 3, 32000, bf16, bf16), (143, 3, 32000, bf16, bf16),    # 1278 and 1287 workgroups
+    (20, 16, 40000, bf16, f32),      # 16 rows of four pieces (five slices in groups of eight lanes: too many)
+    (60, 4, 50257, f32, bf16), (25, 17, 32000, bf16, bf16),      # 17 rows: too many pieces
+])
+@pytest.mark.parametrize("five", [False, True])
+def test_round_up_to_the_stop_position_beyond_the_small_targets(B, K, V, dt, tt, five):
+    pool = dict(rules=(0, 1, 2, 3, 4), thresholds=(0.6, 0.8, 0.2, 0.2, 0.4)) if five else dict(rules=(0, 1, 2), thresholds=(0.6, 0.8, 0.2))
+    rnd = mixed_round(B, K, V, dt, tt, seed=B + K)
+    assert rnd["target"].numel() * rnd["target"].element_size() > 24 << 20
+    rnd["draft"][::2] *= 3                                       # peaked rows beside flat ones: stop positions of 1 and more
+    tp = binding.Tapout(B, K, V, **pool)
+    arm = (torch.arange(B, device=DEV, dtype=torch.int32) % len(pool["rules"])).contiguous()
+    if five:
+        arm %= 3                                                 # (the stateful rules need a previous draft: played in the trajectory tests)
+    c = pu.check_round_call(tp, rnd, arm, truncate=True, **pool)
+    assert c["icdf_flagged"] <= 1 and c["accept_flagged"] + c["stop_flagged"] <= 2 + 4 * B * K // 500
+
+
 @pytest.mark.parametrize("dt,vec", [(f32, 4), (bf16, 8)])
 @pytest.mark.parametrize("off", [0, 3])
 def test_maxima_met_by_several_threads(dt, vec, off):
