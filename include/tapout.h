@@ -611,18 +611,21 @@ TAPOUT_API tapout_status tapout_set_option(tapout_ctx *ctx, const char *name, in
  */
 enum {
     TAPOUT_PROFILE_SELECT = 0,          /* bandit select                                            */
-    TAPOUT_PROFILE_DRAFT_PASS = 1,      /* streaming pass over the draft logits                     */
+    TAPOUT_PROFILE_DRAFT_PASS = 1,      /* streaming pass over the draft logits (with the sums of a */
+                                        /* draft-token draw where tokens are drawn)                 */
     TAPOUT_PROFILE_DRAFT_FINALIZE = 2,  /* signals + stop scan, where it is a launch of its own: it */
-                                        /* rides in SAMPLE_SLICES where tokens are drawn, and in    */
-                                        /* VERIFY_LOCATE where tapout_round defers it               */
-    TAPOUT_PROFILE_TARGET_PASS = 3,     /* streaming pass over the target logits                    */
+                                        /* rides in SAMPLE_LOCATE where tokens of few rows are      */
+                                        /* drawn, and in VERIFY_LOCATE where tapout_round defers    */
+                                        /* it; up to the stop position tapout_round may stream      */
+                                        /* target rows 0 and 1 in this launch                       */
+    TAPOUT_PROFILE_TARGET_PASS = 3,     /* streaming pass over the target logits (over the rows     */
+                                        /* from 2 on in that case)                                  */
     TAPOUT_PROFILE_VERIFY_HEAD = 4,     /* accept tests, first rejection, emitted prefix            */
     TAPOUT_PROFILE_VERIFY_SLICES = 5,   /* final token: slice sums of the row pair                  */
     TAPOUT_PROFILE_VERIFY_LOCATE = 6,   /* final token: normalisers, slice, token                   */
     TAPOUT_PROFILE_UPDATE = 7,          /* bandit update                                            */
     TAPOUT_PROFILE_SAMPLE_HEAD = 8,     /* no such launch any more: always 0 launches               */
-    TAPOUT_PROFILE_SAMPLE_SLICES = 9,   /* draft-token sampling: slice sums of every draft row;     */
-                                        /* signals + stop scan                                      */
+    TAPOUT_PROFILE_SAMPLE_SLICES = 9,   /* no such launch any more: always 0 launches               */
     TAPOUT_PROFILE_SAMPLE_LOCATE = 10,  /* draft-token sampling: slice, token                       */
     TAPOUT_PROFILE_STREAM_PAIR = 11,    /* tapout_round: draft and target rows in one streaming pass */
     TAPOUT_PROFILE_KINDS = 12

@@ -1,6 +1,7 @@
 // Device code of the draft epilogue (see finalize.hip), in a header because several kernels run it: the epilogue kernel
 // of its own, and the final-token locate kernel of a whole-round call, whose launch carries the epilogue's
-// workgroups beside its own (as does the slice kernel of the draft-token draw).
+// workgroups beside its own (as do the token search of the draft-token draw, and the launch that streams the first target rows
+// of a round up to the stop position).
 #pragma once
 #include <type_traits>
 

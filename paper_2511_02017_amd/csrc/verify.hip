@@ -57,15 +57,17 @@ constexpr int kStampWgs = 1 << 16;
 __device__ unsigned long long g_stamps_slices[kStampWgs * 8];      // slice kernel, by linear workgroup index
 __device__ unsigned long long g_stamps_head[kStampWgs * 4];        // accept decisions inside it, same index
 __device__ unsigned long long g_stamps_locate[4096 * 8];           // locate kernel (and the draft epilogue's workgroups in its launch)
+#define HEAD_STAMP_BY(who, slot) do { if (who) g_stamps_head[WG_LINEAR() * 4 + (slot)] = wall_clock64(); } while (0)
 #define WG_LINEAR() ((int)(((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) & (kStampWgs - 1)))
 #define WG_STAMP(table, per, wg, slot) do { if (threadIdx.x == 0) table[(wg) * (per) + (slot)] = wall_clock64(); } while (0)
 #define WG_STAMP_LANE0(table, per, wg, slot) do { if ((threadIdx.x & (kWave - 1)) == 0) table[(wg) * (per) + (slot)] = wall_clock64(); } while (0)
 #else
 #define WG_LINEAR() 0
+#define HEAD_STAMP_BY(who, slot) do {} while (0)
 #define WG_STAMP(table, per, wg, slot) do {} while (0)
 #define WG_STAMP_LANE0(table, per, wg, slot) do {} while (0)
 #endif
-#define HEAD_STAMP(slot) WG_STAMP(g_stamps_head, 4, WG_LINEAR(), slot)
+#define HEAD_STAMP(slot) HEAD_STAMP_BY(threadIdx.x == 0, slot)
 #define LOCATE_STAMP(slot) WG_STAMP(g_stamps_locate, 8, (int)(blockIdx.x & 4095), slot)
 
 namespace {
@@ -273,7 +275,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
         }
         if (row0 == 0) request_table();
         asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(u), "v"(qv1), "v"(qS), "v"(qx), "v"(qh));     // every request is out before the first wait
-        HEAD_STAMP(0);                                                     // first requests answered
+        HEAD_STAMP_BY(vt == 0, 0);                                        // first requests answered
         if (row0 == 0) {
             shT[tid] = tv;
             n = __builtin_amdgcn_readfirstlane(n);
@@ -320,7 +322,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
             lq = (float)((double)x - lse_q);
             dl = (float)lse_q;
         }
-        HEAD_STAMP(1);                                                     // row merged
+        HEAD_STAMP_BY(vt == 0, 1);                                        // row merged
         const bool lead = sl == 0 && row <= n;
         int32_t top1 = (SHARDED && r.cand >= 0 && r.cand < a.V) ? r.cand : 0;      // a shard's argmax is exact and global
         // Greedy sequences decide on the argmax; the others only report it: their leading lane looks at the window last.
@@ -349,7 +351,7 @@ __device__ inline SampleJob verify_head_lanes(const VerifyArgs &a, int b, bool w
                 if (a.target_top1) a.target_top1[it] = top1;
             }
         }
-        HEAD_STAMP(2);                                                     // lse, log p(tok), accept decision
+        HEAD_STAMP_BY(vt == 0, 2);                                        // lse, log p(tok), accept decision
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                       // the table's copy
     __syncthreads();
