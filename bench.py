@@ -70,9 +70,10 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_names(w, torch):
+def kernel_names(w, torch, sample_draft=False):
+    draft = 1 if w.draft_dtype == torch.bfloat16 else 0
     return {"target_pass": f"stream_pass_kernel<{1 if w.target_dtype == torch.bfloat16 else 0}, false>",
-            "draft_pass": f"stream_pass_kernel<{1 if w.draft_dtype == torch.bfloat16 else 0}, true>",
+            "draft_pass": f"stream_draw_kernel<{draft}>" if sample_draft else f"stream_pass_kernel<{draft}, true>",
             "verify_slices": "verify_slices"}
 
 
@@ -218,7 +219,7 @@ def run_workload(args, name, steps, warmup, kernel_steps, headline):
         prof_round = {k: tp.profile_read(k) for k in kinds}
     tp.profile_enable((), 0)
     kslots = [(first_k + i) % ring_n for i in range(kernel_steps)]
-    names = kernel_names(w, torch)
+    names = kernel_names(w, torch, sample_draft)
     names["stream_pair"] = f"stream_pair_kernel<{1 if w.draft_dtype == torch.bfloat16 else 0}, {1 if w.target_dtype == torch.bfloat16 else 0}>"
     # the final-token slice pass reads one row pair per sampled sequence (draft + target row of the first rejected
     # position, or the last target row alone when nothing was rejected)
