@@ -356,6 +356,28 @@ def test_shard_rows_and_sums_by_one_workgroup(B, K, V, G, dt):
     assert (got["top1_id"].cpu().numpy()[live] == ods["top1_id"][live]).all()
 
 
+@pytest.mark.parametrize("batches", [1, 2, 3, 4])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_shard_records_keep_the_precision_of_their_format(batches, dt):
+    """The sums of a record are binary32 numbers, off by 2^-24 / sqrt(3) of themselves (root mean square) at worst from that rounding alone.
+    What comes before it has to stay below: terms good to about 2^-23 and a thread's sums of up to 128 of them, both averaged over 256 threads
+    (2^-23 / 16), and no binary32 reduction over the threads, which by itself is as much again: a fifth is allowed on top."""
+    B, K, V = 512, 4, batches * 1024 * (4 if dt == f32 else 8)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    x = (torch.randn(B, K, V, generator=g, device=DEV) * 0.5).to(dt)
+    rec = binding.Tapout(B, K, V).shard_stats(x, 0, torch.full((B,), K, dtype=torch.int32, device=DEV)).reshape(B * K, 8)
+    M, S, T = (rec[:, i].view(f32).double() for i in range(3))
+    y = x.reshape(B * K, V).double() * 1.4426950408889634
+    first = y.argmax(-1, keepdim=True)
+    assert torch.equal(rec[:, 4].long(), first[:, 0]) and torch.equal(M, x.reshape(B * K, V).double().amax(-1))
+    rest = lambda e: e.scatter(1, first, 0.0).sum(-1)  # noqa: E731
+    R = torch.ceil(M * 1.4426950408889634)
+    e = torch.exp2(y - R[:, None])
+    assert torch.allclose(S, rest(e), rtol=1e-5, atol=0.0)     # (the reference is the integer above the maximum)
+    for got, want in ((S, rest(e)), (T, rest(e * (y - R[:, None])))):
+        assert ((got - want) / want).pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5
+
+
 @pytest.mark.parametrize("P", [1, 2, 3, 16, 17])
 def test_shard_records_from_any_number_of_slices(P):
     """Sixteen slices of a shard's row are merged across lanes, seventeen one after the other: the same record."""
