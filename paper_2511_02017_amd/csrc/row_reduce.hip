@@ -468,18 +468,22 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
                 t0 = __uint_as_float(r1.x); hs0 = __uint_as_float(r1.y); ht0 = __uint_as_float(r1.z);
             }
         }
-        Sum S = scaled(s0, -dil), T = 0.0f;
+        Sum S = scaled(s0, -dil);
+        double T = 0.0;
         p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0; p.pad[2] = 0;
         if constexpr (FULL) {
-            const Sum Hs = scaled(hs0, -dil), Ht = scaled(ht0 - (Sum)dl * hs0, -dil);
-            T = scaled(t0 - (Sum)dl * s0, -dil);
-            if (Ml == -INFINITY) T = 0.0f;                      // (a record without a finite maximum: d is no distance)
+            const Sum Hs = scaled(hs0, -dil);
+            const bool holds = met_it && (int)r0.z == p.cand;
+            // T in double from here on: going over to the slice's reference adds up to three times the sum's own rounding, which four
+            // records do not average out (error of the entropy, root mean square, V = 8000, logits of spread 2: 3.5e-8 with binary32, 3.1e-8 so;
+            // V = 128256, 64 sequences up to the stop position 58.7 / 59.0 us).  The other wavefronts' set-apart batches join in before.
+            const double s1 = (double)s0 + (holds ? 0.0 : (double)hs0), t1 = (double)t0 + (holds ? 0.0 : (double)ht0);
+            T = scaled(fma(-(double)dl, s1, t1), -dil);
+            if (Ml == -INFINITY) T = 0.0;                      // (a record without a finite maximum: d is no distance)
             // The batch with the slice's first maximum stays out (the epilogue adds its elements back from the
             // logits); the set-apart batches of the other wavefronts are ordinary data.  A NaN or an infinity
             // inside the left-out batch must still poison the sums: x - x is 0 for finite x only.
-            const bool holds = met_it && (int)r0.z == p.cand;
             S += holds ? Hs - Hs : Hs;
-            T += holds || Ml == -INFINITY ? (Sum)0.0f : Ht;
             p.v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, 0, kBits);
             T = quad_sum(T);
             // the left-out batch's own sum (same reference): S + this is the slice's sum over every element, to

@@ -169,6 +169,20 @@ def test_maxima_met_by_several_threads(dt, vec, off):
     assert c["accept_flagged"] == 0 and c["icdf_flagged"] <= 1
 
 
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_entropy_is_as_good_as_its_format(dt):
+    """Whatever the four wavefronts of a slice add to the entropy's error stays, root mean square over many rows, below what a binary32 result
+    may be off by from its own rounding (2^-24 / sqrt(3)); the rounding itself takes 2^-24 / sqrt(3) / 1.75 of that at an entropy near 7."""
+    B, K, V = 2048, 2, 8000
+    g = torch.Generator(device=DEV).manual_seed(11)
+    x = (torch.randn(B, K, V, generator=g, device=DEV) * 2).to(dt)
+    H = binding.Tapout(B, K, V).draft_stats(x)["entropy"].double()
+    lp = torch.log_softmax(x.double(), -1)
+    want = -(lp.exp() * lp).sum(-1)
+    assert 6.5 < want.mean() < 7.5
+    assert ((H - want) / want).pow(2).mean().sqrt() <= 2.0 ** -24 / 3 ** 0.5
+
+
 @pytest.mark.parametrize("B,V", [
     (128, 8191), (129, 8191), (320, 8191), (321, 8191),          # four slices a row: four wavefronts share one, two, two, none
     (102, 8200), (103, 8200),                                    # five: the last workgroup of two-way sharing has half its wavefronts idle
