@@ -243,9 +243,11 @@ inline bool own_q_shape(int K, int nsplit_target, int nsplit_draft)
 
 // Draft-token sampling (Algorithm 1, the sampling step of the draft loop): the inverse CDF of every live draft row.  The draft
 // pass leaves the sums of exponentials it runs over beside its partials; a launch behind it finds the tokens.
-// Sums of exp(x) in the logits' own scale are good for rows whose maximum lies in these bounds (bfloat16 rows, whose values from
-// -63.5 down count as 0, from kDrawLowTab on); others are summed again where their token is drawn.
-constexpr float kDrawLow = -700.0f, kDrawHigh = 700.0f, kDrawLowTab = -14.0f;
+// Sums of exp(x) in the logits' own scale are good for rows whose maximum lies between kDrawLow + 100 and kDrawHigh; others are summed again
+// where their token is drawn.  bfloat16: the table holds values up to kTabEnd, and counts those from -kTabEnd down as 0, which is good
+// beside a value of kDrawLowTab or more (each of them is below e^-43 of it; 256000 of them are 4e-14 of the sum, where a computed
+// exponential is good to 2e-13).
+constexpr float kDrawLow = -700.0f, kDrawHigh = 700.0f, kDrawLowTab = -20.0f, kTabEnd = 63.5f;
 // Draw slices of a streaming slice of `per` vectors: kStreamU, of kBlock vectors each, in every batch it takes.
 inline int draw_batches(int per) { return (per + kBlock * kStreamU - 1) / (kBlock * kStreamU); }
 struct DrawArgs {

@@ -87,7 +87,7 @@ __device__ inline double wave_incl_scan_d(double v, double *total)
 // ---- exponentials of bfloat16 logits from a table -----------------------------------------
 // A bfloat16 logit has 2^16 possible values, and those between 2^-12 and 2^6 in magnitude (all a softmax row holds
 // besides masked entries and the odd tiny one) are 2 * 2302 of them: exp(x) itself, correctly rounded on the host,
-// comes from a table of 36 KB in LDS with four integer instructions and one LDS read instead of the thirteen
+// comes from a table of 36 KB in LDS with three integer instructions and one LDS read instead of the thirteen
 // instructions of exp_fast.  The row's exponent reference is applied once per slice, to the sums:
 //   a_j = exp(t_j - ref_p) = E[t_j] c_t,  b_j = exp(d_j - ref_q) = E[d_j] c_d,   c_t = exp(-ref_p), c_d = exp(-ref_q)
 //   a_j - L~ b_j = c_t (E[t_j] - L' E[d_j]),  L' = L~ c_d / c_t
@@ -95,11 +95,12 @@ __device__ inline double wave_incl_scan_d(double v, double *total)
 // end.  A row of another element type keeps exp_fast and c = 1.
 // Layout: T[2 idx] for positive values, T[2 idx + 1] for negative ones.  Entry pair idx = 1 .. kTabTop - 1 is the magnitude with
 // bfloat16 bits kTabLo15 + idx - 1.
-// Pair kTabTop stands for every magnitude from 63.5 up (and NaN): 0 for either sign.  That is exact for -inf (a
+// Pair kTabTop stands for every magnitude from kTabEnd = 63.5 up (and NaN): 0 for either sign.  That is exact for -inf (a
 // masked entry) and an error below e^-49 of the row's largest term for any other logit <= -63.5 given the condition
 // on the references that tab_job_ok checks (row maxima in [-14, 63)); a job outside it takes the computed
-// exponentials.  Pair 0 stands for the magnitudes below 2^-12 (and zeros), which are not in the table, and holds
-// NaN: a chunk's sums show that it met one, and the slice kernel forms that chunk again with tab_exp_any, which
+// exponentials, as does a slice of a draft-token draw whose maximum is not in the table's range (see DrawSums).  Pair 0 stands for
+// the magnitudes below 2^-12 (and zeros), which are not in the table, and holds NaN: a vector's or chunk's sums show that it met one.
+// The draft pass of a draw then forms the sum again, computed; the slice kernel forms the chunk again with tab_exp_any, which
 // evaluates 1 + x + x^2/2 + x^3/6 for them (error < 2e-16).
 constexpr int kTabTop = 18 * 128 - 1;
 constexpr uint32_t kTabLo15 = (uint32_t)(127 - 12) << 7;            // bfloat16 magnitude bits of 2^-12

@@ -297,8 +297,8 @@ __device__ inline int wave_vectors(int first, int end)
 
 // ---- slice sums of the draft-token draw, on the way ------------------------------------------------
 // The inverse CDF of a draft row runs over sums of exponentials in double.  They need no row maximum if they are kept in the
-// logits' own scale: exp(x) as it is, from the table for bfloat16 values, computed for binary32 ones, is in range for every logit in
-// (-600, 700), and a row that holds larger ones is summed again where its token is drawn.  So the pass that reads the rows for
+// logits' own scale: exp(x) as it is, from the table for bfloat16 values, computed for binary32 ones, is in range for rows whose maximum
+// lies in [-600, 700); others are summed again where their token is drawn.  So the pass that reads the rows for
 // their statistics forms these sums too.  A draw slice is one vector per thread, kBlock vectors: a batch holds kStreamU of them,
 // each wavefront leaves its own sums, [draw slice][wavefront].
 // Slices a workgroup works on side by side, and workgroups of a compute unit.  bfloat16: two slices share a copy of the table, so that
@@ -364,14 +364,24 @@ struct DrawSums {
         return e;
     }
     // Which of a batch's sums v have to be formed again (again()), a bit each: those of vectors that hold a value which is not in
-    // the table.  v1: the thread's maximum so far, this batch included.
-    __device__ inline uint32_t missing(const double (&v)[kStreamU], float v1) const
+    // the table.
+    __device__ inline uint32_t missing(const double (&v)[kStreamU]) const
     {
         if constexpr (DT != TAPOUT_BF16) return 0u;
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < kStreamU; ++u) m |= __builtin_amdgcn_ballot_w64(v[u] != v[u]) != 0 ? 1u << u : 0u;
-        return __builtin_amdgcn_ballot_w64(v1 >= 63.5f) != 0 || !table ? (1u << kStreamU) - 1 : m;
+        return m;
+    }
+    // Whether the slice is not for the table, which counts everything beyond it as 0: a thread of the wavefront has met a value above it, or
+    // none has met one beside which what lies below doesn't matter (see kDrawLowTab).  Not where all is masked so far.  v1: the thread's
+    // maximum so far.  From the batch on that shows it nothing is looked up any more, and the slice's sums are computed from its logits
+    // once more when its statistics are done and their registers free.  (us per call, bfloat16 logits around -40, all of it left to the
+    // one workgroup that draws a row's token / this: V = 128256, 64 sequences of 8 rows 110 / 79, of one 51 / 19, V = 50257, 48 sequences of 7
+    // 54 / 37; one row of V = 128256 46.1 / 13.5, where logits in the table's range take 11.7.)
+    __device__ inline bool off_table(float v1) const
+    {
+        return __builtin_amdgcn_ballot_w64(v1 >= kTabEnd) != 0 || (__builtin_amdgcn_ballot_w64(v1 >= kDrawLowTab) == 0 && __builtin_amdgcn_ballot_w64(v1 >= kDrawLow) != 0);
     }
     // The sum of vector u of batch bi once more, computed, with a thread's lone element (its exponential) beside it.  The lane that
     // stored the first one stores it.
@@ -690,13 +700,15 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
         const u32x4 *vp = (const u32x4 *)(at.row + (int64_t)at.head * Elem<DT>::size);
         draw.out = d.sums + ((int64_t)(at.b * a.KK + at.k) * a.nsplit + at.s) * ((int64_t)d.nb * U * (kBlock / kWave));
         ThreadState<true> st;
+        bool off = kTab && !draw.table;                                      // the slice's sums are computed, behind everything else
         if (at.on && at.s == 0 && tid < at.head) st.fold_single(load_elem<DT>(at.row, tid), tid);
         const bool heads = at.on && at.s == 0 && at.head > 0, tails = at.on && at.s == a.nsplit - 1 && at.tail > 0;
         for (int b0 = 0; at.on && b0 < d.nb; b0 += 16) {                     // sixteen batches, then what is missing of their sums
             const int b1 = min(b0 + 16, d.nb), b1d = min(b1, at.nbatch);
             uint64_t missing = 0;
+            int bi = b0;
 #pragma unroll 1
-            for (int bi = b0; bi < b1d; ++bi) {
+            for (; bi < b1d && !off; ++bi) {
                 const int i = at.v0 + bi * (U * kBlock) + tid;
                 u32x4 w[U];
                 int n = U;
@@ -704,10 +716,21 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
                 else { load_batch<DT, U, true>(w, vp, i, at.v1e); n = wave_vectors<U>(at.v0 + bi * (U * kBlock), at.v1e); }
                 double v[U] = {0.0, 0.0, 0.0, 0.0};
                 fold_batch<DT, true, U>(st, w, n, i, at.head, [&](int u) { v[u] = draw.vector(w[u]); });
-                missing |= (uint64_t)draw.missing(v, st.v1) << ((bi - b0) * U);
+                missing |= (uint64_t)draw.missing(v) << ((bi - b0) * U);
                 draw.store(v, bi);
+                if constexpr (kTab) off = draw.off_table(st.v1);
             }
-            for (int bi = max(b0, at.nbatch); bi < b1; ++bi) {               // a slice shorter than the others
+            if constexpr (kTab) {
+#pragma unroll 1
+                for (; bi < b1d; ++bi) {                                     // the statistics alone
+                    const int i = at.v0 + bi * (U * kBlock) + tid;
+                    u32x4 w[U];
+                    load_batch<DT, U, true>(w, vp, i, at.v1e);
+                    fold_batch<DT, true, U>(st, w, U, i, at.head);
+                }
+                if (off) continue;
+            }
+            for (bi = max(b0, at.nbatch); bi < b1; ++bi) {                   // a slice shorter than the others
                 const double v[U] = {0.0, 0.0, 0.0, 0.0};
                 draw.store(v, bi);
             }
@@ -732,6 +755,21 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
             st.fold_single(load_elem<DT>(at.row, j), j);
         }
         finish_slice<DT, true, 2 * kParts, kParts>(a, st, at.s, at.b * a.KK + at.k, 0u, false, (turn & 1) * kParts + part, at.on);
+        if constexpr (kTab) {
+            for (int bi = 0; __builtin_expect(off && at.on, 0) && bi < d.nb; ++bi) {
+                u32x4 w[U];
+                load_batch<DT, U, true>(w, vp, at.v0 + bi * (U * kBlock) + tid, at.v1e);
+                double v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = draw.computed(w[u]);
+                    asm volatile("" : "+v"(v[u]));
+                }
+                if (heads && bi == 0 && tid < at.head) v[0] += draw.computed(load_elem<DT>(at.row, tid));
+                if (tails && bi == d.nb - 1 && tid < at.tail) v[U - 1] += draw.computed(load_elem<DT>(at.row, at.head + at.nvec * VEC + tid));
+                draw.store(v, bi);
+            }
+        }
         at.s += d.step_s; at.k += d.step_k; at.b += d.step_b;
         if (at.s >= a.nsplit) { at.s -= a.nsplit; ++at.k; }
         if (at.k >= a.KK) { at.k -= a.KK; ++at.b; }

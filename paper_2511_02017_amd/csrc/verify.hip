@@ -1375,8 +1375,7 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
     Rows r;
     r.trow = r.drow = rowp;
     int phase = 0, token = -1;
-    const bool tab = DT == TAPOUT_BF16 && !(a.vflags & kVerifyNoExpTable);
-    if (__builtin_expect(M >= (tab ? kDrawLowTab : kDrawLow + 100.0f) && M < kDrawHigh, 1)) {
+    if (__builtin_expect(M >= kDrawLow + 100.0f && M < kDrawHigh, 1)) {
         // the sums in the reference of the row's maximum
         const double scale = exp_fast_d(-(double)M, shT);
         auto sum4 = [&](const d2 &lo, const d2 &hi) { return ((lo.x + lo.y) + (hi.x + hi.y)) * scale; };

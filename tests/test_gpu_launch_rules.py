@@ -322,6 +322,30 @@ def test_draft_token_draw_at_every_magnitude(V, K, off, options, dt):
         assert torch.equal(o[key], again[key]), key
 
 
+@pytest.mark.parametrize("B,K,V", [(1, 1, 128256), (16, 2, 50257)])
+@pytest.mark.parametrize("shift", [-17, -22, -40, -500, 60, 75, 600])
+def test_draft_tokens_of_rows_off_the_table_are_found_in_the_draft_pass_sums(B, K, V, shift):
+    """Rows of bfloat16 logits that the table of exponentials does not hold: the sums come from the draft pass all the same, and the launch
+    that finds the tokens takes what it takes for any row (to sum a row of this size again it took eight times as long)."""
+    g = torch.Generator(device=DEV).manual_seed(V + shift)
+    x = torch.randn(B, K, V, generator=g, device=DEV) * 2
+    x[0, 0, V // 3:] = float("-inf")
+    u = torch.rand(B, K, generator=g, device=DEV)
+    tp = binding.Tapout(B, K, V, draft_sampling=True)
+    took = []
+    for d in (x.to(bf16), (x + shift).to(bf16)):
+        o = tp.draft_stats(d, u_draft=u)
+        ref = orc.draft_sample(pu.host_logits(d), u.cpu().numpy(), nthreads=16)
+        near = ref["icdf_margin"] <= pu.TAU_S
+        assert near.sum() <= 1 and (o["sampled_tok"].cpu().numpy()[~near] == ref["tok"][~near]).all()
+        tp.profile_enable(("sample_locate",), 40)
+        for _ in range(40):
+            tp.draft_stats(d, u_draft=u)
+        torch.cuda.synchronize()
+        took.append(tp.profile_read("sample_locate")[0])
+    assert took[1] < 2 * took[0]
+
+
 @pytest.mark.parametrize("G,V", [(1, 3000), (3, 9001), (16, 20000), (17, 20011), (64, 40000), (70, 33000)])
 @pytest.mark.parametrize("dt", [f32, bf16])
 def test_vocabulary_shards_merged_across_lanes(G, V, dt):
