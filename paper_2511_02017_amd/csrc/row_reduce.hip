@@ -662,8 +662,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 }
 
 // The draft pass with the slice sums of the draft-token draw (see DrawSums).  As many workgroups as are resident at once, so that the
-// 36 KB table of bfloat16 exponentials is copied to LDS once per workgroup; every slice is as long as the next, and a fixed stride
-// keeps them level.
+// 36 KB table of bfloat16 exponentials is copied to LDS once per workgroup.  Every slice is as long as the next, and they are dealt out with
+// a fixed stride, which keeps full drafts level.  Draft positions come first in their order: drafts that stop early leave late
+// positions empty, and every workgroup has early and late ones.  (Sequences first, a stride that K times the slices of a row divides
+// gave each workgroup its own positions.  us per call, V = 128256, 64 sequences of 8 rows, sequences first / this: two of the rows live
+// bfloat16 44.4 / 23.2, binary32 34.3 / 29.1, four 45.3 / 32.2, 53.2 / 43.6, 2 to 8 at random 46.7 / 47.2, 62.9 / 66.6, all 52 / 52, 81 / 78;
+// V = 32000, 512 sequences of 16 rows, bfloat16 173 / 67, 170 / 117, 170 / 167, 179 / 183.  Random lengths gain little: a workgroup whose
+// slices are all live is as slow as in a full draft.  The sequences turned against each other from position to position as well
+// 48.0 and 73.0 there, and 0.4 us in a call of one row.)
 template <int DT>
 __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgpu_waves_per_eu(DrawShape<DT>::parts * DrawShape<DT>::per_cu))) void stream_draw_kernel(RowReduceArgs a, DrawArgs d)
 {
@@ -680,8 +686,8 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
     {
         const int first = (int)blockIdx.x * kParts + part, row = first / a.nsplit;
         at.s = first - row * a.nsplit;
-        at.b = row / a.KK;
-        at.k = row - at.b * a.KK;
+        at.k = row / n_seq;
+        at.b = row - at.k * n_seq;
     }
     if (part == 0) shT[tid] = tv;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
@@ -690,9 +696,9 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
     draw.T = shT; draw.E = shE;
     draw.table = kTab && !(d.vflags & kVerifyNoExpTable);
     for (int turn = 0; turn < d.turns; ++turn) {
-        at.on = at.b < n_seq;
+        at.on = at.k < a.KK;
         at.on = at.on && (!a.len || at.k < a.len[at.b]);
-        at.row = (const char *)a.base + ((int64_t)(at.on ? at.b : 0) * a.stride_b + (int64_t)at.k * a.stride_k) * Elem<DT>::size;
+        at.row = (const char *)a.base + ((int64_t)at.b * a.stride_b + (int64_t)(at.on ? at.k : 0) * a.stride_k) * Elem<DT>::size;
         row_geometry<DT>(at.row, a.V, at.head, at.nvec, at.tail);
         at.v0 = min(at.s * a.per, at.nvec);
         at.v1e = min(at.v0 + a.per, at.nvec);
@@ -770,9 +776,9 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
                 draw.store(v, bi);
             }
         }
-        at.s += d.step_s; at.k += d.step_k; at.b += d.step_b;
-        if (at.s >= a.nsplit) { at.s -= a.nsplit; ++at.k; }
-        if (at.k >= a.KK) { at.k -= a.KK; ++at.b; }
+        at.s += d.step_s; at.b += d.step_b; at.k += d.step_k;
+        if (at.s >= a.nsplit) { at.s -= a.nsplit; ++at.b; }
+        if (at.b >= n_seq) { at.b -= n_seq; ++at.k; }
     }
 }
 
@@ -819,7 +825,8 @@ static hipError_t launch_draw(const RowReduceArgs &a, DrawArgs d, hipStream_t st
     const int64_t units = (int64_t)a.n_rows * a.nsplit, slots = 256 * DrawShape<DT>::per_cu * kParts;
     d.turns = (int)((units + slots - 1) / slots);
     const int wgs = (int)((units + (int64_t)d.turns * kParts - 1) / ((int64_t)d.turns * kParts)), step = wgs * kParts;
-    d.step_s = step % a.nsplit; d.step_k = step / a.nsplit % a.KK; d.step_b = step / a.nsplit / a.KK;
+    const int n_seq = a.n_rows / a.KK;
+    d.step_s = step % a.nsplit; d.step_b = step / a.nsplit % n_seq; d.step_k = step / a.nsplit / n_seq;
     launch_kernel(stream_draw_kernel<DT>, dim3(wgs), dim3(kBlock * kParts), st, tm, a, d);
     return hipGetLastError();
 }

@@ -346,6 +346,25 @@ def test_draft_tokens_of_rows_off_the_table_are_found_in_the_draft_pass_sums(B, 
     assert took[1] < 2 * took[0]
 
 
+@pytest.mark.parametrize("B,K,V,dt", [(64, 8, 128256, bf16), (64, 8, 128256, f32), (512, 16, 32000, bf16)])
+def test_short_drafts_with_drawn_tokens_take_less_of_the_draft_pass(B, K, V, dt):
+    """Where a quarter of the rows is live every compute unit has its share of them: half the time of the full block, at most three quarters
+    with what a launch costs by itself.  (All of a workgroup's slices at the same draft position: as long as the full block.)"""
+    x = torch.randn(1, K, V, device=DEV).to(dt).expand(B, K, V).contiguous()
+    u = torch.rand(B, K, device=DEV)
+    tp = binding.Tapout(B, K, V, draft_sampling=True)
+    took = []
+    for n in (K, K // 4):
+        k_len = torch.full((B,), n, dtype=torch.int32, device=DEV)
+        tp.draft_stats(x, k_len=k_len, u_draft=u)
+        tp.profile_enable(("draft_pass",), 20)
+        for _ in range(20):
+            tp.draft_stats(x, k_len=k_len, u_draft=u)
+        torch.cuda.synchronize()
+        took.append(tp.profile_read("draft_pass")[0])
+    assert took[1] < 0.75 * took[0]
+
+
 @pytest.mark.parametrize("G,V", [(1, 3000), (3, 9001), (16, 20000), (17, 20011), (64, 40000), (70, 33000)])
 @pytest.mark.parametrize("dt", [f32, bf16])
 def test_vocabulary_shards_merged_across_lanes(G, V, dt):
