@@ -140,8 +140,10 @@ typedef struct {
     double adaedl_eps;                    /* step of lambda (0.01)                              */
     double adaedl_rate0;                  /* initial smoothed acceptance rate (= adaedl_alpha)  */
     int32_t draft_sampling;               /* 1: tapout_draft_stats may draw the draft tokens    */
-                                          /* (u_draft); sizes the scratch for slice sums of     */
-                                          /* every draft row                                    */
+                                          /* (u_draft); adds scratch for the sums of every      */
+                                          /* draft row: about 170 bytes for 4096 elements of a  */
+                                          /* row, at least 1 MB, at most 256 MB or 8 bytes for  */
+                                          /* 2048 elements, whichever is more                   */
     int32_t adaedl_steer;                 /* 0: lambda follows the smoothed rate; 1: r itself   */
 } tapout_config;
 

@@ -1,5 +1,6 @@
 // C ABI of libtapout: argument validation, scratch ownership, launch sequencing.
 // Every entry point validates on the host, then only enqueues kernels.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -18,7 +19,7 @@ struct tapout_ctx {
     Partial *part = nullptr;      size_t part_cap = 0;       // slice partials of the draft pass (and of a shard pass)
     Partial *part_t = nullptr;                                 // slice partials of the target pass (same capacity)
     double *part1 = nullptr, *part2 = nullptr;                // slice sums of the inverse CDFs
-    double *draw_sums = nullptr;  size_t draw_cap = 0;         // sums of exponentials of the draft-token draw (see draw_sums_needed)
+    size_t draw_cap = 0;                                       // of them, those that a draft-token draw may use (see draw_sums_room)
     double *sampled_lse = nullptr;                             // [max_batch, max_k] lse of the draft rows (draft-token sampling only)
     JobRecord *jobs = nullptr;                                 // per sequence: what its final token is drawn from, and its band list
     uint32_t *flags_ws = nullptr;
@@ -194,12 +195,20 @@ Slices choose_slices(const tapout_ctx *ctx, int64_t rows, int KK, int V, int dty
     return choose_slices(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, KK, V, dtype);
 }
 
-// Sums that the draft pass leaves for the draft-token draw, and how many a context has room for: a sum per wavefront, vector
-// of a batch and batch of every slice; n slices of `per` vectors are no more than vecs / kBatchVecs + 2 n + 1 batches, since
-// `per` exceeds an even share by less than a batch and 64 vectors.
+// Sums that the draft pass leaves for the draft-token draw: a sum per wavefront, vector of a batch and batch of every slice.
 constexpr size_t kDrawSumsPerBatch = kStreamU * (kBlock / kWave);
 size_t draw_sums_needed(int64_t rows, int nsplit, int per) { return (size_t)rows * nsplit * draw_batches(per) * kDrawSumsPerBatch; }
-size_t draw_sums_room(size_t rows, size_t partials, int V) { return (rows * ((size_t)V / 4 / kBatchVecs + 2) + 3 * partials) * kDrawSumsPerBatch; }
+// How many a context has room for: those of the default slices (of whole batches, or of more than two each, so that they are at
+// most a third more batches than the row has, and two) up to 256 MB, a fiftieth of the logits of such a call or less; not fewer
+// than 1 MB of them, nor than a sum per slice of every row, which is what a call takes that has no room for the others (it reads the
+// rows again where the tokens are drawn).  Sums for every slice that the options allow took 34 MB for 64 sequences of 8 rows of 128256
+// instead of 3, 300 MB for 512 of 16 of 256000 instead of 90.
+size_t draw_sums_room(size_t rows, int V, int nsl)
+{
+    const size_t batches = ((size_t)V / 4 + kBatchVecs - 1) / kBatchVecs, wanted = rows * (batches + batches / 3 + 2) * kDrawSumsPerBatch;
+    const size_t most = ((size_t)256 << 20) / sizeof(double), least = ((size_t)1 << 20) / sizeof(double);
+    return std::max({std::min(wanted, most), least, rows * (size_t)nsl});
+}
 
 // ---- device address of the static scratch, per device ------------------------------------------------
 constexpr size_t kStaticPartials = TAPOUT_STATIC_MAX_PARTIALS;
@@ -353,10 +362,14 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     by_bytes_max = by_bytes_max < 1 ? 1 : (by_bytes_max > kStageCap ? kStageCap : by_bytes_max);
     c->part_cap = rows * (size_t)by_bytes_max + kMaxWgsTarget;   // rows * nsplit under either rule of choose_slices
     c->positions = cfg->granularity == TAPOUT_TOKEN_LEVEL ? cfg->max_k : 1;
-    if (cfg->draft_sampling) c->draw_cap = draw_sums_room((size_t)cfg->max_batch * cfg->max_k, c->part_cap, cfg->vocab);
     const size_t nstate = (size_t)cfg->n_bandits * c->positions * cfg->n_arms;
     c->nsl_max = (cfg->vocab + kSampleSlice - 1) / kSampleSlice;
-    const size_t nsums = (size_t)cfg->max_batch * 5;             // five per slice of a sequence's row pair
+    // five per slice of a sequence's row pair; the sums of a draw, which are done with before a verification starts, lie in their place
+    size_t nsums = (size_t)cfg->max_batch * 5 * c->nsl_max;
+    if (cfg->draft_sampling) {
+        c->draw_cap = draw_sums_room((size_t)cfg->max_batch * cfg->max_k, cfg->vocab, c->nsl_max);
+        nsums = std::max(nsums, c->draw_cap);
+    }
     // 2^(k/256), then exp(x) of every bfloat16 x with 2^-12 <= |x| < 63.5: entry 2 idx (x > 0) or 2 idx + 1 (x < 0),
     // idx = 1 + (magnitude bits - (115 << 7)); idx 0 stands for all smaller magnitudes and holds NaN (the kernels
     // notice and compute), the last idx for all larger ones and holds zeros
@@ -379,9 +392,8 @@ tapout_status tapout_create(tapout_ctx **out, const tapout_config *cfg)
     }
     bool ok = hipMalloc(&c->part, c->part_cap * sizeof(Partial)) == hipSuccess
            && hipMalloc(&c->part_t, c->part_cap * sizeof(Partial)) == hipSuccess
-           && hipMalloc(&c->part1, nsums * c->nsl_max * sizeof(double)) == hipSuccess
+           && hipMalloc(&c->part1, nsums * sizeof(double)) == hipSuccess
            && hipMalloc(&c->part2, (size_t)cfg->max_batch * c->nsl_max * sizeof(double)) == hipSuccess
-           && (!cfg->draft_sampling || hipMalloc(&c->draw_sums, c->draw_cap * sizeof(double)) == hipSuccess)
            && (!cfg->draft_sampling || hipMalloc(&c->sampled_lse, (size_t)cfg->max_batch * cfg->max_k * sizeof(double)) == hipSuccess)
            && hipMalloc(&c->exp_table, table.size() * sizeof(double)) == hipSuccess
            && hipMemcpy(c->exp_table, table.data(), table.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess
@@ -425,7 +437,7 @@ tapout_status tapout_destroy(tapout_ctx *ctx)
     profile_release(ctx);
     (void)hipFree(ctx->part); (void)hipFree(ctx->part_t); (void)hipFree(ctx->part1); (void)hipFree(ctx->part2);
     (void)hipFree(ctx->jobs); (void)hipFree(ctx->flags_ws); (void)hipFree(ctx->arm_played);
-    (void)hipFree(ctx->exp_table); (void)hipFree(ctx->sampled_lse); (void)hipFree(ctx->draw_sums);
+    (void)hipFree(ctx->exp_table); (void)hipFree(ctx->sampled_lse);
     (void)hipFree(ctx->sum_r); (void)hipFree(ctx->sum_r2); (void)hipFree(ctx->count);
     (void)hipFree(ctx->prev_entropy); (void)hipFree(ctx->accept_rate); (void)hipFree(ctx->lambda); (void)hipFree(ctx->round_entropy);
     delete ctx;
@@ -560,15 +572,17 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
     SampleArgs sa{};
     if (u_draft) {
         DrawArgs d{};
-        d.sums = ctx->draw_sums; d.exp_table = ctx->exp_table; d.nb = draw_batches(r.per);
+        d.sums = ctx->part1; d.exp_table = ctx->exp_table;
+        d.nb = draw_sums_needed(rows, nsplit, r.per) <= ctx->draw_cap ? draw_batches(r.per) : 0;
         d.vflags = ctx->exp_lookup ? 0 : kVerifyNoExpTable;
-        if (draw_sums_needed(rows, nsplit, r.per) > ctx->draw_cap) return fail(ctx, TAPOUT_EINVAL, "internal: draw buffer too small");
         sa.base = draft->ptr; sa.dtype = draft->dtype; sa.stride_b = draft->stride_b; sa.stride_k = draft->stride_k;
         sa.vflags = d.vflags;
         sa.B = B; sa.K = K; sa.V = V; sa.nsplit = nsplit; sa.per = r.per; sa.nb = d.nb;
         sa.part = ctx->part; sa.k_len = k_len; sa.u = u_draft; sa.tok = sampled_tok; sa.logq_tok = logq_tok;
-        sa.sums = ctx->draw_sums; sa.exp_table = ctx->exp_table;
-        e = timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_stream_draw(r, draft->dtype, d, st, tm); });
+        sa.sums = ctx->part1; sa.exp_table = ctx->exp_table;
+        e = timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) {
+            return d.nb ? launch_stream_draw(r, draft->dtype, d, st, tm) : launch_row_reduce(r, draft->dtype, true, st, tm);
+        });
     } else {
         e = pair ? stream_pair(ctx, r, draft->dtype, *pair, st)
                  : timed(ctx, TAPOUT_PROFILE_DRAFT_PASS, [&](Timing tm) { return launch_row_reduce(r, draft->dtype, true, st, tm); });

@@ -264,7 +264,7 @@ struct SampleArgs {
     int32_t B, K, V, nsplit, per, nb;      // how the draft pass cut the rows
     const Partial *part; const int32_t *k_len; const float *u;
     int32_t *tok; float *logq_tok;    // [B, K] token of each live row (-1: bad row) and its log q (or NULL)
-    double *sums;                 // DrawArgs::sums
+    double *sums;                 // DrawArgs::sums; nb == 0: there are none, but room for a sum per kSampleSlice elements of every row
     const double *lse;            // [B * K] from the epilogue, or NULL: it runs beside this launch, and each row forms its own
     const double *exp_table;
 };

@@ -1332,12 +1332,14 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
     constexpr int kParts = kBlock / kWave, kVec = Elem<DT>::vec;
     const int row = (int)blockIdx.x - (OWN ? a.B : 0), b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
     const int per_split = a.nb * kStreamU, n_slices = a.nsplit * per_split;
-    double *ps = a.sums + (int64_t)row * n_slices * kParts;
+    const int nsl = (a.V + kSampleSlice - 1) / kSampleSlice;
+    double *ps = a.sums + (int64_t)row * (n_slices > 0 ? n_slices * kParts : nsl);
     // everything is requested before anything is looked at: one round trip
     const int npl = slices_per_lane(n_slices), s0 = (tid & (kWave - 1)) * npl;
     typedef double d2 __attribute__((ext_vector_type(2)));
     static_assert(kParts == 4, "two loads a slice");
-    auto request = [&](int s, d2 &lo, d2 &hi) { const d2 *p = (const d2 *)(ps + (int64_t)min(s, n_slices - 1) * kParts); lo = p[0]; hi = p[1]; };
+    const double *first = n_slices > 0 ? ps : a.sums;
+    auto request = [&](int s, d2 &lo, d2 &hi) { const d2 *p = (const d2 *)(first + (int64_t)max(min(s, n_slices - 1), 0) * kParts); lo = p[0]; hi = p[1]; };
     d2 x0, y0, x1, y1;
     request(s0, x0, y0);
     request(s0 + 1, x1, y1);
@@ -1375,7 +1377,7 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
     Rows r;
     r.trow = r.drow = rowp;
     int phase = 0, token = -1;
-    if (__builtin_expect(M >= kDrawLow + 100.0f && M < kDrawHigh, 1)) {
+    if (__builtin_expect(n_slices > 0 && M >= kDrawLow + 100.0f && M < kDrawHigh, 1)) {
         // the sums in the reference of the row's maximum
         const double scale = exp_fast_d(-(double)M, shT);
         auto sum4 = [&](const d2 &lo, const d2 &hi) { return ((lo.x + lo.y) + (hi.x + hi.y)) * scale; };
@@ -1399,8 +1401,7 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
         };
         if (Z > 0.0) token = find_token<DT, DT>(w, r, a.V, n_slices, shT, (double)u32v * Z, weight, start, &shl, phase);
     } else {
-        // logits beyond the range of the sums: all over again in the reference of the row's maximum (the sums' place holds them)
-        const int nsl = (a.V + kSampleSlice - 1) / kSampleSlice;
+        // logits beyond the range of the sums, or no sums: all over again in the reference of the row's maximum (the sums' place holds them)
         __syncthreads();                                                 // every wavefront has its sums
         const double Z = slice_weights<DT, DT>(w, r, a.V, nsl, shT, ps);
         if (Z > 0.0) token = find_token<DT, DT>(w, r, a.V, nsl, shT, (double)u32v * Z, [&](int s, int) { return ps[s]; }, whole_slice_start, &shl, phase);

@@ -346,6 +346,51 @@ def test_draft_tokens_of_rows_off_the_table_are_found_in_the_draft_pass_sums(B, 
     assert took[1] < 2 * took[0]
 
 
+def _context_bytes(*a, **kw):
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    tp = binding.Tapout(*a, **kw)
+    return tp, free - torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("B,K,V,most", [
+    (1, 1, 100, 1 << 20), (64, 8, 128256, 4 << 20), (512, 16, 256000, 96 << 20),
+    (65535, 16, 32000, 256 << 20),                              # (8 KB a row would be 8 GB)
+])
+def test_draft_sampling_takes_little_memory(B, K, V, most):
+    """The sums of a draw: 128 bytes for every 16 KB of binary32 logits, a third more at most, up to 256 MB, and 1 MB; a row's lse."""
+    a, plain = _context_bytes(B, K, V)
+    b, drawing = _context_bytes(B, K, V, draft_sampling=True)
+    a.close(), b.close()
+    assert drawing - plain <= most + B * K * 8 + (4 << 20)      # (device memory is given out in pieces of up to 2 MB)
+
+
+@pytest.mark.parametrize("B,K,V,dt", [(48, 8, 40003, bf16), (40, 8, 40000, f32), (13, 70, 40001, bf16), (200, 8, 20000, bf16)])
+def test_draft_token_draw_without_room_for_its_sums(B, K, V, dt):
+    """Slices so fine that their sums find no room: the tokens are found all the same, from the rows read again, and every other output is the
+    one without a draw."""
+    rnd = random_round(B, K, V, dt, seed=V)
+    rnd["draft"][0, 0] += 80.0
+    rnd["draft"][1, 0] = float("-inf")
+    g = torch.Generator().manual_seed(V)
+    u = torch.rand(B, K, generator=g)
+    k_len = torch.randint(0, K + 1, (B,), generator=g, dtype=torch.int32)
+    k_len[:2] = K
+    tp = binding.Tapout(B, K, V, draft_sampling=True)
+    tp.set_option("min_slice", 256)
+    tp.set_option("wgs_target", 65536)
+    out = tp.draft_stats(rnd["draft"], k_len=k_len.to(DEV), u_draft=u.to(DEV), arm=random_arms(B, seed=1))
+    live = np.arange(K)[None, :] < k_len.numpy()[:, None]
+    ref = orc.draft_sample(pu.host_logits(rnd["draft"]), u.numpy(), k_len=k_len.numpy(), nthreads=16)
+    tok, near = out["sampled_tok"].cpu().numpy(), ref["icdf_margin"] <= pu.TAU_S
+    assert near[live].sum() <= 2 and (tok[live & ~near] == ref["tok"][live & ~near]).all() and (tok[~live] == -1).all()
+    given = tp.draft_stats(rnd["draft"], draft_tok=out["sampled_tok"], k_len=k_len.to(DEV), arm=random_arms(B, seed=1))
+    on = torch.from_numpy(live).to(DEV)
+    for key in (*pu.STAT_KEYS, "top1_id"):
+        assert torch.equal(torch.nan_to_num(out[key][on].float(), nan=7.0), torch.nan_to_num(given[key][on].float(), nan=7.0)), key
+    assert torch.equal(out["n_stop"], given["n_stop"]) and torch.equal(out["flags"], given["flags"])
+
+
 @pytest.mark.parametrize("B,K,V,dt", [(64, 8, 128256, bf16), (64, 8, 128256, f32), (512, 16, 32000, bf16)])
 def test_short_drafts_with_drawn_tokens_take_less_of_the_draft_pass(B, K, V, dt):
     """Where a quarter of the rows is live every compute unit has its share of them: half the time of the full block, at most three quarters
