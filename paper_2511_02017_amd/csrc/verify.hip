@@ -648,7 +648,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(T
     __shared__ double shT[256];
     __shared__ __align__(16) unsigned char sh_raw[kRaw];
     __shared__ HeadLanes sh_lanes[1];
-    __shared__ double sh_sums[SPLIT > 1 || kTotals ? WAVES : 1][kSliceVals];
+    __shared__ double sh_sums[SPLIT > 1 || kTotals ? WAVES : 1][kSliceVals];        // (see kMeet)
     static_assert(kTotals || sizeof shT + sizeof sh_raw + sizeof sh_lanes + sizeof sh_sums <= 32 * 1280, "four workgroups' LDS per compute unit");
     warm_args(a);
     [[maybe_unused]] const int wg = WG_LINEAR();
@@ -735,13 +735,9 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(T
     }
     if constexpr (!FUSED) __syncthreads();                       // (FUSED: the decisions' last barrier has published the tables)
     WG_STAMP(g_stamps_slices, 8, wg, 2);                         // tables in LDS, rows requested
-    if (!live) {
-        if constexpr (kTotals) {
-            if (lane < kSliceVals) sh_sums[wave][lane] = 0.0;
-            __syncthreads();
-        }
-        return;
-    }
+    // A wavefront without a slice has nothing to add; where wavefronts' sums meet (SPLIT, kTotals) it comes to the barrier with the others.
+    constexpr bool kMeet = SPLIT > 1 || kTotals;
+    if (!kMeet && !live) return;
     ExpRef rp, rq;
     rp.set((double)job.ref_p); rq.set((double)job.ref_q);
     const TabScale sc = tab_scale(job, tab_t, tab_d, shT);
@@ -829,7 +825,8 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(T
     };
     using std::false_type; using std::true_type;
     static_assert(kTabT == kTabD, "the table serves both rows or neither");
-    if constexpr (kTabT) {
+    if (kMeet && !live) {}
+    else if constexpr (kTabT) {
         // (a job on one row, the bonus position, has no draft row: the pass then sums the target row alone)
         // (the whole slice was requested ahead: no request is left for the loop)
         if (__builtin_expect(tab_t, 1)) pass(true_type{}, true_type{}, true_type{}); else pass(false_type{}, false_type{}, true_type{});
@@ -841,12 +838,12 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(T
     A = wave_sum_d(A) * sc.ct;
     if (resid) { Bs = wave_sum_d(Bs) * sc.cd; R = wave_sum_d(R) * sc.ct; D = wave_sum_d(D) * sc.cd; U = wave_sum_d(U) * sc.cd; }
     double *o = a.part1 + ((int64_t)b * a.nsl + s) * kSliceVals;
-    if constexpr (SPLIT == 1 && !kTotals) {
+    if constexpr (!kMeet) {
         if (lane == 0) { o[0] = A; o[1] = Bs; o[2] = R; o[3] = D; o[4] = U; }
     } else {
         if (lane == 0) { double *m = sh_sums[wave]; m[0] = A; m[1] = Bs; m[2] = R; m[3] = D; m[4] = U; }
-        __syncthreads();                                         // (wavefronts without a slice have left)
-        if (part == 0 && lane < kSliceVals) {
+        __syncthreads();
+        if (live && part == 0 && lane < kSliceVals) {
             // the slice's other wavefronts: the next ones, or in the writer's workgroup the ones before
             double sum = sh_sums[wave][lane];
 #pragma unroll
