@@ -332,14 +332,16 @@ __device__ inline void draft_finalize_staged(const DraftFinalArgs &a, const int 
 // log2 of the lanes per piece of a sequence of so many (row, slice) pieces.
 __device__ inline int draft_lanes_shift(int pieces) { return pieces > kFinalBlock / 2 ? 0 : (pieces > kFinalBlock / 4 ? 1 : 2); }
 
-// The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.
-template <bool SHARDED>
+// The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.  STAGED = false: where lane_merge_fits holds, for a
+// kernel that other workgroups share.
+template <bool SHARDED, bool STAGED = true>
 __device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
 {
-    __shared__ __align__(16) unsigned char lds[sizeof(Partial) * kStageCap + 5 * kScanCap + 16];
+    __shared__ __align__(16) unsigned char lds[STAGED ? sizeof(Partial) * kStageCap + 5 * kScanCap + 16 : 6 * kWave];
     const int msh = lane_merge_shift(a.K, a.nsplit), pieces = msh < 0 ? 0 : a.K << msh;
-    if (__builtin_expect(msh < 0, 0)) draft_finalize_staged<SHARDED>(a, b, lds);
-    else if (SHARDED || draft_lanes_shift(pieces) == 0) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
+    if constexpr (STAGED)
+        if (__builtin_expect(msh < 0, 0)) { draft_finalize_staged<SHARDED>(a, b, lds); return; }
+    if (SHARDED || draft_lanes_shift(pieces) == 0) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
     else if constexpr (!SHARDED) {
         if (draft_lanes_shift(pieces) == 1) draft_finalize_lanes<false, 1>(a, b, lds, msh);
         else draft_finalize_lanes<false, 2>(a, b, lds, msh);

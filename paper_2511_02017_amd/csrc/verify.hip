@@ -1136,7 +1136,7 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     }
     if constexpr (FIN)
         if ((int)blockIdx.x < a.B) {
-            draft_finalize_body<false>(fin, blockIdx.x);
+            draft_finalize_body<false, false>(fin, blockIdx.x);
 #ifdef TAPOUT_WG_STAMPS
             __syncthreads();
 #endif
@@ -1644,7 +1644,7 @@ hipError_t launch_verify(const VerifyArgs &a, int pass, hipStream_t st, Timing t
     static const DraftFinalArgs no_fin{};
     const bool with_fin = fin != nullptr;
     if (!a.exp_table) return hipErrorInvalidValue;           // every pass reads it
-    if (((a.vflags & kVerifyOwnQ) != 0) != with_fin || (fin && (a.shards > 0 || fin->shards > 0 || fin->B != a.B)))
+    if (((a.vflags & kVerifyOwnQ) != 0) != with_fin || (fin && (a.shards > 0 || fin->shards > 0 || fin->B != a.B || !own_q_shape(a.K, a.nsplit, fin->nsplit))))
         return hipErrorInvalidValue;
     if (!fin) fin = &no_fin;
     if (pass == 0) {
