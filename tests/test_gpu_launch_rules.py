@@ -142,9 +142,65 @@ def test_round_up_to_the_stop_position_beyond_the_small_targets(B, K, V, dt, tt,
     tp = binding.Tapout(B, K, V, **pool)
     arm = (torch.arange(B, device=DEV, dtype=torch.int32) % len(pool["rules"])).contiguous()
     if five:
-        arm %= 3                                                 # (the stateful rules need a previous draft: played in the trajectory tests)
+        arm %= 3                                                 # (the stateful rules need a previous draft: played in the test below)
     c = pu.check_round_call(tp, rnd, arm, truncate=True, **pool)
     assert c["icdf_flagged"] <= 1 and c["accept_flagged"] + c["stop_flagged"] <= 2 + 4 * B * K // 500
+
+
+@pytest.mark.parametrize("dt,tt", [(bf16, bf16), (f32, f32), (bf16, f32)])
+def test_round_up_to_the_stop_position_with_stateful_rules(dt, tt):
+    """The first two target rows beside the epilogue, with arms whose rules carry state from draft to draft: every output and the state of
+    several rounds are the bits of the separate calls, and so are the rounds replayed from HIP graphs with eager work between them."""
+    B, K, V = 64, 6, 32001
+    pool = dict(rules=(0, 1, 2, 3, 4), thresholds=(0.6, 0.8, 0.2, 0.2, 0.4))
+    rounds = []
+    for i in range(3):
+        rnd = mixed_round(B, K, V, dt, tt, seed=40 + i)
+        rnd["draft"][i::2] *= 3                                  # peaked rows beside flat ones
+        assert rnd["target"].numel() * rnd["target"].element_size() > 24 << 20
+        rounds.append((rnd, torch.where(torch.arange(B, device=DEV) % 5 < 1, i, 3 + (torch.arange(B, device=DEV) + i) % 2).to(torch.int32)))
+    order = [0, 1, 2, 2, 1, 0, 1]
+    bits = lambda outs: {k: v.cpu().view(torch.int32) if v.dtype == f32 else v.cpu() for o in outs for k, v in o.items()}  # noqa: E731
+    named = lambda d, v: ({"d_" + k: x for k, x in d.items()}, {"v_" + k: x for k, x in v.items()})  # noqa: E731
+    state = lambda tp: (*(x.tobytes() for x in tp.bandit_get_state(moments=True)), *(tp.rule_state_get()[k].tobytes() for k in ("prev_entropy", "accept_rate", "lam")))  # noqa: E731
+
+    ref, expect = binding.Tapout(B, K, V, **pool), []
+    for i in order:
+        rnd, arm = rounds[i]
+        ds = ref.draft_stats(rnd["draft"], rnd["draft_tok"], rnd["k_len"], arm)
+        vf = ref.verify(rnd["target"], rnd["draft"], ds["lse"], ds["logq_tok"], rnd["draft_tok"], ds["n_stop"], rnd["u_accept"], rnd["u_sample"], greedy=rnd["greedy"])
+        ref.bandit_update(arm, vf["accept_len"], ds["n_stop"], rnd["k_len"])
+        torch.cuda.synchronize()
+        expect.append((bits(named(ds, vf)), state(ref)))
+    stops = torch.cat([e[0]["d_n_stop"] for e in expect])
+    assert (stops < K).any() and (stops > 1).any()
+
+    for graphed in (False, True):
+        tp = binding.Tapout(B, K, V, **pool)
+        arm = torch.zeros(B, dtype=torch.int32, device=DEV)
+        calls = [tp.prepare_round_call(rnd, arm, True) for rnd, _ in rounds]
+        fresh = [[(t, t.clone()) for o in (c[1]["draft"], c[1]["verify"]) for t in o.values()] for c in calls]     # (rows behind the stop position stay as they are)
+        stream, junk = torch.cuda.Stream(), torch.zeros(1 << 20, device=DEV)
+        runs = [lambda c=c: c[0](stream.cuda_stream) for c in calls]
+        if graphed:
+            graphs = []
+            for launch, _ in calls:
+                graphs.append(torch.cuda.CUDAGraph())
+                with torch.cuda.graph(graphs[-1], stream=stream):
+                    launch(torch.cuda.current_stream().cuda_stream)
+            runs = [g.replay for g in graphs]
+        with torch.cuda.stream(stream):
+            for step, i in enumerate(order):
+                arm.copy_(rounds[i][1])
+                for t, was in fresh[i]:
+                    t.copy_(was)
+                runs[i]()
+                junk.add_(1.0)
+                stream.synchronize()
+                got = bits(named(calls[i][1]["draft"], calls[i][1]["verify"]))
+                for k, v in expect[step][0].items():
+                    assert torch.equal(got[k], v), (graphed, step, k)
+                assert state(tp) == expect[step][1], (graphed, step)
 
 
 @pytest.mark.parametrize("dt,vec", [(f32, 4), (bf16, 8)])
@@ -259,13 +315,18 @@ def test_token_level_bandit_at_the_edges_of_its_workgroups(policy, shared, B, K,
     (1, 1, 5, bf16),                  # one short slice
     (1, 1, 2048, f32), (1, 3, 2049, bf16),
     (3, 7, 4099, bf16),               # rows at every alignment
-    (64, 1, 131072, bf16),            # 4096 slices: one per resident wavefront
-    (65, 1, 131080, f32),             # one more row: some wavefronts take a second slice, of another row
-    (9, 16, 70001, bf16),             # steps over sequences and positions at once
-    (1400, 3, 2500, f32),             # fewer slices per row than the step
+    (64, 1, 131072, bf16), (65, 1, 131080, f32), (9, 16, 70001, bf16),       # rows of many slices, one slice to a workgroup's half
+    (2047, 1, 3000, bf16), (2048, 1, 3000, bf16), (683, 3, 3000, bf16),      # 2047, 2048 slices: one for every half that is resident; 2049: two
+    (1535, 1, 2500, f32), (1536, 1, 2500, f32), (1537, 1, 2500, f32),        # the same of binary32 rows, 1536 workgroups
+    (300, 7, 9001, bf16), (150, 16, 20001, bf16),                            # three turns of two slices a row and of three
+    (1400, 3, 2500, f32), (700, 3, 9001, f32),
+    (96, 7, 5001, bf16), (110, 6, 5001, bf16),                               # 768 and 770 workgroups with the epilogue's: in one launch, in two
+    (96, 7, 5001, f32), (110, 6, 5001, f32),
 ])
 @pytest.mark.parametrize("ragged", [False, True])
-def test_draft_token_draw_with_a_wavefront_per_slice(B, K, V, dt, ragged):
+def test_draft_token_draw_over_resident_workgroups(B, K, V, dt, ragged):
+    """The draft pass of a draw has as many workgroups as are resident, each of which takes a slice (bfloat16: two side by side) and goes on by
+    a fixed step to slices of other rows, sequences and positions; the launch behind it carries the epilogue where few rows are drawn."""
     rnd = random_round(B, K, V, dt, seed=V + B)
     tp = binding.Tapout(B, K, V, draft_sampling=True)
     g = torch.Generator().manual_seed(V)
@@ -291,7 +352,8 @@ def test_draft_token_draw_with_a_wavefront_per_slice(B, K, V, dt, ragged):
 
 
 @pytest.mark.parametrize("V,K,off,options", [
-    (9001, 2, 0, {}), (9001, 2, 3, {"exp_lookup": 0}), (2055, 70, 1, {}),           # 70 rows: the epilogue in a launch of its own
+    (9001, 2, 0, {}), (9001, 2, 3, {"exp_lookup": 0}),
+    (2055, 70, 1, {}), (2055, 80, 1, {}),                                           # 70 rows: the staged epilogue beside the draw; 80: in a launch of its own
     (7, 2, 1, {}), (40000, 2, 0, {"wgs_target": 1, "slice_bytes": 1 << 22}),        # no whole vector in some rows; slices of many batches
     (150001, 1, 5, {"wgs_target": 1, "slice_bytes": 1 << 22}),                      # more than sixteen of them
     (9001, 2, 0, {"min_slice": 256}),                                               # draw slices shorter than their batch
