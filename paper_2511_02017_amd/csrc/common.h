@@ -271,8 +271,9 @@ struct SampleArgs {
 // Tokens.  fin: the draft epilogue, to run in the same launch (a.lse NULL; where sample_own_lse holds), or NULL.
 hipError_t launch_sample(const SampleArgs &a, const DraftFinalArgs *fin, hipStream_t st, Timing tm);
 // Every row forms its lse itself while that costs no second round of workgroups (three are resident per compute unit: the epilogue's
-// LDS and registers), and its pieces fit a wavefront.  (us: 512 rows 7.4 in one launch; 2400 rows 22.7, apart 5.4 + 13.1; one sequence of
-// 100 rows 11.5, apart 11.4 + 4.2.)
+// LDS and registers), and its pieces fit a wavefront.  (us per call, apart / in one launch, bfloat16, V = 32000: 576 workgroups 26.0 / 23.2, 765
+// 33.6 / 29.7, 768 of one row a sequence 22.8 / 20.2; then 864 33.4 / 32.2, 1152 38.3 / 37.8, 1400 32.7 / 33.3, 2304 57.4 / 61.8; V = 128256 765
+// 70.3 / 65.8, 864 73.0 / 71.6, 1152 83.0 / 86.3; binary32 765 99.8 / 97.1, 864 105.5 / 106.2, 1152 139.9 / 144.9.)
 inline bool sample_own_lse(int B, int K, int nsplit) { return (int64_t)B * (K + 1) <= 768 && nsplit <= kWave; }
 
 // Final token over vocabulary shards (see tapout_shard_final_sums / tapout_shard_final_token).  The VerifyArgs
