@@ -243,7 +243,6 @@ __device__ inline float wave_sum_last(float v)
 __device__ inline double wave_sum_last(double v) { return wave_sum_d(v); }
 // The value of one lane, in a scalar register.
 __device__ inline float of_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-__device__ inline double of_lane(double v, int lane) { return lane_d(v, lane); }
 __device__ inline float scaled(float v, int e) { return ldexpf(v, e); }
 __device__ inline double scaled(double v, int e) { return ldexp(v, e); }
 __device__ inline u32x4 two_doubles(double a, double b)
@@ -263,7 +262,6 @@ template <> struct NegInfVec<TAPOUT_F32>  { static constexpr uint32_t word = 0xf
 template <> struct NegInfVec<TAPOUT_BF16> { static constexpr uint32_t word = 0xff80ff80u; };
 
 __device__ inline float quad_sum(float v) { v += dpp_mov<0xB1>(v); return v + dpp_mov<0x4E>(v); }
-__device__ inline double quad_sum(double v) { return lanes_sum(v, 0, 2); }
 
 template <int DT, int U, bool CHECKED>
 __device__ inline void load_batch(u32x4 (&w)[U], const u32x4 *vp, int i, int end)
@@ -395,18 +393,18 @@ struct DrawSums {
 
 // What a workgroup leaves of slice `split` of a row: the threads' sums reduced, its Partial written.  tok_bits: the logit of the row's
 // token, if the slice holds it.  set: which of kSets copies of the records in LDS; on: there is a slice (all threads come to the barrier).
-// RECORD: the slice is the whole row, rowp, and what is left is the row's shard record: the left-out batch back in, all but the
-// first maximum, whose index is exact and global.  From the threads on its sums are added in double, as the merge of several slices
-// adds theirs: a row of two to four batches brings its longer sums of a thread, and in binary32 the reduction behind them would come
-// on top (root mean square of the relative error of S, two batches of bfloat16, logits of spread 0.5: slices merged 4.4e-8, all in binary32 5.8e-8,
-// this 3.1e-8; us per call, 64 sequences of 8 rows, in binary32 / this 7.1 / 7.3).
+// RECORD: the slice is the whole row, rowp, and what is left is the row's shard record: everything but the first maximum, whose index
+// is exact and global.  From the threads on its sums are added in double, and each wavefront's first maximum as a term of its own, as the
+// merge of several slices does: a row of two to four batches brings its longer sums of a thread, and a binary32 reduction would come
+// on top (root mean square of the relative error of S, two batches of bfloat16, logits of spread 0.5: slices merged 4.4e-8, in binary32
+// 5.8e-8, this 3.1e-8; spread 5 2.33e-7, 2.40e-7, 2.28e-7; us per call, 64 sequences of 8 rows, in binary32 / this 7.0 / 7.2).
 template <int DT, bool FULL, int kSets = 1, int PARTS = 1, bool RECORD = false>
 __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FULL> &st, const int split, const int row, const uint32_t tok_bits,
                                     const bool holds_tok, const int set = 0, const bool on = true, const char *rowp = nullptr, const int vocab_offset = 0)
 {
     static_assert(!RECORD || FULL, "a record holds all statistics");
     using Sum = std::conditional_t<RECORD, double, float>;
-    __shared__ u32x4 sh_rec[kSets][kBlock / kWave][RECORD ? 3 : 2];
+    __shared__ u32x4 sh_rec[kSets][kBlock / kWave][2];
     const int tid = PARTS > 1 ? threadIdx.x & (kBlock - 1) : threadIdx.x;
     // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
     // What a slice costs besides its loads is this chain of instructions (a wavefront issues one in about nine cycles here), in
@@ -434,29 +432,58 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
     }
     // FULL: that thread's set-apart batch stays out of the wavefront's sums and goes into the record on its own (every other
     // thread's is ordinary data); its second maximum counts, of the others the maximum does
-    Sum hs = 0.0f, ht = 0.0f;
     float v2w = -INFINITY;
     if constexpr (FULL) {
-        hs = of_lane(s_hi, owner);
-        ht = of_lane(t_hi, owner);
-        s += lane == owner ? 0.0f : s_hi;
-        t += lane == owner ? 0.0f : t_hi;
+        s += lane == owner ? (Sum)0.0f : s_hi;
+        t += lane == owner ? (Sum)0.0f : t_hi;
         v2w = wave_max(lane == owner ? st.v2 : st.v1);
         t = wave_sum_last(t);
     }
     s = wave_sum_last(s);
-    if (lane == kWave - 1) {
-        if constexpr (RECORD) {
+    if constexpr (RECORD) {
+        if (lane == kWave - 1) {
             sh_rec[set][wave][0] = u32x4{__float_as_uint(Mw), 0u, (uint32_t)cw, __float_as_uint(v2w)};
             sh_rec[set][wave][1] = two_doubles(s, t);
-            sh_rec[set][wave][2] = two_doubles(hs, ht);
-        } else {
+        }
+        __syncthreads();
+        if (wave > 0) return;
+        // Four lanes for each wavefront's record, one for each vector of its set-apart batch, which comes back from the logits (and poisons the
+        // sums where it holds a NaN or an infinity): all but the wavefront's first maximum, which is a term of its own unless it is the row's.
+        constexpr int kVecBits = 2, kBits = 4;
+        static_assert(kStreamU == 1 << kVecBits && kBlock / kWave == 1 << (kBits - kVecBits), "sixteen lanes");
+        const int u = lane & (kStreamU - 1), from = (lane >> kVecBits) & (kBlock / kWave - 1);
+        const u32x4 r0 = sh_rec[set][from][0], r1 = sh_rec[set][from][1];
+        const float Ml = __uint_as_float(r0.x);
+        const int cl = (int)r0.z;
+        const BatchVecs<1> bt = batch_issue_vecs<1>(batch_geom(rowp, DT, a.V, 0, a.per), DT, a.V, cl, u, a.out);
+        const float M = lanes_max(Ml, kVecBits, kBits), R = ref_of_max(M), dl = R - ref_of_max(Ml);
+        const int dil = (int)fminf(fmaxf(dl, -1.0e9f), 1.0e9f), cand = lanes_min(Ml == M ? cl : 0x7fffffff, kVecBits, kBits);
+        const bool holds = Ml == M && cl == cand;
+        const double s0 = double_of(r1.x, r1.y);
+        double S = ldexp(s0, -dil), T = Ml == -INFINITY ? 0.0 : ldexp(fma(-(double)dl, s0, double_of(r1.z, r1.w)), -dil);
+        if (!holds && Ml > -INFINITY) {
+            const float y = __builtin_fmaf(Ml, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
+            S += (double)e;
+            T += (double)e * (double)fmaxf(y, -200.0f);
+        }
+        const float v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, kVecBits, kBits);
+        const BatchExtra x = batch_sum<DT>(R, Ml, true, bt, u);
+        const int idx = lanes_min(holds ? x.idx : 0x7fffffff, 0, kBits);
+        S = lanes_sum(S, kVecBits, kBits) + lanes_sum((double)x.sa, 0, kBits);
+        T = lanes_sum(T, kVecBits, kBits) + lanes_sum((double)x.ta, 0, kBits);
+        if (tid == 0) {
+            u32x4 *o = (u32x4 *)(a.out + row);
+            o[0] = u32x4{__float_as_uint(M), __float_as_uint((float)S), __float_as_uint((float)T), __float_as_uint(v2)};
+            o[1] = u32x4{(uint32_t)(vocab_offset + (idx >= 0 && idx < a.V ? idx : 0)), holds_tok ? (DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000u, 0u, 0u};
+        }
+    } else {
+        const float hs = FULL ? of_lane(s_hi, owner) : 0.0f, ht = FULL ? of_lane(t_hi, owner) : 0.0f;
+        if (lane == kWave - 1) {
             sh_rec[set][wave][0] = u32x4{__float_as_uint(Mw), __float_as_uint(s), (uint32_t)cw, __float_as_uint(v2w)};
             if constexpr (FULL) sh_rec[set][wave][1] = u32x4{__float_as_uint(t), __float_as_uint(hs), __float_as_uint(ht), 0u};
         }
-    }
-    __syncthreads();
-    if (wave == 0) {
+        __syncthreads();
+        if (wave > 0) return;
         constexpr int kBits = 2;                                // four records, one on each lane of a quad
         static_assert(kBlock / kWave == 1 << kBits, "a record per wavefront");
         const u32x4 r0 = sh_rec[set][lane & 3][0];
@@ -467,52 +494,30 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
         Partial p;
         p.v1 = M;
         p.cand = lanes_min(met_it ? (int)r0.z : 0x7fffffff, 0, kBits);
-        Sum s0, t0 = 0.0f, hs0 = 0.0f, ht0 = 0.0f;
-        if constexpr (RECORD) {
-            const u32x4 r1 = sh_rec[set][lane & 3][1], r2 = sh_rec[set][lane & 3][2];
-            s0 = double_of(r1.x, r1.y); t0 = double_of(r1.z, r1.w); hs0 = double_of(r2.x, r2.y); ht0 = double_of(r2.z, r2.w);
-        } else {
-            s0 = __uint_as_float(r0.y);
-            if constexpr (FULL) {
-                const u32x4 r1 = sh_rec[set][lane & 3][1];
-                t0 = __uint_as_float(r1.x); hs0 = __uint_as_float(r1.y); ht0 = __uint_as_float(r1.z);
-            }
-        }
-        Sum S = scaled(s0, -dil);
-        double T = 0.0;
-        p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0; p.pad[2] = 0;
+        const float s0 = __uint_as_float(r0.y);
+        p.T = 0.0f; p.v2 = -INFINITY; p.pad[1] = 0;
         if constexpr (FULL) {
-            const Sum Hs = scaled(hs0, -dil);
+            const u32x4 r1 = sh_rec[set][lane & 3][1];
+            const float hs0 = __uint_as_float(r1.y);
             const bool holds = met_it && (int)r0.z == p.cand;
-            // T in double from here on: going over to the slice's reference adds up to three times the sum's own rounding, which four
-            // records do not average out (error of the entropy, root mean square, V = 8000, logits of spread 2: 3.5e-8 with binary32, 3.1e-8 so;
-            // V = 128256, 64 sequences up to the stop position 58.7 / 59.0 us).  The other wavefronts' set-apart batches join in before.
-            const double s1 = (double)s0 + (holds ? 0.0 : (double)hs0), t1 = (double)t0 + (holds ? 0.0 : (double)ht0);
-            T = scaled(fma(-(double)dl, s1, t1), -dil);
-            if (Ml == -INFINITY) T = 0.0;                      // (a record without a finite maximum: d is no distance)
             // The batch with the slice's first maximum stays out (the epilogue adds its elements back from the
             // logits); the set-apart batches of the other wavefronts are ordinary data.  A NaN or an infinity
             // inside the left-out batch must still poison the sums: x - x is 0 for finite x only.
-            S += holds ? Hs - Hs : Hs;
+            // In double from here on: going over to the slice's reference adds up to three times the sum's own rounding to T, which four
+            // records do not average out (errors, root mean square: entropy, V = 8000, logits of spread 2, 3.5e-8 in binary32, 3.1e-8 so; margin,
+            // V = 32000, 32 sequences of 8 rows 8.0e-8 and 7.5e-8; us per round, V = 128256, 64 sequences 67.9 / 67.9, up to the stop position 58.7 / 59.0).
+            const double s1 = (double)s0 + (double)(holds ? hs0 - hs0 : hs0), t1 = (double)__uint_as_float(r1.x) + (double)(holds ? 0.0f : __uint_as_float(r1.z));
+            const double T = Ml == -INFINITY ? 0.0 : ldexp(fma(-(double)dl, s1, t1), -dil);       // (a record without a finite maximum: dl is no distance)
             p.v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, 0, kBits);
-            T = quad_sum(T);
+            p.S = (float)lanes_sum(ldexp(s1, -dil), 0, kBits);
+            p.T = (float)lanes_sum(T, 0, kBits);
             // the left-out batch's own sum (same reference): S + this is the slice's sum over every element, to
             // binary32 precision, for a reader that wants the row's lse before the epilogue has run
-            if constexpr (!RECORD) p.pad[1] = __float_as_int(quad_sum(holds ? Hs : 0.0f));
+            p.pad[1] = __float_as_int(quad_sum(holds ? ldexpf(hs0, -dil) : 0.0f));
+        } else {
+            p.S = quad_sum(ldexpf(s0, -dil));
         }
-        S = quad_sum(S);
-        p.S = (float)S; p.T = (float)T;
         p.pad[0] = holds_tok ? (int)(DT == TAPOUT_F32 ? tok_bits : tok_bits << 16) : 0x7fc00000;
-        if constexpr (RECORD) {
-            // a vector of the batch per lane of the quad (no finite maximum: nothing is left out)
-            const int u = lane & 3;
-            const BatchVecs<1> bt = batch_issue_vecs<1>(batch_geom(rowp, DT, a.V, 0, a.per), DT, a.V, p.cand, u, a.out);
-            const BatchExtra x = batch_sum<DT>(ref_of_max(M), M, true, bt, u);
-            const int idx = lanes_min(x.idx, 0, kBits);
-            p.S = (float)(S + lanes_sum((double)x.sa, 0, kBits));
-            p.T = (float)(T + lanes_sum((double)x.ta, 0, kBits));
-            p.cand = vocab_offset + (idx >= 0 && idx < a.V ? idx : 0);
-        }
         if (tid == 0 && on) {
             u32x4 *o = (u32x4 *)(a.out + (int64_t)row * a.nsplit + split);
             o[0] = u32x4{__float_as_uint(p.v1), __float_as_uint(p.S), __float_as_uint(p.T), __float_as_uint(p.v2)};
