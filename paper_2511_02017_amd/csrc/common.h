@@ -64,7 +64,7 @@ struct JobRecord {
 };
 static_assert(sizeof(JobRecord) == 160, "job record layout");
 
-__host__ __device__ inline float ref_of_max(float v1)
+__host__ __device__ __forceinline__ float ref_of_max(float v1)
 {
     // integer-valued reference >= v1*log2e; 0 for a slice without finite maximum
     return (v1 == -INFINITY) ? 0.0f : ceilf(v1 * kLog2e);
@@ -235,6 +235,13 @@ inline bool lane_merge_fits(int rows, int nsplit)
     while ((1 << sh) < nsplit) ++sh;
     return (rows << sh) <= 512;
 }
+// ... and a workgroup has a lane for every piece.
+inline bool lanes_in_one_pass(int rows, int nsplit)
+{
+    int sh = 0;
+    while ((1 << sh) < nsplit) ++sh;
+    return (rows << sh) <= kBlock;
+}
 // The accept decisions can take log q(tok) from the draft partials themselves (kVerifyOwnQ) for these shapes.
 inline bool own_q_shape(int K, int nsplit_target, int nsplit_draft)
 {
@@ -374,7 +381,7 @@ struct IntPair { int a, b; };
 __device__ inline IntPair swap16(int v) { auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false); return {(int)r[0], (int)r[1]}; }
 __device__ inline IntPair swap32(int v) { auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false); return {(int)r[0], (int)r[1]}; }
 template <class F>
-__device__ inline int lanes_reduce_i(int v, int lo, int hi, F f)
+__device__ __forceinline__ int lanes_reduce_i(int v, int lo, int hi, F f)
 {
     if (lo <= 0 && hi > 0) v = f(v, dpp_mov<0xB1>(v));
     if (lo <= 1 && hi > 1) v = f(v, dpp_mov<0x4E>(v));
@@ -384,8 +391,8 @@ __device__ inline int lanes_reduce_i(int v, int lo, int hi, F f)
     if (hi > 5) { const IntPair p = swap32(v); v = f(p.a, p.b); }
     return v;
 }
-__device__ inline int lanes_min(int v, int lo, int hi) { return lanes_reduce_i(v, lo, hi, [](int x, int y) { return min(x, y); }); }
-__device__ inline float lanes_max(float v, int lo, int hi)                   // of the numbers: a NaN gives way
+__device__ __forceinline__ int lanes_min(int v, int lo, int hi) { return lanes_reduce_i(v, lo, hi, [](int x, int y) { return min(x, y); }); }
+__device__ __forceinline__ float lanes_max(float v, int lo, int hi)                   // of the numbers: a NaN gives way
 {
     return __int_as_float(lanes_reduce_i(__float_as_int(v), lo, hi, [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
 }
@@ -403,7 +410,7 @@ __device__ inline void lanes_top2(float &m1, float &m2, int lo, int hi)
     if (hi > 4) { const IntPair p = swap16(__float_as_int(m1)), q = swap16(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
     if (hi > 5) { const IntPair p = swap32(__float_as_int(m1)), q = swap32(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
 }
-__device__ inline double lanes_sum(double v, int lo, int hi)
+__device__ __forceinline__ double lanes_sum(double v, int lo, int hi)
 {
     if (lo <= 0 && hi > 0) v += dpp_mov<0xB1>(v);
     if (lo <= 1 && hi > 1) v += dpp_mov<0x4E>(v);
@@ -413,7 +420,7 @@ __device__ inline double lanes_sum(double v, int lo, int hi)
     if (hi > 5) { const IntPair h = swap32(__double2hiint(v)), l = swap32(__double2loint(v)); v = __hiloint2double(h.a, l.a) + __hiloint2double(h.b, l.b); }
     return v;
 }
-__device__ inline void lanes_sum2(double &s, double &t, int lo, int hi)
+__device__ __forceinline__ void lanes_sum2(double &s, double &t, int lo, int hi)
 {
     s = lanes_sum(s, lo, hi);
     t = lanes_sum(t, lo, hi);
@@ -661,7 +668,7 @@ struct BatchGeom {
     const char *row;
     int32_t head, nvec, v0, v1e;      // the row's unaligned elements and whole vectors; the slice's vectors [v0, v1e)
 };
-__device__ inline BatchGeom batch_geom(const void *row, int dtype, int32_t V, int split, int per)
+__device__ __forceinline__ BatchGeom batch_geom(const void *row, int dtype, int32_t V, int split, int per)
 {
     const int esz = dtype == TAPOUT_F32 ? 4 : 2, vsh = dtype == TAPOUT_F32 ? 2 : 3, VEC = 1 << vsh;
     BatchGeom g;
@@ -725,7 +732,7 @@ struct BatchVecs {
     int32_t search;       // which of the lane's vectors the candidate is (else outside 0 .. NV - 1)
 };
 template <int NV>
-__device__ inline BatchVecs<NV> batch_issue_vecs(const BatchGeom &g, int dtype, int32_t V, int32_t cand, int u0, const void *safe)
+__device__ __forceinline__ BatchVecs<NV> batch_issue_vecs(const BatchGeom &g, int dtype, int32_t V, int32_t cand, int u0, const void *safe)
 {
     const int esz = dtype == TAPOUT_F32 ? 4 : 2, vsh = dtype == TAPOUT_F32 ? 2 : 3;
     BatchVecs<NV> b;
@@ -817,7 +824,7 @@ __device__ inline BatchExtra batch_extra(const Piece &p, const BatchRegs &b, int
 // Sums of a lane's vectors of a left-out batch in the row's reference R; excl: the piece holds the row's first maximum M,
 // which stays out and whose index is idx.  (See batch_extra_t for the search and the masked logits.)
 template <int DT, int NV>
-__device__ inline BatchExtra batch_sum(float R, float M, bool excl, const BatchVecs<NV> &b, int u0)
+__device__ __forceinline__ BatchExtra batch_sum(float R, float M, bool excl, const BatchVecs<NV> &b, int u0)
 {
     constexpr int VEC = Elem<DT>::vec;
     BatchExtra o;

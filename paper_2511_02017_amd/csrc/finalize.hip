@@ -28,11 +28,21 @@ namespace tapout {
 
 namespace {
 
-template <bool SHARDED>
-__global__ __launch_bounds__(kFinalBlock) void draft_finalize_kernel(DraftFinalArgs a)
+// A kernel for each path (and element type): compiled together they kept 124 scalars in vector registers' lanes, to be written and read back
+// one by one on the way.
+template <bool SHARDED, int DT, bool ONCE>
+__global__ __launch_bounds__(kFinalBlock) void draft_finalize_lanes_kernel(DraftFinalArgs a)
 {
+    __shared__ __align__(16) unsigned char lds[kLanesLds];
     warm_args(a);
-    draft_finalize_body<SHARDED>(a, blockIdx.x);
+    draft_finalize_lanes<SHARDED, ONCE>(a, blockIdx.x, lds, DT, lane_merge_shift(a.K, a.nsplit));
+}
+template <bool SHARDED>
+__global__ __launch_bounds__(kFinalBlock) void draft_finalize_staged_kernel(DraftFinalArgs a)
+{
+    __shared__ __align__(16) unsigned char lds[kStagedLds];
+    warm_args(a);
+    draft_finalize_staged<SHARDED>(a, blockIdx.x, lds);
 }
 
 // ---- vocabulary shards -----------------------------------------------------------------------
@@ -83,8 +93,16 @@ __global__ __launch_bounds__(kFinalBlock) void shard_merge_kernel(ShardMergeArgs
 
 hipError_t launch_draft_finalize(const DraftFinalArgs &a, hipStream_t st, Timing tm)
 {
-    if (a.shards > 0) launch_kernel(draft_finalize_kernel<true>, dim3(a.B), dim3(kFinalBlock), st, tm, a);
-    else launch_kernel(draft_finalize_kernel<false>, dim3(a.B), dim3(kFinalBlock), st, tm, a);
+    void (*kernel)(DraftFinalArgs);
+    auto lanes = [&](auto sharded, auto dtype) -> void (*)(DraftFinalArgs) {
+        return lanes_in_one_pass(a.K, a.nsplit) ? draft_finalize_lanes_kernel<decltype(sharded)::value, decltype(dtype)::value, true>
+                                                : draft_finalize_lanes_kernel<decltype(sharded)::value, decltype(dtype)::value, false>;
+    };
+    using F32 = std::integral_constant<int, TAPOUT_F32>; using BF16 = std::integral_constant<int, TAPOUT_BF16>;
+    if (!lane_merge_fits(a.K, a.nsplit)) kernel = a.shards > 0 ? draft_finalize_staged_kernel<true> : draft_finalize_staged_kernel<false>;
+    else if (a.shards > 0) kernel = lanes(std::true_type{}, F32{});      // (records have no element type)
+    else kernel = a.dtype == TAPOUT_F32 ? lanes(std::false_type{}, F32{}) : lanes(std::false_type{}, BF16{});
+    launch_kernel(kernel, dim3(a.B), dim3(kFinalBlock), st, tm, a);
     return hipGetLastError();
 }
 

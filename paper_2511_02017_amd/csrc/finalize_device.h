@@ -16,7 +16,9 @@ __device__ inline bool rule_fires(int rule, float h, float H, float p1, float ma
 {
     // decisions on the returned binary32 signals, widened to double (strict inequalities of Table 1)
     switch (rule) {
-    case TAPOUT_RULE_SVIP:    return sqrt((double)H) > (double)h;
+    // sqrt(H) > h as H > h^2: H and h have 24 significant bits, h^2 is exact in double, and where H differs from it, it does by 2^-48 of
+    // itself or more, the root by 2^-49: more than the rounding of a square root moves it
+    case TAPOUT_RULE_SVIP:    return h < 0.0f ? H >= 0.0f : (double)H > (double)h * (double)h;
     case TAPOUT_RULE_MAXCONF: return (double)p1 < (double)h;
     default:                  return (double)margin < (double)h;
     }
@@ -79,8 +81,9 @@ __device__ inline bool stateful_fires(const DraftFinalArgs &a, int b, int arm, i
 // A row on its lanes: from the partial (w0, w1) of this lane's piece, if it has one (mine), to the statistics of the row, the
 // same bits in every one of the row's 2^gsh lanes.  u: which of the piece's lanes this is, g: the piece's place in its row.  The
 // second memory round trip: token_logit() and this lane's vectors of the left-out batch.
+// dtype and gsh are constants wherever the caller knows them: what depends on them is then no branch on the way.
 template <bool SHARDED, int USH, class TokenLogit>
-__device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, bool mine, int u, int gsh, TokenLogit token_logit)
+__device__ __forceinline__ Piece row_on_lanes(const DraftFinalArgs &a, const int dtype, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, bool mine, int u, const int gsh, TokenLogit token_logit)
 {
     constexpr int NV = kStreamU >> USH;                               // vectors per lane
     const float v1 = mine ? __uint_as_float(w0.x) : -INFINITY;
@@ -89,7 +92,7 @@ __device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g
     if (!mine || (v1 == -INFINITY && !(S != S))) { S = 0.0f; T = 0.0f; v2 = -INFINITY; cand = 0x7fffffff; }     // nothing in it
     float xt = token_logit();
     BatchVecs<NV> bt{};
-    if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, a.dtype, a.V, cand, u * NV, a.part);
+    if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, dtype, a.V, cand, u * NV, a.part);
     // the row's maximum, second maximum and the piece that holds its first maximum
     float M = v1;
     lanes_top2(M, v2, USH, gsh);
@@ -114,7 +117,7 @@ __device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g
         xt = lanes_max(xt, USH, gsh);
     } else {
         // the batch's elements in the row's reference, all but the row's first maximum
-        const BatchExtra x = a.dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
+        const BatchExtra x = dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
         Sd += (double)x.sa; Td += (double)x.ta; idx = x.idx;
     }
     Piece t;
@@ -125,6 +128,30 @@ __device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g
     return t;
 }
 
+// log2 of the lanes per piece of a sequence of so many (row, slice) pieces.
+__device__ inline int draft_lanes_shift(int pieces) { return pieces > kFinalBlock / 2 ? 0 : (pieces > kFinalBlock / 4 ? 1 : 2); }
+
+// f(msh, ush) with the lanes of a row's pieces (lane_merge_shift, not negative) and of a piece as constants, for pieces that fit one pass (K << msh
+// <= kFinalBlock, K <= 64).  USH: what ush is, or -1.
+template <int USH, class F>
+__device__ __forceinline__ void on_lanes(int msh, int ush, F f)
+{
+    auto with = [&](auto m) __attribute__((always_inline)) {
+        constexpr int M = decltype(m)::value;
+        if constexpr (USH >= 0) f(m, std::integral_constant<int, USH>{});
+        else if constexpr (M == 0) f(m, std::integral_constant<int, 2>{});
+        else if (ush == 2) f(m, std::integral_constant<int, 2>{});
+        else if constexpr (M == 1) f(m, std::integral_constant<int, 1>{});
+        else if (ush == 1) f(m, std::integral_constant<int, 1>{});
+        else f(m, std::integral_constant<int, 0>{});
+    };
+    if (msh <= 1) {
+        if (msh == 0) with(std::integral_constant<int, 0>{}); else with(std::integral_constant<int, 1>{});
+    } else if (msh == 2) with(std::integral_constant<int, 2>{});
+    else if (msh == 3) with(std::integral_constant<int, 3>{});
+    else with(std::integral_constant<int, 4>{});
+}
+
 // ---- lane path: few rows and slices (see lane_merge_shift) -----------------------------------------
 // A wavefront of these small kernels executes an instruction about every nine cycles whatever it is, so what counts is
 // the number of instructions from the first request to the last store.  Every (row, slice) piece has 2^USH lanes of its
@@ -133,19 +160,27 @@ __device__ inline Piece row_on_lanes(const DraftFinalArgs &a, const BatchGeom &g
 // and then only sum.  Two or four lanes per piece where the workgroup has that many to spare.  No LDS between a row's
 // lanes and its signals.  (Pairwise merges of whole records, the batch by one lane, and the row totals handed to a
 // thread per row through LDS: launch 8.4 us at V = 128256, B = 64, K = 8, this 6.5; one sequence at V = 32000 6.2 / 4.7.)
-template <bool SHARDED, int USH>
-__device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b, unsigned char *lds, const int msh)
+//
+// ONCE: the pieces have their lanes in one pass, and there is no loop: the compiler formed everything that stays the same from pass to
+// pass (addresses and checks of ten outputs, constants) ahead of it, two hundred instructions in front of the first request.
+// The row's reductions run with their lanes as constants then (on_lanes): a step that may or may not be wanted is a branch.
+// (With the loop, and the lanes as variables: launch of its own, V = 32000, one sequence, binary32 4.8 us, now 4.4; rounds up to the stop position
+// V = 32000, one sequence 18.7 / 18.3 us, V = 128256, one sequence 20.8 / 20.2, drawn tokens of 64 rows 15.65 / 15.5.)
+// FEW: few_pieces holds.
+template <bool SHARDED, bool ONCE, bool FEW = false>
+__device__ __forceinline__ void draft_finalize_lanes(const DraftFinalArgs &a, const int b, unsigned char *lds, const int dtype, const int msh)
 {
-    constexpr int U = 1 << USH;                                       // lanes per piece
+    const int ush = SHARDED || !ONCE ? 0 : (FEW ? 2 : draft_lanes_shift(a.K << msh)), U = 1 << ush;      // lanes per piece
     float *sh_H = (float *)lds;                                       // [64] entropies of the sequence (stateful rules)
     uint8_t *sh_dec = lds + 4 * kWave, *sh_flag = sh_dec + kWave;     // [64] each: decisions, flags
-    const int K = a.K, tid = threadIdx.x, gsh = msh + USH;            // 2^gsh lanes per row
-    const int u = tid & (U - 1), sl = (tid >> USH) & ((1 << msh) - 1), per_pass = kFinalBlock >> gsh;
+    const int K = a.K, tid = threadIdx.x, gsh = msh + ush;            // 2^gsh lanes per row
+    const int u = tid & (U - 1), sl = (tid >> ush) & ((1 << msh) - 1), per_pass = kFinalBlock >> gsh;
     const bool want_tok = a.draft_tok && a.logq_tok, tok_mode = a.arm_stride > 0;
     int kb = a.k_len ? a.k_len[b] : K;
     int arm = (a.arm && !tok_mode) ? a.arm[b] : -1;                   // sequence-level bandit: one arm for all steps
     float H_carry = a.prev_entropy ? a.prev_entropy[b] : NAN;
-    for (int row0 = 0; row0 < K; row0 += per_pass) {                  // one pass but for long drafts of many slices
+    int row0 = 0;
+    do {
         const int row = row0 + (tid >> gsh), row_c = min(row, K - 1);
         const int64_t i = (int64_t)b * K + row;
         // First memory round trip: the partial, the row's token and arm (and above the sequence's values).  A lane without a
@@ -160,16 +195,22 @@ __device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b
         BatchGeom g{};
         const char *row_p = nullptr;
         if constexpr (!SHARDED) {
-            row_p = (const char *)row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, row_c);
-            g = batch_geom(row_p, a.dtype, a.V, sl, a.per);
+            row_p = (const char *)row_address(a.base, dtype, a.stride_b, a.stride_k, b, row_c);
+            g = batch_geom(row_p, dtype, a.V, sl, a.per);
             asm volatile("" :: "v"(g.row), "v"(g.head), "v"(g.nvec), "v"(g.v0), "v"(g.v1e));
         }
         asm volatile("" :: "v"(w0), "v"(w1), "v"(tok), "v"(arm_k), "v"(kb), "v"(arm), "v"(H_carry));
         if (row0 == 0) { kb = kb > K ? K : (kb < 0 ? 0 : kb); arm = __builtin_amdgcn_readfirstlane(arm); }
         const bool live = row < kb, mine = live && sl < a.nsplit;     // rows beyond k_len hold stale partials
-        const Piece t = row_on_lanes<SHARDED, USH>(a, g, w0, w1, mine, u, gsh, [&]() {
+        auto token_logit = [&]() __attribute__((always_inline)) {
             if constexpr (SHARDED) return mine ? __uint_as_float(w1.y) : NAN;     // the shard that owns the token sent its logit, the others NaN
-            else return want_tok && live && tok >= 0 && tok < a.V ? load_elem_rt(row_p, a.dtype, tok) : NAN;
+            else return want_tok && live && tok >= 0 && tok < a.V ? load_elem_rt(row_p, dtype, tok) : NAN;
+        };
+        Piece t;
+        if constexpr (!ONCE) t = row_on_lanes<SHARDED, 0>(a, dtype, g, w0, w1, mine, u, msh, token_logit);
+        else on_lanes<SHARDED ? 0 : (FEW ? 2 : -1)>(msh, ush, [&](auto m, auto us) __attribute__((always_inline)) {
+            constexpr int USH = decltype(us)::value;
+            t = row_on_lanes<SHARDED, USH>(a, dtype, g, w0, w1, mine, u, decltype(m)::value + USH, token_logit);
         });
         if (live && (tid & ((1 << gsh) - 1)) == 0) {
             const RowOut o = emit_row(a, i, row_total<true>(t), want_tok, tok, t.xt);
@@ -187,7 +228,8 @@ __device__ inline void draft_finalize_lanes(const DraftFinalArgs &a, const int b
                 }
             }
         }
-    }
+        row0 += per_pass;
+    } while (!ONCE && row0 < K);
     __syncthreads();
     // the sequence: rows are lanes of the first wavefront, ballots give the stop position and the flags
     if (tid < kWave) {
@@ -329,30 +371,24 @@ __device__ inline void draft_finalize_staged(const DraftFinalArgs &a, const int 
     }
 }
 
-// log2 of the lanes per piece of a sequence of so many (row, slice) pieces.
-__device__ inline int draft_lanes_shift(int pieces) { return pieces > kFinalBlock / 2 ? 0 : (pieces > kFinalBlock / 4 ? 1 : 2); }
+constexpr size_t kLanesLds = 6 * kWave;
 
-// The epilogue of sequence b; called by all kFinalBlock threads of a workgroup.  STAGED = false: where lane_merge_fits holds, for a
-// kernel that other workgroups share.
-template <bool SHARDED, bool STAGED = true>
-__device__ inline void draft_finalize_body(const DraftFinalArgs &a, const int b)
+// The epilogue of sequence b where lane_merge_fits holds; called by all kFinalBlock threads of a workgroup.
+template <bool SHARDED>
+__device__ __forceinline__ void draft_finalize_on_lanes(const DraftFinalArgs &a, const int b, const int dtype)
 {
-    __shared__ __align__(16) unsigned char lds[STAGED ? sizeof(Partial) * kStageCap + 5 * kScanCap + 16 : 6 * kWave];
-    const int msh = lane_merge_shift(a.K, a.nsplit), pieces = msh < 0 ? 0 : a.K << msh;
-    if constexpr (STAGED)
-        if (__builtin_expect(msh < 0, 0)) { draft_finalize_staged<SHARDED>(a, b, lds); return; }
-    if (SHARDED || draft_lanes_shift(pieces) == 0) draft_finalize_lanes<SHARDED, 0>(a, b, lds, msh);
-    else if constexpr (!SHARDED) {
-        if (draft_lanes_shift(pieces) == 1) draft_finalize_lanes<false, 1>(a, b, lds, msh);
-        else draft_finalize_lanes<false, 2>(a, b, lds, msh);
-    }
+    __shared__ __align__(16) unsigned char lds[kLanesLds];
+    const int msh = lane_merge_shift(a.K, a.nsplit);
+    if (__builtin_expect(a.K << msh > kFinalBlock, 0)) draft_finalize_lanes<SHARDED, false>(a, b, lds, dtype, msh);
+    else draft_finalize_lanes<SHARDED, true>(a, b, lds, dtype, msh);
 }
-
 // The same where few_pieces holds, for a kernel that needs the registers for something else (80 instead of 140).
-__device__ inline void draft_finalize_few(const DraftFinalArgs &a, const int b)
+__device__ __forceinline__ void draft_finalize_few(const DraftFinalArgs &a, const int b, const int dtype)
 {
-    __shared__ __align__(16) unsigned char lds[6 * kWave];
-    draft_finalize_lanes<false, 2>(a, b, lds, lane_merge_shift(a.K, a.nsplit));
+    __shared__ __align__(16) unsigned char lds[kLanesLds];
+    draft_finalize_lanes<false, true, true>(a, b, lds, dtype, lane_merge_shift(a.K, a.nsplit));
 }
+// The staged path's LDS.
+constexpr size_t kStagedLds = sizeof(Partial) * kStageCap + 5 * kScanCap + 16;
 
 }  // namespace tapout

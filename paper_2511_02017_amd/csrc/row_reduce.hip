@@ -625,12 +625,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 
 // The draft epilogue's workgroups and, behind them, target rows 0 and 1 of every sequence: up to the stop position those two are read
 // whatever it turns out to be, and the epilogue alone leaves the chip idle.
-template <int TD>
+template <int DD, int TD>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void epilogue_stream_kernel(DraftFinalArgs f, RowReduceArgs t, int n_seq)
 {
     static_assert(kBlock == kFinalBlock, "the epilogue runs in this kernel's workgroups");
     warm_args(f, t);
-    if ((int)blockIdx.x < n_seq) { draft_finalize_few(f, blockIdx.x); return; }
+    if ((int)blockIdx.x < n_seq) { draft_finalize_few(f, blockIdx.x, DD); return; }
     const int i = (int)blockIdx.x - n_seq, row = i / t.nsplit, b = row / kFirstRows;
     stream_pass_body<TD, false>(t, i - row * t.nsplit, row - b * kFirstRows, b);
 }
@@ -854,8 +854,10 @@ hipError_t launch_epilogue_stream(const DraftFinalArgs &f, RowReduceArgs t, int 
     if (!epilogue_streams(f.B, f.K, f.nsplit, t.nsplit) || f.shards > 0 || f.B != n_seq || f.K + 1 != t.KK || t.arm_dst) return hipErrorInvalidValue;
     t.len = nullptr; t.len_mode = 0;                          // rows 0 and 1 whatever the stop position
     const dim3 grid((unsigned)(n_seq + n_seq * kFirstRows * t.nsplit)), block(kBlock);
-    if (t_dtype == TAPOUT_F32) launch_kernel(epilogue_stream_kernel<TAPOUT_F32>, grid, block, st, tm, f, t, n_seq);
-    else launch_kernel(epilogue_stream_kernel<TAPOUT_BF16>, grid, block, st, tm, f, t, n_seq);
+    void (*kernel)(DraftFinalArgs, RowReduceArgs, int);
+    if (t_dtype == TAPOUT_F32) kernel = f.dtype == TAPOUT_F32 ? epilogue_stream_kernel<TAPOUT_F32, TAPOUT_F32> : epilogue_stream_kernel<TAPOUT_BF16, TAPOUT_F32>;
+    else kernel = f.dtype == TAPOUT_F32 ? epilogue_stream_kernel<TAPOUT_F32, TAPOUT_BF16> : epilogue_stream_kernel<TAPOUT_BF16, TAPOUT_BF16>;
+    launch_kernel(kernel, grid, block, st, tm, f, t, n_seq);
     return hipGetLastError();
 }
 hipError_t launch_stream_rest(RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm)

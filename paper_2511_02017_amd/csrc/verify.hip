@@ -1139,7 +1139,7 @@ __global__ __launch_bounds__(kVBlock) void verify_locate(VerifyArgs a, DraftFina
     }
     if constexpr (FIN)
         if ((int)blockIdx.x < a.B) {
-            draft_finalize_body<false, false>(fin, blockIdx.x);
+            draft_finalize_on_lanes<false>(fin, blockIdx.x, DD);
 #ifdef TAPOUT_WG_STAMPS
             __syncthreads();
 #endif
@@ -1292,12 +1292,12 @@ __device__ inline float row_ref_finish(RowRefRegs r, const Partial *p, int nspli
 }
 
 // The row's lse in double, the same bits in every lane as the draft epilogue leaves in its outputs: its lane path's arithmetic on
-// the same lanes (see draft_finalize_body), every group of a row's lanes with the same row.
+// the same lanes (see draft_finalize_lanes), every group of a row's lanes with the same row.
 template <int USH>
-__device__ inline double row_lse_lanes(const DraftFinalArgs &a, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, int msh)
+__device__ __forceinline__ double row_lse_lanes(const DraftFinalArgs &a, const int dtype, const BatchGeom &g, const u32x4 &w0, const u32x4 &w1, const int msh)
 {
     const int sl = (int)(threadIdx.x >> USH) & ((1 << msh) - 1);
-    const Piece t = row_on_lanes<false, USH>(a, g, w0, w1, sl < a.nsplit, threadIdx.x & ((1 << USH) - 1), msh + USH, []() { return NAN; });
+    const Piece t = row_on_lanes<false, USH>(a, dtype, g, w0, w1, sl < a.nsplit, threadIdx.x & ((1 << USH) - 1), msh + USH, []() { return NAN; });
     return row_signals(row_total<true>(t), a.V > 1).lse;
 }
 
@@ -1318,19 +1318,27 @@ __device__ inline double row_lse_staged(const DraftFinalArgs &a, const BatchGeom
 }
 
 // Tokens: one workgroup per draft row finds the draw slice (see DrawSums) and the element that hold u * Z, and forms log q(tok).
-// OWN: the draft epilogue's workgroups ride in this launch, ahead of the others, and every row forms its lse itself, from the
-// partials, while the elements travel; else the epilogue has run and left it.
-template <int DT, bool OWN>
+// OWN, kOwnLanes or kOwnStaged: the draft epilogue's workgroups ride in this launch, ahead of the others, and every row forms its lse itself,
+// from the partials, while the elements travel, both on that path of the epilogue; 0: the epilogue has run and left it.
+constexpr int kOwnLanes = 1, kOwnStaged = 2;
+template <int DT, int OWN>
 __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, DraftFinalArgs fin)
 {
-    if constexpr (OWN) {
+    if constexpr (OWN != 0) {
         warm_args(a, fin);
-        if ((int)blockIdx.x < a.B) { draft_finalize_body<false>(fin, blockIdx.x); return; }
+        if ((int)blockIdx.x < a.B) {
+            if constexpr (OWN == kOwnLanes) draft_finalize_on_lanes<false>(fin, blockIdx.x, DT);
+            else {
+                __shared__ __align__(16) unsigned char lds[kStagedLds];
+                draft_finalize_staged<false>(fin, blockIdx.x, lds);
+            }
+            return;
+        }
     } else warm_args(a);
     __shared__ double shT[256];
     __shared__ LocateShared shl;
     constexpr int kParts = kBlock / kWave, kVec = Elem<DT>::vec;
-    const int row = (int)blockIdx.x - (OWN ? a.B : 0), b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
+    const int row = (int)blockIdx.x - (OWN != 0 ? a.B : 0), b = row / a.K, k = row - b * a.K, tid = threadIdx.x;
     const int per_split = a.nb * kStreamU, n_slices = a.nsplit * per_split;
     const int nsl = (a.V + kSampleSlice - 1) / kSampleSlice;
     double *ps = a.sums + (int64_t)row * (n_slices > 0 ? n_slices * kParts : nsl);
@@ -1352,10 +1360,9 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
     [[maybe_unused]] BatchGeom g{};
     [[maybe_unused]] u32x4 w0{}, w1{};
     [[maybe_unused]] int msh = 0, ush = 0;
-    if constexpr (OWN) {
-        msh = lane_merge_shift(a.K, a.nsplit);
-        ush = msh < 0 ? 0 : draft_lanes_shift(a.K << msh);
-        const int sl = msh < 0 ? tid & (kWave - 1) : (tid >> ush) & ((1 << msh) - 1);
+    if constexpr (OWN != 0) {
+        if constexpr (OWN == kOwnLanes) { msh = lane_merge_shift(a.K, a.nsplit); ush = draft_lanes_shift(a.K << msh); }
+        const int sl = OWN == kOwnStaged ? tid & (kWave - 1) : (tid >> ush) & ((1 << msh) - 1);
         const u32x4 *pp = (const u32x4 *)(a.part + (int64_t)row * a.nsplit + min(sl, a.nsplit - 1));
         w0 = pp[0]; w1 = pp[1];
         g = batch_geom(rowp, DT, a.V, sl, a.per);
@@ -1406,9 +1413,10 @@ __global__ __launch_bounds__(kVBlock) void sample_locate_kernel(SampleArgs a, Dr
         const double Z = slice_weights<DT, DT>(w, r, a.V, nsl, shT, ps);
         if (Z > 0.0) token = find_token<DT, DT>(w, r, a.V, nsl, shT, (double)u32v * Z, [&](int s, int) { return ps[s]; }, whole_slice_start, &shl, phase);
     }
-    if constexpr (OWN) {
-        if (__builtin_expect(msh < 0, 0)) lse = row_lse_staged(fin, g, w0, w1);
-        else lse = ush == 0 ? row_lse_lanes<0>(fin, g, w0, w1, msh) : (ush == 1 ? row_lse_lanes<1>(fin, g, w0, w1, msh) : row_lse_lanes<2>(fin, g, w0, w1, msh));
+    if constexpr (OWN == kOwnStaged) lse = row_lse_staged(fin, g, w0, w1);
+    else if constexpr (OWN == kOwnLanes) {
+        if (__builtin_expect(a.K << msh > kFinalBlock, 0)) lse = row_lse_lanes<0>(fin, DT, g, w0, w1, msh);
+        else on_lanes<-1>(msh, ush, [&](auto m, auto u) __attribute__((always_inline)) { lse = row_lse_lanes<decltype(u)::value>(fin, DT, g, w0, w1, decltype(m)::value); });
     }
     if (tid == 0) {
         if (token < 0) token = 0;
@@ -1637,8 +1645,11 @@ hipError_t launch_sample(const SampleArgs &a, const DraftFinalArgs *fin, hipStre
     if (!a.exp_table || (fin != nullptr) != (a.lse == nullptr)) return hipErrorInvalidValue;
     if (fin && (fin->B != a.B || fin->shards > 0 || !sample_own_lse(a.B, a.K, a.nsplit))) return hipErrorInvalidValue;
     const dim3 grid(a.B * a.K + (fin ? a.B : 0)), block(kVBlock);
-    if (a.dtype == TAPOUT_F32) launch_kernel(fin ? sample_locate_kernel<TAPOUT_F32, true> : sample_locate_kernel<TAPOUT_F32, false>, grid, block, st, tm, a, fin ? *fin : no_fin);
-    else launch_kernel(fin ? sample_locate_kernel<TAPOUT_BF16, true> : sample_locate_kernel<TAPOUT_BF16, false>, grid, block, st, tm, a, fin ? *fin : no_fin);
+    const int own = !fin ? 0 : (lane_merge_fits(a.K, a.nsplit) ? kOwnLanes : kOwnStaged);
+    void (*kernel)(SampleArgs, DraftFinalArgs);
+    if (a.dtype == TAPOUT_F32) kernel = own == 0 ? sample_locate_kernel<TAPOUT_F32, 0> : (own == kOwnLanes ? sample_locate_kernel<TAPOUT_F32, kOwnLanes> : sample_locate_kernel<TAPOUT_F32, kOwnStaged>);
+    else kernel = own == 0 ? sample_locate_kernel<TAPOUT_BF16, 0> : (own == kOwnLanes ? sample_locate_kernel<TAPOUT_BF16, kOwnLanes> : sample_locate_kernel<TAPOUT_BF16, kOwnStaged>);
+    launch_kernel(kernel, grid, block, st, tm, a, fin ? *fin : no_fin);
     return hipGetLastError();
 }
 

@@ -661,3 +661,44 @@ def test_round_up_to_the_stop_position_ignores_target_rows_beyond_it(B, V, dt):
             a, b = (torch.nan_to_num(x[k].float(), nan=7.0) for x in (got, want))
             assert torch.equal(a, b), k
         assert (rows & (torch.arange(K + 1, device=DEV)[None, :] <= rnd["k_len"][:, None])).sum() >= B      # (some of them up to k_len)
+
+
+@pytest.mark.parametrize("P,Ks", [
+    (1, (1, 63, 64)),                 # a lane or more for every slice of a row: 1, 2, 4, 8, 16 of them, and four, two
+    (2, (32, 33, 64)),                # or one lane for a slice up to 64, 128 and 256 slices of a sequence; beyond 256 two passes
+    (3, (16, 17, 32, 33, 64)),
+    (8, (8, 9, 16, 17, 32, 33)),
+    (13, (1, 4, 5, 8, 9, 16, 17)),
+])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_draft_epilogue_at_every_arrangement_of_its_lanes(P, Ks, dt):
+    for K in Ks:
+        B, V = 2, P * 256 + 37 * K
+        rnd = mixed_round(B, K, V, dt, dt, seed=P * 100 + K)
+        tp = binding.Tapout(B, K, V, draft_sampling=True)
+        force_slices(tp, B * K, P)
+        c = pu.check_round(tp, rnd, arm=random_arms(B, seed=K))
+        assert c["accept_flagged"] + c["icdf_flagged"] + c["stop_flagged"] <= 1
+        # the tokens' launch forms a row's lse on the same lanes
+        out = tp.draft_stats(rnd["draft"], u_draft=torch.rand(B, K, generator=torch.Generator().manual_seed(K)).to(DEV))
+        given = tp.draft_stats(rnd["draft"], draft_tok=out["sampled_tok"])
+        for n in ("lse", "entropy", "p_top1", "p_top2", "margin", "top1_id", "logq_tok", "flags"):
+            assert torch.equal(out[n], given[n]), (P, K, n)
+
+
+def test_entropy_rule_beside_its_threshold():
+    """sqrt(H) > h is decided without the root: at thresholds next to the root of the entropy that the library returns, on either side, and at
+    thresholds whose square it is."""
+    V, K = 4096, 8
+    g = torch.Generator().manual_seed(5)
+    x = (torch.randn(1, K, V, generator=g) * torch.linspace(0.0, 9.0, K)[None, :, None]).to(DEV)
+    H = binding.Tapout(1, K, V).draft_stats(x)["entropy"].cpu().numpy()[0]
+    near = []
+    for r in np.sqrt(H.astype(np.float64)).astype(np.float32):
+        near += [r, np.nextafter(r, np.float32(0)), np.nextafter(r, np.float32(99))]
+    near += [np.float32(0.0), np.float32(-1.0), np.float32(1e-30)]
+    for h in near:
+        tp = binding.Tapout(1, K, V, rules=(binding.RULE_SVIP,), thresholds=(float(h),))
+        out = tp.draft_stats(x, arm=torch.zeros(1, dtype=torch.int32, device=DEV))
+        assert np.array_equal(out["entropy"].cpu().numpy()[0], H)
+        assert np.array_equal(out["stop_fired"].cpu().numpy()[0].astype(bool), np.sqrt(H.astype(np.float64)) > np.float64(h)), h
