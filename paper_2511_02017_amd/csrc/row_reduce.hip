@@ -302,10 +302,10 @@ __device__ inline int wave_vectors(int first, int end)
 // Slices a workgroup works on side by side, and workgroups of a compute unit.  bfloat16: two slices share a copy of the table, so that
 // four copies in LDS serve eight wavefronts per SIMD (64 registers); binary32: no table, six wavefronts (72 registers).  The kernel
 // is bound by vector instructions (rocprofv3 at V = 128256, 512 rows, bfloat16: vector ALU busy 66 %, LDS in use 34 %): us per call with four / six / eight wavefronts per
-// SIMD 53.5 / 53.9 / 49.5, 64 rows 14.9 / 14.8 / 15.4; a batch asked for ahead of the one at hand changed nothing.
+// SIMD 53.5 / 53.9 / 49.5, 64 rows 14.9 / 14.8 / 15.4; a batch asked for ahead of the one at hand changed nothing there.
 template <int DT> struct DrawShape;
-template <> struct DrawShape<TAPOUT_BF16> { static constexpr int parts = 2, per_cu = 4; };
-template <> struct DrawShape<TAPOUT_F32>  { static constexpr int parts = 1, per_cu = 6; };
+template <> struct DrawShape<TAPOUT_BF16> { static constexpr int parts = 2, per_cu = 4, few_per_cu = 3; };
+template <> struct DrawShape<TAPOUT_F32>  { static constexpr int parts = 1, per_cu = 6, few_per_cu = 6; };
 template <int DT>
 struct DrawSums {
     const double *T, *E;             // tables in LDS: 2^(k/256) and, for bfloat16, exp(x)
@@ -675,8 +675,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
 // V = 32000, 512 sequences of 16 rows, bfloat16 173 / 67, 170 / 117, 170 / 167, 179 / 183.  Random lengths gain little: a workgroup whose
 // slices are all live is as slow as in a full draft.  The sequences turned against each other from position to position as well
 // 48.0 and 73.0 there, and 0.4 us in a call of one row.)
-template <int DT>
-__global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgpu_waves_per_eu(DrawShape<DT>::parts * DrawShape<DT>::per_cu))) void stream_draw_kernel(RowReduceArgs a, DrawArgs d)
+// FEW: every workgroup takes one slice (of bfloat16 rows: two side by side), and its first batch travels with the table instead of behind it: with
+// few rows a slice is hardly more than that.  The batch takes registers: 80, so that three workgroups of bfloat16 rows fit a compute unit; calls of more
+// (four are resident then, all with one slice as well) and of several slices to a workgroup keep 64.  us per call, one row a sequence, behind the
+// table / with it: bfloat16, V = 32000, 1, 16, 64 sequences 11.2 / 10.9, 12.9 / 12.3, 13.7 / 13.0, V = 128256 12.1 / 11.6, 13.0 / 12.5, 16.2 / 15.7; binary32, which has no
+// table, 9.45 / 9.2, 10.2 / 9.9, 11.2 / 11.05 and 11.4 / 11.2, 12.4 / 12.3, 18.2 / 18.0 (0.15 of each by the epilogue's straight path in the second launch).
+template <int DT, bool FEW>
+__global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgpu_waves_per_eu(DrawShape<DT>::parts * (FEW ? DrawShape<DT>::few_per_cu : DrawShape<DT>::per_cu)))) void stream_draw_kernel(RowReduceArgs a, DrawArgs d)
 {
     constexpr bool kTab = DT == TAPOUT_BF16;
     constexpr int VEC = Elem<DT>::vec, U = kStreamU, kParts = DrawShape<DT>::parts;
@@ -694,13 +699,11 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
         at.k = row / n_seq;
         at.b = row - at.k * n_seq;
     }
-    if (part == 0) shT[tid] = tv;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
-    __syncthreads();
     DrawSums<DT> draw;
     draw.T = shT; draw.E = shE;
     draw.table = kTab && !(d.vflags & kVerifyNoExpTable);
-    for (int turn = 0; turn < d.turns; ++turn) {
+    // The slice at hand: its place and, once it is known, its row.
+    auto take = [&]() {
         at.on = at.k < a.KK;
         at.on = at.on && (!a.len || at.k < a.len[at.b]);
         at.row = (const char *)a.base + ((int64_t)at.b * a.stride_b + (int64_t)(at.on ? at.k : 0) * a.stride_k) * Elem<DT>::size;
@@ -708,6 +711,20 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
         at.v0 = min(at.s * a.per, at.nvec);
         at.v1e = min(at.v0 + a.per, at.nvec);
         at.nbatch = (at.v1e - at.v0 + U * kBlock - 1) / (U * kBlock);
+    };
+    [[maybe_unused]] u32x4 first[U];
+    [[maybe_unused]] int n_first = 0;
+    if constexpr (FEW) {
+        take();
+        const u32x4 *vp = (const u32x4 *)(at.row + (int64_t)at.head * Elem<DT>::size);
+        if (at.on && at.v0 + U * kBlock <= at.v1e) { load_batch<DT, U, false>(first, vp, at.v0 + tid, at.v1e); n_first = U; }
+        else if (at.on) { load_batch<DT, U, true>(first, vp, at.v0 + tid, at.v1e); n_first = wave_vectors<U>(at.v0, at.v1e); }
+    }
+    if (part == 0) shT[tid] = tv;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the copy to LDS
+    __syncthreads();
+    for (int turn = 0; turn < (FEW ? 1 : d.turns); ++turn) {
+        if constexpr (!FEW) take();
         const u32x4 *vp = (const u32x4 *)(at.row + (int64_t)at.head * Elem<DT>::size);
         draw.out = d.sums + ((int64_t)(at.b * a.KK + at.k) * a.nsplit + at.s) * ((int64_t)d.nb * U * (kBlock / kWave));
         ThreadState<true> st;
@@ -723,7 +740,11 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
                 const int i = at.v0 + bi * (U * kBlock) + tid;
                 u32x4 w[U];
                 int n = U;
-                if (at.v0 + (bi + 1) * (U * kBlock) <= at.v1e) load_batch<DT, U, false>(w, vp, i, at.v1e);
+                if (FEW && bi == 0) {
+                    n = n_first;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) w[u] = first[u];
+                } else if (at.v0 + (bi + 1) * (U * kBlock) <= at.v1e) load_batch<DT, U, false>(w, vp, i, at.v1e);
                 else { load_batch<DT, U, true>(w, vp, i, at.v1e); n = wave_vectors<U>(at.v0 + bi * (U * kBlock), at.v1e); }
                 double v[U] = {0.0, 0.0, 0.0, 0.0};
                 fold_batch<DT, true, U>(st, w, n, i, at.head, [&](int u) { v[u] = draw.vector(w[u]); });
@@ -832,7 +853,8 @@ static hipError_t launch_draw(const RowReduceArgs &a, DrawArgs d, hipStream_t st
     const int wgs = (int)((units + (int64_t)d.turns * kParts - 1) / ((int64_t)d.turns * kParts)), step = wgs * kParts;
     const int n_seq = a.n_rows / a.KK;
     d.step_s = step % a.nsplit; d.step_b = step / a.nsplit % n_seq; d.step_k = step / a.nsplit / n_seq;
-    launch_kernel(stream_draw_kernel<DT>, dim3(wgs), dim3(kBlock * kParts), st, tm, a, d);
+    const bool few = wgs <= 256 * DrawShape<DT>::few_per_cu && d.turns == 1;      // all resident at once (see the kernel)
+    launch_kernel(few ? stream_draw_kernel<DT, true> : stream_draw_kernel<DT, false>, dim3(wgs), dim3(kBlock * kParts), st, tm, a, d);
     return hipGetLastError();
 }
 

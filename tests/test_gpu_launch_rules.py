@@ -320,6 +320,7 @@ def test_token_level_bandit_at_the_edges_of_its_workgroups(policy, shared, B, K,
     (1535, 1, 2500, f32), (1536, 1, 2500, f32), (1537, 1, 2500, f32),        # the same of binary32 rows, 1536 workgroups
     (300, 7, 9001, bf16), (150, 16, 20001, bf16),                            # three turns of two slices a row and of three
     (1400, 3, 2500, f32), (700, 3, 9001, f32),
+    (1535, 1, 3001, bf16), (1536, 1, 3001, bf16), (1537, 1, 3001, bf16),     # 768 workgroups whose first batch travels with the table, 769 whose doesn't
     (96, 7, 5001, bf16), (110, 6, 5001, bf16),                               # 768 and 770 workgroups with the epilogue's: in one launch, in two
     (96, 7, 5001, f32), (110, 6, 5001, f32),
 ])
