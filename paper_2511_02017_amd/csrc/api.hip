@@ -193,7 +193,7 @@ Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t row
     const Slices all = cut_in_batches((int)want, V, dtype);
     if (few_wgs == 0 || staged) return all;
     // A draft pass with the epilogue behind it: half or a quarter as many slices, of whole batches, so that the epilogue has four lanes for
-    // each (few_pieces), where the pass gains by it too: a workgroup costs about 0.6 batches beside the batches it takes, and a launch what
+    // each (draft_lanes_shift), where the pass gains by it too: a workgroup costs about 0.6 batches beside the batches it takes, and a launch what
     // the compute unit with the most of them has.  Three workgroups to a compute unit at least, no more than a tenth of the batches' vectors
     // missing, and no slice so long that so few workgroups of it leave the memory waiting (40960 elements).  us, with all slices / so many, draft
     // pass and epilogue, with drawn tokens, round up to the stop position (whose first target rows then run beside the epilogue), K = 8:

@@ -132,8 +132,8 @@ __device__ __forceinline__ Piece row_on_lanes(const DraftFinalArgs &a, const int
 __device__ inline int draft_lanes_shift(int pieces) { return pieces > kFinalBlock / 2 ? 0 : (pieces > kFinalBlock / 4 ? 1 : 2); }
 
 // f(msh, ush) with the lanes of a row's pieces (lane_merge_shift, not negative) and of a piece as constants, for pieces that fit one pass (K << msh
-// <= kFinalBlock, K <= 64).  USH: what ush is, or -1.
-template <int USH, class F>
+// <= kFinalBlock, K <= 64).  USH: what ush is, or -1.  TWO: two lanes a piece or four.
+template <int USH, bool TWO = false, class F>
 __device__ __forceinline__ void on_lanes(int msh, int ush, F f)
 {
     auto with = [&](auto m) __attribute__((always_inline)) {
@@ -141,7 +141,7 @@ __device__ __forceinline__ void on_lanes(int msh, int ush, F f)
         if constexpr (USH >= 0) f(m, std::integral_constant<int, USH>{});
         else if constexpr (M == 0) f(m, std::integral_constant<int, 2>{});
         else if (ush == 2) f(m, std::integral_constant<int, 2>{});
-        else if constexpr (M == 1) f(m, std::integral_constant<int, 1>{});
+        else if constexpr (M == 1 || TWO) f(m, std::integral_constant<int, 1>{});
         else if (ush == 1) f(m, std::integral_constant<int, 1>{});
         else f(m, std::integral_constant<int, 0>{});
     };
@@ -166,11 +166,11 @@ __device__ __forceinline__ void on_lanes(int msh, int ush, F f)
 // The row's reductions run with their lanes as constants then (on_lanes): a step that may or may not be wanted is a branch.
 // (With the loop, and the lanes as variables: launch of its own, V = 32000, one sequence, binary32 4.8 us, now 4.4; rounds up to the stop position
 // V = 32000, one sequence 18.7 / 18.3 us, V = 128256, one sequence 20.8 / 20.2, drawn tokens of 64 rows 15.65 / 15.5.)
-// FEW: few_pieces holds.
+// FEW: few_pieces holds, and with it two or four lanes a piece.
 template <bool SHARDED, bool ONCE, bool FEW = false>
 __device__ __forceinline__ void draft_finalize_lanes(const DraftFinalArgs &a, const int b, unsigned char *lds, const int dtype, const int msh)
 {
-    const int ush = SHARDED || !ONCE ? 0 : (FEW ? 2 : draft_lanes_shift(a.K << msh)), U = 1 << ush;      // lanes per piece
+    const int ush = SHARDED || !ONCE ? 0 : draft_lanes_shift(a.K << msh), U = 1 << ush;      // lanes per piece
     float *sh_H = (float *)lds;                                       // [64] entropies of the sequence (stateful rules)
     uint8_t *sh_dec = lds + 4 * kWave, *sh_flag = sh_dec + kWave;     // [64] each: decisions, flags
     const int K = a.K, tid = threadIdx.x, gsh = msh + ush;            // 2^gsh lanes per row
@@ -208,7 +208,7 @@ __device__ __forceinline__ void draft_finalize_lanes(const DraftFinalArgs &a, co
         };
         Piece t;
         if constexpr (!ONCE) t = row_on_lanes<SHARDED, 0>(a, dtype, g, w0, w1, mine, u, msh, token_logit);
-        else on_lanes<SHARDED ? 0 : (FEW ? 2 : -1)>(msh, ush, [&](auto m, auto us) __attribute__((always_inline)) {
+        else on_lanes<SHARDED ? 0 : -1, FEW>(msh, ush, [&](auto m, auto us) __attribute__((always_inline)) {
             constexpr int USH = decltype(us)::value;
             t = row_on_lanes<SHARDED, USH>(a, dtype, g, w0, w1, mine, u, decltype(m)::value + USH, token_logit);
         });
@@ -382,7 +382,7 @@ __device__ __forceinline__ void draft_finalize_on_lanes(const DraftFinalArgs &a,
     if (__builtin_expect(a.K << msh > kFinalBlock, 0)) draft_finalize_lanes<SHARDED, false>(a, b, lds, dtype, msh);
     else draft_finalize_lanes<SHARDED, true>(a, b, lds, dtype, msh);
 }
-// The same where few_pieces holds, for a kernel that needs the registers for something else (80 instead of 140).
+// The same where few_pieces holds, for a kernel that needs the registers for something else.
 __device__ __forceinline__ void draft_finalize_few(const DraftFinalArgs &a, const int b, const int dtype)
 {
     __shared__ __align__(16) unsigned char lds[kLanesLds];
