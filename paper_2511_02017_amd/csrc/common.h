@@ -141,12 +141,14 @@ inline bool few_pieces(int K, int nsplit)
     while (p < nsplit) p *= 2;
     return p <= 16 && K <= 64 && K * p <= 128;
 }
-// The epilogue streams the first target rows beside it while that is about one round of workgroups (six are resident per compute unit).
+// The epilogue streams the first target rows beside it while that is one or two rounds of workgroups (six or eight are resident per compute unit).
 // us per round up to the stop position, V = 128256, bfloat16, 64 sequences, K = 8, apart / together 60.9 / 59.3 (92.0 / 89.1 diffuse rows,
 // 57.6 / 54.1 Zipf-like ones), 24 sequences, K = 4 34.9 / 33.9 (36.4 / 33.9, 32.9 / 30.1); V = 256000, binary32, 32 sequences, K = 3
 // 64.0 / 61.6 (63.4 / 56.6, 61.4 / 55.6); two lanes a piece, V = 128256, K = 8, bfloat16, 14 sequences 30.0 / 28.35, binary32, 8 sequences 29.7 / 26.75,
-// V = 256000, bfloat16, 8 sequences 34.8 / 31.5, V = 50257, K = 16, bfloat16, 16 sequences 30.1 / 27.6; beyond 1280 workgroups V = 100001, 100 sequences 63.5 / 64.4, V = 151936, 200 sequences 185 / 189.
-inline bool epilogue_streams(int B, int K, int d_nsplit, int t_nsplit) { return few_pieces(K, d_nsplit) && (int64_t)B * (1 + kFirstRows * t_nsplit) <= 1280; }
+// V = 256000, bfloat16, 8 sequences 34.8 / 31.5, V = 50257, K = 16, bfloat16, 16 sequences 30.1 / 27.6; 1300 to
+// 2000 workgroups, V = 32000, binary32, 90 sequences, K = 8 47.0 / 43.95, V = 100001, bfloat16, 90 sequences 66.5 / 63.8; 2700, 300 sequences, K = 3, V = 32000
+// 55.3 / 51.8, V = 128256 124.1 / 117.0, binary32 190.5 / 184.9; 3600, 400 sequences, K = 2, V = 128256 127.9 / 129.2, V = 100001, binary32 165.1 / 166.5.
+inline bool epilogue_streams(int B, int K, int d_nsplit, int t_nsplit) { return few_pieces(K, d_nsplit) && (int64_t)B * (1 + kFirstRows * t_nsplit) <= 3072; }
 
 // One record per live row of a vocabulary shard from its slice partials (see tapout_shard_stats).
 struct ShardMergeArgs {

@@ -129,7 +129,7 @@ def test_final_token_of_rows_of_several_slices_per_lane(V, dt, tt):
 @pytest.mark.parametrize("B,K,V,dt,tt", [
     (64, 6, 32001, bf16, bf16),      # the first two target rows beside the epilogue, the others behind them; rows at every alignment
     (32, 1, 256000, bf16, bf16),     # no others
-    (142, 3, 32000, bf16, bf16), (143, 3, 32000, bf16, bf16),    # 1278 and 1287 workgroups
+    (341, 3, 32000, bf16, bf16), (342, 3, 32000, bf16, bf16),    # 3069 and 3078 workgroups
     (20, 16, 40000, bf16, f32),      # 16 rows of five slices in groups of eight: 128 pieces of two lanes, the most
     (20, 17, 40000, bf16, f32),      # 17 rows: too many
     (60, 4, 50257, f32, bf16), (25, 17, 32000, bf16, bf16),      # four lanes a piece; two
