@@ -742,11 +742,7 @@ tapout_status tapout_shard_stats(tapout_ctx *ctx, const tapout_logits *shard,
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = (int64_t)B * KK;
     Slices slices = choose_slices(ctx, rows, KK, Vs, shard->dtype);
-    // Rows of a few batches are read by one workgroup each, which writes the row's record itself; the merge of several slices is a
-    // launch of its own (us per call, slices and merge / whole rows, 8 rows a sequence, bfloat16: 2 batches, 1 / 64 / 256 sequences 7.4 / 5.2, 9.9 / 7.3, 18.5 / 14.7;
-    // 4 batches 7.5 / 7.1, 12.9 / 10.4, 28.1 / 26.4; 6 batches 7.6 / 9.0, 15.9 / 14.6, 8 batches 7.5 / 10.7, 18.0 / 18.0; binary32 2 batches 7.0 / 5.1,
-    // 8.9 / 5.6, 17.0 / 12.2; 4 batches 6.9 / 6.4, 11.5 / 8.3, 27.5 / 24.8).
-    if (ctx->min_slice == 0 && Vs <= 4 * kBatchVecs * (shard->dtype == TAPOUT_F32 ? 4 : 8)) slices = cut_evenly(1, Vs, shard->dtype);
+    if (ctx->min_slice == 0 && shard_rows_whole(rows, Vs, shard->dtype == TAPOUT_F32 ? 4 : 8)) slices = cut_evenly(1, Vs, shard->dtype);
     const int nsplit = slices.n;
     if ((size_t)(rows * nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
     RowReduceArgs r{shard->ptr, shard->stride_b, shard->stride_k, Vs, KK, nsplit, slices.per, (int32_t)rows, len, rows_mode, ctx->part};

@@ -393,18 +393,19 @@ struct DrawSums {
 
 // What a workgroup leaves of slice `split` of a row: the threads' sums reduced, its Partial written.  tok_bits: the logit of the row's
 // token, if the slice holds it.  set: which of kSets copies of the records in LDS; on: there is a slice (all threads come to the barrier).
-// RECORD: the slice is the whole row, rowp, and what is left is the row's shard record: everything but the first maximum, whose index
+// RECORD > 0: the slice is the whole row, rowp, read by so many wavefronts, and what is left is the row's shard record: everything but the first maximum, whose index
 // is exact and global.  From the threads on its sums are added in double, and each wavefront's first maximum as a term of its own, as the
 // merge of several slices does: a row of two to four batches brings its longer sums of a thread, and a binary32 reduction would come
 // on top (root mean square of the relative error of S, two batches of bfloat16, logits of spread 0.5: slices merged 4.4e-8, in binary32
 // 5.8e-8, this 3.1e-8; spread 5 2.33e-7, 2.40e-7, 2.28e-7; us per call, 64 sequences of 8 rows, in binary32 / this 7.0 / 7.2).
-template <int DT, bool FULL, int kSets = 1, int PARTS = 1, bool RECORD = false>
+template <int DT, bool FULL, int kSets = 1, int PARTS = 1, int RECORD = 0>
 __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FULL> &st, const int split, const int row, const uint32_t tok_bits,
                                     const bool holds_tok, const int set = 0, const bool on = true, const char *rowp = nullptr, const int vocab_offset = 0)
 {
-    static_assert(!RECORD || FULL, "a record holds all statistics");
-    using Sum = std::conditional_t<RECORD, double, float>;
-    __shared__ u32x4 sh_rec[kSets][kBlock / kWave][2];
+    static_assert(RECORD == 0 || FULL, "a record holds all statistics");
+    using Sum = std::conditional_t<RECORD != 0, double, float>;
+    constexpr int kWaves = RECORD != 0 ? RECORD : kBlock / kWave;
+    __shared__ u32x4 sh_rec[kSets][kWaves][2];
     const int tid = PARTS > 1 ? threadIdx.x & (kBlock - 1) : threadIdx.x;
     // Every wavefront brings its sums to its own maximum and leaves one record; the first wavefront merges the four, a lane each.
     // What a slice costs besides its loads is this chain of instructions (a wavefront issues one in about nine cycles here), in
@@ -440,7 +441,7 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
         t = wave_sum_last(t);
     }
     s = wave_sum_last(s);
-    if constexpr (RECORD) {
+    if constexpr (RECORD != 0) {
         if (lane == kWave - 1) {
             sh_rec[set][wave][0] = u32x4{__float_as_uint(Mw), 0u, (uint32_t)cw, __float_as_uint(v2w)};
             sh_rec[set][wave][1] = two_doubles(s, t);
@@ -449,9 +450,9 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
         if (wave > 0) return;
         // Four lanes for each wavefront's record, one for each vector of its set-apart batch, which comes back from the logits (and poisons the
         // sums where it holds a NaN or an infinity): all but the wavefront's first maximum, which is a term of its own unless it is the row's.
-        constexpr int kVecBits = 2, kBits = 4;
-        static_assert(kStreamU == 1 << kVecBits && kBlock / kWave == 1 << (kBits - kVecBits), "sixteen lanes");
-        const int u = lane & (kStreamU - 1), from = (lane >> kVecBits) & (kBlock / kWave - 1);
+        constexpr int kVecBits = 2, kBits = kWaves == 4 ? 4 : (kWaves == 8 ? 5 : 6);
+        static_assert(kStreamU == 1 << kVecBits && kWaves == 1 << (kBits - kVecBits), "a wavefront's lanes");
+        const int u = lane & (kStreamU - 1), from = (lane >> kVecBits) & (kWaves - 1);
         const u32x4 r0 = sh_rec[set][from][0], r1 = sh_rec[set][from][1];
         const float Ml = __uint_as_float(r0.x);
         const int cl = (int)r0.z;
@@ -526,8 +527,9 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
     }
 }
 
-// The work of one workgroup: slice `split` of row k of sequence b.
-template <int DT, bool FULL, bool RECORD = false>
+// The work of one workgroup: slice `split` of row k of sequence b.  RECORD (see finish_slice): kBlock threads for every fourth
+// of it, which take the row's batches in turn.
+template <int DT, bool FULL, int RECORD = 0>
 __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split, const int k, const int b, const int vocab_offset = 0)
 {
     constexpr int VEC = Elem<DT>::vec;
@@ -535,8 +537,9 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
     // and six wavefronts per SIMD instead of eight, which still beats two vectors at full occupancy
     // (measured; three, six and eight vectors and an explicit prefetch of the next batch are all slower).
     constexpr int U = kStreamU;
+    constexpr int kParts = RECORD > kBlock / kWave ? RECORD * kWave / kBlock : 1;
 
-    const int tid = threadIdx.x;
+    const int tid = kParts > 1 ? threadIdx.x & (kBlock - 1) : threadIdx.x, part = kParts > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock) : 0;
     int n_active;                                   // rows of sequence b this pass reads
     if (a.len_mode == 0) {                          // draft rows: k < k_len[b]
         n_active = a.len ? a.len[b] : a.KK;
@@ -556,7 +559,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
         int zero;
         asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
         tk = a.tok[(int64_t)b * a.tok_rows + k + zero];
-        if constexpr (RECORD) tk -= vocab_offset;
+        if constexpr (RECORD != 0) tk -= vocab_offset;
     }
     const char *rowp = (const char *)a.base + ((int64_t)b * a.stride_b + (int64_t)k * a.stride_k) * Elem<DT>::size;
     int head, nvec, tail;
@@ -568,17 +571,17 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
 
     ThreadState<FULL> st;
     // unaligned head (first slice) and tail (last slice): one element per thread
-    if (split == 0 && tid < head) st.fold_single(load_elem<DT>(rowp, tid), tid);
+    if (split == 0 && part == 0 && tid < head) st.fold_single(load_elem<DT>(rowp, tid), tid);
     {
         const int nbatch = (v1e - v0 + U * kBlock - 1) / (U * kBlock), nfull = (v1e - v0) / (U * kBlock);
-        int i = v0 + tid;
+        int i = v0 + part * (U * kBlock) + tid;
         // A compute unit issues the loads of its oldest wavefront first, so of the eight workgroups that share
         // it the ones dispatched first run ahead and the rest trail by up to a third of the launch; the chip
         // then drains with few loads in flight.  Lowering a wavefront's priority as it gets through its slice
         // keeps the workgroups of a compute unit level (measured: launch 0.6 us shorter for the draft pass).
         const int q1 = nbatch / 4, q2 = nbatch / 2, q3 = (3 * nbatch) / 4;
         __builtin_amdgcn_s_setprio(3);
-        for (int bi = 0; bi < nbatch; ++bi, i += U * kBlock) {
+        for (int bi = part; bi < nbatch; bi += kParts, i += kParts * U * kBlock) {
             if (bi == q1) __builtin_amdgcn_s_setprio(2);
             if (bi == q2) __builtin_amdgcn_s_setprio(1);
             if (bi == q3) __builtin_amdgcn_s_setprio(0);
@@ -594,7 +597,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
     uint32_t tok_bits = 0;
     bool holds_tok = false;
     {
-        const int t = __builtin_amdgcn_readfirstlane(tid < kWave ? tk : -1);
+        const int t = __builtin_amdgcn_readfirstlane(tid < kWave && part == 0 ? tk : -1);
         const int e0 = split == 0 ? 0 : head + v0 * VEC, e1 = split == a.nsplit - 1 ? a.V : head + v1e * VEC;
         if (t >= e0 && t < e1) {
             // the row's address once more, from scalar registers (the zero is opaque to the compiler): holding the
@@ -606,7 +609,7 @@ __device__ inline void stream_pass_body(const RowReduceArgs &a, const int split,
             holds_tok = true;
         }
     }
-    if (split == a.nsplit - 1 && tid < tail) {
+    if (split == a.nsplit - 1 && part == 0 && tid < tail) {
         int32_t j = head + nvec * VEC + tid;
         st.fold_single(load_elem<DT>(rowp, j), j);
     }
@@ -642,12 +645,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
     stream_pass_body<TD, false>(a, blockIdx.x, blockIdx.y + kFirstRows, blockIdx.z);
 }
 
-// A workgroup per row of a vocabulary shard: the row's record, with no launch behind this one to merge slices.
-template <int DT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void stream_record_kernel(RowReduceArgs a, int vocab_offset)
+// A workgroup per row of a vocabulary shard: the row's record, with no launch behind this one to merge slices.  WAVES: four, or eight or sixteen
+// that share the row's batches (shard_record_waves).
+template <int DT, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(6))) void stream_record_kernel(RowReduceArgs a, int vocab_offset)
 {
     warm_args(a);
-    stream_pass_body<DT, true, true>(a, 0, blockIdx.x, blockIdx.y, vocab_offset);
+    stream_pass_body<DT, true, WAVES>(a, 0, blockIdx.x, blockIdx.y, vocab_offset);
 }
 
 // Draft rows and target rows of a round in ONE launch: grid = (slice, row, 2 * sequences), the first half of the
@@ -819,7 +823,9 @@ hipError_t launch(const RowReduceArgs &a, hipStream_t st, Timing tm)
 template <int DT>
 hipError_t launch_record(const RowReduceArgs &a, int vocab_offset, hipStream_t st, Timing tm)
 {
-    launch_kernel(stream_record_kernel<DT>, dim3((unsigned)a.KK, (unsigned)(a.n_rows / a.KK)), dim3(kBlock), st, tm, a, vocab_offset);
+    const int waves = shard_record_waves(a.n_rows, a.V, Elem<DT>::vec);
+    void (*kernel)(RowReduceArgs, int) = waves == 4 ? stream_record_kernel<DT, 4> : (waves == 8 ? stream_record_kernel<DT, 8> : stream_record_kernel<DT, 16>);
+    launch_kernel(kernel, dim3((unsigned)a.KK, (unsigned)(a.n_rows / a.KK)), dim3(waves * kWave), st, tm, a, vocab_offset);
     return hipGetLastError();
 }
 

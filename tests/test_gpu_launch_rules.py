@@ -503,6 +503,12 @@ def test_vocabulary_shards_merged_across_lanes(G, V, dt):
     (191, 1, 8200, 2, bf16), (192, 1, 8200, 2, bf16),           # three slices of a sequence in workgroups of their own, in one
     (192, 1, 65560, 2, f32), (200, 1, 65600, 2, bf16),          # seventeen and sixteen slices
     (200, 2, 20000, 3, f32), (65, 2, 4000, 2, bf16),            # four, one
+    (64, 4, 32770, 2, bf16), (43, 6, 32770, 2, bf16),           # 256 rows of two batches, shared by eight wavefronts; 258, by four
+    (32, 8, 24000, 2, f32), (26, 10, 24000, 2, f32),            # 256 and 260 of three
+    (64, 8, 65530, 2, bf16), (57, 9, 32760, 2, f32),            # 512 and 513 of four
+    (5, 3, 98300, 2, bf16), (5, 3, 98310, 2, bf16),             # six batches a row, and one element more: slices again
+    (16, 4, 65536, 2, f32), (21, 3, 65536, 2, f32),             # eight: 64 rows whole, 63 in slices
+    (64, 4, 131050, 2, f32), (130, 4, 49100, 2, f32),           # sixteen batches; 520 rows of six, by eight wavefronts
 ])
 def test_shard_rows_and_sums_by_one_workgroup(B, K, V, G, dt):
     rnd = mixed_round(B, K, V, dt, dt, seed=V)
@@ -724,3 +730,25 @@ def test_draft_pass_in_as_many_slices_as_the_epilogue_has_lanes_for(B, K, V, dt,
     ref = orc.draft_sample(pu.host_logits(rnd["draft"]), u.numpy(), k_len=np.full(B, K, dtype=np.int32), nthreads=16)
     near = ref["icdf_margin"] <= pu.TAU_S
     assert near.sum() <= 1 and (out["sampled_tok"].cpu().numpy()[~near] == ref["tok"][~near]).all()
+
+
+@pytest.mark.parametrize("B,batches", [(64, 2), (64, 3), (64, 4), (64, 6), (64, 8), (64, 16), (256, 8), (256, 16), (384, 6)])
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_records_of_long_rows_keep_the_precision_of_their_format(B, batches, dt):
+    """Rows shared by eight and sixteen wavefronts, and a thread's sums of up to 256 terms: the bound of the test above."""
+    K, V = 4, batches * 1024 * (4 if dt == f32 else 8)
+    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 0.5).to(dt)
+    rec = binding.Tapout(B, K, V).shard_stats(x, 0, torch.full((B,), K, dtype=torch.int32, device=DEV)).reshape(B * K, 8)
+    M, S, T = (rec[:, i].view(f32).double() for i in range(3))
+    err = []
+    for b in range(0, B * K, 128):
+        y = x.reshape(B * K, V)[b:b + 128].double() * 1.4426950408889634
+        first = y.argmax(-1, keepdim=True)
+        assert torch.equal(rec[b:b + 128, 4].long(), first[:, 0])
+        R = torch.ceil(M[b:b + 128] * 1.4426950408889634)[:, None]
+        e = torch.exp2(y - R)
+        for got, term in ((S, e), (T, e * (y - R))):
+            want = term.scatter(1, first, 0.0).sum(-1)
+            err.append((got[b:b + 128] - want) / want)
+    s, t = torch.cat(err[::2]), torch.cat(err[1::2])
+    assert s.pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5 and t.pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5
