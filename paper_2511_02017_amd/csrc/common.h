@@ -27,7 +27,7 @@ struct Partial {
     float v1;        // slice maximum (NaN entries ignored), -inf for an empty slice
     float S;
     float T;         // draft rows only
-    float v2;        // second largest value of the slice counting duplicates (draft rows only)
+    float v2;        // draft rows: the largest value outside the batch that S and T leave out (shard records: the second largest value, duplicates counted)
     int32_t cand;    // element index at which the 8- (bf16) / 4- (f32) element vector holding the first maximum starts
                      // (shard records: the global index of the first maximum itself)
     int32_t pad[3];  // pad[0]: bits of the logit of the row's token if the slice / shard holds it, else NaN
@@ -424,20 +424,6 @@ __device__ __forceinline__ float lanes_max(float v, int lo, int hi)             
 {
     return __int_as_float(lanes_reduce_i(__float_as_int(v), lo, hi, [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
 }
-// largest and second largest, duplicates counted; m1, m2 of a lane: its own pair
-__device__ inline void lanes_top2(float &m1, float &m2, int lo, int hi)
-{
-    auto step = [&](float a1, float a2, float b1, float b2) {
-        m2 = fmaxf(fmaxf(fminf(a1, b1), a2), b2);
-        m1 = fmaxf(a1, b1);
-    };
-    if (lo <= 0 && hi > 0) step(m1, m2, dpp_mov<0xB1>(m1), dpp_mov<0xB1>(m2));
-    if (lo <= 1 && hi > 1) step(m1, m2, dpp_mov<0x4E>(m1), dpp_mov<0x4E>(m2));
-    if (lo <= 2 && hi > 2) step(m1, m2, dpp_mov<0x141>(m1), dpp_mov<0x141>(m2));
-    if (lo <= 3 && hi > 3) step(m1, m2, dpp_mov<0x140>(m1), dpp_mov<0x140>(m2));
-    if (hi > 4) { const IntPair p = swap16(__float_as_int(m1)), q = swap16(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
-    if (hi > 5) { const IntPair p = swap32(__float_as_int(m1)), q = swap32(__float_as_int(m2)); step(__int_as_float(p.a), __int_as_float(q.a), __int_as_float(p.b), __int_as_float(q.b)); }
-}
 __device__ __forceinline__ double lanes_sum(double v, int lo, int hi)
 {
     if (lo <= 0 && hi > 0) v += dpp_mov<0xB1>(v);
@@ -796,8 +782,9 @@ __device__ __forceinline__ BatchVecs<NV> batch_issue_vecs(const BatchGeom &g, in
 
 // The elements of a piece's left-out batch, except the first one equal to the piece's maximum M: their two sums
 // relative to ref_of_max(M) (binary32 terms as in the streaming pass: they are small, or the row is not peaked) and
-// the index of that first maximum (0x7fffffff if the batch does not hold it).
-struct BatchExtra { float sa, ta; int32_t idx; };
+// the index of that first maximum (0x7fffffff if the batch does not hold it).  m2: the largest of these elements (with the
+// partial's v2, the largest value outside the batch, it makes the piece's second maximum).
+struct BatchExtra { float sa, ta; int32_t idx; float m2; };
 
 // The first maximum lies in the candidate vector (the thread's running maximum reached M there: the vectors before it
 // in the batch are below M, equal values after it are duplicates and count as ordinary terms), so only that vector is
@@ -809,9 +796,9 @@ __device__ inline BatchExtra batch_extra_t(float M, const BatchRegs &b)
     constexpr int VEC = Elem<DT>::vec;
     const float R = ref_of_max(M);
     BatchExtra o;
-    o.sa = 0.0f; o.ta = 0.0f; o.idx = 0x7fffffff;
+    o.sa = 0.0f; o.ta = 0.0f; o.idx = 0x7fffffff; o.m2 = -INFINITY;
     auto sums = [&](bool clamp) {
-        float sa = 0.0f, ta = 0.0f;
+        float sa = 0.0f, ta = 0.0f, m2 = -INFINITY;
         int32_t idx = 0x7fffffff;
         if (b.valid & 0x100u) {
             const float x = __uint_as_float(b.single);
@@ -819,6 +806,7 @@ __device__ inline BatchExtra batch_extra_t(float M, const BatchRegs &b)
             else {
                 const float y = __builtin_fmaf(x, kLog2e, -R), e = __builtin_amdgcn_exp2f(y);
                 sa = e; ta = e * (clamp ? fmaxf(y, -200.0f) : y);
+                m2 = x;
             }
         }
 #pragma unroll
@@ -833,11 +821,12 @@ __device__ inline BatchExtra batch_extra_t(float M, const BatchRegs &b)
                 const float y = __builtin_fmaf(x[j], kLog2e, -R);
                 const float e = first ? 0.0f : __builtin_amdgcn_exp2f(y);
                 if (search) idx = first ? b.first + u * kBlock * VEC + j : idx;
+                m2 = fmaxf(m2, first ? -INFINITY : x[j]);
                 sa += e;
                 ta = __builtin_fmaf(e, clamp ? fmaxf(y, -200.0f) : y, ta);
             }
         }
-        o.sa = sa; o.ta = ta; o.idx = idx;
+        o.sa = sa; o.ta = ta; o.idx = idx; o.m2 = m2;
     };
     sums(false);
     if (o.ta != o.ta) sums(true);
@@ -845,8 +834,43 @@ __device__ inline BatchExtra batch_extra_t(float M, const BatchRegs &b)
 }
 __device__ inline BatchExtra batch_extra(const Piece &p, const BatchRegs &b, int dtype)
 {
-    if (piece_empty(p) || !b.valid) { BatchExtra o; o.sa = 0.0f; o.ta = 0.0f; o.idx = 0x7fffffff; return o; }
+    if (piece_empty(p) || !b.valid) { BatchExtra o; o.sa = 0.0f; o.ta = 0.0f; o.idx = 0x7fffffff; o.m2 = -INFINITY; return o; }
     return dtype == TAPOUT_F32 ? batch_extra_t<TAPOUT_F32>(p.M, b) : batch_extra_t<TAPOUT_BF16>(p.M, b);
+}
+
+// A vector's maximum, and its second largest value, duplicates counted; NaN values are passed over (v_med3 of a NaN is the
+// lesser of the other two).  Each is one block of instructions: a statement per instruction makes the compiler put a wait
+// state after each.
+__device__ __forceinline__ float vector_max(const float (&x)[1]) { return x[0]; }
+__device__ __forceinline__ float vector_max(const float (&x)[4])
+{
+    float m;
+    asm("v_max3_f32 %0, %1, %2, %3\n\tv_max_f32 %0, %0, %4" : "=&v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
+    return m;
+}
+__device__ __forceinline__ float vector_max(const float (&x)[8])
+{
+    float m;
+    asm("v_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5\n\tv_max3_f32 %0, %0, %6, %7\n\tv_max_f32 %0, %0, %8"
+        : "=&v"(m)
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+    return m;
+}
+__device__ __forceinline__ float vector_second(const float (&x)[4])
+{
+    float first, second, a;
+    asm("v_max_f32 %0, %3, %4\n\tv_med3_f32 %1, %7, %3, %4\n\tv_med3_f32 %2, %0, %5, %6\n\tv_max_f32 %1, %1, %2"
+        : "=&v"(first), "=&v"(second), "=&v"(a) : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(-INFINITY));
+    return second;
+}
+__device__ __forceinline__ float vector_second(const float (&x)[8])
+{
+    float first, second, a;
+    asm("v_max_f32 %0, %3, %4\n\tv_med3_f32 %1, %11, %3, %4\n\tv_med3_f32 %2, %0, %5, %6\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %5, %6\n\t"
+        "v_med3_f32 %2, %0, %7, %8\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %7, %8\n\tv_med3_f32 %2, %0, %9, %10\n\tv_max_f32 %1, %1, %2"
+        : "=&v"(first), "=&v"(second), "=&v"(a)
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), "v"(-INFINITY));
+    return second;
 }
 
 // Sums of a lane's vectors of a left-out batch in the row's reference R; excl: the piece holds the row's first maximum M,
@@ -856,18 +880,39 @@ __device__ __forceinline__ BatchExtra batch_sum(float R, float M, bool excl, con
 {
     constexpr int VEC = Elem<DT>::vec;
     BatchExtra o;
+    // the candidate vector, if this lane has it: where its first maximum is, and what comes next
+    u32x4 ws = b.w[0];
+#pragma unroll
+    for (int n = 1; n < NV; ++n) ws = b.search == n ? b.w[n] : ws;
+    const bool search = excl && b.search >= 0 && ((b.valid >> (b.search & (NV - 1))) & 1u) != 0 && b.search < NV;
+    int at = -1;
+    {
+        float x[VEC];
+        unpack<DT>(ws, x);
+#pragma unroll
+        for (int j = VEC - 1; j >= 0; --j) at = x[j] == M ? j : at;            // the lowest one stays
+        at = search ? at : -1;
+        o.m2 = at >= 0 ? vector_second(x) : -INFINITY;
+    }
+    const int32_t found = at >= 0 ? b.first + b.search * (kBlock * VEC) + at : 0x7fffffff;
+    // (the other vectors' maxima)
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+        float x[VEC];
+        unpack<DT>(b.w[n], x);
+        o.m2 = ((b.valid >> n) & 1u) != 0 && !(at >= 0 && n == b.search) ? fmaxf(o.m2, vector_max(x)) : o.m2;
+    }
+    asm volatile("" : "+v"(o.m2));
     auto sums = [&](bool clamp) {
         float sa[2] = {0.0f, 0.0f}, ta[2] = {0.0f, 0.0f};
-        int32_t idx = 0x7fffffff;
+        int32_t idx = found;
 #pragma unroll
         for (int n = 0; n < NV; ++n) {
-            const bool on = (b.valid >> n) & 1u, search = excl && n == b.search;
+            const bool on = (b.valid >> n) & 1u;
             const u32x4 w = {on ? b.w[n].x : 0u, on ? b.w[n].y : 0u, on ? b.w[n].z : 0u, on ? b.w[n].w : 0u};   // stand-in data may be anything
             float x[VEC];
             unpack<DT>(w, x);
-#pragma unroll
-            for (int j = VEC - 1; j >= 0; --j) idx = (search && on && x[j] == M) ? b.first + n * kBlock * VEC + j : idx;      // the lowest one stays
-            const int skip = idx - (b.first + n * kBlock * VEC);
+            const int skip = NV == 1 || n == b.search ? at : -1;
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
                 const float y = __builtin_fmaf(x[j], kLog2e, -R);
@@ -897,7 +942,7 @@ __device__ inline void batch_fix(Piece &p, const BatchRegs &b, int dtype)
 {
     const BatchExtra x = batch_extra(p, b, dtype);
     p.S += (double)x.sa; p.T += (double)x.ta;
-    p.idx = x.idx;
+    p.idx = x.idx; p.v2 = fmaxf(p.v2, x.m2);
 }
 
 // Sequential merge of the `n` pieces of one row held as Partials (LDS or memory) at stride `stride` records.

@@ -93,9 +93,8 @@ __device__ __forceinline__ Piece row_on_lanes(const DraftFinalArgs &a, const int
     float xt = token_logit();
     BatchVecs<NV> bt{};
     if constexpr (!SHARDED) bt = batch_issue_vecs<NV>(g, dtype, a.V, cand, u * NV, a.part);
-    // the row's maximum, second maximum and the piece that holds its first maximum
-    float M = v1;
-    lanes_top2(M, v2, USH, gsh);
+    // the row's maximum and the piece that holds the first of it
+    const float M = lanes_max(v1, USH, gsh);
     const bool holds = v1 == M && cand != 0x7fffffff;
     const int32_t first = lanes_min(holds ? cand : 0x7fffffff, USH, gsh);
     const bool wins = holds && cand == first;
@@ -106,6 +105,7 @@ __device__ __forceinline__ Piece row_on_lanes(const DraftFinalArgs &a, const int
     double Td = u == 0 ? ldexp((double)T - (double)d * (double)S, -di) : 0.0;
     if (S == 0.0f && T == 0.0f) { Sd = 0.0; Td = 0.0; }           // (0 * inf)
     int32_t idx = 0x7fffffff;
+    v2 = wins ? v2 : v1;                                          // the second maximum: outside the winner's batch, of the others the maximum
     if constexpr (SHARDED) {
         // a record leaves its maximum out: an ordinary term here unless it is the row's first maximum
         idx = wins ? cand : 0x7fffffff;
@@ -119,9 +119,10 @@ __device__ __forceinline__ Piece row_on_lanes(const DraftFinalArgs &a, const int
         // the batch's elements in the row's reference, all but the row's first maximum
         const BatchExtra x = dtype == TAPOUT_F32 ? batch_sum<TAPOUT_F32>(R, M, wins, bt, u * NV) : batch_sum<TAPOUT_BF16>(R, M, wins, bt, u * NV);
         Sd += (double)x.sa; Td += (double)x.ta; idx = x.idx;
+        v2 = fmaxf(v2, x.m2);                                     // ... or in it
     }
     Piece t;
-    t.M = M; t.v2 = v2; t.xt = xt;
+    t.M = M; t.v2 = lanes_max(v2, 0, gsh); t.xt = xt;
     t.idx = lanes_min(idx, 0, gsh);
     lanes_sum2(Sd, Td, 0, gsh);
     t.S = Sd; t.T = Td;
@@ -289,7 +290,7 @@ __device__ inline void draft_finalize_staged(const DraftFinalArgs &a, const int 
                 Piece e = piece_from_partial(sh_part[i]);
                 const BatchRegs bt = batch_issue(row_address(a.base, a.dtype, a.stride_b, a.stride_k, b, k), a.dtype, a.V, e.idx, sl, a.per, a.part);
                 batch_fix(e, bt, a.dtype);
-                sh_part[i].S = (float)e.S; sh_part[i].T = (float)e.T; sh_part[i].cand = e.idx;
+                sh_part[i].S = (float)e.S; sh_part[i].T = (float)e.T; sh_part[i].cand = e.idx; sh_part[i].v2 = e.v2;
             }
             __syncthreads();
         }

@@ -63,56 +63,23 @@ __device__ inline float max2(float a, float b)
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
-__device__ inline float min2(float a, float b)
-{
-    float r;
-    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
 
 // Headroom (in powers of two) added to a thread's reference when it has to be
 // raised, so that a slowly growing running maximum raises it only a few times.
 constexpr float kHeadroom = 8.0f;
 
-// Running maximum (and second maximum) over the values of one 16-byte vector, as one block of instructions: a
-// statement per instruction makes the compiler put a wait state after each.
-template <bool FULL>
-__device__ inline void vector_max(float &v1, float &v2, const float (&x)[8])
+template <int N>
+__device__ inline void widen(const u32x4 &w, float (&x)[N])
 {
-    if constexpr (FULL) {
-        float t;
-        asm("v_med3_f32 %2, %0, %3, %4\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\t"
-            "v_med3_f32 %2, %0, %5, %6\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %5, %6\n\t"
-            "v_med3_f32 %2, %0, %7, %8\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %7, %8\n\t"
-            "v_med3_f32 %2, %0, %9, %10\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %9, %10"
-            : "+v"(v1), "+v"(v2), "=&v"(t)
-            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
-    } else {
-        asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\tv_max3_f32 %0, %0, %5, %6\n\tv_max3_f32 %0, %0, %7, %8"
-            : "+v"(v1)
-            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
-    }
-}
-template <bool FULL>
-__device__ inline void vector_max(float &v1, float &v2, const float (&x)[4])
-{
-    if constexpr (FULL) {
-        float t;
-        asm("v_med3_f32 %2, %0, %3, %4\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\t"
-            "v_med3_f32 %2, %0, %5, %6\n\tv_max_f32 %1, %1, %2\n\tv_max3_f32 %0, %0, %5, %6"
-            : "+v"(v1), "+v"(v2), "=&v"(t)
-            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
-    } else {
-        asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4"
-            : "+v"(v1)
-            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
-    }
+    if constexpr (N == 8) unpack<TAPOUT_BF16>(w, x);
+    else if constexpr (N == 4) unpack<TAPOUT_F32>(w, x);
+    else x[0] = __uint_as_float(w.x);
 }
 
 template <bool FULL>
 struct ThreadState {
     float v1 = -INFINITY;   // running maximum
-    float v2 = -INFINITY;   // running second largest (FULL only)
+    float v2 = -INFINITY;   // FULL: the largest value outside the batch in which the running maximum appeared
     float R = -1.0e30f;     // integer reference: every x seen so far has x*log2e <= R (+ rounding); -1e30: none yet
     float s = 0.0f;         // sum 2^(x*log2e - R); FULL: without the batch in which the running maximum appeared
     float t = 0.0f;         // sum 2^y * y (FULL only), likewise
@@ -120,12 +87,12 @@ struct ThreadState {
     float t_hi = 0.0f;
     int32_t cand = 0x7fffffff;
 
-    // Raise the reference so that it covers the running maximum (rare after the first few vectors).
-    // sb, tb: the sums of the batch in progress (FULL).
-    __device__ inline void cover_max(float &sb, float &tb)
+    // Raise the reference so that it covers a vector's maximum m (rare after the first few vectors).
+    // sb, tb: the sums of the batch in progress.
+    __device__ inline void cover(float m, float &sb, float &tb)
     {
-        if (__builtin_fmaf(v1, kLog2e, -R) > 0.0f) {          // also the first finite value (nothing is summed yet then)
-            float Rn = ceilf(v1 * kLog2e) + kHeadroom;
+        if (__builtin_fmaf(m, kLog2e, -R) > 0.0f) {           // also the first finite value (nothing is summed yet then)
+            float Rn = ceilf(m * kLog2e) + kHeadroom;
             float d = Rn - R;
             int di = (int)fminf(fmaxf(d, -1.0e9f), 1.0e9f);
             if constexpr (FULL) {
@@ -133,44 +100,38 @@ struct ThreadState {
                 t_hi = ldexpf(t_hi - d * s_hi, -di);
                 tb = ldexpf(tb - d * sb, -di);
                 s_hi = ldexpf(s_hi, -di);
-                sb = ldexpf(sb, -di);
             }
             s = ldexpf(s, -di);
+            sb = ldexpf(sb, -di);
             R = Rn;
         }
     }
 
-    // A batch of U vectors of N values each (vector u starts at element index first + u * stride of the row), vector
-    // by vector: maxima (`first + u * stride` is remembered as the argmax candidate when vector u raises the running
-    // maximum), reference check, sums.  The entropy sum of a vector is formed without looking at the terms; a masked
-    // (-inf) logit gives 0 * -inf = NaN there, and only then the vector is summed again with the exponent clamped (one
-    // comparison per vector instead of one clamp per element).
-    // n: the vectors behind the n-th hold nothing in the whole wavefront and are passed over.  each(u): called when vector u has been
-    // folded.
+    // A batch of U vectors of N values each (vector u starts at element index first + u * stride of the row), vector by vector:
+    // maximum, reference check, sums.  n: the vectors behind the n-th hold nothing in the whole wavefront and are passed over.
+    //
+    // What can wait is done once per batch: the running maximum, the largest value outside its batch (the row's second
+    // maximum is one of those or lies in the set-apart batch, which the epilogue reads again anyway) and which vector holds
+    // the maximum, the first of several (remembered as the argmax candidate).  With the second maximum and the candidate kept vector
+    // by vector the maxima took 1.5 instructions an element instead of 0.5.  The tokens' draw, which this arithmetic bounds: 46.4
+    // -> 44.8 us for 512 rows of 128256 bf16 logits, 33.2 -> 32.1 for 256 rows of 151936; the draft pass waits for memory: 28.6 ->
+    // 28.4 at the first size.
+    //
+    // The entropy sum of a vector is formed without looking at the terms; a masked (-inf) logit gives 0 * -inf = NaN there, and only
+    // then the vector is summed again with the exponent clamped (one comparison per vector instead of one clamp per element).
+    // each(u): called when vector u has been folded.
     template <int U, int N, class Each>
     __device__ inline void fold_batch(const u32x4 (&w)[U], int n, int32_t first, int32_t stride, Each each)
     {
-        bool grew = false;                                    // a lane mask in scalar registers
-        float sb = 0.0f, tb = 0.0f;
+        float vm[U], sb = 0.0f, tb = 0.0f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            vm[u] = -INFINITY;
             if (U > 1 && u >= n) continue;
-            float x[N];
-            if constexpr (N == 8) unpack<TAPOUT_BF16>(w[u], x);
-            else if constexpr (N == 4) unpack<TAPOUT_F32>(w[u], x);
-            else x[0] = __uint_as_float(w[u].x);
-            const float old = v1;
-            if constexpr (N == 1) {
-                if constexpr (FULL) v2 = max2(v2, min2(v1, x[0]));
-                v1 = max2(v1, x[0]);
-            } else {
-                vector_max<FULL>(v1, v2, x);
-            }
-            const bool g = v1 > old;
-            cand = g ? first + u * stride : cand;
-            grew |= g;
-            cover_max(sb, tb);
-            float y[N], e[N];
+            float x[N], y[N], e[N];
+            widen<N>(w[u], x);
+            vm[u] = vector_max(x);
+            cover(vm[u], sb, tb);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 y[i] = __builtin_fmaf(x[i], kLog2e, -R);
@@ -189,13 +150,22 @@ struct ThreadState {
 #pragma unroll
                     for (int i = 0; i < N; ++i) tv = __builtin_fmaf(e[i], fmaxf(y[i], -200.0f), tv);
                 }
-                sb = u == 0 ? sv : sb + sv;                   // (a sum started from 0.0f would cost an addition: -0 + 0)
                 tb = u == 0 ? tv : tb + tv;
-            } else {
-                s += sv;
             }
+            sb = u == 0 ? sv : sb + sv;                        // (a sum started from 0.0f would cost an addition: -0 + 0)
             each(u);
         }
+        float bm = vm[0];
+        if constexpr (U == 4) bm = max2(max3(vm[0], vm[1], vm[2]), vm[3]);
+        static_assert(U == 1 || U == 4, "the maximum of a batch's vectors");
+        const bool grew = bm > v1;                             // a lane mask in scalar registers
+        if constexpr (FULL) v2 = med3(v1, v2, bm);
+        v1 = max2(v1, bm);
+        int32_t at = U - 1;
+#pragma unroll
+        for (int u = U - 2; u >= 0; --u) at = vm[u] == bm ? u : at;
+        asm("" : "+v"(at));                                    // (a number below four is in the instruction, its product with the stride in a register)
+        cand = grew ? first + at * stride : cand;
         if constexpr (FULL) {
             // If the running maximum grew inside the batch, its sums become the set-apart ones and the batch that held
             // the previous maximum joins the rest; else it joins the rest itself.
@@ -203,6 +173,8 @@ struct ThreadState {
             t += grew ? t_hi : tb;
             s_hi = grew ? sb : s_hi;
             t_hi = grew ? tb : t_hi;
+        } else {
+            s += sb;
         }
     }
 
@@ -383,10 +355,11 @@ struct DrawSums {
     }
     // The sum of vector u of batch bi once more, computed, with a thread's lone element (its exponential) beside it.  The lane that
     // stored the first one stores it.
-    __device__ inline void again(const u32x4 &w, double lone, int bi, int u) const
+    __device__ inline void again(const u32x4 &w, double lone, int bi, int u, int tid) const
     {
+        asm volatile("" : "+v"(tid));                        // (else what is formed of it here waits in registers from the kernel's start on)
         const double x = wave_sum_d(computed(w) + lone);
-        const int lane = threadIdx.x & (kWave - 1), row = ((u & 1) << 1) | (u >> 1), wave = (threadIdx.x & (kBlock - 1)) / kWave;
+        const int lane = tid & (kWave - 1), row = ((u & 1) << 1) | (u >> 1), wave = tid / kWave;
         if (lane == row * 16) out[(bi * kStreamU + u) * (kBlock / kWave) + wave] = x;
     }
 };
@@ -467,8 +440,8 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
             S += (double)e;
             T += (double)e * (double)fmaxf(y, -200.0f);
         }
-        const float v2 = lanes_max(holds ? __uint_as_float(r0.w) : Ml, kVecBits, kBits);
         const BatchExtra x = batch_sum<DT>(R, Ml, true, bt, u);
+        const float v2 = lanes_max(fmaxf(holds ? __uint_as_float(r0.w) : Ml, x.m2), 0, kBits);
         const int idx = lanes_min(holds ? x.idx : 0x7fffffff, 0, kBits);
         S = lanes_sum(S, kVecBits, kBits) + lanes_sum((double)x.sa, 0, kBits);
         T = lanes_sum(T, kVecBits, kBits) + lanes_sum((double)x.ta, 0, kBits);
@@ -783,7 +756,7 @@ __global__ __launch_bounds__(kBlock * DrawShape<DT>::parts) __attribute__((amdgp
                 int32_t j = -1;
                 if (heads && bi == 0 && u == 0 && tid < at.head) j = tid;
                 if (tails && bi == d.nb - 1 && u == U - 1 && tid < at.tail) j = at.head + at.nvec * VEC + tid;
-                draw.again(w, j >= 0 ? draw.computed(load_elem<DT>(at.row, j)) : 0.0, bi, u);
+                draw.again(w, j >= 0 ? draw.computed(load_elem<DT>(at.row, j)) : 0.0, bi, u, tid);
             }
         }
         if (at.on && at.s == a.nsplit - 1 && tid < at.tail) {

@@ -752,3 +752,32 @@ def test_records_of_long_rows_keep_the_precision_of_their_format(B, batches, dt)
             err.append((got[b:b + 128] - want) / want)
     s, t = torch.cat(err[::2]), torch.cat(err[1::2])
     assert s.pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5 and t.pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5
+
+
+@pytest.mark.parametrize("K,P", [(24, 3), (24, 13), (70, 3), (24, 0)])      # lanes in one pass and in two, one slice after the other; shard records
+@pytest.mark.parametrize("dt", [f32, bf16])
+def test_second_maximum_wherever_it_lies(K, P, dt):
+    """The second largest value in the vector, the batch, the thread, the slice of the largest and outside of them, before and behind it, and as
+    large as it: probabilities and margin within the 1e-5 max(|value|, 1e-3) of all statistics."""
+    vec = 8 if dt == bf16 else 4
+    batch = 4 * 256 * vec
+    V = (P or 4) * 2 * batch + 5
+    p = 2 * batch * ((P or 4) // 2) + 256 * vec + 7 * vec + 2         # in the second vector of a thread's first batch of a slice
+    off = [1, -1, vec, -vec, 256 * vec, -256 * vec, 512 * vec, batch, batch + 1, -batch, 2 * batch - 300 * vec, V - 1 - p]
+    off = [off[k % 12] for k in range(K)]
+    x = torch.randn(1, K, V, generator=torch.Generator().manual_seed(P)).to(dt)
+    for k in range(K):
+        x[0, k, p] = 9.0
+        x[0, k, p + off[k]] = 9.0 if k % 24 >= 12 else 8.5
+    tp = binding.Tapout(1, K, V)
+    if P:
+        force_slices(tp, K, P)
+        out = tp.draft_stats(x.to(DEV))
+    else:
+        cut = [0, V // 2 - 1000, V]
+        rec = torch.stack([tp.shard_stats(x[:, :, i:j].contiguous().to(DEV), i).clone() for i, j in zip(cut, cut[1:])])
+        out = tp.draft_stats_sharded(rec, 1, K, V)
+    two = torch.softmax(x.double(), -1).topk(2, -1).values
+    for n, w in {"p_top1": two[..., 0], "p_top2": two[..., 1], "margin": two[..., 0] - two[..., 1]}.items():
+        assert ((out[n].cpu().double() - w).abs() <= 1e-5 * w.abs().clamp(min=1e-3)).all(), n
+    assert out["top1_id"][0].tolist() == [p + (min(0, off[k]) if k % 24 >= 12 else 0) for k in range(K)]
