@@ -218,9 +218,10 @@ __device__ __forceinline__ void draft_finalize_lanes(const DraftFinalArgs &a, co
         float threshold_seq = 0.0f;
         auto pick_rule = [&]() __attribute__((always_inline)) {
             if (tok_mode || !a.arm) return;
-            const bool ok = arm >= 0 && arm < a.n_arms;
-            rule_seq = ok ? pick8(a.rule, arm) : -1;
-            threshold_seq = pick8(a.threshold, ok ? arm : 0);
+            const int one = __builtin_amdgcn_readfirstlane(arm);
+            const bool ok = one >= 0 && one < a.n_arms;
+            rule_seq = ok ? pick8(a.rule, one) : -1;
+            threshold_seq = pick8(a.threshold, ok ? one : 0);
             asm volatile("" : "+s"(rule_seq), "+s"(threshold_seq));
         };
         Piece t;
