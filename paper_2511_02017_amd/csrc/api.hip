@@ -136,7 +136,6 @@ Slices cut_evenly(int n, int V, int dtype)
     return Slices{n, ((((V + vec - 1) / vec + 1 + n - 1) / n) + 63) & ~63};
 }
 constexpr int kBatchVecs = kBlock * kStreamU;
-constexpr int kFewPiecesWgs = 768, kFewPiecesWgsDraw = 1024;
 Slices cut_in_batches(int n, int V, int dtype)
 {
     const int vecs = V / (dtype == TAPOUT_F32 ? 4 : 8);
@@ -147,10 +146,8 @@ Slices cut_in_batches(int n, int V, int dtype)
     return Slices{n, whole > kBatchVecs && (vecs + whole - 1) / whole == n ? (even + 63) & ~63 : whole};
 }
 
-// KK: rows per sequence, over which one workgroup of an epilogue merges the partials.  few_wgs: of a draft pass on its own, behind which nothing
-// runs but the epilogue (and in a round up to the stop position beside it the first target rows): from how many workgroups on it may be cut
-// coarser than it would be by itself; else 0.
-Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t rows, int KK, int V, int dtype, int few_wgs = 0)
+// KK: rows per sequence, over which one workgroup of an epilogue merges the partials.
+Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t rows, int KK, int V, int dtype)
 {
     if (min_slice > 0) return cut_evenly(slices_by_elements(wgs_target, min_slice, slice_bytes, rows, V, dtype), V, dtype);
     // By itself a slice is one or two whole batches where rows are few: a slice of half a batch pays a workgroup's fixed
@@ -190,36 +187,12 @@ Slices choose_slices(int wgs_target, int min_slice, int slice_bytes, int64_t row
     if ((nb + pb - 1) / pb > cap) pb = (nb + cap - 1) / cap;
     if (pb <= 2) want = (nb + pb - 1) / pb;
     if (want > kStageCap) want = kStageCap;       // an epilogue stages whole rows of partials in LDS
-    const Slices all = cut_in_batches((int)want, V, dtype);
-    if (few_wgs == 0 || staged) return all;
-    // A draft pass with the epilogue behind it: half or a quarter as many slices, of whole batches, so that the epilogue has four lanes for
-    // each (draft_lanes_shift), where the pass gains by it too: a workgroup costs about 0.6 batches beside the batches it takes, and a launch what
-    // the compute unit with the most of them has.  Three workgroups to a compute unit at least, no more than a tenth of the batches' vectors
-    // missing, and no slice so long that so few workgroups of it leave the memory waiting (40960 elements).  us, with all slices / so many, draft
-    // pass and epilogue, with drawn tokens, round up to the stop position (whose first target rows then run beside the epilogue), K = 8:
-    // V = 128256, bfloat16, 16 sequences 14.2 / 13.5, 21.4 / 20.7, 31.7 / 28.1, 32 sequences 20.2 / 18.8, 32.5 / 29.4, 44.0 / 40.5; binary32, 16 sequences
-    // 17.2 / 16.5, 28.2 / 26.7, 35.8 / 31.6; K = 16, bfloat16, 16 sequences 19.9 / 17.5, 33.0 / 30.1, 42.4 / 36.5; V = 151936, binary32, 32 sequences 33.6 / 31.4,
-    // 56.8 / 50.5, 62.4 / 58.9.  Where the rule says no: V = 151936, bfloat16, 32 sequences (2.3 batches a slice) 21.6 / 23.1 for the pass; V = 50257,
-    // binary32, 48 sequences, K = 13 (3.1 batches) 27.1 / 30.7; V = 256000, bfloat16, 24 sequences, K = 16 (7.8 batches) 41.3 / 43.0; of 768
-    // workgroups, V = 128256, 12 sequences, bfloat16 12.6 / 12.3 and 32.9 / 30.2, binary32 14.6 / 14.7 and 35.7 / 31.7, of 512, 8 sequences 11.2 / 11.3 and 26.4 / 27.8,
-    // 12.0 / 13.3 and 29.7 / 27.6.
-    // Contexts that draw draft tokens from 1024 workgroups on (the same cut for calls with a draw and without): of 768, drawn tokens of those 12
-    // sequences bfloat16 18.4 / 19.6, binary32 22.3 / 23.7.
-    int few = 16;
-    while (few > 1 && KK * few > 64) few /= 2;
-    if (few >= all.n || rows * few < few_wgs) return all;
-    const int vec = dtype == TAPOUT_F32 ? 4 : 8;
-    auto batches = [](const Slices &c) { return (int64_t)(c.per + kBatchVecs - 1) / kBatchVecs; };
-    auto cost = [&](const Slices &c) { return (rows * c.n + 255) / 256 * (5 * batches(c) + 3); };
-    const Slices fewer = cut_in_batches(few, V, dtype);
-    const bool whole_batches = 10 * few * batches(fewer) * kBatchVecs <= 11 * vecs, short_enough = batches(fewer) * kBatchVecs * vec <= 40960;
-    return whole_batches && short_enough && 10 * cost(fewer) <= 9 * cost(all) ? fewer : all;
+    return cut_in_batches((int)want, V, dtype);
 }
 
-Slices choose_slices(const tapout_ctx *ctx, int64_t rows, int KK, int V, int dtype, bool draft = false)
+Slices choose_slices(const tapout_ctx *ctx, int64_t rows, int KK, int V, int dtype)
 {
-    const int few_wgs = !draft ? 0 : (ctx->cfg.draft_sampling ? kFewPiecesWgsDraw : kFewPiecesWgs);
-    return choose_slices(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, KK, V, dtype, few_wgs);
+    return choose_slices(ctx->wgs_target, ctx->min_slice, ctx->slice_bytes, rows, KK, V, dtype);
 }
 
 // Sums that the draft pass leaves for the draft-token draw: a sum per wavefront, vector of a batch and batch of every slice.
@@ -582,7 +555,7 @@ tapout_status draft_stats_impl(tapout_ctx *ctx, const tapout_logits *draft,
     DeviceGuard guard(ctx->cfg.device);
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = (int64_t)B * K;
-    if (slices.n <= 0) slices = choose_slices(ctx, rows, K, V, draft->dtype, true);
+    if (slices.n <= 0) slices = choose_slices(ctx, rows, K, V, draft->dtype);
     const int nsplit = slices.n;
     if ((size_t)(rows * nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
 
@@ -695,7 +668,7 @@ tapout_status tapout_draft_stats_static(const tapout_logits *draft, int32_t B, i
     if ((uint64_t)rows * (uint64_t)bound > kStaticPartials)
         return fail(nullptr, TAPOUT_EINVAL, "B * K * slices = %lld x %d exceeds the static scratch of %zu slice partials",
                     (long long)rows, bound, kStaticPartials);
-    Slices slices = choose_slices(4096, 0, 65536, rows, K, V, draft->dtype, kFewPiecesWgs);
+    Slices slices = choose_slices(4096, 0, 65536, rows, K, V, draft->dtype);
     if ((uint64_t)rows * (uint64_t)slices.n > kStaticPartials) slices = choose_slices(4096, 4096, 65536, rows, K, V, draft->dtype);
     const int nsplit = slices.n;
     int dev = -1;
@@ -1051,7 +1024,7 @@ tapout_status tapout_round(tapout_ctx *ctx, const tapout_round_args *a, void *st
     // lanes; the stateful rules' epilogue hands entropies to the end of the round, so it keeps its place): then the
     // epilogue, a latency-bound kernel of B workgroups, runs beside the final-token locate kernel, another one, in
     // one launch.
-    const Slices d_slices = !pair || pair_all ? choose_slices(ctx, (int64_t)a->B * a->K, a->K, a->V, a->draft->dtype, true)
+    const Slices d_slices = !pair || pair_all ? choose_slices(ctx, (int64_t)a->B * a->K, a->K, a->V, a->draft->dtype)
                                   : ctx->min_slice > 0 ? cut_evenly(c.slices.n, a->V, a->draft->dtype) : cut_in_batches(c.slices.n, a->V, a->draft->dtype);
     const bool defer = given && !ctx->stateful && ctx->defer_epilogue &&
                        own_q_shape(a->K, c.slices.n, d_slices.n);

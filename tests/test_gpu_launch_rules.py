@@ -714,12 +714,12 @@ def test_entropy_rule_beside_its_threshold():
 
 
 @pytest.mark.parametrize("B,K,V,dt,tt", [
-    (12, 8, 128256, bf16, bf16), (11, 8, 128256, bf16, bf16),        # 768 workgroups of eight slices a row, and 704: sixteen slices
-    (16, 16, 128259, bf16, bf16),                                    # four slices of four batches a row, at every alignment
-    (16, 8, 151936, bf16, bf16),                                     # eight slices would be of two batches and a third: ten of two
-    (16, 8, 151936, f32, f32), (20, 5, 128256, f32, bf16),
+    (12, 8, 128256, bf16, bf16), (11, 8, 128256, bf16, bf16),        # sixteen slices of a batch: two lanes each in the epilogue
+    (16, 16, 128259, bf16, bf16),                                    # one lane each; rows at every alignment
+    (16, 8, 151936, bf16, bf16),                                     # ten of two batches
+    (16, 8, 151936, f32, f32), (20, 5, 128256, f32, bf16),           # sixteen of two batches and a third, of two
 ])
-def test_draft_pass_in_as_many_slices_as_the_epilogue_has_lanes_for(B, K, V, dt, tt):
+def test_draft_pass_of_a_mid_sized_batch(B, K, V, dt, tt):
     rnd = mixed_round(B, K, V, dt, tt, seed=V + K)
     tp = binding.Tapout(B, K, V)
     arm = random_arms(B, seed=K)
@@ -730,6 +730,42 @@ def test_draft_pass_in_as_many_slices_as_the_epilogue_has_lanes_for(B, K, V, dt,
     ref = orc.draft_sample(pu.host_logits(rnd["draft"]), u.numpy(), k_len=np.full(B, K, dtype=np.int32), nthreads=16)
     near = ref["icdf_margin"] <= pu.TAU_S
     assert near.sum() <= 1 and (out["sampled_tok"].cpu().numpy()[~near] == ref["tok"][~near]).all()
+
+
+STATS = ("lse", "entropy", "p_top1", "p_top2", "margin", "top1_id", "logq_tok", "flags")
+
+
+def _same_bits(a, b, names=STATS):
+    return [n for n in names if not torch.equal(a[n], b[n])]
+
+
+@pytest.mark.parametrize("B,K,V,dt", [(12, 8, 128256, bf16), (14, 15, 47000, f32), (18, 14, 160000, bf16)])
+def test_statistics_do_not_depend_on_who_may_draw_tokens(B, K, V, dt):
+    """The same bits from a context that draws tokens, with a draw and without, from one that does not, and from the entry point without one."""
+    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 2).to(dt)
+    draws, plain = binding.Tapout(B, K, V, draft_sampling=True), binding.Tapout(B, K, V)
+    first = draws.draft_stats(x, u_draft=torch.rand(B, K, generator=torch.Generator().manual_seed(K)).to(DEV))
+    for other in (draws.draft_stats(x, draft_tok=first["sampled_tok"]), plain.draft_stats(x, draft_tok=first["sampled_tok"]),
+                  binding.draft_stats_static(x, draft_tok=first["sampled_tok"])):
+        assert not _same_bits(first, other)
+
+
+@pytest.mark.parametrize("B,K,V,dt,opts,P", [
+    (24, 16, 128256, bf16, {}, 16),                                  # slices of one batch also where rows are many: in short drafts few are live
+    (64, 8, 128256, bf16, {"slice_bytes": 16384}, 16), (64, 8, 128256, bf16, {"wgs_target": 8192}, 16),
+    (24, 16, 128256, bf16, {"wgs_target": 65536}, 16),
+    (64, 8, 128256, bf16, {"wgs_target": 1, "slice_bytes": 131072}, 1),
+])
+def test_draft_pass_is_cut_as_its_options_say(B, K, V, dt, opts, P):
+    """The bits of the same cut asked for by the smallest slice."""
+    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 2).to(dt)
+    tok = torch.randint(0, V, (B, K), generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    a, b = binding.Tapout(B, K, V), binding.Tapout(B, K, V)
+    for name, v in opts.items():
+        a.set_option(name, v)
+    b.set_option("slice_bytes", 1 << 22)
+    force_slices(b, B * K, P, min_slice=8000)
+    assert not _same_bits(a.draft_stats(x, draft_tok=tok), b.draft_stats(x, draft_tok=tok))
 
 
 @pytest.mark.parametrize("B,batches", [(64, 2), (64, 3), (64, 4), (64, 6), (64, 8), (64, 16), (256, 8), (256, 16), (384, 6)])
