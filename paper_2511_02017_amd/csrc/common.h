@@ -102,25 +102,26 @@ hipError_t launch_shard_records(const RowReduceArgs &a, int vocab_offset, int dt
 // While there is no more than a workgroup to a compute unit they shorten the chain that the launch is (us per call, rows of 2 / 3 / 4 batches, 256
 // rows, four wavefronts bfloat16 6.1 / 6.9 / 9.4, binary32 5.4 / 6.6 / 8.0, with more 5.3 / 6.2 / 7.2 and 4.5 / 5.8 / 6.2; 8 rows 5.45 / 6.3 / 7.6, 4.85 / 6.05 / 6.0); then
 // their reductions get in each other's way (320 rows 6.5 / 8.2 / 10.2, 5.35 / 6.5 / 8.4, with more 6.6 / 8.8 / 9.8, 5.6 / 7.4 / 8.1), for long rows later: 512 rows of
-// 4 batches 10.7 / 10.2, 576 rows 11.8 / 14.0; of 8 batches, 768 rows sixteen 24.3, eight 20.0, 1536 rows eight 41.6, four 37.3.
+// 4 batches 10.7 / 10.2, 576 rows 11.8 / 14.0.
 inline int shard_record_waves(int64_t n_rows, int V, int vec)
 {
-    const int batch = kBlock * kStreamU, batches = (V / vec + batch - 1) / batch, more = batches <= 2 ? 8 : 16;
+    const int batch = kBlock * kStreamU, batches = (V / vec + batch - 1) / batch;
     if (batches <= 1) return 4;
-    if (batches <= 3) return n_rows <= 256 ? more : 4;
-    return n_rows <= 512 ? more : (batches > 4 && n_rows <= 1024 ? 8 : 4);
+    if (batches <= 3) return n_rows <= 256 ? (batches == 2 ? 8 : 16) : 4;
+    return n_rows <= 512 ? 16 : 4;
 }
 // A shard's rows are read whole, by a workgroup each that writes the row's record; longer ones, and more of them, in slices that a launch behind the
 // pass merges.  us per call, slices and merge / whole rows, bfloat16: 2 batches, 8 / 512 / 2048 rows 7.4 / 4.8, 9.9 / 7.1, 18.5 / 15.2; 4 batches 7.5 / 6.0, 12.9 / 10.1,
-// 28.1 / 27.2; 6 batches 7.7 / 6.8, 15.9 / 12.5, 39.7 / 40.4 (1536 rows 30.5 / 29.4); 8 batches, 1 / 64 / 512 / 1536 rows 7.5 / 7.65, 8.7 / 8.2, 18.8 / 15.1, 40.8 / 37.3;
-// 16 batches, 64 / 256 / 1024 rows 10.3 / 12.1, 19.1 / 14.75, 50.8 / 49.3; binary32 the same way: 8 rows of 4 batches 7.0 / 5.4, 6 7.0 / 5.7, 64 of 8 7.6 / 6.5, 256 of
-// 16 16.1 / 13.2.
+// 28.1 / 27.2.  Beyond 4 batches up to a workgroup to a compute unit: more rows gain where all of them are live, and lose in short drafts, whose
+// few live rows then leave most of the chip idle (all live / a quarter: 8 batches, 8 rows a sequence, 256 rows 13.4 / 9.5 and 12.6 / 9.0, 512 rows 19.2 / 14.8 and
+// 14.0 / 13.1, 1536 rows 43.4 / 36.7 and 20.7 / 27.2; 6 batches, 64 rows 8.8 / 7.8 and 8.1 / 7.6, 256 rows 11.8 / 8.5 and 9.2 / 8.2, 320 rows 13.3 / 11.6 and 10.1 / 11.1,
+// 1024 rows 25.2 / 21.6 and 14.4 / 16.7; binary32, 8 batches, 256 rows 11.5 / 8.7 and 10.7 / 7.9, 1536 rows 37.0 / 33.1 and 18.5 / 23.7; 16 batches, 256 rows bfloat16 18.9 / 14.4 and
+// 12.7 / 13.0, binary32 16.6 / 13.7 and 11.0 / 11.0, 320 rows 18.7 / 19.4 and 11.2 / 16.4).  One sequence of 8 batches 7.5 / 7.65.
 inline bool shard_rows_whole(int64_t n_rows, int V, int vec)
 {
     const int64_t batch = (int64_t)kBlock * kStreamU * vec;
     if (V <= 4 * batch) return true;
-    if (n_rows > 1536) return false;
-    return V <= 6 * batch || (n_rows >= 64 && V <= 8 * batch) || (n_rows >= 256 && n_rows <= 1024 && V <= 16 * batch);
+    return n_rows <= 256 && (V <= 6 * batch || (n_rows >= 64 && V <= 8 * batch));
 }
 // Draft pass (all statistics) and target pass of the same sequences in one launch.
 hipError_t launch_row_reduce_pair(const RowReduceArgs &d, int d_dtype, const RowReduceArgs &t, int t_dtype, hipStream_t st, Timing tm);

@@ -508,7 +508,7 @@ def test_vocabulary_shards_merged_across_lanes(G, V, dt):
     (64, 8, 65530, 2, bf16), (57, 9, 32760, 2, f32),            # 512 and 513 of four
     (5, 3, 98300, 2, bf16), (5, 3, 98310, 2, bf16),             # six batches a row, and one element more: slices again
     (16, 4, 65536, 2, f32), (21, 3, 65536, 2, f32),             # eight: 64 rows whole, 63 in slices
-    (64, 4, 131050, 2, f32), (130, 4, 49100, 2, f32),           # sixteen batches; 520 rows of six, by eight wavefronts
+    (64, 4, 131050, 2, f32), (130, 4, 49100, 2, f32),           # in slices: sixteen batches; 520 rows of six
 ])
 def test_shard_rows_and_sums_by_one_workgroup(B, K, V, G, dt):
     rnd = mixed_round(B, K, V, dt, dt, seed=V)
@@ -554,6 +554,22 @@ def test_shard_records_keep_the_precision_of_their_format(batches, dt):
     assert torch.allclose(S, rest(e), rtol=1e-5, atol=0.0)     # (the reference is the integer above the maximum)
     for got, want in ((S, rest(e)), (T, rest(e * (y - R[:, None])))):
         assert ((got - want) / want).pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5
+
+
+@pytest.mark.parametrize("B,K,V,dt,P", [
+    (64, 4, 32756, f32, 1), (43, 6, 32756, f32, 8),             # 256 rows of eight batches whole, 258 in slices
+    (16, 4, 32756, f32, 1), (21, 3, 32756, f32, 8),             # 64 and 63 of them
+    (32, 8, 49100, bf16, 1), (43, 6, 49100, bf16, 6),           # 256 and 258 rows of six
+    (96, 8, 64128, f32, 6), (192, 8, 48000, bf16, 3),           # more rows: few are live in short drafts, a workgroup each would leave the chip idle
+])
+def test_long_shard_rows_are_read_whole_up_to_a_workgroup_per_compute_unit(B, K, V, dt, P):
+    """The bits of the same cut asked for by the smallest slice."""
+    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 2).to(dt)
+    a, b = binding.Tapout(B, K, V), binding.Tapout(B, K, V)
+    b.set_option("slice_bytes", 1 << 22)
+    force_slices(b, B * K, P, min_slice=1000)
+    k_len = torch.full((B,), K, dtype=torch.int32, device=DEV)
+    assert torch.equal(a.shard_stats(x, 7, k_len), b.shard_stats(x, 7, k_len))
 
 
 @pytest.mark.parametrize("P", [1, 2, 3, 16, 17])
@@ -771,7 +787,7 @@ def test_draft_pass_is_cut_as_its_options_say(B, K, V, dt, opts, P):
 @pytest.mark.parametrize("B,batches", [(64, 2), (64, 3), (64, 4), (64, 6), (64, 8), (64, 16), (256, 8), (256, 16), (384, 6)])
 @pytest.mark.parametrize("dt", [f32, bf16])
 def test_records_of_long_rows_keep_the_precision_of_their_format(B, batches, dt):
-    """Rows shared by eight and sixteen wavefronts, and a thread's sums of up to 256 terms: the bound of the test above."""
+    """Rows shared by eight and sixteen wavefronts, and rows in slices: the bound of the test above."""
     K, V = 4, batches * 1024 * (4 if dt == f32 else 8)
     x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 0.5).to(dt)
     rec = binding.Tapout(B, K, V).shard_stats(x, 0, torch.full((B,), K, dtype=torch.int32, device=DEV)).reshape(B * K, 8)
