@@ -568,7 +568,9 @@ TAPOUT_API tapout_status tapout_rule_state_set(tapout_ctx *ctx, const float *pre
  *   "min_slice"   smallest slice of a row, in elements, at least 256; 0 (default):
  *                 a slice is at least one batch of the streaming kernel's loads
  *                 (16 KB), and rows are cut no finer than the epilogues merge
- *                 quickly
+ *                 quickly.  With this and the two above at their defaults
+ *                 tapout_shard_stats reads rows of up to four batches (in launches
+ *                 of up to 256 rows up to eight) in one piece
  *   "fuse_head"   tapout_verify only: 1 = no launch of its own for the accept
  *                 decisions, every workgroup of the final-token slice kernel
  *                 takes them again for its sequence (pays while that kernel

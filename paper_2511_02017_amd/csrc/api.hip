@@ -14,6 +14,8 @@
 
 using namespace tapout;
 
+constexpr int kWgsTarget = 4096, kSliceBytes = 65536;           // the options' defaults
+
 struct tapout_ctx {
     tapout_config cfg;
     Partial *part = nullptr;      size_t part_cap = 0;       // slice partials of the draft pass (and of a shard pass)
@@ -34,9 +36,9 @@ struct tapout_ctx {
     float *round_entropy = nullptr;                            // [max_batch, max_k] entropies of the last draft_stats call
     int round_K = 0;                                           // its K (0: no draft_stats call yet)
     int positions = 1;                                         // bandits per slot: 1, or max_k for token-level bandits
-    int wgs_target = 4096;        // workgroups a streaming launch aims for
+    int wgs_target = kWgsTarget;  // workgroups a streaming launch aims for
     int min_slice = 0;            // smallest slice (elements) a row is cut into; 0: whole batches of the streaming kernel (choose_slices)
-    int slice_bytes = 65536;      // slice size aimed for when the rows alone give enough workgroups
+    int slice_bytes = kSliceBytes; // slice size aimed for when the rows alone give enough workgroups
     int fuse_head = -1;           // tapout_verify: accept decisions inside the slice kernel (1), in a launch of their own (0), by size (-1)
     int exp_lookup = 1;           // final token: exponentials of bfloat16 row pairs from the table (1) or computed (0)
     int defer_epilogue = 1;       // tapout_round: the draft epilogue may run beside the final-token locate kernel (1) or keeps its own launch (0)
@@ -664,12 +666,12 @@ tapout_status tapout_draft_stats_static(const tapout_logits *draft, int32_t B, i
     }
     const int64_t rows = (int64_t)B * K;
     // what is accepted: the documented bound; how the rows are cut: as a context with default options would
-    const int bound = slices_by_elements(4096, 4096, 65536, rows, V, draft->dtype);
+    const int bound = slices_by_elements(kWgsTarget, 4096, kSliceBytes, rows, V, draft->dtype);
     if ((uint64_t)rows * (uint64_t)bound > kStaticPartials)
         return fail(nullptr, TAPOUT_EINVAL, "B * K * slices = %lld x %d exceeds the static scratch of %zu slice partials",
                     (long long)rows, bound, kStaticPartials);
-    Slices slices = choose_slices(4096, 0, 65536, rows, K, V, draft->dtype);
-    if ((uint64_t)rows * (uint64_t)slices.n > kStaticPartials) slices = choose_slices(4096, 4096, 65536, rows, K, V, draft->dtype);
+    Slices slices = choose_slices(kWgsTarget, 0, kSliceBytes, rows, K, V, draft->dtype);
+    if ((uint64_t)rows * (uint64_t)slices.n > kStaticPartials) slices = choose_slices(kWgsTarget, 4096, kSliceBytes, rows, K, V, draft->dtype);
     const int nsplit = slices.n;
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -715,7 +717,9 @@ tapout_status tapout_shard_stats(tapout_ctx *ctx, const tapout_logits *shard,
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = (int64_t)B * KK;
     Slices slices = choose_slices(ctx, rows, KK, Vs, shard->dtype);
-    if (ctx->min_slice == 0 && shard_rows_whole(rows, Vs, shard->dtype == TAPOUT_F32 ? 4 : 8)) slices = cut_evenly(1, Vs, shard->dtype);
+    // (by itself: a context whose options say how its rows are cut has them cut so)
+    const bool by_default = ctx->min_slice == 0 && ctx->wgs_target == kWgsTarget && ctx->slice_bytes == kSliceBytes;
+    if (by_default && shard_rows_whole(rows, Vs, shard->dtype == TAPOUT_F32 ? 4 : 8)) slices = cut_evenly(1, Vs, shard->dtype);
     const int nsplit = slices.n;
     if ((size_t)(rows * nsplit) > ctx->part_cap) return fail(ctx, TAPOUT_EINVAL, "internal: partial buffer too small");
     RowReduceArgs r{shard->ptr, shard->stride_b, shard->stride_k, Vs, KK, nsplit, slices.per, (int32_t)rows, len, rows_mode, ctx->part};

@@ -556,6 +556,18 @@ def test_shard_records_keep_the_precision_of_their_format(batches, dt):
         assert ((got - want) / want).pow(2).mean().sqrt() <= 1.2 * 2.0 ** -24 / 3 ** 0.5
 
 
+def _records_as_if_cut_into(B, K, V, dt, P, opts=()):
+    """A context with these options leaves the records, bit by bit, of one that is asked for P slices by the smallest slice."""
+    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 2).to(dt)
+    a, b = binding.Tapout(B, K, V), binding.Tapout(B, K, V)
+    for name, v in opts:
+        a.set_option(name, v)
+    b.set_option("slice_bytes", 1 << 22)
+    force_slices(b, B * K, P, min_slice=1000)
+    k_len = torch.full((B,), K, dtype=torch.int32, device=DEV)
+    return torch.equal(a.shard_stats(x, 7, k_len), b.shard_stats(x, 7, k_len))
+
+
 @pytest.mark.parametrize("B,K,V,dt,P", [
     (64, 4, 32756, f32, 1), (43, 6, 32756, f32, 8),             # 256 rows of eight batches whole, 258 in slices
     (16, 4, 32756, f32, 1), (21, 3, 32756, f32, 8),             # 64 and 63 of them
@@ -563,13 +575,12 @@ def test_shard_records_keep_the_precision_of_their_format(batches, dt):
     (96, 8, 64128, f32, 6), (192, 8, 48000, bf16, 3),           # more rows: few are live in short drafts, a workgroup each would leave the chip idle
 ])
 def test_long_shard_rows_are_read_whole_up_to_a_workgroup_per_compute_unit(B, K, V, dt, P):
-    """The bits of the same cut asked for by the smallest slice."""
-    x = (torch.randn(B, K, V, generator=torch.Generator(device=DEV).manual_seed(V), device=DEV) * 2).to(dt)
-    a, b = binding.Tapout(B, K, V), binding.Tapout(B, K, V)
-    b.set_option("slice_bytes", 1 << 22)
-    force_slices(b, B * K, P, min_slice=1000)
-    k_len = torch.full((B,), K, dtype=torch.int32, device=DEV)
-    assert torch.equal(a.shard_stats(x, 7, k_len), b.shard_stats(x, 7, k_len))
+    assert _records_as_if_cut_into(B, K, V, dt, P)
+
+
+@pytest.mark.parametrize("name,value,P", [("slice_bytes", 16384, 8), ("wgs_target", 8192, 8), ("wgs_target", 512, 2), ("wgs_target", 65536, 8)])
+def test_shard_rows_are_cut_as_the_options_say(name, value, P):
+    assert _records_as_if_cut_into(64, 4, 32756, f32, P, ((name, value),))
 
 
 @pytest.mark.parametrize("P", [1, 2, 3, 16, 17])
