@@ -818,29 +818,37 @@ def test_records_of_long_rows_keep_the_precision_of_their_format(B, batches, dt)
 
 
 @pytest.mark.parametrize("K,P", [(24, 3), (24, 13), (70, 3), (24, 0)])      # lanes in one pass and in two, one slice after the other; shard records
+@pytest.mark.parametrize("at", [0, 1])
 @pytest.mark.parametrize("dt", [f32, bf16])
-def test_second_maximum_wherever_it_lies(K, P, dt):
+def test_second_maximum_wherever_it_lies(K, P, at, dt):
     """The second largest value in the vector, the batch, the thread, the slice of the largest and outside of them, before and behind it, and as
     large as it: probabilities and margin within the 1e-5 max(|value|, 1e-3) of all statistics."""
     vec = 8 if dt == bf16 else 4
     batch = 4 * 256 * vec
-    V = (P or 4) * 2 * batch + 5
-    p = 2 * batch * ((P or 4) // 2) + 256 * vec + 7 * vec + 2         # in the second vector of a thread's first batch of a slice
-    off = [1, -1, vec, -vec, 256 * vec, -256 * vec, 512 * vec, batch, batch + 1, -batch, 2 * batch - 300 * vec, V - 1 - p]
-    off = [off[k % 12] for k in range(K)]
+    # the largest value in thread 7's second vector of batch `at` of a slice of two batches, or of a shard of four: that slice or shard starts at
+    # element `start` of what a row of `length` elements is cut from, whose first whole vector lies where 16 bytes are aligned
+    V = (2047 * P if P else 8 * 1024) * vec - 3
+    cut = [0, V] if P else [0, 4 * batch - 1000, V]
+    start, length = cut[-2], V - cut[-2]
+    slices = 2 * batch * (P // 2)
+    off = [1, -1, vec, -vec, 256 * vec, -256 * vec, 512 * vec, batch, batch + 1, -batch, 2 * batch - 300 * vec, 0]
     x = torch.randn(1, K, V, generator=torch.Generator().manual_seed(P)).to(dt)
+    largest, second = [], []
     for k in range(K):
+        p = start + -(k * length) % vec + slices + at * batch + (256 + 7) * vec + 2
+        q = p + off[k % 12] if k % 12 < 11 else V - 1
         x[0, k, p] = 9.0
-        x[0, k, p + off[k]] = 9.0 if k % 24 >= 12 else 8.5
+        x[0, k, q] = 9.0 if k % 24 >= 12 else 8.5
+        largest.append(p)
+        second.append(q)
     tp = binding.Tapout(1, K, V)
     if P:
-        force_slices(tp, K, P)
+        force_slices(tp, K, P)                                        # of (2047 P + P) / P = 2048 vectors
         out = tp.draft_stats(x.to(DEV))
     else:
-        cut = [0, V // 2 - 1000, V]
         rec = torch.stack([tp.shard_stats(x[:, :, i:j].contiguous().to(DEV), i).clone() for i, j in zip(cut, cut[1:])])
         out = tp.draft_stats_sharded(rec, 1, K, V)
     two = torch.softmax(x.double(), -1).topk(2, -1).values
     for n, w in {"p_top1": two[..., 0], "p_top2": two[..., 1], "margin": two[..., 0] - two[..., 1]}.items():
         assert ((out[n].cpu().double() - w).abs() <= 1e-5 * w.abs().clamp(min=1e-3)).all(), n
-    assert out["top1_id"][0].tolist() == [p + (min(0, off[k]) if k % 24 >= 12 else 0) for k in range(K)]
+    assert out["top1_id"][0].tolist() == [min(p, q) if k % 24 >= 12 else p for k, (p, q) in enumerate(zip(largest, second))]
