@@ -729,7 +729,8 @@ tapout_status tapout_shard_stats(tapout_ctx *ctx, const tapout_logits *shard,
                              [&](Timing tm) { return launch_shard_records(r, vocab_offset, shard->dtype, st, tm); });
         return e == hipSuccess ? TAPOUT_OK : hip_fail(ctx, e, "shard pass launch");
     }
-    // the draft pass also tracks the second maximum and the entropy sum; target rows need neither, but a record has one layout
+    // a draft pass: also the largest value outside the left-out batch, from which the merge forms the second maximum, and the entropy sum; target
+    // rows need neither, but a record has one layout
     hipError_t e = timed(ctx, rows_mode ? TAPOUT_PROFILE_TARGET_PASS : TAPOUT_PROFILE_DRAFT_PASS,
                          [&](Timing tm) { return launch_row_reduce(r, shard->dtype, true, st, tm); });
     if (e != hipSuccess) return hip_fail(ctx, e, "shard pass launch");

@@ -159,7 +159,7 @@ hipError_t launch_epilogue_stream(const DraftFinalArgs &f, RowReduceArgs t, int 
 hipError_t launch_stream_rest(RowReduceArgs t, int t_dtype, hipStream_t st, Timing tm);
 
 // A sequence's draft rows are so few pieces that the epilogue has two lanes for each or four (draft_lanes_shift): with one lane and four vectors each it
-// takes 120 registers, with these 75, which leave the streaming workgroups beside it their six wavefronts per SIMD.
+// takes 120 registers, with these 73 (binary32 57), which leave the streaming workgroups beside it their six wavefronts per SIMD.
 inline bool few_pieces(int K, int nsplit)
 {
     int p = 1;

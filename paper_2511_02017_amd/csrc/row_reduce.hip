@@ -13,10 +13,12 @@
 // Per thread the softmax sums are kept online in the base-2 domain against an
 // integer reference R >= max * log2 e: y = fma(x, log2e, -R) has a single
 // rounding, 2^y comes from the hardware exp2, and moving to a larger reference
-// is an exact ldexp.  Top-2 values are tracked with max3 / med3 on pairs
-// (second largest of {v1, a, b, v2} = max(med3(v1, a, b), v2) while v2 <= v1).
-// Only the 16-byte window in which the thread's maximum first appeared is
-// remembered; the exact argmax index is recovered later from that window.
+// is an exact ldexp.  The maximum, and for draft rows the largest value outside
+// the batch of vectors in which it appeared, are kept once per batch; with the
+// second largest value inside that batch, which the epilogue reads again (below),
+// the latter gives the row's second maximum.  Only the 16-byte window in which
+// the thread's maximum first appeared is remembered; the exact argmax index is
+// recovered later from that window.
 //
 // Draft rows: the entropy of a peaked row is a small number made of small
 // terms, and a binary32 sum that also holds the row's dominant term rounds
@@ -405,7 +407,7 @@ __device__ inline void finish_slice(const RowReduceArgs &a, const ThreadState<FU
         owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(st.v1 == Mw && st.cand == cw));
     }
     // FULL: that thread's set-apart batch stays out of the wavefront's sums and goes into the record on its own (every other
-    // thread's is ordinary data); its second maximum counts, of the others the maximum does
+    // thread's is ordinary data).  Largest value outside that batch: of that thread the one it kept (st.v2), of the others the maximum
     float v2w = -INFINITY;
     if constexpr (FULL) {
         s += lane == owner ? (Sum)0.0f : s_hi;
